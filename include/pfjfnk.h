@@ -173,8 +173,8 @@ int pf_residual(pf_problem* pb, const double* U, const double* Uprev, const doub
  * capture, tight serving loops, harnesses that forbid hipMalloc.  F =
  * F(U; Uprev) for the thermal model of params (order-1 elements, 2-D or 3-D),
  * bit for bit equal to pf_residual on a handle of the same params.  The
- * kernels' scratch (3-D: tile-face partial sums, 2-D: element vectors) is a
- * fixed array of 64 MiB inside the library, one copy per device, held from the
+ * kernels' scratch (3-D: tile-face partial sums; 2-D: none) is a fixed
+ * array of 64 MiB inside the library, one copy per device, held from the
  * first call on that device until the process ends; its device address is
  * looked up on that first call.  Meshes whose scratch exceeds it -- beyond
  * 2727 tiles of 16^3 elements in 3-D (128^3 and 192^3 fit, 256^3 does not),
@@ -403,7 +403,7 @@ typedef struct {
 } pf_freegrowth_params;
 
 /* Switch the handle to the free-growth model (host; allocates the history
- * field and the element buffer, 16 (order 1, 2-D), 16 (order 1, 3-D: 8
+ * field and, in 3-D and for order 2, the element buffer: 16 (order 1, 3-D: 8
  * corners) or 18 (order 2) doubles per element).  PF_ERR_INVALID_ARG,
  * PF_ERR_OOM. */
 int pf_set_freegrowth(pf_problem* pb, const pf_freegrowth_params* fg);

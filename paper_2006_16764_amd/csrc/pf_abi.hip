@@ -789,8 +789,7 @@ int pf_create(const pf_params* params, int gmres_m_max, pf_problem** out) {
   long long rb = (n / 2 + 255) / 256;
   pb->n_red_blocks = (int)std::min<long long>(std::max<long long>(rb, 1), 1024);
   pb->n_elem_blocks = elem_blocks(pb);
-  const int NA = 1 << pb->geo.dim;
-  pb->elem_buf_len = pb->geo.dim == 2 ? (long long)4 * NA * pb->geo.n_elems : 1;
+  pb->elem_buf_len = 1;  // grown by the models whose kernels take two passes
   pb->side_len = pb->geo.dim == 3 ? fused3_side_len(pb->geo) : 1;
   if (hipMalloc(&pb->red_partials, (size_t)kRedRows * pb->n_red_blocks * sizeof(double)) !=
           hipSuccess ||
@@ -1197,8 +1196,7 @@ int pf_set_alloy(pf_problem* pb, const pf_alloy_params* a) {
     set_error("alloy parameters need 0 < k <= 1, l_T > 0 and finite x_iso, v_pull");
     return PF_ERR_INVALID_ARG;
   }
-  const int NA = 1 << pb->geo.dim;
-  const long long need = (long long)2 * NA * pb->geo.n_elems;
+  const long long need = pb->geo.dim == 3 ? (long long)2 * 8 * pb->geo.n_elems : 1;
   if (pb->elem_buf_len < need) {
     if (pb->elem_buf) PF_HIP_CHECK(hipFree(pb->elem_buf));
     pb->elem_buf = nullptr;

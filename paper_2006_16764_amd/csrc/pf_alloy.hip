@@ -2,16 +2,17 @@
 // analytic Jv of the part of the theta step that depends on the new state,
 // and the explicit part fixed by the previous state.
 //
-// Two passes as for the 2-D thermal kernels: k_alloy_elem evaluates every
-// element once (one thread per element; Gauss rule by the sum-factorised
-// quad3/quad2 of pf_element.h) into the element buffer, then the shared
-// gather kernel forms the node sums in a fixed order.  Unlike the thermal u
+// 2-D: the single-pass tiles of pf_tile2.h.  3-D: two passes, k_alloy_elem3
+// evaluates every element once (one thread per element; Gauss rule by the
+// sum-factorised quad3 of pf_element.h) into the element buffer, then the
+// shared gather kernel forms the node sums in a fixed order.  Unlike the thermal u
 // equation the solute equation is nonlinear (one-sided mobility,
 // anti-trapping current, cu phihat source), so both fields go through the
 // Gauss rule.  The analytic tangent evaluates the same pointwise function on
 // dual numbers (value, directional derivative): forward-mode differentiation
 // of exactly the residual's arithmetic.
 #include "pf_dual.h"
+#include "pf_tile2.h"
 
 namespace pf {
 
@@ -184,22 +185,18 @@ struct AlloyElement {
   }
 };
 
+// The element vector of element ex (along axis 0) whose first corner is node
+// base; sx, sy (, sz) are the node strides.  ge: the cell integral of cu a^2.
 template <int DIM, int MODE>
-__global__ void __launch_bounds__(kAlloyBlock)
-    k_alloy_elem(Geo G, AlloyConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
-                 const double2* __restrict__ V, const double* __restrict__ eps_dev,
-                 const double* __restrict__ hist, double* __restrict__ E, double* __restrict__ coef) {
+__device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C, int ex,
+                                              long long base, const double2* __restrict__ U,
+                                              const double2* __restrict__ Up,
+                                              const double2* __restrict__ V,
+                                              const double* __restrict__ eps_dev,
+                                              const double* __restrict__ hist,
+                                              double (&out)[2][1 << DIM], double& ge) {
   constexpr int NA = 1 << DIM;
-  // blockIdx.y is the element layer (0 in 2-D): coordinates from 32-bit arithmetic
-  const int pe = G.n[0] * G.n[1];
-  const int q = (int)blockIdx.x * kAlloyBlock + (int)threadIdx.x;
-  if (q >= pe) return;
-  const int ey = q / G.n[0];
-  const int ex = q - ey * G.n[0];
-  const int ez = (int)blockIdx.y;
-  const long long e = (long long)ez * pe + q;
   const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
-  const long long base = ex + s1 * (ey + (long long)G.nn[1] * ez);
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
   double u0[NA], u1[NA], p0[NA], p1[NA], hs[NA], xc[NA], v0[NA], v1[NA];
 #pragma unroll
@@ -222,15 +219,54 @@ __global__ void __launch_bounds__(kAlloyBlock)
     hs[a] = C.use_hist ? hist[node] : 0.0;
     xc[a] = fma((double)(ex + (a & 1)), C.h0, C.x0);
   }
-  double out[2][NA];
-  double ge = 0.0;
   AlloyElement<DIM, MODE == MODE_FD ? MODE_RES : MODE>::run(G, C, u0, u1, p0, p1, hs, xc, v0, v1,
                                                             out, ge);
-  if (MODE == MODE_RES && coef) coef[e] = ge / ((double)NA * G.jac);
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(kTile2Threads)
+    k_alloy_tile2(Geo G, AlloyConst C, const double2* __restrict__ U,
+                  const double2* __restrict__ Up, const double2* __restrict__ V,
+                  const double* __restrict__ eps_dev, const double* __restrict__ hist,
+                  const double2* __restrict__ F0, double2* __restrict__ F,
+                  double* __restrict__ coef) {
+  __shared__ double sh[2 * 3 * kTile2Threads];
+  const Tile2 P = tile2_pos(G);
+  double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  double ge = 0.0;
+  if (P.elem) {
+    alloy_element<2, MODE>(G, C, P.ex, P.base, U, Up, V, eps_dev, hist, out, ge);
+    if (MODE == MODE_RES && coef && P.node)
+      coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
+  }
+  double acc[2];
+  tile2_sum<2>(P, out, sh, acc);
+  tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(kAlloyBlock)
+    k_alloy_elem3(Geo G, AlloyConst C, const double2* __restrict__ U,
+                  const double2* __restrict__ Up, const double2* __restrict__ V,
+                  const double* __restrict__ eps_dev, const double* __restrict__ hist,
+                  double* __restrict__ E, double* __restrict__ coef) {
+  // blockIdx.y is the element layer: coordinates from 32-bit arithmetic
+  const int pe = G.n[0] * G.n[1];
+  const int q = (int)blockIdx.x * kAlloyBlock + (int)threadIdx.x;
+  if (q >= pe) return;
+  const int ey = q / G.n[0];
+  const int ex = q - ey * G.n[0];
+  const int ez = (int)blockIdx.y;
+  const long long e = (long long)ez * pe + q;
+  const long long base = ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez);
+  double out[2][8];
+  double ge = 0.0;
+  alloy_element<3, MODE>(G, C, ex, base, U, Up, V, eps_dev, hist, out, ge);
+  if (MODE == MODE_RES && coef) coef[e] = ge / (8.0 * G.jac);
 #pragma unroll
   for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int a = 0; a < NA; ++a) E[(long long)(o * NA + a) * G.n_elems + e] = out[o][a];
+    for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = out[o][a];
 }
 
 __global__ void k_history(long long n, const double2* __restrict__ Un,
@@ -240,38 +276,27 @@ __global__ void k_history(long long n, const double2* __restrict__ Un,
     hist[i] = c * (Un[i].x - Unm1[i].x);
 }
 
-template <int DIM>
-int launch_elem(pf_problem* pb, const AlloyConst& C, int mode, const double* U, const double* Uprev,
-                const double* v, const double* eps_dev, double* coef, hipStream_t s) {
+template <int MODE>
+int launch_mode(pf_problem* pb, const AlloyConst& C, const double* U, const double* Uprev,
+                const double* v, const double* F0, const double* eps_dev, double* out0,
+                double* coef, hipStream_t s) {
   const Geo& G = pb->geo;
-  const dim3 eb((unsigned)(((long long)G.n[0] * G.n[1] + kAlloyBlock - 1) / kAlloyBlock),
-                (unsigned)G.n[2]);
   auto U2 = reinterpret_cast<const double2*>(U);
   auto P2 = reinterpret_cast<const double2*>(Uprev);
   auto V2 = reinterpret_cast<const double2*>(v);
-  switch (mode) {
-    case MODE_RES:
-      hipLaunchKernelGGL((k_alloy_elem<DIM, MODE_RES>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2,
-                         P2, nullptr, nullptr, pb->hist, pb->elem_buf, coef);
-      break;
-    case MODE_FD:
-      hipLaunchKernelGGL((k_alloy_elem<DIM, MODE_FD>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2,
-                         P2, V2, eps_dev, pb->hist, pb->elem_buf, nullptr);
-      break;
-    default:
-      hipLaunchKernelGGL((k_alloy_elem<DIM, MODE_JVP>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C,
-                         U2, P2, V2, nullptr, pb->hist, pb->elem_buf, nullptr);
-      break;
+  if (G.dim == 2) {
+    hipLaunchKernelGGL((k_alloy_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G, C,
+                       U2, P2, V2, eps_dev, pb->hist, reinterpret_cast<const double2*>(F0),
+                       reinterpret_cast<double2*>(out0), coef);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
   }
+  const dim3 eb((unsigned)(((long long)G.n[0] * G.n[1] + kAlloyBlock - 1) / kAlloyBlock),
+                (unsigned)G.n[2]);
+  hipLaunchKernelGGL((k_alloy_elem3<MODE>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2, P2, V2,
+                     eps_dev, pb->hist, pb->elem_buf, coef);
   PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
-}
-
-int launch_elem_dim(pf_problem* pb, const AlloyConst& C, int mode, const double* U,
-                    const double* Uprev, const double* v, const double* eps_dev, double* coef,
-                    hipStream_t s) {
-  if (pb->geo.dim == 3) return launch_elem<3>(pb, C, mode, U, Uprev, v, eps_dev, coef, s);
-  return launch_elem<2>(pb, C, mode, U, Uprev, v, eps_dev, coef, s);
+  return launch_gather3(pb, out0, F0, eps_dev, MODE == MODE_FD ? 1 : 0, s);
 }
 
 }  // namespace
@@ -298,8 +323,9 @@ int launch_alloy(pf_problem* pb, int mode, const double* U, const double* Uprev,
     return PF_ERR_INVALID_ARG;
   }
   const AlloyConst C = alloy_const(pb, pb->t_new, pb->params.theta, 1);
-  PF_TRY(launch_elem_dim(pb, C, mode, U, Uprev, v, eps_dev, coef, s));
-  return launch_gather2(pb, out0, F0, eps_dev, mode == MODE_FD ? 1 : 0, s);
+  if (mode == MODE_RES) return launch_mode<MODE_RES>(pb, C, U, Uprev, v, F0, eps_dev, out0, coef, s);
+  if (mode == MODE_FD) return launch_mode<MODE_FD>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
+  return launch_mode<MODE_JVP>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
 }
 
 int alloy_explicit(pf_problem* pb, const double* Un, double t_n, double* E, hipStream_t s) {
@@ -311,8 +337,7 @@ int alloy_explicit(pf_problem* pb, const double* Un, double t_n, double* E, hipS
   // the residual at (U^n; U^n) with weight 1 and no history is the spatial
   // operator at U^n: the time and rate terms vanish
   const AlloyConst C = alloy_const(pb, t_n, 1.0, 0);
-  PF_TRY(launch_elem_dim(pb, C, MODE_RES, Un, Un, nullptr, nullptr, nullptr, s));
-  PF_TRY(launch_gather2(pb, E, nullptr, nullptr, 0, s));
+  PF_TRY(launch_mode<MODE_RES>(pb, C, Un, Un, nullptr, nullptr, nullptr, E, nullptr, s));
   return blas_axpby(1.0 - th, E, 0.0, E, E, pb->n_dof, s);
 }
 

@@ -4,12 +4,14 @@
 // order-1 elements (2-D and 3-D, through quad2/quad3 of pf_element.h) and on
 // order-2 (biquadratic, 9-node) elements in 2-D.
 //
-// Two passes as for the alloy model: one thread per element evaluates the
-// element vectors into the element buffer, then a fixed-order gather forms
-// the node sums (the order-1 gather of pf_residual.hip, or the order-2 gather
-// below, which sums the 1, 2 or 4 elements sharing a node).  The analytic
+// Order 1 in 2-D: the single-pass tiles of pf_tile2.h.  Otherwise two passes:
+// one thread per element evaluates the element vectors into the element
+// buffer, then a fixed-order gather forms the node sums (the 3-D gather of
+// pf_residual.hip, or the order-2 gather below, which sums the 1, 2 or 4
+// elements sharing a node).  The analytic
 // tangent runs the pointwise template on dual numbers.
 #include "pf_dual.h"
+#include "pf_tile2.h"
 
 namespace pf {
 
@@ -117,21 +119,18 @@ struct PhysFgJvp {
   }
 };
 
+// The element vector of the element whose first corner is node base.  ca: the
+// cell integral of a^2.
 template <int DIM, int MODE>
-__global__ void __launch_bounds__(kFgBlock)
-    k_fg_elem(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
-              const double2* __restrict__ V, const double* __restrict__ eps_dev,
-              const double* __restrict__ hist, double* __restrict__ E, double* __restrict__ coef) {
+__device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long long base,
+                                           const double2* __restrict__ U,
+                                           const double2* __restrict__ Up,
+                                           const double2* __restrict__ V,
+                                           const double* __restrict__ eps_dev,
+                                           const double* __restrict__ hist,
+                                           double (&out)[2][1 << DIM], double& ca) {
   constexpr int NA = 1 << DIM;
-  const long long e = (long long)blockIdx.x * kFgBlock + threadIdx.x;
-  if (e >= G.n_elems) return;
-  const long long n0 = G.n[0], n1 = G.n[1];
-  const long long ex = e % n0;
-  const long long rest = e / n0;
-  const long long ey = (DIM == 2) ? rest : rest % n1;
-  const long long ez = (DIM == 2) ? 0 : rest / n1;
   const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
-  const long long base = ex + s1 * (ey + (long long)G.nn[1] * ez);
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
   double ng[4][NA], nv[3][NA];
 #pragma unroll
@@ -153,7 +152,7 @@ __global__ void __launch_bounds__(kFgBlock)
     nv[1][a] = u.y - up.y;
     nv[2][a] = C.use_hist ? hist[node] : 0.0;
   }
-  double out[2][NA], dummy[1][NA];
+  double dummy[1][NA];
 #pragma unroll
   for (int a = 0; a < NA; ++a) out[0][a] = out[1][a] = 0.0;
   if constexpr (MODE == MODE_JVP) {
@@ -170,12 +169,50 @@ __global__ void __launch_bounds__(kFgBlock)
     PhysFgRes<DIM> ph(G, C);
     if constexpr (DIM == 3) quad3<2, 3, 2, 0>(G, ng2, nv, out, dummy, ph);
     else quad2<2, 3, 2, 0>(G, ng2, nv, out, dummy, ph);
-    if (MODE == MODE_RES && coef) coef[e] = ph.ca / ((double)NA * G.jac);
+    ca = ph.ca;
   }
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(kTile2Threads)
+    k_fg_tile2(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
+               const double2* __restrict__ V, const double* __restrict__ eps_dev,
+               const double* __restrict__ hist, const double2* __restrict__ F0,
+               double2* __restrict__ F, double* __restrict__ coef) {
+  __shared__ double sh[2 * 3 * kTile2Threads];
+  const Tile2 P = tile2_pos(G);
+  double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  double ca = 0.0;
+  if (P.elem) {
+    fg_element<2, MODE>(G, C, P.base, U, Up, V, eps_dev, hist, out, ca);
+    if (MODE == MODE_RES && coef && P.node)
+      coef[P.ex + (long long)G.n[0] * P.ey] = ca / (4.0 * G.jac);
+  }
+  double acc[2];
+  tile2_sum<2>(P, out, sh, acc);
+  tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(kFgBlock)
+    k_fg_elem3(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
+               const double2* __restrict__ V, const double* __restrict__ eps_dev,
+               const double* __restrict__ hist, double* __restrict__ E, double* __restrict__ coef) {
+  const long long e = (long long)blockIdx.x * kFgBlock + threadIdx.x;
+  if (e >= G.n_elems) return;
+  const long long n0 = G.n[0], n1 = G.n[1];
+  const long long ex = e % n0;
+  const long long rest = e / n0;
+  const long long ey = rest % n1, ez = rest / n1;
+  double out[2][8];
+  double ca = 0.0;
+  fg_element<3, MODE>(G, C, ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez), U, Up, V,
+                      eps_dev, hist, out, ca);
+  if (MODE == MODE_RES && coef) coef[e] = ca / (8.0 * G.jac);
 #pragma unroll
   for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int a = 0; a < NA; ++a) E[(long long)(o * NA + a) * G.n_elems + e] = out[o][a];
+    for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = out[o][a];
 }
 
 // ----------------------------------------------------------------- order 2 (2-D)
@@ -388,68 +425,44 @@ FgConst fg_const(const pf_problem* pb, double theta, int use_hist) {
   return C;
 }
 
-int launch_elem(pf_problem* pb, const FgConst& C, int mode, const double* U, const double* Uprev,
-                const double* v, const double* eps_dev, double* coef, hipStream_t s) {
+template <int MODE>
+int launch_mode(pf_problem* pb, const FgConst& C, const double* U, const double* Uprev,
+                const double* v, const double* F0, const double* eps_dev, double* out0,
+                double* coef, hipStream_t s) {
   const Geo& G = pb->geo;
+  const int fd = MODE == MODE_FD ? 1 : 0;
   auto U2 = reinterpret_cast<const double2*>(U);
   auto P2p = reinterpret_cast<const double2*>(Uprev);
   auto V2 = reinterpret_cast<const double2*>(v);
+  auto F02 = reinterpret_cast<const double2*>(F0);
+  auto out2 = reinterpret_cast<double2*>(out0);
   if (pb->params.order == 2) {
     const long long ne = (long long)C.n_macro[0] * C.n_macro[1];
-    const unsigned eb = (unsigned)((ne + kFgBlock - 1) / kFgBlock);
-    if (mode == MODE_RES)
-      hipLaunchKernelGGL(k_fg_q2<MODE_RES>, dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p, nullptr,
-                         nullptr, pb->hist, pb->elem_buf, coef);
-    else if (mode == MODE_FD)
-      hipLaunchKernelGGL(k_fg_q2<MODE_FD>, dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p, V2,
-                         eps_dev, pb->hist, pb->elem_buf, nullptr);
-    else
-      hipLaunchKernelGGL(k_fg_q2<MODE_JVP>, dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p, V2,
-                         nullptr, pb->hist, pb->elem_buf, nullptr);
-  } else {
-    const unsigned eb = (unsigned)((G.n_elems + kFgBlock - 1) / kFgBlock);
-    if (G.dim == 3) {
-      if (mode == MODE_RES)
-        hipLaunchKernelGGL((k_fg_elem<3, MODE_RES>), dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p,
-                           nullptr, nullptr, pb->hist, pb->elem_buf, coef);
-      else if (mode == MODE_FD)
-        hipLaunchKernelGGL((k_fg_elem<3, MODE_FD>), dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p,
-                           V2, eps_dev, pb->hist, pb->elem_buf, nullptr);
-      else
-        hipLaunchKernelGGL((k_fg_elem<3, MODE_JVP>), dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p,
-                           V2, nullptr, pb->hist, pb->elem_buf, nullptr);
-    } else {
-      if (mode == MODE_RES)
-        hipLaunchKernelGGL((k_fg_elem<2, MODE_RES>), dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p,
-                           nullptr, nullptr, pb->hist, pb->elem_buf, coef);
-      else if (mode == MODE_FD)
-        hipLaunchKernelGGL((k_fg_elem<2, MODE_FD>), dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p,
-                           V2, eps_dev, pb->hist, pb->elem_buf, nullptr);
-      else
-        hipLaunchKernelGGL((k_fg_elem<2, MODE_JVP>), dim3(eb), dim3(kFgBlock), 0, s, G, C, U2, P2p,
-                           V2, nullptr, pb->hist, pb->elem_buf, nullptr);
-    }
+    hipLaunchKernelGGL((k_fg_q2<MODE>), dim3((unsigned)((ne + kFgBlock - 1) / kFgBlock)),
+                       dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, pb->hist, pb->elem_buf, coef);
+    PF_HIP_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(k_fg_q2_gather, dim3((unsigned)((G.n_nodes + 255) / 256)), dim3(256), 0, s, G,
+                       C, pb->elem_buf, out2, F02, eps_dev, fd);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
   }
+  if (G.dim == 2) {
+    hipLaunchKernelGGL((k_fg_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G, C, U2,
+                       P2p, V2, eps_dev, pb->hist, F02, out2, coef);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
+  }
+  hipLaunchKernelGGL((k_fg_elem3<MODE>), dim3((unsigned)((G.n_elems + kFgBlock - 1) / kFgBlock)),
+                     dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, pb->hist, pb->elem_buf, coef);
   PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
-}
-
-int gather(pf_problem* pb, const FgConst& C, double* out0, const double* F0, const double* eps_dev,
-           int fd, hipStream_t s) {
-  if (pb->params.order != 2) return launch_gather2(pb, out0, F0, eps_dev, fd, s);
-  const unsigned nb = (unsigned)((pb->geo.n_nodes + 255) / 256);
-  hipLaunchKernelGGL(k_fg_q2_gather, dim3(nb), dim3(256), 0, s, pb->geo, C, pb->elem_buf,
-                     reinterpret_cast<double2*>(out0), reinterpret_cast<const double2*>(F0),
-                     eps_dev, fd);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+  return launch_gather3(pb, out0, F0, eps_dev, fd, s);
 }
 
 }  // namespace
 
 long long fg_elem_buf_len(const pf_problem* pb) {
   if (pb->params.order == 2) return (long long)2 * 9 * pb->params.n[0] * pb->params.n[1];
-  return (long long)2 * (1 << pb->geo.dim) * pb->geo.n_elems;
+  return pb->geo.dim == 3 ? (long long)2 * 8 * pb->geo.n_elems : 1;
 }
 
 int launch_fg(pf_problem* pb, int mode, const double* U, const double* Uprev, const double* v,
@@ -459,8 +472,9 @@ int launch_fg(pf_problem* pb, int mode, const double* U, const double* Uprev, co
     return PF_ERR_INVALID_ARG;
   }
   const FgConst C = fg_const(pb, pb->params.theta, 1);
-  PF_TRY(launch_elem(pb, C, mode, U, Uprev, v, eps_dev, coef, s));
-  return gather(pb, C, out0, F0, eps_dev, mode == MODE_FD ? 1 : 0, s);
+  if (mode == MODE_RES) return launch_mode<MODE_RES>(pb, C, U, Uprev, v, F0, eps_dev, out0, coef, s);
+  if (mode == MODE_FD) return launch_mode<MODE_FD>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
+  return launch_mode<MODE_JVP>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
 }
 
 int fg_explicit(pf_problem* pb, const double* Un, double* E, hipStream_t s) {
@@ -472,8 +486,7 @@ int fg_explicit(pf_problem* pb, const double* Un, double* E, hipStream_t s) {
   // the residual at (U^n; U^n) with weight 1 and no history is the spatial
   // operator at U^n: the time and rate terms vanish
   const FgConst C = fg_const(pb, 1.0, 0);
-  PF_TRY(launch_elem(pb, C, MODE_RES, Un, Un, nullptr, nullptr, nullptr, s));
-  PF_TRY(gather(pb, C, E, nullptr, nullptr, 0, s));
+  PF_TRY(launch_mode<MODE_RES>(pb, C, Un, Un, nullptr, nullptr, nullptr, E, nullptr, s));
   return blas_axpby(1.0 - th, E, 0.0, E, E, pb->n_dof, s);
 }
 

@@ -103,16 +103,13 @@ int launch_fused3(pf_problem* pb, int mode, const double* U, const double* Uprev
                   const double* F0, const double* eps_dev, double* out0, double* out1,
                   double* vjp_part, double* coef, hipStream_t s);
 
-// The thermal residual alone with caller-provided scratch: 3-D through the
-// fused kernel with side buffer `side` (fused3_residual_side_len(G) doubles),
-// 2-D through the two-pass kernels with element buffer `elem`
-// (residual2_elem_len(G) doubles).  Same kernels as pf_residual.
+// The thermal residual alone: 3-D through the fused kernel with caller-provided
+// side buffer `side` (fused3_residual_side_len(G) doubles), 2-D through the
+// single-pass tiles (no scratch).  Same kernels as pf_residual.
 long long fused3_residual_side_len(const Geo& G);
 int launch_fused3_residual(const Geo& G, double* side, const double* U, const double* Uprev,
                            double* F, hipStream_t s);
-long long residual2_elem_len(const Geo& G);
-int launch_residual2(const Geo& G, double* elem, const double* U, const double* Uprev, double* F,
-                     hipStream_t s);
+int launch_residual2(const Geo& G, const double* U, const double* Uprev, double* F, hipStream_t s);
 // Host-side argument checks shared by the entry points (pf_abi.hip).
 int check_params(const pf_params* p);
 int check_vec(const void* p, const char* name);
@@ -124,9 +121,9 @@ int launch_residual_family(pf_problem* pb, int mode, const double* U, const doub
                            const double* v, const double* F0, const double* eps_dev,
                            double* out0, double* out1, double* gparams_partial,
                            hipStream_t s, double* coef = nullptr);
-// Node sums of the element buffer (pf_residual.hip): out0 = sums, or
+// Node sums of the 3-D element buffer (pf_residual.hip): out0 = sums, or
 // (sums - F0)/eps when fd != 0.
-int launch_gather2(pf_problem* pb, double* out0, const double* F0, const double* eps_dev, int fd,
+int launch_gather3(pf_problem* pb, double* out0, const double* F0, const double* eps_dev, int fd,
                    hipStream_t s);
 
 // Alloy model (pf_alloy.hip).  launch_alloy: modes RES, FD, JVP at pb->t_new
@@ -235,7 +232,7 @@ struct pf_problem {
   double* host_pinned_dev;  // its device alias (reductions write results there)
 
   // residual-family scratch
-  double* elem_buf;      // element contributions (element pass)
+  double* elem_buf;      // element contributions (two-pass alloy and free-growth kernels)
   long long elem_buf_len;
   double* vjp_partials;  // 2 * n_elem_blocks
   double* side_buf;      // 3-D: partial node sums on tile boundaries

@@ -2,9 +2,8 @@
 // device allocation, for callers that cannot allocate (graph capture, tight
 // serving loops, harnesses that forbid hipMalloc).
 //
-// The kernels' scratch -- the tile-face partial sums of the 3-D fused kernel,
-// or the element vectors of the 2-D two-pass kernels -- lives in one fixed
-// array `scratch` inside the library.  Every device that runs the library
+// The scratch of the 3-D fused kernel, its tile-face partial sums, lives in
+// one fixed array `scratch` inside the library (the 2-D kernel needs none).  Every device that runs the library
 // holds its own copy of it from module load until the process ends.  In host
 // code the array's name is only a host-side stand-in, so its device address is
 // looked up once per device (hipGetSymbolAddress, with that device current)
@@ -17,8 +16,11 @@ namespace pf {
 
 namespace {
 
-// 64 MiB: 2727 tiles of 16^3 elements (192^3 fits) or 2^20 elements in 2-D.
+// 64 MiB: 2727 tiles of 16^3 elements (192^3 fits).  2-D meshes are accepted up
+// to the documented 2^20 elements, the former size of their element vectors (8
+// doubles each) in the array.
 constexpr long long kScratchBytes = 64LL << 20;
+constexpr long long kElemDoubles2 = 8;
 constexpr long long kScratchDoubles = kScratchBytes / (long long)sizeof(double);
 
 static __device__ __align__(256) double scratch[kScratchDoubles];
@@ -69,16 +71,16 @@ extern "C" int pf_residual_noalloc(const pf_params* params, const double* U, con
   pf_params p = *params;
   p.order = 1;
   const Geo G = make_geo(p);
-  const long long need = G.dim == 3 ? fused3_residual_side_len(G) : residual2_elem_len(G);
+  const long long need = G.dim == 3 ? fused3_residual_side_len(G) : kElemDoubles2 * G.n_elems;
   if (need > kScratchDoubles) {
     set_error("pf_residual_noalloc: mesh needs " + std::to_string(need * 8) +
               " bytes of scratch, more than the fixed " + std::to_string(kScratchBytes) +
               " (3-D: at most 2727 tiles of 16^3 elements; 2-D: at most 2^20 elements)");
     return PF_ERR_INVALID_ARG;
   }
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (G.dim == 2) return launch_residual2(G, U, Uprev, F, s);
   double* scr = nullptr;
   PF_TRY(scratch_address(&scr));
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (G.dim == 3) return launch_fused3_residual(G, scr, U, Uprev, F, s);
-  return launch_residual2(G, scr, U, Uprev, F, s);
+  return launch_fused3_residual(G, scr, U, Uprev, F, s);
 }

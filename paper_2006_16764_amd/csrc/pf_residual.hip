@@ -1,60 +1,44 @@
-// Residual-family kernels: F(U), fused finite-difference Jv, analytic Jv and
-// the vector-Jacobian product, all from one element routine (pf_element.h).
+// 2-D residual-family kernels: F(U), fused finite-difference Jv, analytic Jv
+// and the vector-Jacobian products, all from one element routine
+// (pf_element.h) with the single-pass node sums of pf_tile2.h; deterministic,
+// no atomics, no colouring.  The VJP's two parameter sums are reduced per
+// workgroup in a fixed tree (every element counted by the one tile that owns
+// its first node) and then across workgroups in a fixed order.
 //
-// Two passes, both deterministic:
-//   k_elem   one thread per element: gathers its 2^d corner values (16-byte
-//            interleaved loads), evaluates the element vectors by sum
-//            factorisation and stores them structure-of-arrays,
-//            E[(o * 2^d + a) * n_elems + e];
-//   k_gather one thread per node: sums the contributions of the <= 2^d
-//            elements around it in a fixed order and writes the interleaved
-//            result (no atomics, no colouring).
-// The VJP's two parameter sums are reduced per block in a fixed tree and then
-// across blocks in a fixed order.
-#include "pf_element.h"
+// Also here: the gather pass of the two-pass 3-D alloy and free-growth kernels
+// and the dispatch of the residual family over models and dimensions.
+#include "pf_tile2.h"
 
 namespace pf {
 
 namespace {
 
-constexpr int kElemBlock = 256;
-
-template <int DIM>
-__device__ __forceinline__ void corner_nodes(const Geo& G, long long e, long long (&node)[1 << DIM]) {
-  const long long n0 = G.n[0], n1 = G.n[1];
-  const long long ex = e % n0;
-  const long long rest = e / n0;
-  const long long ey = (DIM == 2) ? rest : rest % n1;
-  const long long ez = (DIM == 2) ? 0 : rest / n1;
-  const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
-  const long long base = ex + s1 * (ey + (long long)G.nn[1] * ez);
-#pragma unroll
-  for (int a = 0; a < (1 << DIM); ++a)
-    node[a] = base + (a & 1) + ((a >> 1) & 1) * s1 + (DIM == 3 ? ((a >> 2) & 1) * s2 : 0);
-}
-
-template <int DIM, int MODE>
-__global__ void __launch_bounds__(kElemBlock)
-    k_elem(Geo G, const double2* __restrict__ U, const double2* __restrict__ Up,
-           const double2* __restrict__ V, const double* __restrict__ eps_dev,
-           double* __restrict__ E, double* __restrict__ vjp_part, double* __restrict__ coef) {
-  constexpr int NA = 1 << DIM;
+template <int MODE>
+__global__ void __launch_bounds__(kTile2Threads)
+    k_tile2(Geo G, const double2* __restrict__ U, const double2* __restrict__ Up,
+            const double2* __restrict__ V, const double* __restrict__ eps_dev,
+            const double2* __restrict__ F0, double2* __restrict__ out0,
+            double2* __restrict__ out1, double* __restrict__ vjp_part, double* __restrict__ coef) {
   constexpr int NO = (MODE == MODE_VJP) ? 4 : 2;
-  const long long e = (long long)blockIdx.x * kElemBlock + threadIdx.x;
-  const bool active = e < G.n_elems;
-  double ge = 0.0, gl = 0.0;
-  if (active) {
-    long long node[NA];
-    corner_nodes<DIM>(G, e, node);
-    double u0[NA], u1[NA], p0[NA], p1[NA], v0[NA], v1[NA];
-    double eps = 0.0;
-    if (MODE == MODE_FD) eps = *eps_dev;
+  __shared__ double sh[NO * 3 * kTile2Threads];
+  const Tile2 P = tile2_pos(G);
+  double out[NO][4];
 #pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      double2 u = U[node[a]];
-      const double2 up = Up[node[a]];
+  for (int o = 0; o < NO; ++o)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) out[o][a] = 0.0;
+  double ge = 0.0, gl = 0.0;
+  if (P.elem) {
+    double u0[4], u1[4], p0[4], p1[4], v0[4], v1[4];
+    double eps = 0.0;
+    if (MODE == MODE_FD) eps = eps_dev[0];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const long long node = P.base + (a & 1) + (a >> 1) * (long long)G.nn[0];
+      double2 u = U[node];
+      const double2 up = Up[node];
       double2 v = make_double2(0.0, 0.0);
-      if (MODE != MODE_RES) v = V[node[a]];
+      if (MODE != MODE_RES) v = V[node];
       if (MODE == MODE_FD) {
         u.x = fma(eps, v.x, u.x);
         u.y = fma(eps, v.y, u.y);
@@ -66,43 +50,42 @@ __global__ void __launch_bounds__(kElemBlock)
       v0[a] = v.x;
       v1[a] = v.y;
     }
-    double out[NO][NA];
-    Element<DIM, MODE>::run(G, u0, u1, p0, p1, v0, v1, out, ge, gl);
-    if (MODE == MODE_RES && coef) coef[e] = ge / ((double)NA * G.jac);
-#pragma unroll
-    for (int o = 0; o < NO; ++o)
-#pragma unroll
-      for (int a = 0; a < NA; ++a) E[(long long)(o * NA + a) * G.n_elems + e] = out[o][a];
+    Element<2, MODE>::run(G, u0, u1, p0, p1, v0, v1, out, ge, gl);
+    if (MODE == MODE_RES && coef && P.node)
+      coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
   }
-  if (MODE == MODE_VJP) {
-    // fixed-order block reduction of the two parameter sums
-    __shared__ double red[2][kElemBlock];
-    red[0][threadIdx.x] = ge;
-    red[1][threadIdx.x] = gl;
+  double acc[NO];
+  tile2_sum<NO>(P, out, sh, acc);
+  if (out0) tile2_write(P, acc[0], acc[1], out0, MODE == MODE_FD, F0, eps_dev);
+  if (MODE == MODE_VJP && out1) tile2_write(P, acc[2 % NO], acc[3 % NO], out1, false, nullptr, nullptr);
+  if (MODE == MODE_VJP || MODE == MODE_VJPP) {
+    // fixed-order workgroup reduction of the two parameter sums
     __syncthreads();
-    for (int w = kElemBlock / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) {
-        red[0][threadIdx.x] += red[0][threadIdx.x + w];
-        red[1][threadIdx.x] += red[1][threadIdx.x + w];
+    double* red = sh;
+    const int t = (int)threadIdx.x;
+    red[t] = P.node ? ge : 0.0;  // ge, gl are 0 where the element does not exist
+    red[kTile2Threads + t] = P.node ? gl : 0.0;
+    __syncthreads();
+    for (int w = kTile2Threads / 2; w > 0; w >>= 1) {
+      if (t < w) {
+        red[t] += red[t + w];
+        red[kTile2Threads + t] += red[kTile2Threads + t + w];
       }
       __syncthreads();
     }
-    if (threadIdx.x == 0) {
-      vjp_part[blockIdx.x] = red[0][0];
-      vjp_part[gridDim.x + blockIdx.x] = red[1][0];
+    if (t == 0) {
+      vjp_part[blockIdx.x] = red[0];
+      vjp_part[gridDim.x + blockIdx.x] = red[kTile2Threads];
     }
   }
 }
 
-// Sum the element contributions around every node.  NO = 2 (one output
-// vector) or 4 (VJP: gU then gUprev).  mode FD: out0 = (sum - F0)/eps.
-template <int DIM, int NO>
+// Sum of the element contributions around every node of a 3-D mesh (one
+// thread per node, fixed order): out0 = sums, or (sums - F0)/eps when fd.
 __global__ void __launch_bounds__(256)
-    k_gather(Geo G, const double* __restrict__ E, double2* __restrict__ out0,
-             double2* __restrict__ out1, const double2* __restrict__ F0,
-             const double* __restrict__ eps_dev, int fd) {
-  constexpr int NA = 1 << DIM;
-  // blockIdx.y is the node plane (0 in 2-D): coordinates from 32-bit arithmetic
+    k_gather3(Geo G, const double* __restrict__ E, double2* __restrict__ out0,
+              const double2* __restrict__ F0, const double* __restrict__ eps_dev, int fd) {
+  // blockIdx.y is the node plane: coordinates from 32-bit arithmetic
   const int pn = G.nn[0] * G.nn[1];
   const int q = (int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
   if (q >= pn) return;
@@ -110,13 +93,11 @@ __global__ void __launch_bounds__(256)
   const int ix = q - iy * G.nn[0];
   const int iz = (int)blockIdx.y;
   const long long i = (long long)iz * pn + q;
-  double acc[NO];
+  double acc[2] = {0.0, 0.0};
 #pragma unroll
-  for (int o = 0; o < NO; ++o) acc[o] = 0.0;
-#pragma unroll
-  for (int bz = 0; bz < (DIM == 3 ? 2 : 1); ++bz) {
-    const int ez = iz - 1 + bz + (DIM == 3 ? 0 : 1);
-    if (DIM == 3 && (ez < 0 || ez >= G.n[2])) continue;
+  for (int bz = 0; bz < 2; ++bz) {
+    const int ez = iz - 1 + bz;
+    if (ez < 0 || ez >= G.n[2]) continue;
 #pragma unroll
     for (int by = 0; by < 2; ++by) {
       const int ey = iy - 1 + by;
@@ -125,10 +106,10 @@ __global__ void __launch_bounds__(256)
       for (int bx = 0; bx < 2; ++bx) {
         const int ex = ix - 1 + bx;
         if (ex < 0 || ex >= G.n[0]) continue;
-        const long long e = ex + (long long)G.n[0] * (ey + (long long)G.n[1] * (DIM == 3 ? ez : 0));
-        const int a = (1 - bx) + 2 * (1 - by) + (DIM == 3 ? 4 * (1 - bz) : 0);
+        const long long e = ex + (long long)G.n[0] * (ey + (long long)G.n[1] * ez);
+        const int a = (1 - bx) + 2 * (1 - by) + 4 * (1 - bz);
 #pragma unroll
-        for (int o = 0; o < NO; ++o) acc[o] += E[(long long)(o * NA + a) * G.n_elems + e];
+        for (int o = 0; o < 2; ++o) acc[o] += E[(long long)(o * 8 + a) * G.n_elems + e];
       }
     }
   }
@@ -147,86 +128,56 @@ __global__ void __launch_bounds__(256)
     out0[i] = o;
     return;
   }
-  if (out0) out0[i] = make_double2(acc[0], acc[1]);
-  if (NO == 4 && out1) out1[i] = make_double2(acc[2 % NO], acc[3 % NO]);
+  out0[i] = make_double2(acc[0], acc[1]);
 }
 
-template <int DIM>
-int launch_dim(pf_problem* pb, int mode, const double* U, const double* Uprev, const double* v,
-               const double* F0, const double* eps_dev, double* out0, double* out1,
-               double* vjp_part, double* coef, hipStream_t s) {
-  const Geo& G = pb->geo;
-  const unsigned eb = (unsigned)((G.n_elems + kElemBlock - 1) / kElemBlock);
-  const dim3 nb((unsigned)(((long long)G.nn[0] * G.nn[1] + 255) / 256), (unsigned)G.nn[2]);
-  auto U2 = reinterpret_cast<const double2*>(U);
-  auto P2 = reinterpret_cast<const double2*>(Uprev);
-  auto V2 = reinterpret_cast<const double2*>(v);
-  switch (mode) {
-    case MODE_RES:
-      hipLaunchKernelGGL((k_elem<DIM, MODE_RES>), dim3(eb), dim3(kElemBlock), 0, s, G, U2, P2,
-                         nullptr, nullptr, pb->elem_buf, nullptr, coef);
-      break;
-    case MODE_FD:
-      hipLaunchKernelGGL((k_elem<DIM, MODE_FD>), dim3(eb), dim3(kElemBlock), 0, s, G, U2, P2, V2,
-                         eps_dev, pb->elem_buf, nullptr, nullptr);
-      break;
-    case MODE_JVP:
-      hipLaunchKernelGGL((k_elem<DIM, MODE_JVP>), dim3(eb), dim3(kElemBlock), 0, s, G, U2, P2, V2,
-                         nullptr, pb->elem_buf, nullptr, nullptr);
-      break;
-    case MODE_VJPU:
-      hipLaunchKernelGGL((k_elem<DIM, MODE_VJPU>), dim3(eb), dim3(kElemBlock), 0, s, G, U2, P2, V2,
-                         nullptr, pb->elem_buf, nullptr, nullptr);
-      break;
-    default:
-      hipLaunchKernelGGL((k_elem<DIM, MODE_VJP>), dim3(eb), dim3(kElemBlock), 0, s, G, U2, P2, V2,
-                         nullptr, pb->elem_buf, vjp_part, nullptr);
-      break;
-  }
-  PF_HIP_CHECK(hipGetLastError());
-  if (mode == MODE_VJP) {
-    hipLaunchKernelGGL((k_gather<DIM, 4>), dim3(nb), dim3(256), 0, s, G, pb->elem_buf,
-                       reinterpret_cast<double2*>(out0), reinterpret_cast<double2*>(out1),
-                       nullptr, nullptr, 0);
-  } else {
-    hipLaunchKernelGGL((k_gather<DIM, 2>), dim3(nb), dim3(256), 0, s, G, pb->elem_buf,
-                       reinterpret_cast<double2*>(out0), nullptr,
-                       reinterpret_cast<const double2*>(F0), eps_dev, mode == MODE_FD ? 1 : 0);
-  }
+template <int MODE>
+int launch_tile2(const Geo& G, const double* U, const double* Uprev, const double* v,
+                 const double* F0, const double* eps_dev, double* out0, double* out1,
+                 double* vjp_part, double* coef, hipStream_t s) {
+  hipLaunchKernelGGL((k_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G,
+                     reinterpret_cast<const double2*>(U), reinterpret_cast<const double2*>(Uprev),
+                     reinterpret_cast<const double2*>(v), eps_dev,
+                     reinterpret_cast<const double2*>(F0), reinterpret_cast<double2*>(out0),
+                     reinterpret_cast<double2*>(out1), vjp_part, coef);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
+}
+
+// 2-D thermal modes.  MODE_VJPP's one output goes through out0.
+int launch_dim2(const Geo& G, int mode, const double* U, const double* Uprev, const double* v,
+                const double* F0, const double* eps_dev, double* out0, double* out1,
+                double* vjp_part, double* coef, hipStream_t s) {
+  switch (mode) {
+    case MODE_RES:
+      return launch_tile2<MODE_RES>(G, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+    case MODE_FD:
+      return launch_tile2<MODE_FD>(G, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+    case MODE_JVP:
+      return launch_tile2<MODE_JVP>(G, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+    case MODE_VJPU:
+      return launch_tile2<MODE_VJPU>(G, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+    case MODE_VJPP:
+      return launch_tile2<MODE_VJPP>(G, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+    default:
+      return launch_tile2<MODE_VJP>(G, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+  }
 }
 
 }  // namespace
 
-long long residual2_elem_len(const Geo& G) { return (long long)2 * 4 * G.n_elems; }
-
-int launch_residual2(const Geo& G, double* elem, const double* U, const double* Uprev, double* F,
-                     hipStream_t s) {
-  const unsigned eb = (unsigned)((G.n_elems + kElemBlock - 1) / kElemBlock);
-  const dim3 nb((unsigned)(((long long)G.nn[0] * G.nn[1] + 255) / 256), (unsigned)G.nn[2]);
-  hipLaunchKernelGGL((k_elem<2, MODE_RES>), dim3(eb), dim3(kElemBlock), 0, s, G,
-                     reinterpret_cast<const double2*>(U), reinterpret_cast<const double2*>(Uprev),
-                     nullptr, nullptr, elem, nullptr, nullptr);
-  PF_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL((k_gather<2, 2>), dim3(nb), dim3(256), 0, s, G, elem,
-                     reinterpret_cast<double2*>(F), nullptr, nullptr, nullptr, 0);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+int launch_residual2(const Geo& G, const double* U, const double* Uprev, double* F, hipStream_t s) {
+  return launch_tile2<MODE_RES>(G, U, Uprev, nullptr, nullptr, nullptr, F, nullptr, nullptr, nullptr,
+                                s);
 }
 
-int launch_gather2(pf_problem* pb, double* out0, const double* F0, const double* eps_dev, int fd,
+int launch_gather3(pf_problem* pb, double* out0, const double* F0, const double* eps_dev, int fd,
                    hipStream_t s) {
   const Geo& G = pb->geo;
   const dim3 nb((unsigned)(((long long)G.nn[0] * G.nn[1] + 255) / 256), (unsigned)G.nn[2]);
-  if (G.dim == 3)
-    hipLaunchKernelGGL((k_gather<3, 2>), dim3(nb), dim3(256), 0, s, G, pb->elem_buf,
-                       reinterpret_cast<double2*>(out0), nullptr,
-                       reinterpret_cast<const double2*>(F0), eps_dev, fd);
-  else
-    hipLaunchKernelGGL((k_gather<2, 2>), dim3(nb), dim3(256), 0, s, G, pb->elem_buf,
-                       reinterpret_cast<double2*>(out0), nullptr,
-                       reinterpret_cast<const double2*>(F0), eps_dev, fd);
+  hipLaunchKernelGGL(k_gather3, dim3(nb), dim3(256), 0, s, G, pb->elem_buf,
+                     reinterpret_cast<double2*>(out0), reinterpret_cast<const double2*>(F0),
+                     eps_dev, fd);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }
@@ -237,22 +188,21 @@ int launch_residual_family(pf_problem* pb, int mode, const double* U, const doub
                            double* coef) {
   if (pb->model == 1) return launch_alloy(pb, mode, U, Uprev, v, F0, eps_dev, out0, coef, s);
   if (pb->model == 2) return launch_fg(pb, mode, U, Uprev, v, F0, eps_dev, out0, coef, s);
+  // MODE_VJPP: out1 receives (dF/dUprev)^T w; its kernels write their one
+  // output through out0 (which the parameter sums alone leave NULL)
   if (mode == MODE_VJPP) {
-    // out1 receives (dF/dUprev)^T w; the fused 3-D kernel writes its one
-    // output through out0, the 2-D path runs the full adjoint without gU
-    if (pb->geo.dim == 3)
-      return launch_fused3(pb, MODE_VJPP, U, Uprev, v, F0, eps_dev, out1, nullptr, vjp_part, coef, s);
-    return launch_dim<2>(pb, MODE_VJP, U, Uprev, v, F0, eps_dev, nullptr, out1, vjp_part, coef, s);
+    out0 = out1;
+    out1 = nullptr;
   }
   if (pb->geo.dim == 3)
     return launch_fused3(pb, mode, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
-  return launch_dim<2>(pb, mode, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
+  return launch_dim2(pb->geo, mode, U, Uprev, v, F0, eps_dev, out0, out1, vjp_part, coef, s);
 }
 
 // Number of per-block partial sums the VJP writes (one per workgroup).
 int elem_blocks(const pf_problem* pb) {
   if (pb->geo.dim == 3) return fused3_tiles(pb->geo);
-  return (int)((pb->geo.n_elems + kElemBlock - 1) / kElemBlock);
+  return (int)tile2_blocks(pb->geo);
 }
 
 }  // namespace pf
