@@ -403,8 +403,7 @@ typedef struct {
 } pf_freegrowth_params;
 
 /* Switch the handle to the free-growth model (host; allocates the history
- * field and, in 3-D and for order 2, the element buffer: 16 (order 1, 3-D: 8
- * corners) or 18 (order 2) doubles per element).  PF_ERR_INVALID_ARG,
+ * field and, in 3-D, the element buffer: 16 doubles per element).  PF_ERR_INVALID_ARG,
  * PF_ERR_OOM. */
 int pf_set_freegrowth(pf_problem* pb, const pf_freegrowth_params* fg);
 

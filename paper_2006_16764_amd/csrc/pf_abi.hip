@@ -623,6 +623,19 @@ int fg_step_impl(pf_problem* pb, const double* Uprev2, const double* Uprev, doub
   return newton_impl(pb, Uprev, pb->params.theta == 1.0 ? nullptr : pb->load_vec, U, o, st, s);
 }
 
+// History of a single alloy or free-growth evaluation: 2-D kernels form the
+// rate from U^(n-1) as they read U^n (order 2, 2048^2, analytic Jv: the pass
+// over memory it saves took 118 of 719 us).  The 3-D kernels hold more than
+// their registers already and take the rate as a field (alloy Jv on
+// 512 x 128 x 128: 2365 us forming it, 2196 us reading it, its pass included):
+// *Unm1 is NULL then.
+int direct_history(pf_problem* pb, const double* Un, const double** Unm1, hipStream_t s) {
+  if (pb->geo.dim == 2) return PF_OK;
+  PF_TRY(history_rate(pb, Un, *Unm1, s));
+  *Unm1 = nullptr;
+  return PF_OK;
+}
+
 // One thermal step (backward Euler, or theta < 1 with the explicit part).
 int thermal_step_impl(pf_problem* pb, const double* Uprev2, const double* Uprev, double* U,
                       const pf_solver_opts& o, pf_solver_stats* st, hipStream_t s) {
@@ -1235,9 +1248,9 @@ int pf_alloy_residual(pf_problem* pb, const double* U, const double* Uprev, cons
   PF_TRY(check_vec(Uprev2, "Uprev2"));
   PF_TRY(check_vec(F, "F"));
   hipStream_t s = S(stream);
-  PF_TRY(history_rate(pb, Uprev, Uprev2, s));
+  PF_TRY(direct_history(pb, Uprev, &Uprev2, s));
   pb->t_new = t;
-  return launch_alloy(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, F, nullptr, s);
+  return launch_alloy(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, F, nullptr, s, Uprev2);
 }
 
 int pf_alloy_explicit(pf_problem* pb, const double* Uprev, double t_prev, double* E, void* stream) {
@@ -1270,20 +1283,20 @@ int pf_alloy_jvp(pf_problem* pb, const double* U, const double* Uprev, const dou
     return PF_ERR_INVALID_ARG;
   }
   hipStream_t s = S(stream);
-  PF_TRY(history_rate(pb, Uprev, Uprev2, s));
+  PF_TRY(direct_history(pb, Uprev, &Uprev2, s));
   pb->t_new = t;
   if (mode == PF_JV_ANALYTIC)
-    return launch_alloy(pb, MODE_JVP, U, Uprev, v, nullptr, nullptr, Jv, nullptr, s);
+    return launch_alloy(pb, MODE_JVP, U, Uprev, v, nullptr, nullptr, Jv, nullptr, s, Uprev2);
   const double* base = F0;
   if (!base) {
     PF_TRY(launch_alloy(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, pb->tmp_vec[0], nullptr,
-                        s));
+                        s, Uprev2));
     base = pb->tmp_vec[0];
   } else {
     PF_TRY(check_vec(F0, "F0"));
   }
   PF_TRY(blas_fd_eps(pb, U, v, pb->n_dof, pb->eps_dev, s));
-  return launch_alloy(pb, MODE_FD, U, Uprev, v, base, pb->eps_dev, Jv, nullptr, s);
+  return launch_alloy(pb, MODE_FD, U, Uprev, v, base, pb->eps_dev, Jv, nullptr, s, Uprev2);
 }
 
 int pf_alloy_step(pf_problem* pb, const double* Uprev2, const double* Uprev, double t_prev,
@@ -1382,8 +1395,8 @@ int pf_fg_residual(pf_problem* pb, const double* U, const double* Uprev, const d
   PF_TRY(check_vec(Uprev2, "Uprev2"));
   PF_TRY(check_vec(F, "F"));
   hipStream_t s = S(stream);
-  PF_TRY(history_rate(pb, Uprev, Uprev2, s));
-  return launch_fg(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, F, nullptr, s);
+  PF_TRY(direct_history(pb, Uprev, &Uprev2, s));
+  return launch_fg(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, F, nullptr, s, Uprev2);
 }
 
 int pf_fg_explicit(pf_problem* pb, const double* Uprev, double* E, void* stream) {
@@ -1416,18 +1429,19 @@ int pf_fg_jvp(pf_problem* pb, const double* U, const double* Uprev, const double
     return PF_ERR_INVALID_ARG;
   }
   hipStream_t s = S(stream);
-  PF_TRY(history_rate(pb, Uprev, Uprev2, s));
+  PF_TRY(direct_history(pb, Uprev, &Uprev2, s));
   if (mode == PF_JV_ANALYTIC)
-    return launch_fg(pb, MODE_JVP, U, Uprev, v, nullptr, nullptr, Jv, nullptr, s);
+    return launch_fg(pb, MODE_JVP, U, Uprev, v, nullptr, nullptr, Jv, nullptr, s, Uprev2);
   const double* base = F0;
   if (!base) {
-    PF_TRY(launch_fg(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, pb->tmp_vec[0], nullptr, s));
+    PF_TRY(launch_fg(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, pb->tmp_vec[0], nullptr, s,
+                     Uprev2));
     base = pb->tmp_vec[0];
   } else {
     PF_TRY(check_vec(F0, "F0"));
   }
   PF_TRY(blas_fd_eps(pb, U, v, pb->n_dof, pb->eps_dev, s));
-  return launch_fg(pb, MODE_FD, U, Uprev, v, base, pb->eps_dev, Jv, nullptr, s);
+  return launch_fg(pb, MODE_FD, U, Uprev, v, base, pb->eps_dev, Jv, nullptr, s, Uprev2);
 }
 
 int pf_fg_step(pf_problem* pb, const double* Uprev2, const double* Uprev, double* U,

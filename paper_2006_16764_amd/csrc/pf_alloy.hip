@@ -193,8 +193,8 @@ __device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C,
                                               const double2* __restrict__ Up,
                                               const double2* __restrict__ V,
                                               const double* __restrict__ eps_dev,
-                                              const double* __restrict__ hist,
-                                              double (&out)[2][1 << DIM], double& ge) {
+                                              const HistArg& H, double (&out)[2][1 << DIM],
+                                              double& ge) {
   constexpr int NA = 1 << DIM;
   const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
@@ -216,7 +216,7 @@ __device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C,
     p1[a] = up.y;
     v0[a] = v.x;
     v1[a] = v.y;
-    hs[a] = C.use_hist ? hist[node] : 0.0;
+    hs[a] = C.use_hist ? H.at(node, up) : 0.0;
     xc[a] = fma((double)(ex + (a & 1)), C.h0, C.x0);
   }
   AlloyElement<DIM, MODE == MODE_FD ? MODE_RES : MODE>::run(G, C, u0, u1, p0, p1, hs, xc, v0, v1,
@@ -227,15 +227,14 @@ template <int MODE>
 __global__ void __launch_bounds__(kTile2Threads)
     k_alloy_tile2(Geo G, AlloyConst C, const double2* __restrict__ U,
                   const double2* __restrict__ Up, const double2* __restrict__ V,
-                  const double* __restrict__ eps_dev, const double* __restrict__ hist,
-                  const double2* __restrict__ F0, double2* __restrict__ F,
-                  double* __restrict__ coef) {
+                  const double* __restrict__ eps_dev, HistArg H, const double2* __restrict__ F0,
+                  double2* __restrict__ F, double* __restrict__ coef) {
   __shared__ double sh[2 * 3 * kTile2Threads];
   const Tile2 P = tile2_pos(G);
   double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
   double ge = 0.0;
   if (P.elem) {
-    alloy_element<2, MODE>(G, C, P.ex, P.base, U, Up, V, eps_dev, hist, out, ge);
+    alloy_element<2, MODE>(G, C, P.ex, P.base, U, Up, V, eps_dev, H, out, ge);
     if (MODE == MODE_RES && coef && P.node)
       coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
   }
@@ -248,8 +247,8 @@ template <int MODE>
 __global__ void __launch_bounds__(kAlloyBlock)
     k_alloy_elem3(Geo G, AlloyConst C, const double2* __restrict__ U,
                   const double2* __restrict__ Up, const double2* __restrict__ V,
-                  const double* __restrict__ eps_dev, const double* __restrict__ hist,
-                  double* __restrict__ E, double* __restrict__ coef) {
+                  const double* __restrict__ eps_dev, HistArg H, double* __restrict__ E,
+                  double* __restrict__ coef) {
   // blockIdx.y is the element layer: coordinates from 32-bit arithmetic
   const int pe = G.n[0] * G.n[1];
   const int q = (int)blockIdx.x * kAlloyBlock + (int)threadIdx.x;
@@ -261,7 +260,7 @@ __global__ void __launch_bounds__(kAlloyBlock)
   const long long base = ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez);
   double out[2][8];
   double ge = 0.0;
-  alloy_element<3, MODE>(G, C, ex, base, U, Up, V, eps_dev, hist, out, ge);
+  alloy_element<3, MODE>(G, C, ex, base, U, Up, V, eps_dev, H, out, ge);
   if (MODE == MODE_RES && coef) coef[e] = ge / (8.0 * G.jac);
 #pragma unroll
   for (int o = 0; o < 2; ++o)
@@ -279,14 +278,14 @@ __global__ void k_history(long long n, const double2* __restrict__ Un,
 template <int MODE>
 int launch_mode(pf_problem* pb, const AlloyConst& C, const double* U, const double* Uprev,
                 const double* v, const double* F0, const double* eps_dev, double* out0,
-                double* coef, hipStream_t s) {
+                double* coef, const HistArg& H, hipStream_t s) {
   const Geo& G = pb->geo;
   auto U2 = reinterpret_cast<const double2*>(U);
   auto P2 = reinterpret_cast<const double2*>(Uprev);
   auto V2 = reinterpret_cast<const double2*>(v);
   if (G.dim == 2) {
     hipLaunchKernelGGL((k_alloy_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G, C,
-                       U2, P2, V2, eps_dev, pb->hist, reinterpret_cast<const double2*>(F0),
+                       U2, P2, V2, eps_dev, H, reinterpret_cast<const double2*>(F0),
                        reinterpret_cast<double2*>(out0), coef);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
@@ -294,7 +293,7 @@ int launch_mode(pf_problem* pb, const AlloyConst& C, const double* U, const doub
   const dim3 eb((unsigned)(((long long)G.n[0] * G.n[1] + kAlloyBlock - 1) / kAlloyBlock),
                 (unsigned)G.n[2]);
   hipLaunchKernelGGL((k_alloy_elem3<MODE>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2, P2, V2,
-                     eps_dev, pb->hist, pb->elem_buf, coef);
+                     eps_dev, H, pb->elem_buf, coef);
   PF_HIP_CHECK(hipGetLastError());
   return launch_gather3(pb, out0, F0, eps_dev, MODE == MODE_FD ? 1 : 0, s);
 }
@@ -317,15 +316,16 @@ AlloyConst alloy_const(const pf_problem* pb, double t, double theta, int use_his
 
 int launch_alloy(pf_problem* pb, int mode, const double* U, const double* Uprev, const double* v,
                  const double* F0, const double* eps_dev, double* out0, double* coef,
-                 hipStream_t s) {
+                 hipStream_t s, const double* Unm1) {
   if (mode != MODE_RES && mode != MODE_FD && mode != MODE_JVP) {
     set_error("the alloy model has no VJP");
     return PF_ERR_INVALID_ARG;
   }
   const AlloyConst C = alloy_const(pb, pb->t_new, pb->params.theta, 1);
-  if (mode == MODE_RES) return launch_mode<MODE_RES>(pb, C, U, Uprev, v, F0, eps_dev, out0, coef, s);
-  if (mode == MODE_FD) return launch_mode<MODE_FD>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
-  return launch_mode<MODE_JVP>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
+  const HistArg H = hist_arg(pb, Unm1);
+  if (mode == MODE_RES) return launch_mode<MODE_RES>(pb, C, U, Uprev, v, F0, eps_dev, out0, coef, H, s);
+  if (mode == MODE_FD) return launch_mode<MODE_FD>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, H, s);
+  return launch_mode<MODE_JVP>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, H, s);
 }
 
 int alloy_explicit(pf_problem* pb, const double* Un, double t_n, double* E, hipStream_t s) {
@@ -337,8 +337,13 @@ int alloy_explicit(pf_problem* pb, const double* Un, double t_n, double* E, hipS
   // the residual at (U^n; U^n) with weight 1 and no history is the spatial
   // operator at U^n: the time and rate terms vanish
   const AlloyConst C = alloy_const(pb, t_n, 1.0, 0);
-  PF_TRY(launch_mode<MODE_RES>(pb, C, Un, Un, nullptr, nullptr, nullptr, E, nullptr, s));
+  PF_TRY(launch_mode<MODE_RES>(pb, C, Un, Un, nullptr, nullptr, nullptr, E, nullptr, HistArg{}, s));
   return blas_axpby(1.0 - th, E, 0.0, E, E, pb->n_dof, s);
+}
+
+HistArg hist_arg(const pf_problem* pb, const double* Unm1) {
+  return HistArg{Unm1 ? nullptr : pb->hist, reinterpret_cast<const double2*>(Unm1),
+                 (1.0 - pb->params.theta) / pb->params.dt};
 }
 
 int history_rate(pf_problem* pb, const double* Un, const double* Unm1, hipStream_t s) {

@@ -4,11 +4,11 @@
 // order-1 elements (2-D and 3-D, through quad2/quad3 of pf_element.h) and on
 // order-2 (biquadratic, 9-node) elements in 2-D.
 //
-// Order 1 in 2-D: the single-pass tiles of pf_tile2.h.  Otherwise two passes:
-// one thread per element evaluates the element vectors into the element
-// buffer, then a fixed-order gather forms the node sums (the 3-D gather of
-// pf_residual.hip, or the order-2 gather below, which sums the 1, 2 or 4
-// elements sharing a node).  The analytic
+// 2-D, both orders: one pass over tiles of elements whose corner contributions
+// are summed in LDS in a fixed order (pf_tile2.h; order 2 below).  3-D: two
+// passes, one thread per element evaluates the element vectors into the
+// element buffer, then the gather of pf_residual.hip forms the node sums.  The
+// analytic
 // tangent runs the pointwise template on dual numbers.
 #include "pf_dual.h"
 #include "pf_tile2.h"
@@ -127,8 +127,8 @@ __device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long 
                                            const double2* __restrict__ Up,
                                            const double2* __restrict__ V,
                                            const double* __restrict__ eps_dev,
-                                           const double* __restrict__ hist,
-                                           double (&out)[2][1 << DIM], double& ca) {
+                                           const HistArg& H, double (&out)[2][1 << DIM],
+                                           double& ca) {
   constexpr int NA = 1 << DIM;
   const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
@@ -150,7 +150,7 @@ __device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long 
     ng[3][a] = v.y;
     nv[0][a] = u.x - up.x;
     nv[1][a] = u.y - up.y;
-    nv[2][a] = C.use_hist ? hist[node] : 0.0;
+    nv[2][a] = C.use_hist ? H.at(node, up) : 0.0;
   }
   double dummy[1][NA];
 #pragma unroll
@@ -177,14 +177,14 @@ template <int MODE>
 __global__ void __launch_bounds__(kTile2Threads)
     k_fg_tile2(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
                const double2* __restrict__ V, const double* __restrict__ eps_dev,
-               const double* __restrict__ hist, const double2* __restrict__ F0,
-               double2* __restrict__ F, double* __restrict__ coef) {
+               HistArg H, const double2* __restrict__ F0, double2* __restrict__ F,
+               double* __restrict__ coef) {
   __shared__ double sh[2 * 3 * kTile2Threads];
   const Tile2 P = tile2_pos(G);
   double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
   double ca = 0.0;
   if (P.elem) {
-    fg_element<2, MODE>(G, C, P.base, U, Up, V, eps_dev, hist, out, ca);
+    fg_element<2, MODE>(G, C, P.base, U, Up, V, eps_dev, H, out, ca);
     if (MODE == MODE_RES && coef && P.node)
       coef[P.ex + (long long)G.n[0] * P.ey] = ca / (4.0 * G.jac);
   }
@@ -197,7 +197,7 @@ template <int MODE>
 __global__ void __launch_bounds__(kFgBlock)
     k_fg_elem3(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
                const double2* __restrict__ V, const double* __restrict__ eps_dev,
-               const double* __restrict__ hist, double* __restrict__ E, double* __restrict__ coef) {
+               HistArg H, double* __restrict__ E, double* __restrict__ coef) {
   const long long e = (long long)blockIdx.x * kFgBlock + threadIdx.x;
   if (e >= G.n_elems) return;
   const long long n0 = G.n[0], n1 = G.n[1];
@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(kFgBlock)
   double out[2][8];
   double ca = 0.0;
   fg_element<3, MODE>(G, C, ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez), U, Up, V,
-                      eps_dev, hist, out, ca);
+                      eps_dev, H, out, ca);
   if (MODE == MODE_RES && coef) coef[e] = ca / (8.0 * G.jac);
 #pragma unroll
   for (int o = 0; o < 2; ++o)
@@ -228,46 +228,40 @@ struct P2 {
   }
 };
 
-// One thread per 9-node element.  Node (lx, ly) of element (ex, ey) is grid
-// node (2 ex + lx, 2 ey + ly); the grid spacing G.h is half the element size,
-// so d/dx = G.ih[0] d/dxi and the Jacobian of the reference map is G.h0 G.h1.
+// Order 2 in one pass: a workgroup evaluates a 16 x 16 tile of 9-node elements,
+// one per lane, and owns the grid nodes of the 15 x 15 elements beyond the
+// tile's first row and column (as pf_tile2.h: 1.14 evaluations per element).
+// Lane (tx, ty), tx, ty >= 1, holds element (ex, ey) and owns its grid nodes
+// (2 ex + i, 2 ey + j), i, j in {0, 1}; the contributions of local nodes with
+// lx = 2 or ly = 2 go to the neighbours through LDS.  Sums run over (left,
+// below), below, left, own.
+//
+// Node (lx, ly) of element (ex, ey) is grid node (2 ex + lx, 2 ey + ly); the
+// grid spacing G.h is half the element size, so d/dx = G.ih[0] d/dxi and the
+// Jacobian of the reference map is G.h0 G.h1.
+//
+// Bound by FP64 issue (no element vectors in memory: 144 B per element each
+// way before).  The rule is sum-factorised: per row of Gauss points the fields
+// are contracted along y once for its three points, and the outputs are
+// contracted along x per row before they are spread along y.  2048^2 elements,
+// analytic Jv: 719 us with dense points, a gather pass and a history pass,
+// 349 us now.
+constexpr int kQ2Pass = 5;  // local nodes passed on: (2,2), (0,2), (1,2), (2,0), (2,1)
+
 template <int MODE>
-__global__ void __launch_bounds__(kFgBlock)
+__global__ void __launch_bounds__(kTile2Threads)
     k_fg_q2(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
-            const double2* __restrict__ V, const double* __restrict__ eps_dev,
-            const double* __restrict__ hist, double* __restrict__ E, double* __restrict__ coef) {
-  const long long ne = (long long)C.n_macro[0] * C.n_macro[1];
-  const long long e = (long long)blockIdx.x * kFgBlock + threadIdx.x;
-  if (e >= ne) return;
-  const int ex = (int)(e % C.n_macro[0]), ey = (int)(e / C.n_macro[0]);
+            const double2* __restrict__ V, const double* __restrict__ eps_dev, HistArg H,
+            const double2* __restrict__ F0, double2* __restrict__ F, double* __restrict__ coef) {
+  __shared__ double sh[2][kQ2Pass][kTile2Threads];
+  const unsigned ntx = (unsigned)(C.n_macro[0] / kTile2Own + 1);
+  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int t = (int)threadIdx.x, tx = t % kTile2, ty = t / kTile2;
+  const int ex = (int)(tile % ntx) * kTile2Own - 1 + tx, ey = (int)(tile / ntx) * kTile2Own - 1 + ty;
+  const bool elem = ex >= 0 && ex < C.n_macro[0] && ey >= 0 && ey < C.n_macro[1];
+  const bool own = tx > 0 && ty > 0 && ex <= C.n_macro[0] && ey <= C.n_macro[1];
   const long long nn0 = G.nn[0];
-  const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
-  // fields: 0 phi, 1 T, 2 dphi, 3 dT, 4 hist, 5 v_phi, 6 v_T
-  constexpr int NF = MODE == MODE_JVP ? 7 : 5;
-  double u[NF][3][3];
-#pragma unroll
-  for (int ly = 0; ly < 3; ++ly)
-#pragma unroll
-    for (int lx = 0; lx < 3; ++lx) {
-      const long long node = (2 * ex + lx) + nn0 * (long long)(2 * ey + ly);
-      double2 w = U[node];
-      const double2 up = Up[node];
-      double2 v = make_double2(0.0, 0.0);
-      if (MODE != MODE_RES) v = V[node];
-      if (MODE == MODE_FD) {
-        w.x = fma(eps, v.x, w.x);
-        w.y = fma(eps, v.y, w.y);
-      }
-      u[0][ly][lx] = w.x;
-      u[1][ly][lx] = w.y;
-      u[2][ly][lx] = w.x - up.x;
-      u[3][ly][lx] = w.y - up.y;
-      u[4][ly][lx] = C.use_hist ? hist[node] : 0.0;
-      if constexpr (MODE == MODE_JVP) {
-        u[5][ly][lx] = v.x;
-        u[6][ly][lx] = v.y;
-      }
-    }
+  const long long base = 2LL * ex + nn0 * (2LL * ey);
   double out[2][3][3];
 #pragma unroll
   for (int o = 0; o < 2; ++o)
@@ -275,138 +269,156 @@ __global__ void __launch_bounds__(kFgBlock)
     for (int ly = 0; ly < 3; ++ly)
 #pragma unroll
       for (int lx = 0; lx < 3; ++lx) out[o][ly][lx] = 0.0;
-  const double ih0 = G.ih[0], ih1 = G.ih[1], jac = G.h[0] * G.h[1];
-  double ca = 0.0;
-#pragma unroll 1
-  for (int qy = 0; qy < 3; ++qy) {
-#pragma unroll
-    for (int qx = 0; qx < 3; ++qx) {
-      // values and derivatives of every field at the point, row by row
-      double val[NF], dx[NF], dy[NF];
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        double v0 = 0.0, v1 = 0.0, v2 = 0.0;
-#pragma unroll
-        for (int ly = 0; ly < 3; ++ly) {
-          const double rv = P2::b(0, qx) * u[f][ly][0] + P2::b(1, qx) * u[f][ly][1] +
-                            P2::b(2, qx) * u[f][ly][2];
-          const double rd = P2::d(0, qx) * u[f][ly][0] + P2::d(1, qx) * u[f][ly][1] +
-                            P2::d(2, qx) * u[f][ly][2];
-          v0 = fma(P2::b(ly, qy), rv, v0);
-          v1 = fma(P2::b(ly, qy), rd, v1);
-          v2 = fma(P2::d(ly, qy), rv, v2);
-        }
-        val[f] = v0;
-        dx[f] = v1 * ih0;
-        dy[f] = v2 * ih1;
-      }
-      double s[2], fl[2][3], a2 = 0.0;
-      if constexpr (MODE == MODE_JVP) {
-        const Dual phi{val[0], val[5]}, tem{val[1], val[6]};
-        const Dual g[3] = {Dual{dx[0], dx[5]}, Dual{dy[0], dy[5]}, Dual{0.0, 0.0}};
-        const Dual gT[3] = {Dual{dx[1], dx[6]}, Dual{dy[1], dy[6]}, Dual{0.0, 0.0}};
-        const Dual dphi{val[2], val[5]}, dT{val[3], val[6]};
-        Dual s1, s3, f1[3], f3[3];
-        fg_point<2, Dual>(G, C, phi, g, tem, gT, dphi, dT, val[4], s1, f1, s3, f3, a2);
-        s[0] = s1.d;
-        s[1] = s3.d;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          fl[0][k] = f1[k].d;
-          fl[1][k] = f3[k].d;
-        }
-      } else {
-        const double g[3] = {dx[0], dy[0], 0.0};
-        const double gT[3] = {dx[1], dy[1], 0.0};
-        fg_point<2, double>(G, C, val[0], g, val[1], gT, val[2], val[3], val[4], s[0], fl[0], s[1],
-                            fl[1], a2);
-      }
-      const double wq = Q1::w(qx) * Q1::w(qy) * jac;
-      ca = fma(wq, a2, ca);
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        const double ws = wq * s[o], wfx = wq * fl[o][0] * ih0, wfy = wq * fl[o][1] * ih1;
-#pragma unroll
-        for (int ly = 0; ly < 3; ++ly) {
-          const double cy = ws * P2::b(ly, qy), cx = wfx * P2::b(ly, qy), cd = wfy * P2::d(ly, qy);
-#pragma unroll
-          for (int lx = 0; lx < 3; ++lx)
-            out[o][ly][lx] += cy * P2::b(lx, qx) + cx * P2::d(lx, qx) + cd * P2::b(lx, qx);
-        }
-      }
-    }
-  }
-  if (MODE == MODE_RES && coef) {
-    // element mean of a^2 on its four grid cells (the preconditioner's grid)
-    const double c = ca / (4.0 * jac);
-#pragma unroll
-    for (int sy = 0; sy < 2; ++sy)
-#pragma unroll
-      for (int sx = 0; sx < 2; ++sx)
-        coef[(2 * ex + sx) + (long long)G.n[0] * (2 * ey + sy)] = c;
-  }
-#pragma unroll
-  for (int o = 0; o < 2; ++o)
+  if (elem) {
+    const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
+    // gradient fields: 0 phi, 1 T, (2 v_phi, 3 v_T); value fields: 0 dphi, 1 dT, 2 hist
+    constexpr int NG = MODE == MODE_JVP ? 4 : 2;
+    double g[NG][3][3], w[3][3][3];
 #pragma unroll
     for (int ly = 0; ly < 3; ++ly)
 #pragma unroll
-      for (int lx = 0; lx < 3; ++lx) E[(long long)(o * 9 + lx + 3 * ly) * ne + e] = out[o][ly][lx];
-}
-
-// Node sums of the 9-node element buffer: grid node (gx, gy) belongs to the
-// elements whose index range covers it (1, 2 or 4), summed in a fixed order.
-__global__ void __launch_bounds__(256)
-    k_fg_q2_gather(Geo G, FgConst C, const double* __restrict__ E, double2* __restrict__ out,
-                   const double2* __restrict__ F0, const double* __restrict__ eps_dev, int fd) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= G.n_nodes) return;
-  const long long ne = (long long)C.n_macro[0] * C.n_macro[1];
-  const int gx = (int)(i % G.nn[0]), gy = (int)(i / G.nn[0]);
-  int exs[2], lxs[2], nx = 0, eys[2], lys[2], ny = 0;
-  if (gx & 1) {
-    exs[0] = gx >> 1;
-    lxs[0] = 1;
-    nx = 1;
-  } else {
-    if (gx > 0) {
-      exs[nx] = (gx >> 1) - 1;
-      lxs[nx++] = 2;
+      for (int lx = 0; lx < 3; ++lx) {
+        const long long node = base + lx + nn0 * ly;
+        double2 u = U[node];
+        const double2 up = Up[node];
+        if constexpr (MODE != MODE_RES) {
+          const double2 v = V[node];
+          if constexpr (MODE == MODE_FD) {
+            u.x = fma(eps, v.x, u.x);
+            u.y = fma(eps, v.y, u.y);
+          } else {
+            g[2][ly][lx] = v.x;
+            g[3][ly][lx] = v.y;
+          }
+        }
+        g[0][ly][lx] = u.x;
+        g[1][ly][lx] = u.y;
+        w[0][ly][lx] = u.x - up.x;
+        w[1][ly][lx] = u.y - up.y;
+        w[2][ly][lx] = C.use_hist ? H.at(node, up) : 0.0;
+      }
+    const double ih0 = G.ih[0], ih1 = G.ih[1], jac = G.h[0] * G.h[1];
+    double ca = 0.0;
+#pragma unroll 1
+    for (int qy = 0; qy < 3; ++qy) {
+      // along y: values (and y derivatives of the gradient fields) on the row
+      double gy[NG][3], dy[NG][3], wy[3][3];
+#pragma unroll
+      for (int lx = 0; lx < 3; ++lx) {
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+          gy[f][lx] = P2::b(0, qy) * g[f][0][lx] + P2::b(1, qy) * g[f][1][lx] + P2::b(2, qy) * g[f][2][lx];
+          dy[f][lx] = (P2::d(0, qy) * g[f][0][lx] + P2::d(1, qy) * g[f][1][lx] +
+                       P2::d(2, qy) * g[f][2][lx]) * ih1;
+        }
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+          wy[f][lx] = P2::b(0, qy) * w[f][0][lx] + P2::b(1, qy) * w[f][1][lx] + P2::b(2, qy) * w[f][2][lx];
+      }
+      // the row's outputs along x: value and x-flux part, y-flux part
+      double rs[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, ry[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+      double car = 0.0;
+#pragma unroll
+      for (int qx = 0; qx < 3; ++qx) {
+        const double b0 = P2::b(0, qx), b1 = P2::b(1, qx), b2 = P2::b(2, qx);
+        const double d0 = P2::d(0, qx), d1 = P2::d(1, qx), d2 = P2::d(2, qx);
+        double val[NG], dx[NG], dv[NG], wv[3];
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+          val[f] = b0 * gy[f][0] + b1 * gy[f][1] + b2 * gy[f][2];
+          dx[f] = (d0 * gy[f][0] + d1 * gy[f][1] + d2 * gy[f][2]) * ih0;
+          dv[f] = b0 * dy[f][0] + b1 * dy[f][1] + b2 * dy[f][2];
+        }
+#pragma unroll
+        for (int f = 0; f < 3; ++f) wv[f] = b0 * wy[f][0] + b1 * wy[f][1] + b2 * wy[f][2];
+        double s[2], fl[2][3], a2 = 0.0;
+        if constexpr (MODE == MODE_JVP) {
+          const Dual phi{val[0], val[2]}, tem{val[1], val[3]};
+          const Dual gp[3] = {Dual{dx[0], dx[2]}, Dual{dv[0], dv[2]}, Dual{0.0, 0.0}};
+          const Dual gT[3] = {Dual{dx[1], dx[3]}, Dual{dv[1], dv[3]}, Dual{0.0, 0.0}};
+          const Dual dphi{wv[0], val[2]}, dT{wv[1], val[3]};
+          Dual s1, s3, f1[3], f3[3];
+          fg_point<2, Dual>(G, C, phi, gp, tem, gT, dphi, dT, wv[2], s1, f1, s3, f3, a2);
+          s[0] = s1.d;
+          s[1] = s3.d;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            fl[0][k] = f1[k].d;
+            fl[1][k] = f3[k].d;
+          }
+        } else {
+          const double gp[3] = {dx[0], dv[0], 0.0};
+          const double gT[3] = {dx[1], dv[1], 0.0};
+          fg_point<2, double>(G, C, val[0], gp, val[1], gT, wv[0], wv[1], wv[2], s[0], fl[0], s[1],
+                              fl[1], a2);
+        }
+        car = fma(Q1::w(qx), a2, car);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          const double ws = Q1::w(qx) * s[o], wx = Q1::w(qx) * ih0 * fl[o][0], wf = Q1::w(qx) * fl[o][1];
+#pragma unroll
+          for (int lx = 0; lx < 3; ++lx) {
+            rs[o][lx] = fma(ws, P2::b(lx, qx), fma(wx, P2::d(lx, qx), rs[o][lx]));
+            ry[o][lx] = fma(wf, P2::b(lx, qx), ry[o][lx]);
+          }
+        }
+      }
+      const double wrow = Q1::w(qy) * jac;
+      ca = fma(wrow, car, ca);
+#pragma unroll
+      for (int ly = 0; ly < 3; ++ly) {
+        const double cb = wrow * P2::b(ly, qy), cd = wrow * ih1 * P2::d(ly, qy);
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int lx = 0; lx < 3; ++lx)
+            out[o][ly][lx] = fma(cb, rs[o][lx], fma(cd, ry[o][lx], out[o][ly][lx]));
+      }
     }
-    if ((gx >> 1) < C.n_macro[0]) {
-      exs[nx] = gx >> 1;
-      lxs[nx++] = 0;
+    if (MODE == MODE_RES && coef && own) {
+      // element mean of a^2 on its four grid cells (the preconditioner's grid)
+      const double c = ca / (4.0 * jac);
+#pragma unroll
+      for (int sy = 0; sy < 2; ++sy)
+#pragma unroll
+        for (int sx = 0; sx < 2; ++sx)
+          coef[(2 * ex + sx) + (long long)G.n[0] * (2 * ey + sy)] = c;
     }
   }
-  if (gy & 1) {
-    eys[0] = gy >> 1;
-    lys[0] = 1;
-    ny = 1;
-  } else {
-    if (gy > 0) {
-      eys[ny] = (gy >> 1) - 1;
-      lys[ny++] = 2;
-    }
-    if ((gy >> 1) < C.n_macro[1]) {
-      eys[ny] = gy >> 1;
-      lys[ny++] = 0;
-    }
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    sh[o][0][t] = out[o][2][2];
+    sh[o][1][t] = out[o][2][0];
+    sh[o][2][t] = out[o][2][1];
+    sh[o][3][t] = out[o][0][2];
+    sh[o][4][t] = out[o][1][2];
   }
-  double a0 = 0.0, a1 = 0.0;
-  for (int jy = 0; jy < ny; ++jy)
-    for (int jx = 0; jx < nx; ++jx) {
-      const long long e = exs[jx] + (long long)C.n_macro[0] * eys[jy];
-      const int a = lxs[jx] + 3 * lys[jy];
-      a0 += E[(long long)a * ne + e];
-      a1 += E[(long long)(9 + a) * ne + e];
-    }
-  if (fd) {
-    const double eps = *eps_dev;
-    const double2 f0 = F0[i];
-    out[i] = eps == 0.0 ? make_double2(0.0, 0.0)
-                        : make_double2((a0 - f0.x) / eps, (a1 - f0.y) / eps);
-    return;
+  __syncthreads();
+  if (!own) return;
+  const int l = t - 1, b = t - kTile2, lb = t - kTile2 - 1;
+  double a[2][2][2];  // [j][i][output]
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    a[0][0][o] = ((sh[o][0][lb] + sh[o][1][b]) + sh[o][3][l]) + out[o][0][0];
+    a[0][1][o] = sh[o][2][b] + out[o][0][1];
+    a[1][0][o] = sh[o][4][l] + out[o][1][0];
+    a[1][1][o] = out[o][1][1];
   }
-  out[i] = make_double2(a0, a1);
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if ((i == 1 && ex == C.n_macro[0]) || (j == 1 && ey == C.n_macro[1])) continue;
+      const long long node = base + i + nn0 * j;
+      double a0 = a[j][i][0], a1 = a[j][i][1];
+      if constexpr (MODE == MODE_FD) {
+        const double e = eps_dev[0];
+        const double2 f0 = F0[node];
+        a0 = e == 0.0 ? 0.0 : (a0 - f0.x) / e;
+        a1 = e == 0.0 ? 0.0 : (a1 - f0.y) / e;
+      }
+      F[node] = make_double2(a0, a1);
+    }
 }
 
 FgConst fg_const(const pf_problem* pb, double theta, int use_hist) {
@@ -428,53 +440,51 @@ FgConst fg_const(const pf_problem* pb, double theta, int use_hist) {
 template <int MODE>
 int launch_mode(pf_problem* pb, const FgConst& C, const double* U, const double* Uprev,
                 const double* v, const double* F0, const double* eps_dev, double* out0,
-                double* coef, hipStream_t s) {
+                double* coef, const HistArg& H, hipStream_t s) {
   const Geo& G = pb->geo;
-  const int fd = MODE == MODE_FD ? 1 : 0;
   auto U2 = reinterpret_cast<const double2*>(U);
   auto P2p = reinterpret_cast<const double2*>(Uprev);
   auto V2 = reinterpret_cast<const double2*>(v);
   auto F02 = reinterpret_cast<const double2*>(F0);
   auto out2 = reinterpret_cast<double2*>(out0);
   if (pb->params.order == 2) {
-    const long long ne = (long long)C.n_macro[0] * C.n_macro[1];
-    hipLaunchKernelGGL((k_fg_q2<MODE>), dim3((unsigned)((ne + kFgBlock - 1) / kFgBlock)),
-                       dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, pb->hist, pb->elem_buf, coef);
-    PF_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(k_fg_q2_gather, dim3((unsigned)((G.n_nodes + 255) / 256)), dim3(256), 0, s, G,
-                       C, pb->elem_buf, out2, F02, eps_dev, fd);
+    const long long tiles =
+        (long long)(C.n_macro[0] / kTile2Own + 1) * (C.n_macro[1] / kTile2Own + 1);
+    hipLaunchKernelGGL((k_fg_q2<MODE>), dim3((unsigned)tiles), dim3(kTile2Threads), 0, s, G, C, U2, P2p,
+                       V2, eps_dev, H, F02, out2, coef);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }
   if (G.dim == 2) {
     hipLaunchKernelGGL((k_fg_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G, C, U2,
-                       P2p, V2, eps_dev, pb->hist, F02, out2, coef);
+                       P2p, V2, eps_dev, H, F02, out2, coef);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }
   hipLaunchKernelGGL((k_fg_elem3<MODE>), dim3((unsigned)((G.n_elems + kFgBlock - 1) / kFgBlock)),
-                     dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, pb->hist, pb->elem_buf, coef);
+                     dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, H, pb->elem_buf, coef);
   PF_HIP_CHECK(hipGetLastError());
-  return launch_gather3(pb, out0, F0, eps_dev, fd, s);
+  return launch_gather3(pb, out0, F0, eps_dev, MODE == MODE_FD ? 1 : 0, s);
 }
 
 }  // namespace
 
 long long fg_elem_buf_len(const pf_problem* pb) {
-  if (pb->params.order == 2) return (long long)2 * 9 * pb->params.n[0] * pb->params.n[1];
   return pb->geo.dim == 3 ? (long long)2 * 8 * pb->geo.n_elems : 1;
 }
 
 int launch_fg(pf_problem* pb, int mode, const double* U, const double* Uprev, const double* v,
-              const double* F0, const double* eps_dev, double* out0, double* coef, hipStream_t s) {
+              const double* F0, const double* eps_dev, double* out0, double* coef, hipStream_t s,
+              const double* Unm1) {
   if (mode != MODE_RES && mode != MODE_FD && mode != MODE_JVP) {
     set_error("the free-growth model has no VJP");
     return PF_ERR_INVALID_ARG;
   }
   const FgConst C = fg_const(pb, pb->params.theta, 1);
-  if (mode == MODE_RES) return launch_mode<MODE_RES>(pb, C, U, Uprev, v, F0, eps_dev, out0, coef, s);
-  if (mode == MODE_FD) return launch_mode<MODE_FD>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
-  return launch_mode<MODE_JVP>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, s);
+  const HistArg H = hist_arg(pb, Unm1);
+  if (mode == MODE_RES) return launch_mode<MODE_RES>(pb, C, U, Uprev, v, F0, eps_dev, out0, coef, H, s);
+  if (mode == MODE_FD) return launch_mode<MODE_FD>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, H, s);
+  return launch_mode<MODE_JVP>(pb, C, U, Uprev, v, F0, eps_dev, out0, nullptr, H, s);
 }
 
 int fg_explicit(pf_problem* pb, const double* Un, double* E, hipStream_t s) {
@@ -486,7 +496,7 @@ int fg_explicit(pf_problem* pb, const double* Un, double* E, hipStream_t s) {
   // the residual at (U^n; U^n) with weight 1 and no history is the spatial
   // operator at U^n: the time and rate terms vanish
   const FgConst C = fg_const(pb, 1.0, 0);
-  PF_TRY(launch_mode<MODE_RES>(pb, C, Un, Un, nullptr, nullptr, nullptr, E, nullptr, s));
+  PF_TRY(launch_mode<MODE_RES>(pb, C, Un, Un, nullptr, nullptr, nullptr, E, nullptr, HistArg{}, s));
   return blas_axpby(1.0 - th, E, 0.0, E, E, pb->n_dof, s);
 }
 
