@@ -96,9 +96,14 @@ struct Level {
 };
 
 template <class T>
+struct Tail2;
+
+template <class T>
 struct Hier {
   std::vector<Level<T>> lv;
   bool allocated = false;
+  size_t tail_at = 0;       // 2-D: first level of the one-workgroup tail (lv.size(): none)
+  std::vector<Tail2<T>> tail;  // its kernel argument (0 or 1)
   double coarse_host[4 * kCoarseDegree];  // per-step (alpha, beta) of the coarsest solve
   double* coarse_dev = nullptr;
 };
@@ -113,9 +118,10 @@ struct GraphCache {
   const void* level0 = nullptr;
 };
 
-// Meshes up to this many unknowns apply the V-cycle as a replayed graph
-// (measured: a 150^2 free-growth step 20 % faster; at 2.1 M unknowns the two
-// copies cost more than the launches saved).
+// 3-D meshes up to this many unknowns apply the V-cycle as a replayed graph
+// (beyond, the two copies cost more than the launches saved).  2-D cycles take
+// few launches and are issued directly (150^2 free-growth step 1.20 ms either
+// way, 512^2 gradient 26.0 ms replayed, 23.9 ms issued).
 constexpr long long kGraphMaxDof = 1LL << 20;
 
 struct PcState {
@@ -673,6 +679,9 @@ __global__ void __launch_bounds__(kT)
   }
 }
 
+
+// ----------------------------------------------------------------- 2-D cycle
+#include "pf_gmg2.h"
 
 // ----------------------------------------------------------------- 2.5-D stencil kernels (3-D)
 // A workgroup owns a 32 x 8 tile of node columns and marches through kz node
@@ -1376,7 +1385,8 @@ int hier_alloc(pf_problem* pb, Hier<T>& H) {
     typename V2<T>::type** bufs[] = {&M.xa, &M.xb, &M.b, &M.r, &M.d};
     for (auto p : bufs)
       if (hipMalloc(p, nb) != hipSuccess) return PF_ERR_OOM;
-    if (hipMalloc(&M.dg, (size_t)M.k.nnodes * sizeof(T)) != hipSuccess) return PF_ERR_OOM;
+    // (the 2-D kernels form diagonals as they go)
+    if (G.dim == 3 && hipMalloc(&M.dg, (size_t)M.k.nnodes * sizeof(T)) != hipSuccess) return PF_ERR_OOM;
     bool even = true;
     int mn = 1 << 30;
     for (int k = 0; k < G.dim; ++k) {
@@ -1431,6 +1441,77 @@ void block_scales(const pf_problem* pb, double* sm, double* sk) {
   }
 }
 
+// coefficients of the level's degree-2 smoother, [k][block]
+template <class T>
+void smoother_coefs(const Level<T>& L, double* al, double* be) {
+  for (int f = 0; f < 2; ++f) {
+    const double hi = kChebSafety * L.lmax[f];
+    double lo = L.lmax[f] / kChebRatio;
+    if (L.lmin[f] > lo) lo = L.lmin[f];
+    double a[2], b[2];
+    cheb_coefs(lo, hi, 2, a, b);
+    for (int k = 0; k < 2; ++k) {
+      al[2 * k + f] = a[k];
+      be[2 * k + f] = b[k];
+    }
+  }
+}
+
+template <class T>
+Cheb2<T> cheb2(const Level<T>& L) {
+  double al[4], be[4];
+  smoother_coefs(L, al, be);
+  Cheb2<T> K;
+  for (int f = 0; f < 2; ++f) {
+    K.be0[f] = (T)be[f];
+    K.al1[f] = (T)al[2 + f];
+    K.be1[f] = (T)be[2 + f];
+  }
+  return K;
+}
+
+// Steps first .. first + S - 1 of the coarsest solve.
+template <class T, int S>
+ChebSteps<T, S> cheb_steps(const Hier<T>& H, int first) {
+  ChebSteps<T, S> K;
+  for (int k = 0; k < S; ++k)
+    for (int f = 0; f < 2; ++f) {
+      K.al[k][f] = (T)H.coarse_host[4 * (first + k) + f];
+      K.be[k][f] = (T)H.coarse_host[4 * (first + k) + 2 + f];
+    }
+  return K;
+}
+
+// The one-workgroup tail of a 2-D hierarchy: from the first level that fits
+// k_tail2's lanes, LDS slots and level count.
+template <class T>
+void tail2_setup(Hier<T>& H) {
+  const size_t n = H.lv.size();
+  size_t at = n;
+  long long slots = 0;
+  while (at > 0 && n - at < kTail2Levels && H.lv[at - 1].k.nnodes <= kTail2Lanes &&
+         slots + H.lv[at - 1].k.nnodes <= kTail2Slots) {
+    --at;
+    slots += H.lv[at].k.nnodes;
+  }
+  H.tail_at = at;
+  H.tail.clear();
+  if (at == n) return;
+  Tail2<T> A{};
+  int off = 0;
+  for (size_t l = at; l < n; ++l) {
+    const int q = (int)(l - at);
+    A.g[q] = H.lv[l].k;
+    A.c[q] = H.lv[l].c;
+    A.K[q] = cheb2(H.lv[l]);
+    A.off[q] = off;
+    off += (int)H.lv[l].k.nnodes;
+  }
+  A.levels = (int)(n - at);
+  A.coarse = cheb_steps<T, kCoarseDegree>(H, 0);
+  H.tail.push_back(A);
+}
+
 template <int DIM, class T>
 int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) {
   double sm[2], sk[2];
@@ -1449,6 +1530,7 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
                          H.lv[l - 1].k, L.k, (const T*)H.lv[l - 1].c, L.c);
     }
     PF_HIP_CHECK(hipGetLastError());
+    if (DIM == 2) continue;
     hipLaunchKernelGGL((k_diag<DIM, T>), plane_grid(L.k), dim3(kT), 0, s, L.k, (const T*)L.c, L.dg);
     PF_HIP_CHECK(hipGetLastError());
   }
@@ -1461,6 +1543,10 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
       H.coarse_host[4 * k + f] = a[k];
       H.coarse_host[4 * k + 2 + f] = b[k];
     }
+  }
+  if (DIM == 2) {
+    tail2_setup(H);
+    return PF_OK;
   }
   PF_HIP_CHECK(hipMemcpy(H.coarse_dev, H.coarse_host, sizeof(H.coarse_host), hipMemcpyHostToDevice));
   return PF_OK;
@@ -1502,22 +1588,6 @@ int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::t
                      reinterpret_cast<double2*>(z64), (const T*)L.dg);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
-}
-
-// coefficients of the level's degree-2 smoother, [k][block]
-template <class T>
-void smoother_coefs(const Level<T>& L, double* al, double* be) {
-  for (int f = 0; f < 2; ++f) {
-    const double hi = kChebSafety * L.lmax[f];
-    double lo = L.lmax[f] / kChebRatio;
-    if (L.lmin[f] > lo) lo = L.lmin[f];
-    double a[2], b[2];
-    cheb_coefs(lo, hi, 2, a, b);
-    for (int k = 0; k < 2; ++k) {
-      al[2 * k + f] = a[k];
-      be[2 * k + f] = b[k];
-    }
-  }
 }
 
 // V-cycle from level l on the right-hand side in lv[l].b (or r64 at level 0);
@@ -1641,6 +1711,108 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
   return PF_OK;
 }
 
+inline dim3 tiles2(const LvK& k, int own) {
+  return dim3((unsigned)((k.nn[0] + own - 1) / own) * (unsigned)((k.nn[1] + own - 1) / own));
+}
+
+template <class T>
+int down2(Level<T>& L, Level<T>& C, const double2* r64, hipStream_t s) {
+  using T2 = typename V2<T>::type;
+  const Cheb2<T> K = cheb2(L);
+  const dim3 grid = tiles2(C.k, kDown2), lanes(kReg2 * kReg2);
+  if (r64)
+    hipLaunchKernelGGL((k_down2<T, true>), grid, lanes, 0, s, L.k, C.k, (const T*)L.c,
+                       (const T2*)nullptr, r64, K, L.xb, C.b);
+  else
+    hipLaunchKernelGGL((k_down2<T, false>), grid, lanes, 0, s, L.k, C.k, (const T*)L.c,
+                       (const T2*)L.b, r64, K, L.xb, C.b);
+  PF_HIP_CHECK(hipGetLastError());
+  return PF_OK;
+}
+
+template <class T>
+int up2(Level<T>& L, Level<T>& C, const typename V2<T>::type* e, const double2* r64, double2* z64,
+        hipStream_t s) {
+  using T2 = typename V2<T>::type;
+  const Cheb2<T> K = cheb2(L);
+  const dim3 grid = tiles2(L.k, kUp2), lanes(kReg2 * kReg2);
+  if (r64)
+    hipLaunchKernelGGL((k_up2<T, true>), grid, lanes, 0, s, L.k, C.k, (const T*)L.c,
+                       (const T2*)nullptr, r64, K, (const T2*)L.xb, e, (T2*)nullptr, z64);
+  else
+    hipLaunchKernelGGL((k_up2<T, false>), grid, lanes, 0, s, L.k, C.k, (const T*)L.c,
+                       (const T2*)L.b, r64, K, (const T2*)L.xb, e, L.xa, z64);
+  PF_HIP_CHECK(hipGetLastError());
+  return PF_OK;
+}
+
+// The coarsest solve on a grid too large for the tail, S steps per launch, the
+// iterate and direction alternating between (xa, d) and (xb, r); result in xb,
+// or z64 when the hierarchy has this one level.
+template <class T, int S, bool TOP>
+int coarsest2(const Hier<T>& H, const Level<T>& B, const double2* r64, double2* z64, hipStream_t s) {
+  using T2 = typename V2<T>::type;
+  static_assert(kCoarseDegree % (2 * S) == 0, "the last of an even number of launches writes xb");
+  const dim3 grid = tiles2(B.k, cheb2_own(S)), lanes(kRegC2 * kRegC2);
+  for (int k = 0; k < kCoarseDegree; k += S) {
+    const bool odd = (k / S) % 2 == 1;
+    const auto K = cheb_steps<T, S>(H, k);
+    const T2 *x = odd ? B.xa : B.xb, *d = odd ? B.d : B.r;
+    T2 *xo = odd ? B.xb : B.xa, *dd = odd ? B.r : B.d;
+    if (k == 0)
+      hipLaunchKernelGGL((k_cheb2<T, S, true, false, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
+                         (const T2*)B.b, r64, K, (const T2*)nullptr, (const T2*)nullptr, xo, dd, z64);
+    else if (k + S < kCoarseDegree)
+      hipLaunchKernelGGL((k_cheb2<T, S, false, false, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
+                         (const T2*)B.b, r64, K, x, d, xo, dd, z64);
+    else
+      hipLaunchKernelGGL((k_cheb2<T, S, false, true, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
+                         (const T2*)B.b, r64, K, x, d, xo, (T2*)nullptr, z64);
+    PF_HIP_CHECK(hipGetLastError());
+  }
+  return PF_OK;
+}
+
+// Coarsest grids of at least this many nodes take 4 steps per launch, smaller
+// ones 8: half the launches, but four times the nodes instead of 1.8 (FP64/FP32
+// cycles with 8 and 4 steps: 204 x 202 nodes 15/13 and 22/19 us, 388 x 252 25/15
+// and 23/19, 512 x 514 54/27 and 38/24, 1024 x 1002 162/77 and 128/64).
+constexpr long long kCheb2Large = 100000;
+
+// One 2-D V-cycle from r to z (see pf_gmg2.h): down to the tail or the coarsest
+// level, there, and back up.
+template <class T>
+int vcycle2(Hier<T>& H, const double* r, double* z, hipStream_t s) {
+  using T2 = typename V2<T>::type;
+  auto r64 = reinterpret_cast<const double2*>(r);
+  auto z64 = reinterpret_cast<double2*>(z);
+  const size_t bottom = H.tail.empty() ? H.lv.size() - 1 : H.tail_at;
+  for (size_t l = 0; l < bottom; ++l)
+    PF_TRY((down2<T>(H.lv[l], H.lv[l + 1], l == 0 ? r64 : nullptr, s)));
+  Level<T>& B = H.lv[bottom];
+  if (!H.tail.empty()) {
+    const dim3 lanes((unsigned)((B.k.nnodes + 63) / 64 * 64));
+    if (bottom == 0)
+      hipLaunchKernelGGL((k_tail2<T, true>), dim3(1), lanes, 0, s, H.tail[0], (const T2*)nullptr, r64,
+                         (T2*)nullptr, z64);
+    else
+      hipLaunchKernelGGL((k_tail2<T, false>), dim3(1), lanes, 0, s, H.tail[0], (const T2*)B.b, r64, B.xb,
+                         z64);
+    PF_HIP_CHECK(hipGetLastError());
+  } else if (B.k.nnodes >= kCheb2Large) {
+    if (bottom == 0) PF_TRY((coarsest2<T, 4, true>(H, B, r64, z64, s)));
+    else PF_TRY((coarsest2<T, 4, false>(H, B, r64, z64, s)));
+  } else {
+    if (bottom == 0) PF_TRY((coarsest2<T, 8, true>(H, B, r64, z64, s)));
+    else PF_TRY((coarsest2<T, 8, false>(H, B, r64, z64, s)));
+  }
+  for (size_t l = bottom; l-- > 0;) {
+    const T2* e = l + 1 == bottom ? H.lv[l + 1].xb : H.lv[l + 1].xa;
+    PF_TRY((up2<T>(H.lv[l], H.lv[l + 1], e, l == 0 ? r64 : nullptr, z64, s)));
+  }
+  return PF_OK;
+}
+
 template <class T>
 int setup_gmg(pf_problem* pb, PcState* st, Hier<T>& H, hipStream_t s) {
   if (!H.allocated) PF_TRY(hier_alloc<T>(pb, H));
@@ -1651,7 +1823,7 @@ int setup_gmg(pf_problem* pb, PcState* st, Hier<T>& H, hipStream_t s) {
 template <class T>
 int apply_gmg(pf_problem* pb, Hier<T>& H, const double* r, double* z, hipStream_t s) {
   if (pb->geo.dim == 3) return vcycle<3, T>(pb, H, 0, r, z, s);
-  return vcycle<2, T>(pb, H, 0, r, z, s);
+  return vcycle2<T>(H, r, z, s);
 }
 
 // The V-cycle on small meshes: r is copied into the fixed input vector, the
@@ -1795,7 +1967,7 @@ int pc_apply(pf_problem* pb, const double* r, double* z, hipStream_t s) {
       return PF_OK;
     }
     default:
-      if (st->graph_enabled && pb->n_dof <= kGraphMaxDof) {
+      if (st->graph_enabled && G.dim == 3 && pb->n_dof <= kGraphMaxDof) {
         if (pb->pc_precision == PF_FP32)
           return apply_gmg_graph<float>(pb, st, st->h32, st->g32, r, z, s);
         return apply_gmg_graph<double>(pb, st, st->h64, st->g64, r, z, s);
