@@ -962,7 +962,7 @@ int pf_vjp(pf_problem* pb, const double* U, const double* Uprev, const double* w
                                   nullptr, s);
   PF_TRY(launch_residual_family(pb, gU ? MODE_VJP : MODE_VJPP, U, Uprev, w, nullptr, nullptr, gU,
                                 gUprev, pb->vjp_partials, s));
-  if (gparams) PF_TRY(blas_reduce_partials(pb->vjp_partials, pb->n_elem_blocks, 2, gparams, 1.0, s));
+  if (gparams) PF_TRY(blas_reduce_partials(pb->vjp_partials, pb->n_elem_blocks, 2, gparams, s));
   return PF_OK;
 }
 
@@ -1156,7 +1156,7 @@ int pf_adjoint_step(pf_problem* pb, const double* U, const double* Uprev, const 
   double* gp_local = pb->red_out + kSlotParams;
   PF_TRY(launch_residual_family(pb, MODE_VJPP, U, Uprev, lam, nullptr, nullptr, nullptr, gP,
                                 pb->vjp_partials, s));
-  PF_TRY(blas_reduce_partials(pb->vjp_partials, pb->n_elem_blocks, 2, gp_local, 1.0, s));
+  PF_TRY(blas_reduce_partials(pb->vjp_partials, pb->n_elem_blocks, 2, gp_local, s));
   PF_TRY(blas_sub_scalars(gparams, gp_local, 2, s));
   if (mu_prev) PF_TRY(blas_axpby(-1.0, gP, 0.0, gP, mu_prev, pb->n_dof, s));
   PF_HIP_CHECK(hipStreamSynchronize(s));
@@ -1508,7 +1508,7 @@ int pf_misfit(pf_problem* pb, const double* U, const double* phi_target, double*
                      reinterpret_cast<const double2*>(U), phi_target,
                      reinterpret_cast<double2*>(dLdU), pb->red_partials);
   PF_HIP_CHECK(hipGetLastError());
-  return blas_reduce_partials(pb->red_partials, nb, 1, L_dev, 1.0, s);
+  return blas_reduce_partials(pb->red_partials, nb, 1, L_dev, s);
 }
 
 int pf_dot(pf_problem* pb, const double* x, const double* y, double* out_dev, void* stream) {

@@ -1,8 +1,16 @@
 // BLAS-1 kernels of the Krylov solver: dot products and norms with
-// deterministic two-stage reductions (a fixed grid of blocks, a fixed
-// wavefront butterfly, then a fixed-order sum of the block partials), the
-// multi-vector products of classical Gram-Schmidt, and vector updates.
-// HBM-bound: every kernel streams its vectors once with 16-byte loads.
+// deterministic reductions, the multi-vector products of classical
+// Gram-Schmidt, and vector updates.  HBM-bound: every kernel streams its vectors
+// once with 16-byte loads; on small vectors the launches and the sums inside a
+// block are what counts.
+//
+// Reductions run in a fixed order over a fixed grid.  Vectors of at most
+// kSmallPairs entry pairs: one workgroup of 1024 lanes per basis vector forms
+// its final sums, one launch.  Longer ones: block partials, then k_reduce.
+// Letting the block that finishes last add the partials instead of a second
+// launch was measured slower (norm of 64^2 4.6 us against 2.9 + 2.4, products on
+// 512^2 39 us): stores, counter and loads beyond the XCD's own L2 take about
+// 1 us each, one after the other, and counter increments 25 ns each.
 #include "pf_internal.h"
 
 namespace pf {
@@ -10,113 +18,221 @@ namespace pf {
 namespace {
 
 constexpr int kRedThreads = 256;
-constexpr int kChunk = 8;  // vectors per multi-dot block row
+constexpr int kSmallThreads = 1024;
+// where one workgroup's sweep costs as much as the second launch: Jacobi step of
+// 64^2 (4225 pairs) 2.34 -> 2.06 ms, of 80^2 2.19 -> 2.01 ms, of 120^2 (14641)
+// 1.69 -> 1.79 ms
+constexpr long long kSmallPairs = 8192;
+constexpr int kChunk = 16;  // most vectors per multi-dot block row
 
-__device__ __forceinline__ double wave_sum(double v) {
+// Sums of M values (a power of two <= 64) over the wavefront's lanes by a
+// butterfly: each halving of the lanes also halves the values a lane carries,
+// M - 1 + log2(64/M) exchanges instead of 6 M.  Lane l ends with the sum of
+// value l / (64 / M) in v[0].
+template <int M, int OFF = 32>
+__device__ __forceinline__ void wave_sums(double* v) {
+  if constexpr (M > 1) {
+    const bool up = (threadIdx.x & OFF) != 0;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+    for (int i = 0; i < M / 2; ++i) {
+      const double keep = up ? v[i + M / 2] : v[i], send = up ? v[i] : v[i + M / 2];
+      v[i] = keep + __shfl_xor(send, OFF, 64);
+    }
+    wave_sums<M / 2, OFF / 2>(v);
+  } else if constexpr (OFF > 0) {
+    v[0] += __shfl_xor(v[0], OFF, 64);
+    wave_sums<1, OFF / 2>(v);
+  }
 }
 
-// Block sum in a fixed order: butterfly inside each 64-lane wavefront, then
-// wavefront 0 adds the 4 wavefront sums in order.
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  v = wave_sum(v);
+// Block sums of M values per lane (WAVES wavefronts, added in order): thread
+// i < M returns with the sum of value i.  sh: WAVES * M doubles.
+template <int M, int WAVES>
+__device__ __forceinline__ double block_sums(double* v, double* sh) {
+  wave_sums<M>(v);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sh[wid] = v;
+  constexpr int per = 64 / M;
+  if (lane % per == 0) sh[wid * M + lane / per] = v[0];
   __syncthreads();
   double t = 0.0;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < M) {
 #pragma unroll
-    for (int w = 0; w < kRedThreads / 64; ++w) t += sh[w];
+    for (int w = 0; w < WAVES; ++w) t += sh[w * M + threadIdx.x];
   }
   return t;
 }
 
-// partials[(c*kChunk + j) * nb + b] = sum over the block's indices of V_j[i] w[i]
-__global__ void __launch_bounds__(kRedThreads)
-    k_multidot(const double* __restrict__ V, long long ld, int k, const double* __restrict__ w,
-               long long n, double* __restrict__ partials) {
-  __shared__ double sh[kRedThreads / 64];
-  const int c = blockIdx.y;
-  const int nb = gridDim.x;
-  double acc[kChunk];
-#pragma unroll
-  for (int j = 0; j < kChunk; ++j) acc[j] = 0.0;
-  const int j0 = c * kChunk;
-  const long long n2 = n / 2;
-  const double2* w2 = reinterpret_cast<const double2*>(w);
-  if (k == 1 && V == w) {
-    // a squared norm: one load per entry instead of two of the same address
-    for (long long i = (long long)blockIdx.x * kRedThreads + threadIdx.x; i < n2;
-         i += (long long)nb * kRedThreads) {
-      const double2 wi = w2[i];
-      acc[0] = fma(wi.x, wi.x, acc[0]);
-      acc[0] = fma(wi.y, wi.y, acc[0]);
-    }
-  } else {
-    for (long long i = (long long)blockIdx.x * kRedThreads + threadIdx.x; i < n2;
-         i += (long long)nb * kRedThreads) {
-      const double2 wi = w2[i];
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j) {
-        if (j0 + j < k) {
-          const double2 vi = reinterpret_cast<const double2*>(V + (long long)(j0 + j) * ld)[i];
-          acc[j] = fma(vi.x, wi.x, acc[j]);
-          acc[j] = fma(vi.y, wi.y, acc[j]);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < kChunk; ++j) {
-    if (j0 + j < k) {
-      const double t = block_sum(acc[j], sh);
-      if (threadIdx.x == 0) partials[(long long)(j0 + j) * nb + blockIdx.x] = t;
-    }
-  }
+// eps = sqrt(2^-52) (1 + sqrt(uu)) / sqrt(vv), 0 when v = 0, and its reciprocal
+// (read by the product kernels instead of dividing).
+__device__ __forceinline__ void write_fd_eps(double uu, double vv, double* eps) {
+  const double nu = sqrt(uu), nv = sqrt(vv);
+  const double e = (nv > 0.0) ? 1.4901161193847656e-08 * (1.0 + nu) / nv : 0.0;
+  eps[0] = e;
+  eps[1] = e == 0.0 ? 0.0 : 1.0 / e;
 }
 
-// z = a x + b y as k_axpby, and the partials of |z|^2 in the squared-norm
-// order of k_multidot (same grid, same per-thread and block sums): with
-// k_reduce, the same |z|^2 as a multi-dot of z with itself.
+// What a norm's last kernel does with |x|^2 beyond storing it: a copy in mapped
+// host memory (read by the host after the stream syncs), and the FD step from
+// it as |v|^2 with |U|^2 at uu (both may be NULL).
+struct NormOut {
+  double* out;
+  double* out_host;
+  const double* uu;
+  double* eps;
+  __device__ __forceinline__ void put(double t) const {
+    *out = t;
+    if (out_host) *out_host = t;
+    if (eps) write_fd_eps(*uu, t, eps);
+  }
+};
+
+// |x_i|^2 of this lane's entry pairs.
+template <int THREADS>
+__device__ __forceinline__ double lane_norm(const double* __restrict__ x, long long n) {
+  const double2* x2 = reinterpret_cast<const double2*>(x);
+  double acc = 0.0;
+#pragma unroll 4
+  for (long long i = (long long)blockIdx.x * THREADS + threadIdx.x; i < n / 2;
+       i += (long long)gridDim.x * THREADS) {
+    const double2 v = x2[i];
+    acc = fma(v.x, v.x, acc);
+    acc = fma(v.y, v.y, acc);
+  }
+  return acc;
+}
+
 __global__ void __launch_bounds__(kRedThreads)
-    k_axpby_norm(double a, const double* __restrict__ x, double b, const double* __restrict__ y,
-                 double* __restrict__ z, long long n, double* __restrict__ partials) {
+    k_norm(const double* __restrict__ x, long long n, double* __restrict__ partials) {
   __shared__ double sh[kRedThreads / 64];
-  const int nb = gridDim.x;
-  const long long n2 = n / 2;
+  double acc = lane_norm<kRedThreads>(x, n);
+  const double t = block_sums<1, kRedThreads / 64>(&acc, sh);
+  if (threadIdx.x == 0) partials[blockIdx.x] = t;
+}
+
+__global__ void __launch_bounds__(kSmallThreads)
+    k_norm_small(const double* __restrict__ x, long long n, NormOut O) {
+  __shared__ double sh[kSmallThreads / 64];
+  double acc = lane_norm<kSmallThreads>(x, n);
+  const double t = block_sums<1, kSmallThreads / 64>(&acc, sh);
+  if (threadIdx.x == 0) O.put(t);
+}
+
+// z = a x + b y as k_axpby, and |z|^2 in the order of k_norm / k_norm_small.
+template <int THREADS>
+__device__ __forceinline__ double lane_axpby_norm(double a, const double* __restrict__ x, double b,
+                                                  const double* __restrict__ y,
+                                                  double* __restrict__ z, long long n) {
   const double2* x2 = reinterpret_cast<const double2*>(x);
   const double2* y2 = reinterpret_cast<const double2*>(y);
   double2* z2 = reinterpret_cast<double2*>(z);
   double acc = 0.0;
-  for (long long i = (long long)blockIdx.x * kRedThreads + threadIdx.x; i < n2;
-       i += (long long)nb * kRedThreads) {
+  for (long long i = (long long)blockIdx.x * THREADS + threadIdx.x; i < n / 2;
+       i += (long long)gridDim.x * THREADS) {
     const double2 u = x2[i], v = y2[i];
     const double2 w = make_double2(fma(a, u.x, b * v.x), fma(a, u.y, b * v.y));
     z2[i] = w;
     acc = fma(w.x, w.x, acc);
     acc = fma(w.y, w.y, acc);
   }
-  const double t = block_sum(acc, sh);
+  return acc;
+}
+
+__global__ void __launch_bounds__(kRedThreads)
+    k_axpby_norm(double a, const double* __restrict__ x, double b, const double* __restrict__ y,
+                 double* __restrict__ z, long long n, double* __restrict__ partials) {
+  __shared__ double sh[kRedThreads / 64];
+  double acc = lane_axpby_norm<kRedThreads>(a, x, b, y, z, n);
+  const double t = block_sums<1, kRedThreads / 64>(&acc, sh);
   if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-// out[j] = scale * sum_b partials[j * nparts + b], fixed order per thread then
-// fixed block butterfly; one block per j.  out_host (may be NULL): the same
-// values into mapped host memory, read by the host after the stream syncs.
+__global__ void __launch_bounds__(kSmallThreads)
+    k_axpby_norm_small(double a, const double* __restrict__ x, double b, const double* __restrict__ y,
+                       double* __restrict__ z, long long n, NormOut O) {
+  __shared__ double sh[kSmallThreads / 64];
+  double acc = lane_axpby_norm<kSmallThreads>(a, x, b, y, z, n);
+  const double t = block_sums<1, kSmallThreads / 64>(&acc, sh);
+  if (threadIdx.x == 0) O.put(t);
+}
+
+// The sum of nparts partials of one row, on thread 0: fixed order per thread,
+// then the block's.
+__device__ __forceinline__ double row_sum(const double* __restrict__ partials, int nparts, double* sh) {
+  double acc = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nparts; b += kRedThreads) acc += partials[b];
+  return block_sums<1, kRedThreads / 64>(&acc, sh);
+}
+
+// out[j] = sum of row j's partials; one block per row.  out_host (may be NULL):
+// the same values in mapped host memory.
 __global__ void __launch_bounds__(kRedThreads)
     k_reduce(const double* __restrict__ partials, int nparts, double* __restrict__ out,
-             double scale, double* __restrict__ out_host) {
+             double* __restrict__ out_host) {
   __shared__ double sh[kRedThreads / 64];
   const int j = blockIdx.x;
-  double acc = 0.0;
-  for (int b = threadIdx.x; b < nparts; b += kRedThreads) acc += partials[(long long)j * nparts + b];
-  const double t = block_sum(acc, sh);
+  const double t = row_sum(partials + (long long)j * nparts, nparts, sh);
   if (threadIdx.x == 0) {
-    out[j] = scale * t;
-    if (out_host) out_host[j] = scale * t;
+    out[j] = t;
+    if (out_host) out_host[j] = t;
+  }
+}
+
+__global__ void __launch_bounds__(kRedThreads)
+    k_reduce_norm(const double* __restrict__ partials, int nparts, NormOut O) {
+  __shared__ double sh[kRedThreads / 64];
+  const double t = row_sum(partials, nparts, sh);
+  if (threadIdx.x == 0) O.put(t);
+}
+
+// Products of K vectors with w over this lane's entry pairs: acc[q] for
+// k0 + q < k.
+template <int K, int THREADS>
+__device__ __forceinline__ void lane_dots(const double* __restrict__ V, long long ld, int k0, int k,
+                                          const double* __restrict__ w, long long n, double* acc) {
+#pragma unroll
+  for (int q = 0; q < K; ++q) acc[q] = 0.0;
+  const double2* w2 = reinterpret_cast<const double2*>(w);
+  for (long long i = (long long)blockIdx.x * THREADS + threadIdx.x; i < n / 2;
+       i += (long long)gridDim.x * THREADS) {
+    const double2 wi = w2[i];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      if (k0 + q < k) {
+        const double2 vi = reinterpret_cast<const double2*>(V + (long long)(k0 + q) * ld)[i];
+        acc[q] = fma(vi.x, wi.x, acc[q]);
+        acc[q] = fma(vi.y, wi.y, acc[q]);
+      }
+    }
+  }
+}
+
+// partials[(k0 + q) * gridDim.x + block]; blockIdx.y takes K vectors.
+template <int K>
+__global__ void __launch_bounds__(kRedThreads)
+    k_multidot(const double* __restrict__ V, long long ld, int k, const double* __restrict__ w,
+               long long n, double* __restrict__ partials) {
+  __shared__ double sh[kRedThreads / 64 * K];
+  const int k0 = blockIdx.y * K;
+  double acc[K];
+  lane_dots<K, kRedThreads>(V, ld, k0, k, w, n, acc);
+  const double t = block_sums<K, kRedThreads / 64>(acc, sh);
+  const int r = k0 + (int)threadIdx.x;
+  if (threadIdx.x < K && r < k) partials[(long long)r * gridDim.x + blockIdx.x] = t;
+}
+
+// One workgroup per vector (blockIdx.y).
+__global__ void __launch_bounds__(kSmallThreads)
+    k_multidot_small(const double* __restrict__ V, long long ld, const double* __restrict__ w,
+                     long long n, double* __restrict__ out, double* __restrict__ out_host) {
+  __shared__ double sh[kSmallThreads / 64];
+  const int r = blockIdx.y;
+  double acc[1];
+  lane_dots<1, kSmallThreads>(V, ld, r, r + 1, w, n, acc);
+  const double t = block_sums<1, kSmallThreads / 64>(acc, sh);
+  if (threadIdx.x == 0) {
+    out[r] = t;
+    if (out_host) out_host[r] = t;
   }
 }
 
@@ -143,26 +259,29 @@ __global__ void __launch_bounds__(256)
 
 // Products of one Gram-Schmidt step with a delayed second projection, in one
 // sweep.  t = V_j (the previous direction, projected once) and w = V_{j+1} (the
-// new operator output); rows of partials:
+// new operator output); rows:
 //   k < j: V_k . t,   j: t . t,   j + 1 + k (k < j): V_k . w,
 //   2j + 1: t . w,    2j + 2: w . w.
 // blockIdx.y takes V_k for k in [KMAX y, KMAX (y + 1)); chunk 0 also forms the
-// three products of t and w.
+// three products of t and w.  The 2 KMAX + 3 sums of a block go through
+// wave_sums together: one by one (with two barriers each) they cost most of the
+// kernel, 34 us with 9 to 16 vectors on 512^2, 19 now.
 template <int KMAX>
 __global__ void __launch_bounds__(kRedThreads)
     k_dcgs_dots(const double* __restrict__ V, long long ld, int j, long long n,
                 double* __restrict__ partials) {
-  __shared__ double sh[kRedThreads / 64];
+  constexpr int kWaves = kRedThreads / 64;
+  __shared__ double sh[kWaves * 2 * KMAX], sh3[kWaves * 4];
   const int nb = gridDim.x;
   const int k0 = blockIdx.y * KMAX;
   const bool first = blockIdx.y == 0;
   const long long n2 = n / 2;
   const double2* t2 = reinterpret_cast<const double2*>(V + (long long)j * ld);
   const double2* w2 = reinterpret_cast<const double2*>(V + (long long)(j + 1) * ld);
-  double at[KMAX], aw[KMAX];
+  double a[2 * KMAX];  // V . t, then V . w
+  double s3[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int q = 0; q < KMAX; ++q) at[q] = aw[q] = 0.0;
-  double tt = 0.0, tw = 0.0, ww = 0.0;
+  for (int q = 0; q < 2 * KMAX; ++q) a[q] = 0.0;
   for (long long i = (long long)blockIdx.x * kRedThreads + threadIdx.x; i < n2;
        i += (long long)nb * kRedThreads) {
     const double2 t = t2[i], w = w2[i];
@@ -170,37 +289,61 @@ __global__ void __launch_bounds__(kRedThreads)
     for (int q = 0; q < KMAX; ++q) {
       if (k0 + q < j) {
         const double2 v = reinterpret_cast<const double2*>(V + (long long)(k0 + q) * ld)[i];
-        at[q] = fma(v.x, t.x, at[q]);
-        at[q] = fma(v.y, t.y, at[q]);
-        aw[q] = fma(v.x, w.x, aw[q]);
-        aw[q] = fma(v.y, w.y, aw[q]);
+        a[q] = fma(v.x, t.x, a[q]);
+        a[q] = fma(v.y, t.y, a[q]);
+        a[KMAX + q] = fma(v.x, w.x, a[KMAX + q]);
+        a[KMAX + q] = fma(v.y, w.y, a[KMAX + q]);
       }
     }
     if (first) {
-      tt = fma(t.x, t.x, tt);
-      tt = fma(t.y, t.y, tt);
-      tw = fma(t.x, w.x, tw);
-      tw = fma(t.y, w.y, tw);
-      ww = fma(w.x, w.x, ww);
-      ww = fma(w.y, w.y, ww);
+      s3[0] = fma(t.x, t.x, s3[0]);
+      s3[0] = fma(t.y, t.y, s3[0]);
+      s3[1] = fma(t.x, w.x, s3[1]);
+      s3[1] = fma(t.y, w.y, s3[1]);
+      s3[2] = fma(w.x, w.x, s3[2]);
+      s3[2] = fma(w.y, w.y, s3[2]);
     }
   }
-#pragma unroll
-  for (int q = 0; q < KMAX; ++q) {
-    if (k0 + q < j) {
-      const double a = block_sum(at[q], sh);
-      if (threadIdx.x == 0) partials[(long long)(k0 + q) * nb + blockIdx.x] = a;
-      const double b = block_sum(aw[q], sh);
-      if (threadIdx.x == 0) partials[(long long)(j + 1 + k0 + q) * nb + blockIdx.x] = b;
-    }
+  if (j > 0) {
+    const double r = block_sums<2 * KMAX, kWaves>(a, sh);
+    const int q = (int)threadIdx.x % KMAX, of_w = (int)threadIdx.x / KMAX;
+    if (threadIdx.x < 2 * KMAX && k0 + q < j)
+      partials[(long long)(of_w * (j + 1) + k0 + q) * nb + blockIdx.x] = r;
   }
   if (first) {
-    const double a = block_sum(tt, sh);
-    if (threadIdx.x == 0) partials[(long long)j * nb + blockIdx.x] = a;
-    const double b = block_sum(tw, sh);
-    if (threadIdx.x == 0) partials[(long long)(2 * j + 1) * nb + blockIdx.x] = b;
-    const double c = block_sum(ww, sh);
-    if (threadIdx.x == 0) partials[(long long)(2 * j + 2) * nb + blockIdx.x] = c;
+    const double r = block_sums<4, kWaves>(s3, sh3);
+    const int row = threadIdx.x == 0 ? j : 2 * j + (int)threadIdx.x;
+    if (threadIdx.x < 3) partials[(long long)row * nb + blockIdx.x] = r;
+  }
+}
+
+// The same with one workgroup per basis vector: block k < j the products of
+// V_k, block j those of t and w.
+__global__ void __launch_bounds__(kSmallThreads)
+    k_dcgs_small(const double* __restrict__ V, long long ld, int j, long long n,
+                 double* __restrict__ out, double* __restrict__ out_host) {
+  __shared__ double sh[kSmallThreads / 64 * 4];
+  const int k = blockIdx.x;
+  const double2* t2 = reinterpret_cast<const double2*>(V + (long long)j * ld);
+  const double2* w2 = reinterpret_cast<const double2*>(V + (long long)(j + 1) * ld);
+  const double2* v2 = reinterpret_cast<const double2*>(V + (long long)k * ld);  // t itself for k = j
+  double s[4] = {0.0, 0.0, 0.0, 0.0};  // v.t, v.w, w.w
+#pragma unroll 4
+  for (long long i = threadIdx.x; i < n / 2; i += kSmallThreads) {
+    const double2 t = t2[i], w = w2[i], v = v2[i];
+    s[0] = fma(v.x, t.x, s[0]);
+    s[0] = fma(v.y, t.y, s[0]);
+    s[1] = fma(v.x, w.x, s[1]);
+    s[1] = fma(v.y, w.y, s[1]);
+    s[2] = fma(w.x, w.x, s[2]);
+    s[2] = fma(w.y, w.y, s[2]);
+  }
+  const double r = block_sums<4, kSmallThreads / 64>(s, sh);
+  const int q = threadIdx.x;
+  if (q < (k == j ? 3 : 2)) {
+    const int row = q == 0 ? k : (q == 1 ? j + 1 + k : 2 * j + 2);
+    out[row] = r;
+    if (out_host) out_host[row] = r;
   }
 }
 
@@ -264,15 +407,6 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// eps = sqrt(2^-52) (1 + sqrt(uu)) / sqrt(vv), 0 when v = 0
-__global__ void k_fd_eps(const double* __restrict__ uu, const double* __restrict__ vv,
-                         double* __restrict__ eps) {
-  const double nu = sqrt(uu[0]), nv = sqrt(vv[0]);
-  const double e = (nv > 0.0) ? 1.4901161193847656e-08 * (1.0 + nu) / nv : 0.0;
-  eps[0] = e;
-  eps[1] = e == 0.0 ? 0.0 : 1.0 / e;  // read by the product kernels instead of dividing
-}
-
 __global__ void k_sub_scalars(double* acc, const double* x, int k) {
   const int j = threadIdx.x;
   if (j < k) acc[j] -= x[j];
@@ -285,32 +419,69 @@ unsigned grid_for(long long n2, int threads, unsigned cap) {
   return (unsigned)b;
 }
 
+inline bool small(long long n) { return n / 2 <= kSmallPairs; }
+
+int reduce_rows(pf_problem* pb, int rows, double* out_dev, double* out_host, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce, dim3(rows), dim3(kRedThreads), 0, s, pb->red_partials, pb->n_red_blocks,
+                     out_dev, out_host);
+  PF_HIP_CHECK(hipGetLastError());
+  return PF_OK;
+}
+
+int reduce_norm(pf_problem* pb, const NormOut& O, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_norm, dim3(1), dim3(kRedThreads), 0, s, pb->red_partials,
+                     pb->n_red_blocks, O);
+  PF_HIP_CHECK(hipGetLastError());
+  return PF_OK;
+}
+
+int norm_sq(pf_problem* pb, const double* x, long long n, const NormOut& O, hipStream_t s) {
+  if (small(n)) {
+    hipLaunchKernelGGL(k_norm_small, dim3(1), dim3(kSmallThreads), 0, s, x, n, O);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
+  }
+  hipLaunchKernelGGL(k_norm, dim3(pb->n_red_blocks), dim3(kRedThreads), 0, s, x, n, pb->red_partials);
+  PF_HIP_CHECK(hipGetLastError());
+  return reduce_norm(pb, O, s);
+}
+
 }  // namespace
 
 int blas_multidot(pf_problem* pb, const double* V, long long ld, int k, const double* w,
                   long long n, double* out_dev, hipStream_t s, double* out_host) {
   if (k <= 0) return PF_OK;
+  if (k == 1 && V == w) return norm_sq(pb, V, n, NormOut{out_dev, out_host, nullptr, nullptr}, s);
+  if (small(n)) {
+    hipLaunchKernelGGL(k_multidot_small, dim3(1, k), dim3(kSmallThreads), 0, s, V, ld, w, n, out_dev,
+                       out_host);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
+  }
   const int nb = pb->n_red_blocks;
-  const int chunks = (k + kChunk - 1) / kChunk;
-  hipLaunchKernelGGL(k_multidot, dim3(nb, chunks), dim3(kRedThreads), 0, s, V, ld, k, w, n,
-                     pb->red_partials);
+  if (k == 1)
+    hipLaunchKernelGGL(k_multidot<1>, dim3(nb), dim3(kRedThreads), 0, s, V, ld, k, w, n, pb->red_partials);
+  else if (k <= 4)
+    hipLaunchKernelGGL(k_multidot<4>, dim3(nb), dim3(kRedThreads), 0, s, V, ld, k, w, n, pb->red_partials);
+  else
+    hipLaunchKernelGGL(k_multidot<kChunk>, dim3(nb, (k + kChunk - 1) / kChunk), dim3(kRedThreads), 0, s,
+                       V, ld, k, w, n, pb->red_partials);
   PF_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL(k_reduce, dim3(k), dim3(kRedThreads), 0, s, pb->red_partials, nb, out_dev, 1.0,
-                     out_host);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+  return reduce_rows(pb, k, out_dev, out_host, s);
 }
 
 int blas_axpby_norm(pf_problem* pb, double a, const double* x, double b, const double* y, double* z,
                     long long n, double* out_dev, hipStream_t s) {
-  const int nb = pb->n_red_blocks;
-  hipLaunchKernelGGL(k_axpby_norm, dim3(nb), dim3(kRedThreads), 0, s, a, x, b, y, z, n,
+  const NormOut O{out_dev, nullptr, nullptr, nullptr};
+  if (small(n)) {
+    hipLaunchKernelGGL(k_axpby_norm_small, dim3(1), dim3(kSmallThreads), 0, s, a, x, b, y, z, n, O);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
+  }
+  hipLaunchKernelGGL(k_axpby_norm, dim3(pb->n_red_blocks), dim3(kRedThreads), 0, s, a, x, b, y, z, n,
                      pb->red_partials);
   PF_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kRedThreads), 0, s, pb->red_partials, nb, out_dev, 1.0,
-                     nullptr);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+  return reduce_norm(pb, O, s);
 }
 
 int blas_dot(pf_problem* pb, const double* x, const double* y, long long n, double* out_dev,
@@ -321,22 +492,26 @@ int blas_dot(pf_problem* pb, const double* x, const double* y, long long n, doub
 int blas_dcgs_dots(pf_problem* pb, const double* V, long long ld, int j, long long n,
                    double* out_dev, hipStream_t s, double* out_host) {
   if (j < 0 || 2 * j + 3 > kRedRows) return PF_ERR_INVALID_ARG;
-  const int nb = pb->n_red_blocks;
-  if (j <= 8) {
-    hipLaunchKernelGGL(k_dcgs_dots<8>, dim3(nb, 1), dim3(kRedThreads), 0, s, V, ld, j, n,
-                       pb->red_partials);
-  } else if (j <= 16) {
-    hipLaunchKernelGGL(k_dcgs_dots<16>, dim3(nb, 1), dim3(kRedThreads), 0, s, V, ld, j, n,
-                       pb->red_partials);
-  } else {
-    hipLaunchKernelGGL(k_dcgs_dots<16>, dim3(nb, (j + 15) / 16), dim3(kRedThreads), 0, s, V, ld,
-                       j, n, pb->red_partials);
+  if (small(n)) {
+    hipLaunchKernelGGL(k_dcgs_small, dim3(j + 1), dim3(kSmallThreads), 0, s, V, ld, j, n, out_dev,
+                       out_host);
+    PF_HIP_CHECK(hipGetLastError());
+    return PF_OK;
   }
+  const int nb = pb->n_red_blocks;
+  double* part = pb->red_partials;
+  // the smallest accumulator set that holds the basis: fewer sums per block
+  if (j <= 2)
+    hipLaunchKernelGGL(k_dcgs_dots<2>, dim3(nb), dim3(kRedThreads), 0, s, V, ld, j, n, part);
+  else if (j <= 4)
+    hipLaunchKernelGGL(k_dcgs_dots<4>, dim3(nb), dim3(kRedThreads), 0, s, V, ld, j, n, part);
+  else if (j <= 8)
+    hipLaunchKernelGGL(k_dcgs_dots<8>, dim3(nb), dim3(kRedThreads), 0, s, V, ld, j, n, part);
+  else
+    hipLaunchKernelGGL(k_dcgs_dots<16>, dim3(nb, (j + 15) / 16), dim3(kRedThreads), 0, s, V, ld, j, n,
+                       part);
   PF_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL(k_reduce, dim3(2 * j + 3), dim3(kRedThreads), 0, s, pb->red_partials, nb,
-                     out_dev, 1.0, out_host);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+  return reduce_rows(pb, 2 * j + 3, out_dev, out_host, s);
 }
 
 int blas_dcgs_update(double* V, long long ld, int j, const double* dots_dev, double hj,
@@ -374,27 +549,18 @@ int blas_axpby(double a, const double* x, double b, const double* y, double* z, 
 
 int blas_fd_eps(pf_problem* pb, const double* U, const double* v, long long n, double* eps_dev,
                 hipStream_t s) {
-  double* nrm = pb->red_out + kSlotFdU;
-  PF_TRY(blas_multidot(pb, U, n, 1, U, n, nrm, s));
-  PF_TRY(blas_multidot(pb, v, n, 1, v, n, nrm + 1, s));
-  hipLaunchKernelGGL(k_fd_eps, dim3(1), dim3(1), 0, s, nrm, nrm + 1, eps_dev);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+  double* uu = pb->red_out + kSlotFdU;
+  PF_TRY(norm_sq(pb, U, n, NormOut{uu, nullptr, nullptr, nullptr}, s));
+  return blas_fd_eps_cached(pb, uu, v, n, eps_dev, s);
 }
 
 int blas_fd_eps_cached(pf_problem* pb, const double* unorm2_dev, const double* v, long long n,
                        double* eps_dev, hipStream_t s) {
-  double* nv = pb->red_out + kSlotFdV;
-  PF_TRY(blas_multidot(pb, v, n, 1, v, n, nv, s));
-  hipLaunchKernelGGL(k_fd_eps, dim3(1), dim3(1), 0, s, unorm2_dev, nv, eps_dev);
-  PF_HIP_CHECK(hipGetLastError());
-  return PF_OK;
+  return norm_sq(pb, v, n, NormOut{pb->red_out + kSlotFdV, nullptr, unorm2_dev, eps_dev}, s);
 }
 
-int blas_reduce_partials(const double* partials, int nparts, int k, double* out_dev, double scale,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3(k), dim3(kRedThreads), 0, s, partials, nparts, out_dev, scale,
-                     nullptr);
+int blas_reduce_partials(const double* partials, int nparts, int k, double* out_dev, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce, dim3(k), dim3(kRedThreads), 0, s, partials, nparts, out_dev, nullptr);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }

@@ -212,8 +212,7 @@ int blas_fd_eps(pf_problem* pb, const double* U, const double* v, long long n, d
 // eps from a precomputed |U|^2 (device scalar) and |v|^2 computed here
 int blas_fd_eps_cached(pf_problem* pb, const double* unorm2_dev, const double* v, long long n,
                        double* eps_dev, hipStream_t s);
-int blas_reduce_partials(const double* partials, int nparts, int k, double* out_dev,
-                         double scale, hipStream_t s);
+int blas_reduce_partials(const double* partials, int nparts, int k, double* out_dev, hipStream_t s);
 int blas_sub_scalars(double* acc_dev, const double* x_dev, int k, hipStream_t s);
 
 // ----------------------------------------------------------------- preconditioner (pf_gmg.hip)
