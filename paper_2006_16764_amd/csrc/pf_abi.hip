@@ -1,7 +1,7 @@
 // C ABI of libpfjfnk: handle management, the residual-family entry points,
 // and the host drivers of the Newton-Krylov method (Sec. 2.2 of the paper):
 // right-preconditioned flexible GMRES with classical Gram-Schmidt applied twice
-// (FP64 Arnoldi, one host synchronisation per iteration), inexact Newton with
+// (FP64 Arnoldi; the host polls each iteration's products), inexact Newton with
 // the forcing term of Eqs. force1-forcing, the backtracking of Eq. glob and
 // the termination test of Eq. tolerance; backward-Euler stepping and one step
 // of its discrete adjoint.
@@ -28,6 +28,15 @@ inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 double now_ms() {
   using namespace std::chrono;
   return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
+}
+
+// End of a [sync] call: its last kernels may still run when the host has taken
+// its decisions.  Keeps the call's own error.
+int finish(hipStream_t s, int rc) {
+  const hipError_t e = hipStreamSynchronize(s);
+  if (rc != PF_OK || e == hipSuccess) return rc;
+  set_error(std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
+  return PF_ERR_HIP;
 }
 
 // Start of a [sync] call's clock: the stream is drained first, so that work the
@@ -186,12 +195,13 @@ int check_opts(const pf_problem* pb, const pf_solver_opts* o) {
 }
 
 
-// |x|: the reduction also writes its result into mapped host memory, so the
-// host reads it after the stream syncs without a copy.
+// |x|: the reduction also writes its result into mapped host memory, which the
+// host polls.
 int norm2(pf_problem* pb, const double* x, double* out, hipStream_t s) {
+  blas_arm(pb, kSlotNorm, 1);
   PF_TRY(blas_multidot(pb, x, pb->n_dof, 1, x, pb->n_dof, pb->red_out + kSlotNorm, s,
                        pb->host_pinned_dev + kSlotNorm));
-  PF_HIP_CHECK(hipStreamSynchronize(s));
+  PF_TRY(blas_wait(pb, kSlotNorm, 1, s));
   *out = std::sqrt(pb->host_pinned[kSlotNorm]);
   return PF_OK;
 }
@@ -250,7 +260,6 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
   double* V = pb->V;
   double* Z = pb->Z;
   double* r = pb->tmp_vec[3];
-  double* ydev = pb->red_out + kSlotY;
   double* dots_dev = pb->red_out + kSlotDots;
   double* hp = pb->host_pinned;
   std::vector<double> H((m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
@@ -290,9 +299,10 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
   // products of V_{j+1} with V_0..V_{j+1}: its second-projection
   // coefficients sv[0..j] and its norm after that projection
   auto finish_products = [&](int j, double* rho_out) -> int {
+    blas_arm(pb, kSlotDots, j + 2);
     PF_TRY(blas_multidot(pb, V, n, j + 2, V + (long long)(j + 1) * n, n, dots_dev, s,
                          pb->host_pinned_dev + kSlotDots));
-    PF_HIP_CHECK(hipStreamSynchronize(s));
+    PF_TRY(blas_wait(pb, kSlotDots, j + 2, s));
     double ssq = 0.0;
     for (int k = 0; k <= j; ++k) {
       sv[k] = hp[kSlotDots + k];
@@ -317,18 +327,19 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
       double* w = V + (long long)(j + 1) * n;
       PF_TRY(pc_apply(pb, vj, zj, s));
       PF_TRY(op.apply(zj, w, s));
+      // products and update are queued together; the host reads both results
+      // while the update runs.  When the column of V_{j-1} turns out to end the
+      // cycle the update was for nothing (x = Z y needs no V).
+      blas_arm(pb, kSlotDots, 2 * j + 3);
+      blas_arm(pb, kSlotScal, 4);
       PF_TRY(blas_dcgs_dots(pb, V, n, j, n, dots_dev, s, pb->host_pinned_dev + kSlotDots));
-      PF_HIP_CHECK(hipStreamSynchronize(s));
+      PF_TRY(blas_dcgs_update(V, n, j, dots_dev, n, pb->host_pinned_dev + kSlotScal, s));
+      PF_TRY(blas_wait(pb, kSlotDots, 2 * j + 3, s));
+      PF_TRY(blas_wait(pb, kSlotScal, 4, s));
       const double* dt = hp + kSlotDots;    // V_k . V_j (k < j), |V_j|^2
       const double* dw = hp + kSlotDots + j + 1;  // V_k . w (k < j), V_j . w, |w|^2
-      // finish V_j: second projection coefficients dt[0..j-1], norm rho
-      double rho = 1.0;
-      if (j > 0) {
-        double ssq = 0.0;
-        for (int k = 0; k < j; ++k) ssq += dt[k] * dt[k];
-        const double r2 = dt[j] - ssq;
-        rho = r2 > 0.0 ? std::sqrt(r2) : 0.0;
-      }
+      // norm of V_j after its second projection, w . V_j after it
+      const double rho = hp[kSlotScal], dot_wv = hp[kSlotScal + 1];
       if (pending) {
         for (int k = 0; k < j; ++k) H[k * m + j - 1] = hcol[k] + eta * dt[k];
         H[j * m + j - 1] = eta * rho;
@@ -345,12 +356,6 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
         }
       }
       // products of w with the finished V_0..V_j
-      double dot_wv = dw[j];
-      if (j > 0) {
-        double c = 0.0;
-        for (int k = 0; k < j; ++k) c += dt[k] * dw[k];
-        dot_wv = (dw[j] - c) / rho;
-      }
       double hsq = 0.0;
       for (int k = 0; k < j; ++k) {
         hcol[k] = dw[k];
@@ -365,10 +370,8 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
       }
       // normalisation of the once-projected w: the Pythagorean estimate while
       // it keeps at least six digits, else the norm itself
-      const double u2 = wsq - hsq;
-      const bool explicit_norm = !(u2 > 1e-12 * wsq);
-      eta = explicit_norm ? 1.0 : std::sqrt(u2);
-      PF_TRY(blas_dcgs_update(V, n, j, dots_dev, hcol[j], 1.0 / rho, 1.0 / eta, n, s));
+      eta = hp[kSlotScal + 2];
+      const bool explicit_norm = hp[kSlotScal + 3] != 0.0;
       if (explicit_norm) {
         PF_TRY(norm2(pb, w, &eta, s));
         if (eta > 0.0) PF_TRY(blas_axpby(1.0 / eta, w, 0.0, w, w, n, s));
@@ -410,12 +413,8 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
       for (int k = i + 1; k < jend; ++k) t -= H[i * m + k] * y[k];
       y[i] = H[i * m + i] != 0.0 ? t / H[i * m + i] : 0.0;
     }
-    std::memcpy(pb->host_pinned + kSlotHostY, y.data(), jend * sizeof(double));
-    PF_HIP_CHECK(hipMemcpyAsync(ydev, pb->host_pinned + kSlotHostY, jend * sizeof(double),
-                                hipMemcpyHostToDevice, s));
-    PF_TRY(blas_combine(pb, Z, n, jend, ydev, x, n, s, !*xset));
+    PF_TRY(blas_combine(Z, n, jend, y.data(), x, n, s, !*xset));
     *xset = true;
-    PF_HIP_CHECK(hipStreamSynchronize(s));
     if (converged || total >= o.gmres_maxit) break;
     // restart: r = b - A x
     PF_TRY(op.apply(x, r, s));
@@ -673,9 +672,10 @@ int evolve_loop(pf_problem* pb, double* states, int steps, pf_solver_stats* stat
     if (rc != PF_OK) {
       acc.status = rc;
       if (stats) *stats = acc;
-      return rc;
+      return finish(s, rc);
     }
   }
+  PF_TRY(finish(s, PF_OK));
   acc.t_total_ms = now_ms() - t0;
   if (stats) *stats = acc;
   return PF_OK;
@@ -1024,7 +1024,7 @@ int pf_linear_solve(pf_problem* pb, const double* U, const double* Uprev, const 
   Op op{pb, U, Uprev, F, kind};
   PF_TRY(op.prepare(s));
   int its = 0;
-  int rc = fgmres(pb, op, b, 1.0, -1.0, x, rtol, *opts, &its, s);
+  const int rc = finish(s, fgmres(pb, op, b, 1.0, -1.0, x, rtol, *opts, &its, s));
   if (stats) {
     stats->gmres_its_total = its;
     stats->gmres_its[0] = its;
@@ -1048,7 +1048,7 @@ int pf_newton_step(pf_problem* pb, const double* Uprev, double* U, const pf_solv
   stats_reset(stats);
   double t0;
   PF_TRY(clock_start(S(stream), &t0));
-  int rc = newton_impl(pb, Uprev, nullptr, U, *opts, stats, S(stream));
+  const int rc = finish(S(stream), newton_impl(pb, Uprev, nullptr, U, *opts, stats, S(stream)));
   if (stats) {
     stats->status = rc;
     stats->t_total_ms = now_ms() - t0;
@@ -1071,7 +1071,8 @@ int pf_newton_step_theta(pf_problem* pb, const double* Uprev2, const double* Upr
   stats_reset(stats);
   double t0;
   PF_TRY(clock_start(S(stream), &t0));
-  const int rc = thermal_step_impl(pb, Uprev2, Uprev, U, *opts, stats, S(stream));
+  const int rc =
+      finish(S(stream), thermal_step_impl(pb, Uprev2, Uprev, U, *opts, stats, S(stream)));
   if (stats) {
     stats->status = rc;
     stats->t_total_ms = now_ms() - t0;
@@ -1151,7 +1152,7 @@ int pf_adjoint_step(pf_problem* pb, const double* U, const double* Uprev, const 
     stats->gmres_its[0] = its;
     stats->status = rc;
   }
-  if (rc != PF_OK) return rc;
+  if (rc != PF_OK) return finish(s, rc);
   double* gP = pb->tmp_vec[4];
   double* gp_local = pb->red_out + kSlotParams;
   PF_TRY(launch_residual_family(pb, MODE_VJPP, U, Uprev, lam, nullptr, nullptr, nullptr, gP,
@@ -1184,7 +1185,7 @@ int pf_adjoint_solve(pf_problem* pb, const double* U, const double* Uprev, const
   PF_TRY(pc_setup(pb, U, opts->pc, opts->pc_precision, s));
   Op op{pb, U, Uprev, nullptr, 2};
   int its = 0;
-  const int rc = fgmres(pb, op, rhs, 1.0, -1.0, lam, opts->tau_r, *opts, &its, s);
+  const int rc = finish(s, fgmres(pb, op, rhs, 1.0, -1.0, lam, opts->tau_r, *opts, &its, s));
   if (stats) {
     stats->gmres_its_total = its;
     stats->gmres_its[0] = its;
@@ -1314,7 +1315,8 @@ int pf_alloy_step(pf_problem* pb, const double* Uprev2, const double* Uprev, dou
   stats_reset(stats);
   double t0;
   PF_TRY(clock_start(S(stream), &t0));
-  int rc = alloy_step_impl(pb, Uprev2, Uprev, t_prev, U, *opts, stats, S(stream));
+  const int rc =
+      finish(S(stream), alloy_step_impl(pb, Uprev2, Uprev, t_prev, U, *opts, stats, S(stream)));
   if (stats) {
     stats->status = rc;
     stats->t_total_ms = now_ms() - t0;
@@ -1459,7 +1461,7 @@ int pf_fg_step(pf_problem* pb, const double* Uprev2, const double* Uprev, double
   stats_reset(stats);
   double t0;
   PF_TRY(clock_start(S(stream), &t0));
-  int rc = fg_step_impl(pb, Uprev2, Uprev, U, *opts, stats, S(stream));
+  const int rc = finish(S(stream), fg_step_impl(pb, Uprev2, Uprev, U, *opts, stats, S(stream)));
   if (stats) {
     stats->status = rc;
     stats->t_total_ms = now_ms() - t0;

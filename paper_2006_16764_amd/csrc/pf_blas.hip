@@ -71,9 +71,14 @@ __device__ __forceinline__ void write_fd_eps(double uu, double vv, double* eps) 
   eps[1] = e == 0.0 ? 0.0 : 1.0 / e;
 }
 
-// What a norm's last kernel does with |x|^2 beyond storing it: a copy in mapped
-// host memory (read by the host after the stream syncs), and the FD step from
-// it as |v|^2 with |U|^2 at uu (both may be NULL).
+// A result for the host, which polls the slot in mapped memory while the stream
+// runs on (blas_wait): a store the host sees at once, not at the kernel's end.
+__device__ __forceinline__ void put_host(double* slot, double v) {
+  __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// What a norm's last kernel does with |x|^2 beyond storing it: a copy for the
+// host, and the FD step from it as |v|^2 with |U|^2 at uu (both may be NULL).
 struct NormOut {
   double* out;
   double* out_host;
@@ -81,7 +86,7 @@ struct NormOut {
   double* eps;
   __device__ __forceinline__ void put(double t) const {
     *out = t;
-    if (out_host) *out_host = t;
+    if (out_host) put_host(out_host, t);
     if (eps) write_fd_eps(*uu, t, eps);
   }
 };
@@ -165,7 +170,7 @@ __device__ __forceinline__ double row_sum(const double* __restrict__ partials, i
 }
 
 // out[j] = sum of row j's partials; one block per row.  out_host (may be NULL):
-// the same values in mapped host memory.
+// the same values for the host.
 __global__ void __launch_bounds__(kRedThreads)
     k_reduce(const double* __restrict__ partials, int nparts, double* __restrict__ out,
              double* __restrict__ out_host) {
@@ -174,7 +179,7 @@ __global__ void __launch_bounds__(kRedThreads)
   const double t = row_sum(partials + (long long)j * nparts, nparts, sh);
   if (threadIdx.x == 0) {
     out[j] = t;
-    if (out_host) out_host[j] = t;
+    if (out_host) put_host(out_host + j, t);
   }
 }
 
@@ -232,15 +237,18 @@ __global__ void __launch_bounds__(kSmallThreads)
   const double t = block_sums<1, kSmallThreads / 64>(acc, sh);
   if (threadIdx.x == 0) {
     out[r] = t;
-    if (out_host) out_host[r] = t;
+    if (out_host) put_host(out_host + r, t);
   }
 }
 
-// x[i] += sum_j coef[j] * V_j[i]  (runtime k, coefficients on the device), or
-// x[i] = that sum (assign)
+// x[i] += sum_j coef[j] * V_j[i] (runtime k, coefficients in the kernel's
+// arguments), or x[i] = that sum (assign)
+struct Coefs {
+  double c[kMaxGmresM];
+};
 __global__ void __launch_bounds__(256)
-    k_combine(const double* __restrict__ V, long long ld, int k, const double* __restrict__ coef,
-              double* __restrict__ x, long long n, int assign) {
+    k_combine(const double* __restrict__ V, long long ld, int k, Coefs coef, double* __restrict__ x,
+              long long n, int assign) {
   const long long n2 = n / 2;
   double2* x2 = reinterpret_cast<double2*>(x);
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n2;
@@ -248,7 +256,7 @@ __global__ void __launch_bounds__(256)
     // assign: x = sum_j coef[j] V_j, the same sums as from an x of zeros
     double2 a = assign ? make_double2(0.0, 0.0) : x2[i];
     for (int j = 0; j < k; ++j) {
-      const double c = coef[j];
+      const double c = coef.c[j];
       const double2 v = reinterpret_cast<const double2*>(V + (long long)j * ld)[i];
       a.x = fma(c, v.x, a.x);
       a.y = fma(c, v.y, a.y);
@@ -343,18 +351,53 @@ __global__ void __launch_bounds__(kSmallThreads)
   if (q < (k == j ? 3 : 2)) {
     const int row = q == 0 ? k : (q == 1 ? j + 1 + k : 2 * j + 2);
     out[row] = r;
-    if (out_host) out_host[row] = r;
+    if (out_host) put_host(out_host + row, r);
+  }
+}
+
+// Sums of three values over the wavefront, on every lane.
+__device__ __forceinline__ void wave_all3(double& a, double& b, double& c) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    a += __shfl_xor(a, off, 64);
+    b += __shfl_xor(b, off, 64);
+    c += __shfl_xor(c, off, 64);
   }
 }
 
 // The two updates of that step in one sweep, in place:
-//   t <- (t - sum_{k<j} cs[k] V_k) * inv_rho           (the final V_j; j > 0)
-//   w <- (w - sum_{k<j} ch[k] V_k - hj t_new) * inv_eta
-// cs and ch are rows of the products above, still on the device.
+//   t <- (t - sum_{k<j} s_k V_k) / rho                  (the final V_j; j > 0)
+//   w <- (w - sum_{k<j} h_k V_k - h_j t_new) / eta
+// with s_k = V_k . t, h_k = V_k . w (rows of the products above, still on the
+// device), rho^2 = t.t - sum s_k^2, h_j = (t.w - sum s_k h_k)/rho and eta the norm
+// of the projected w by Pythagoras, eta^2 = w.w - sum h_k^2 - h_j^2, or 1 when
+// that keeps fewer than six digits (the caller then takes the norm itself).
+// Every wavefront forms these scalars from the products (j < 64: one product
+// per lane), so the sweep follows the products without the host between them;
+// the host, which needs them for the Hessenberg column, gets rho, h_j, eta and
+// whether eta was replaced in scal_host[0..3].
 __global__ void __launch_bounds__(256)
-    k_dcgs_update(double* __restrict__ V, long long ld, int j, const double* __restrict__ cs,
-                  const double* __restrict__ ch, double hj, double inv_rho, double inv_eta,
-                  long long n) {
+    k_dcgs_update(double* __restrict__ V, long long ld, int j, const double* __restrict__ dots,
+                  long long n, double* __restrict__ scal_host) {
+  const double* cs = dots;
+  const double* ch = dots + j + 1;
+  const int lane = threadIdx.x & 63;
+  const double sl = lane < j ? cs[lane] : 0.0, hl = lane < j ? ch[lane] : 0.0;
+  double ss = sl * sl, sh = sl * hl, hh = hl * hl;
+  wave_all3(ss, sh, hh);
+  const double tt = dots[j], tw = dots[2 * j + 1], ww = dots[2 * j + 2];
+  const double rho = j > 0 ? sqrt(fmax(tt - ss, 0.0)) : 1.0;
+  const double hj = j > 0 ? (tw - sh) / rho : tw;
+  const double u2 = ww - fma(hj, hj, hh);
+  const bool replaced = !(u2 > 1e-12 * ww);
+  const double eta = replaced ? 1.0 : sqrt(u2);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    put_host(scal_host, rho);
+    put_host(scal_host + 1, hj);
+    put_host(scal_host + 2, eta);
+    put_host(scal_host + 3, replaced ? 1.0 : 0.0);
+  }
+  const double inv_rho = 1.0 / rho, inv_eta = 1.0 / eta;
   const long long n2 = n / 2;
   double2* t2 = reinterpret_cast<double2*>(V + (long long)j * ld);
   double2* w2 = reinterpret_cast<double2*>(V + (long long)(j + 1) * ld);
@@ -514,20 +557,54 @@ int blas_dcgs_dots(pf_problem* pb, const double* V, long long ld, int j, long lo
   return reduce_rows(pb, 2 * j + 3, out_dev, out_host, s);
 }
 
-int blas_dcgs_update(double* V, long long ld, int j, const double* dots_dev, double hj,
-                     double inv_rho, double inv_eta, long long n, hipStream_t s) {
+int blas_dcgs_update(double* V, long long ld, int j, const double* dots_dev, long long n,
+                     double* scal_host, hipStream_t s) {
+  static_assert(kMaxGmresM <= 64, "one product per lane");
   hipLaunchKernelGGL(k_dcgs_update, dim3(grid_for(n / 2, 256, 8192)), dim3(256), 0, s, V, ld, j,
-                     dots_dev, dots_dev + j + 1, hj, inv_rho, inv_eta, n);
+                     dots_dev, n, scal_host);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }
 
-int blas_combine(pf_problem* pb, const double* V, long long ld, int k, const double* coef_dev,
-                 double* x, long long n, hipStream_t s, bool assign) {
-  (void)pb;
-  if (k <= 0 && !assign) return PF_OK;
-  hipLaunchKernelGGL(k_combine, dim3(grid_for(n / 2, 256, 8192)), dim3(256), 0, s, V, ld, k,
-                     coef_dev, x, n, assign ? 1 : 0);
+// A NaN that no kernel produces (results that are NaN carry another payload).
+static constexpr uint64_t kUnset = 0x7ff4a5a5deadbeefULL;
+
+void blas_arm(pf_problem* pb, int slot, int count) {
+  auto* p = reinterpret_cast<uint64_t*>(pb->host_pinned + slot);
+  for (int i = 0; i < count; ++i) __atomic_store_n(p + i, kUnset, __ATOMIC_RELEASE);
+}
+
+int blas_wait(pf_problem* pb, int slot, int count, hipStream_t s) {
+  const auto* p = reinterpret_cast<const uint64_t*>(pb->host_pinned + slot);
+  bool drained = false;
+  for (int i = 0; i < count; ++i)
+    for (unsigned spin = 1; __atomic_load_n(p + i, __ATOMIC_ACQUIRE) == kUnset; ++spin) {
+      if (drained) {
+        set_error("a reduction ended without its result");
+        return PF_ERR_HIP;
+      }
+      __builtin_ia32_pause();
+      if (spin % 1024) continue;
+      // the stream's own state ends the wait if the result never comes
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        continue;
+      }
+      PF_HIP_CHECK(e);
+      drained = true;  // one more look at the slot
+    }
+  return PF_OK;
+}
+
+int blas_combine(const double* V, long long ld, int k, const double* coef, double* x, long long n,
+                 hipStream_t s, bool assign) {
+  if (k < 0 || k > kMaxGmresM) return PF_ERR_INVALID_ARG;
+  if (k == 0 && !assign) return PF_OK;
+  Coefs c{};
+  for (int j = 0; j < k; ++j) c.c[j] = coef[j];
+  hipLaunchKernelGGL(k_combine, dim3(grid_for(n / 2, 256, 8192)), dim3(256), 0, s, V, ld, k, c, x, n,
+                     assign ? 1 : 0);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }

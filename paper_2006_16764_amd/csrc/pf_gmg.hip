@@ -26,6 +26,7 @@
 // processed by the same thread and stored as interleaved (phi, u) pairs.
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "pf_element.h"
@@ -104,7 +105,8 @@ struct Hier {
   bool allocated = false;
   size_t tail_at = 0;       // 2-D: first level of the one-workgroup tail (lv.size(): none)
   std::vector<Tail2<T>> tail;  // its kernel argument (0 or 1)
-  double coarse_host[4 * kCoarseDegree];  // per-step (alpha, beta) of the coarsest solve
+  bool coarse_sent = false;
+  double coarse_host[4 * kCoarseDegree] = {};  // per-step (alpha, beta) of the coarsest solve
   double* coarse_dev = nullptr;
 };
 
@@ -1534,8 +1536,12 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
     hipLaunchKernelGGL((k_diag<DIM, T>), plane_grid(L.k), dim3(kT), 0, s, L.k, (const T*)L.c, L.dg);
     PF_HIP_CHECK(hipGetLastError());
   }
-  // per-step coefficients of the coarsest solve, [step][alpha0, alpha1, beta0, beta1]
+  // per-step coefficients of the coarsest solve, [step][alpha0, alpha1, beta0, beta1];
+  // copied to the device when they differ from the last set-up's (the copy
+  // waits for the stream)
   const Level<T>& C = H.lv.back();
+  double before[4 * kCoarseDegree];
+  std::memcpy(before, H.coarse_host, sizeof(before));
   for (int f = 0; f < 2; ++f) {
     double a[kCoarseDegree], b[kCoarseDegree];
     cheb_coefs(C.lmin[f], kChebSafety * C.lmax[f], kCoarseDegree, a, b);
@@ -1548,7 +1554,10 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
     tail2_setup(H);
     return PF_OK;
   }
-  PF_HIP_CHECK(hipMemcpy(H.coarse_dev, H.coarse_host, sizeof(H.coarse_host), hipMemcpyHostToDevice));
+  if (!H.coarse_sent || std::memcmp(before, H.coarse_host, sizeof(before)) != 0) {
+    PF_HIP_CHECK(hipMemcpy(H.coarse_dev, H.coarse_host, sizeof(H.coarse_host), hipMemcpyHostToDevice));
+    H.coarse_sent = true;
+  }
   return PF_OK;
 }
 

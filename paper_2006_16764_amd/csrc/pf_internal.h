@@ -167,39 +167,41 @@ long long fg_elem_buf_len(const pf_problem* pb);
 int blas_dot(pf_problem* pb, const double* x, const double* y, long long n, double* out_dev,
              hipStream_t s);
 // out_host (device alias of mapped host memory, may be NULL) receives a copy
-// of the results for the host, valid once the stream has synchronised.
+// of the results for the host.  The host arms the slots before the launch
+// (blas_arm) and polls them (blas_wait) while the stream runs on: waiting for
+// the stream instead cost 5-8 us more per wait and kept the next launch behind it.
+void blas_arm(pf_problem* pb, int slot, int count);
+int blas_wait(pf_problem* pb, int slot, int count, hipStream_t s);
 int blas_multidot(pf_problem* pb, const double* V, long long ld, int k, const double* w,
                   long long n, double* out_dev, hipStream_t s, double* out_host = nullptr);
 // Rows of the reduction workspace (red_partials holds kRedRows * n_red_blocks).
 constexpr int kRedRows = 128;
 
 // Slots of the handle's 1024-double result arrays: red_out on the device and
-// host_pinned (mapped host memory, written by reductions the host waits for).
+// host_pinned (mapped host memory, written by reductions the host polls).
 constexpr int kMaxGmresM = 60;  // largest gmres_m_max pf_create accepts
 constexpr int kRedSlots = 1024;
 constexpr int kSlotFdU = 200;   // red_out: |U|^2 of the FD step size (one-off form)
 constexpr int kSlotFdV = 201;   // red_out: |v|^2 of the FD step size
 constexpr int kSlotUnorm = 203; // red_out: |U|^2 kept for the FD operator of a Krylov solve
 constexpr int kSlotNorm = 250;  // red_out and host_pinned: |x|^2 of a norm the host reads
-constexpr int kSlotHostY = 160; // host_pinned: staging of the FGMRES combination y
-constexpr int kSlotY = 300;     // red_out: the FGMRES combination y (<= kMaxGmresM)
+constexpr int kSlotScal = 260;  // host_pinned: the four scalars of a Gram-Schmidt update
 constexpr int kSlotParams = 400;  // red_out: the two parameter sums of a VJP
 constexpr int kSlotDots = 512;  // red_out and host_pinned: Gram-Schmidt products (<= 2m + 3)
-static_assert(kSlotHostY + kMaxGmresM <= kSlotNorm, "host y staging overlaps the norm slot");
-static_assert(kSlotY + kMaxGmresM <= kSlotParams, "y overlaps the parameter sums");
 static_assert(kSlotDots + 2 * kMaxGmresM + 3 <= kRedSlots, "Gram-Schmidt products overflow");
 static_assert(2 * kMaxGmresM + 3 <= kRedRows, "Gram-Schmidt products exceed the reduction rows");
 // One Gram-Schmidt step with a delayed second projection (t = V_j, w = V_{j+1}):
-// out[0..2j+2] = V_{<j}^T t, t.t, V_{<j}^T w, t.w, w.w in one sweep; then the
-// in-place updates t <- (t - V_{<j} s) inv_rho, w <- (w - V_{<j} h - hj t) inv_eta with
-// s = out[0..j-1] and h = out[j+1..2j] of that product sweep (left on the device).
+// out[0..2j+2] = V_{<j}^T t, t.t, V_{<j}^T w, t.w, w.w in one sweep; then both
+// updates in place from those products, whose scalars rho, h_j, eta and whether
+// eta had to be replaced by 1 go to scal_host (mapped host memory).
 int blas_dcgs_dots(pf_problem* pb, const double* V, long long ld, int j, long long n,
                    double* out_dev, hipStream_t s, double* out_host = nullptr);
-int blas_dcgs_update(double* V, long long ld, int j, const double* dots_dev, double hj,
-                     double inv_rho, double inv_eta, long long n, hipStream_t s);
-// x += sum_{j<k} coef_dev[j] V_j; assign: x = that sum (x not read; zeros when k = 0)
-int blas_combine(pf_problem* pb, const double* V, long long ld, int k, const double* coef_dev,
-                 double* x, long long n, hipStream_t s, bool assign = false);
+int blas_dcgs_update(double* V, long long ld, int j, const double* dots_dev, long long n,
+                     double* scal_host, hipStream_t s);
+// x += sum_{j<k} coef[j] V_j (coef on the host); assign: x = that sum (x not
+// read; zeros when k = 0)
+int blas_combine(const double* V, long long ld, int k, const double* coef, double* x, long long n,
+                 hipStream_t s, bool assign = false);
 int blas_scale_copy(const double* x, const double* alpha_dev, int invert, double* y,
                     long long n, hipStream_t s);
 // z = a x + b y, and |z|^2 into out_dev (device), the value blas_multidot of z with itself gives

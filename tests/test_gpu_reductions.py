@@ -67,3 +67,25 @@ def test_krylov_products(n):
     assert st["gmres_its_total"] > 17
     assert err <= 2 * rtol
     assert pb.close() == 0
+
+
+@pytest.mark.parametrize("n", [(1, 1), (2, 1), (2, 2)], ids=lambda n: f"{n[0]}x{n[1]}")
+def test_krylov_space_exhausted(n):
+    """Meshes of 8 to 18 unknowns: the last vectors of the basis lose their
+    digits to the projections (the norm by Pythagoras is replaced by the norm
+    itself), and the solve ends within as many iterations as unknowns, plus one."""
+    from paper_2006_16764_amd import binding
+    print(f"[case] exhausted Krylov space {n}", flush=True)
+    pb = problem(n, 30)
+    U, Up = dev(inputs.random_state(2, n, 3, 0.5)), dev(inputs.random_state(2, n, 4, 0.5))
+    b = dev(inputs.random_vector(pb.n_nodes, 5))
+    pb.pf_precond_setup(U, binding.PF_PC_NONE)
+    opts = binding.default_opts(pc=binding.PF_PC_NONE, jv_mode=binding.PF_JV_ANALYTIC)
+    x, r = pb.new_vector(), pb.new_vector()
+    st = pb.pf_linear_solve(U, Up, b, x, rtol=1e-13, opts=opts)
+    pb.pf_jvp(U, Up, x, r)
+    err = float((r - b).norm() / b.norm())
+    print(f"[parity] {st['gmres_its_total']} iterations, true residual {err:.3e}", flush=True)
+    assert st["gmres_its_total"] <= pb.n_dof + 1
+    assert err <= 1e-12
+    assert pb.close() == 0
