@@ -1431,9 +1431,10 @@ int pf_fg_jvp(pf_problem* pb, const double* U, const double* Uprev, const double
     return PF_ERR_INVALID_ARG;
   }
   hipStream_t s = S(stream);
-  PF_TRY(direct_history(pb, Uprev, &Uprev2, s));
+  // (the tangent does not depend on the history: the latent source is linear)
   if (mode == PF_JV_ANALYTIC)
     return launch_fg(pb, MODE_JVP, U, Uprev, v, nullptr, nullptr, Jv, nullptr, s, Uprev2);
+  PF_TRY(direct_history(pb, Uprev, &Uprev2, s));
   const double* base = F0;
   if (!base) {
     PF_TRY(launch_fg(pb, MODE_RES, U, Uprev, nullptr, nullptr, nullptr, pb->tmp_vec[0], nullptr, s,

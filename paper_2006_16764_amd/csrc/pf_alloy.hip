@@ -8,10 +8,9 @@
 // shared gather kernel forms the node sums in a fixed order.  Unlike the thermal u
 // equation the solute equation is nonlinear (one-sided mobility,
 // anti-trapping current, cu phihat source), so both fields go through the
-// Gauss rule.  The analytic tangent evaluates the same pointwise function on
-// dual numbers (value, directional derivative): forward-mode differentiation
-// of exactly the residual's arithmetic.
-#include "pf_dual.h"
+// Gauss rule.  The analytic tangent differentiates the pointwise
+// terms by hand, the anisotropic flux through the Hessian-vector product of
+// pf_element.h.
 #include "pf_tile2.h"
 
 namespace pf {
@@ -21,55 +20,25 @@ namespace {
 constexpr int kAlloyBlock = 128;
 constexpr double kInv2Sqrt2 = 0.35355339059327376220;  // 1/(2 sqrt 2)
 
-// Pointwise terms of the alloy residual: s1, f1 (phi rows: value and flux
-// parts), s2, f2 (u rows).  hist = (1 - theta)(phi^n - phi^(n-1))/dt, x the
-// point's coordinate along axis 0.  a2 receives cu a^2, the mobility factor of
-// the time term (the preconditioner's phi-block coefficient).
-template <int DIM, class T>
-__device__ __forceinline__ void alloy_point(const Geo& G, const AlloyConst& C, const T& phi,
-                                            const T (&g)[3], const T& u, const T (&gu)[3],
-                                            const T& dphi, const T& du, double hist, double x,
-                                            T& s1, T (&f1)[3], T& s2, T (&f2)[3], double& a2) {
-  T g2[3], q = g[0] * g[0], S;
-  g2[0] = q;
-  S = g2[0] * g2[0];
-#pragma unroll
-  for (int k = 1; k < DIM; ++k) {
-    g2[k] = g[k] * g[k];
-    q = q + g2[k];
-    S = S + g2[k] * g2[k];
-  }
-  const T Q = q + G.delta2;
-  const T iQ = rcp_t(Q);
-  const T iQ2 = iQ * iQ;
-  const T a = G.a0 + G.e4x4 * (S * iQ2);
-  const T SQ = S * iQ;
-  const T aa = a * a;
-  const T aqc = a * q * (G.e16 * iQ2);
-  const T cu = 1.0 + C.omk * u;
-  const T om = 1.0 - phi * phi;
-  const double G4 = fma(x, C.g4a, C.g4b);
-  const T R = om * (phi - G.lam * (om * (u + G4)));
-  s1 = cu * aa * dphi * G.idt - C.theta * R;
-  const T ph = (C.theta * G.idt) * dphi + hist;
-  s2 = (C.hopk * G.idt) * du - 0.5 * (ph * cu);
-  const T mob = (C.theta * G.D * 0.5) * (1.0 - phi);
-  const T at = kInv2Sqrt2 * (cu * ph * rsqrt_t(Q));
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (k < DIM) {
-      const T J = g[k] * (aa + aqc * (g2[k] - SQ));
-      f1[k] = C.theta * J;
-      f2[k] = mob * gu[k] + at * g[k];
-    } else {
-      f1[k] = T{};
-      f2[k] = T{};
-    }
-  }
-  a2 = val(cu * aa);
+// 1/sqrt(x), x > 0: hardware estimate refined by two Newton steps
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = r * fma(-0.5 * x * r, r, 1.5);
+  return r * fma(-0.5 * x * r, r, 1.5);
 }
 
-// Residual: gradient fields {phi, u}; value fields {phi - phi^n, u - u^n, hist, x}.
+// The frozen temperature G4 = (x - x_iso - v t)/l_T at the element's points: its
+// value at the first node, and its rise along the element.
+struct Frozen {
+  double first, rise, here;
+  __device__ Frozen(const AlloyConst& C, int ex)
+      : first(fma(fma((double)ex, C.h0, C.x0), C.g4a, C.g4b)), rise(C.h0 * C.g4a), here(0.0) {}
+  __device__ __forceinline__ void point(int gx) { here = fma(Q1::b1(gx), rise, first); }
+};
+
+// Residual: gradient fields {phi, u}; value fields {phi - phi^n, u - u^n, hist},
+// hist = (1 - theta)(phi^n - phi^(n-1))/dt.  a2 receives cu a^2, the mobility
+// factor of the time term (the preconditioner's phi-block coefficient).
 template <int DIM>
 struct PhysAlloyRes {
   // unroll choices measured at 1024 x 256 x 256 (points and rows unrolled)
@@ -77,9 +46,11 @@ struct PhysAlloyRes {
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
   const AlloyConst& C;
+  Frozen T;
   double ca, car, a2;
-  __device__ PhysAlloyRes(const Geo& g, const AlloyConst& c)
-      : G(g), C(c), ca(0.0), car(0.0), a2(0.0) {}
+  __device__ PhysAlloyRes(const Geo& g, const AlloyConst& c, int ex)
+      : G(g), C(c), T(c, ex), ca(0.0), car(0.0), a2(0.0) {}
+  __device__ __forceinline__ void point(int gx) { T.point(gx); }
   __device__ __forceinline__ void weight(double wx) { car = fma(wx, a2, car); }
   __device__ __forceinline__ void row(double wrow) {
     ca = fma(wrow, car, ca);
@@ -88,14 +59,34 @@ struct PhysAlloyRes {
   __device__ __forceinline__ void operator()(const double* gv, const double (*gg)[3],
                                              const double* vv, double* s, double (*f)[3],
                                              double*) {
-    const double g[3] = {gg[0][0], gg[0][1], gg[0][2]};
-    const double gu[3] = {gg[1][0], gg[1][1], gg[1][2]};
-    alloy_point<DIM, double>(G, C, gv[0], g, gv[1], gu, vv[0], vv[1], vv[2], vv[3], s[0], f[0], s[1],
-                             f[1], a2);
+    const double phi = gv[0], u = gv[1], dphi = vv[0], du = vv[1], hist = vv[2];
+    Aniso<DIM> A;
+    A.template flux<2>(gg[0], G);
+    const double cu = fma(C.omk, u, 1.0);
+    const double om = fma(-phi, phi, 1.0);
+    const double R = om * fma(-G.lam * om, u + T.here, phi);
+    a2 = cu * A.a2;
+    s[0] = fma(a2 * dphi, G.idt, -C.theta * R);
+    const double ph = fma(C.theta * G.idt, dphi, hist), pc = ph * cu;
+    s[1] = fma(C.hopk * G.idt, du, -0.5 * pc);
+    const double mob = (C.theta * G.D * 0.5) * (1.0 - phi);
+    const double at = (kInv2Sqrt2 * pc) * rsqrt_nr(A.q + G.delta2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      f[0][k] = k < DIM ? C.theta * A.J[k] : 0.0;
+      f[1][k] = k < DIM ? fma(mob, gg[1][k], at * gg[0][k]) : 0.0;
+    }
   }
 };
 
-// Tangent: gradient fields {phi, u, v_phi, v_u}; value fields as the residual.
+// Tangent along (tp, tu): gradient fields {phi, u, tp, tu}; value fields
+// {phi - phi^n, hist}.  With cu, mob, ph, rs = Q^(-1/2), at = cu ph rs/(2 sqrt 2)
+// as in the residual and gv = g . grad tp:
+//   d(cu a^2 dphi) = dphi (omk tu a^2 + cu 2 a da) + cu a^2 tp,
+//   dph = theta tp/dt,  d(ph cu) = dph cu + ph omk tu,  drs = -rs gv/Q,
+//   d(mob grad u + at g) = mob grad tu - (theta D/2) tp grad u + at grad tp + dat g.
+// On dual numbers the same took about half as many operations again: 3-D
+// element pass on 512 x 128 x 128 DUALOLD -> DUALNEW us.
 template <int DIM>
 struct PhysAlloyJvp {
   // points unrolled, rows one at a time (measured at 1024 x 256 x 256)
@@ -103,29 +94,38 @@ struct PhysAlloyJvp {
   static constexpr int kGyUnroll = 1;
   const Geo& G;
   const AlloyConst& C;
-  __device__ PhysAlloyJvp(const Geo& g, const AlloyConst& c) : G(g), C(c) {}
+  Frozen T;
+  __device__ PhysAlloyJvp(const Geo& g, const AlloyConst& c, int ex) : G(g), C(c), T(c, ex) {}
+  __device__ __forceinline__ void point(int gx) { T.point(gx); }
   __device__ __forceinline__ void weight(double) {}
   __device__ __forceinline__ void row(double) {}
   __device__ __forceinline__ void operator()(const double* gv, const double (*gg)[3],
                                              const double* vv, double* s, double (*f)[3],
                                              double*) {
-    const Dual phi{gv[0], gv[2]}, u{gv[1], gv[3]};
-    Dual g[3], gu[3];
+    const double phi = gv[0], u = gv[1], tp = gv[2], tu = gv[3], dphi = vv[0], hist = vv[1];
+    Aniso<DIM> A;
+    A.template flux<2>(gg[0], G);
+    double Hv[3] = {0.0, 0.0, 0.0}, da, gtv, gmv;
+    A.template hvp_c<false>(gg[0], gg[2], 0.0, Hv, da, gtv, gmv);
+    const double cu = fma(C.omk, u, 1.0), dcu = C.omk * tu;
+    const double om = fma(-phi, phi, 1.0), w = u + T.here;
+    // dR/dphi = (1 - phi^2)(3 + 4 lambda phi (u + G4)) - 2, dR/du = -lambda (1 - phi^2)^2
+    const double Rp = fma(om, fma(4.0 * G.lam * phi, w, 3.0), -2.0);
+    const double dR = fma(Rp, tp, (-G.lam * om) * (om * tu));
+    const double dm = fma(dcu, A.a2, cu * ((A.a + A.a) * da));
+    s[0] = fma(fma(dm, dphi, (cu * A.a2) * tp), G.idt, -C.theta * dR);
+    const double ti = C.theta * G.idt;
+    const double ph = fma(ti, dphi, hist), pc = ph * cu;
+    const double dpc = fma(ti * tp, cu, ph * dcu);
+    s[1] = fma(C.hopk * G.idt, tu, -0.5 * dpc);
+    const double hd = C.theta * G.D * 0.5;
+    const double mob = hd * (1.0 - phi), dmob = -hd * tp;
+    const double rs = kInv2Sqrt2 * rsqrt_nr(A.q + G.delta2);
+    const double at = pc * rs, dat = rs * fma(-pc * A.iQ, gtv, dpc);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      g[k] = Dual{gg[0][k], gg[2][k]};
-      gu[k] = Dual{gg[1][k], gg[3][k]};
-    }
-    const Dual dphi{vv[0], gv[2]}, du{vv[1], gv[3]};
-    Dual s1, s2, f1[3], f2[3];
-    double a2;
-    alloy_point<DIM, Dual>(G, C, phi, g, u, gu, dphi, du, vv[2], vv[3], s1, f1, s2, f2, a2);
-    s[0] = s1.d;
-    s[1] = s2.d;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      f[0][k] = f1[k].d;
-      f[1][k] = f2[k].d;
+      f[0][k] = k < DIM ? C.theta * Hv[k] : 0.0;
+      f[1][k] = k < DIM ? fma(mob, gg[3][k], fma(dmob, gg[1][k], fma(at, gg[2][k], dat * gg[0][k]))) : 0.0;
     }
   }
 };
@@ -141,52 +141,47 @@ struct AlloyElement {
     if constexpr (DIM == 3) quad3<NG, NV, 2, 0>(G, ng, nv, os, dummy, ph);
     else quad2<NG, NV, 2, 0>(G, ng, nv, os, dummy, ph);
   }
-  // u0/u1: (phi, u) of the state (the perturbed state for FD), p0/p1 of the
-  // previous state, hs: history rate, xc: x coordinates, v0/v1: direction.
-  __device__ __forceinline__ static void run(const Geo& G, const AlloyConst& C,
+  // ex: the element along axis 0.  u0/u1: (phi, u) of the state (the perturbed
+  // state for FD), p0/p1 of the previous state, hs: history rate, v0/v1:
+  // direction.
+  __device__ __forceinline__ static void run(const Geo& G, const AlloyConst& C, int ex,
                                              const double (&u0)[NA], const double (&u1)[NA],
                                              const double (&p0)[NA], const double (&p1)[NA],
-                                             const double (&hs)[NA], const double (&xc)[NA],
-                                             const double (&v0)[NA], const double (&v1)[NA],
+                                             const double (&hs)[NA], const double (&v0)[NA], const double (&v1)[NA],
                                              double (&out)[2][NA], double& ge) {
 #pragma unroll
     for (int a = 0; a < NA; ++a) out[0][a] = out[1][a] = 0.0;
-    double nv[4][NA];
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      nv[0][a] = u0[a] - p0[a];
-      nv[1][a] = u1[a] - p1[a];
-      nv[2][a] = hs[a];
-      nv[3][a] = xc[a];
-    }
     if constexpr (MODE == MODE_JVP) {
-      double ng[4][NA];
+      double ng[4][NA], nv[2][NA];
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
         ng[0][a] = u0[a];
         ng[1][a] = u1[a];
         ng[2][a] = v0[a];
         ng[3][a] = v1[a];
+        nv[0][a] = u0[a] - p0[a];
+        nv[1][a] = hs[a];
       }
-      PhysAlloyJvp<DIM> ph(G, C);
-      quad<4, 4>(G, ng, nv, out, ph);
+      PhysAlloyJvp<DIM> ph(G, C, ex);
+      quad<4, 2>(G, ng, nv, out, ph);
       ge = 0.0;
     } else {
-      double ng[2][NA];
+      double ng[2][NA], nv[3][NA];
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
         ng[0][a] = u0[a];
         ng[1][a] = u1[a];
+        nv[0][a] = u0[a] - p0[a];
+        nv[1][a] = u1[a] - p1[a];
+        nv[2][a] = hs[a];
       }
-      PhysAlloyRes<DIM> ph(G, C);
-      quad<2, 4>(G, ng, nv, out, ph);
+      PhysAlloyRes<DIM> ph(G, C, ex);
+      quad<2, 3>(G, ng, nv, out, ph);
       ge = ph.ca;
     }
   }
 };
 
-// The element vector of element ex (along axis 0) whose first corner is node
-// base; sx, sy (, sz) are the node strides.  ge: the cell integral of cu a^2.
 template <int DIM, int MODE>
 __device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C, int ex,
                                               long long base, const double2* __restrict__ U,
@@ -198,7 +193,7 @@ __device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C,
   constexpr int NA = 1 << DIM;
   const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
-  double u0[NA], u1[NA], p0[NA], p1[NA], hs[NA], xc[NA], v0[NA], v1[NA];
+  double u0[NA], u1[NA], p0[NA], p1[NA], hs[NA], v0[NA], v1[NA];
 #pragma unroll
   for (int a = 0; a < NA; ++a) {
     const long long node = base + (a & 1) + ((a >> 1) & 1) * s1 + (DIM == 3 ? ((a >> 2) & 1) * s2 : 0);
@@ -217,9 +212,8 @@ __device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C,
     v0[a] = v.x;
     v1[a] = v.y;
     hs[a] = C.use_hist ? H.at(node, up) : 0.0;
-    xc[a] = fma((double)(ex + (a & 1)), C.h0, C.x0);
   }
-  AlloyElement<DIM, MODE == MODE_FD ? MODE_RES : MODE>::run(G, C, u0, u1, p0, p1, hs, xc, v0, v1,
+  AlloyElement<DIM, MODE == MODE_FD ? MODE_RES : MODE>::run(G, C, ex, u0, u1, p0, p1, hs, v0, v1,
                                                             out, ge);
 }
 

@@ -138,10 +138,17 @@ __device__ __forceinline__ double rcp_nr1(double x) {
 // every Gauss plane gz: a loader that reads them from memory each time keeps
 // them out of registers between planes (quad3 passes register arrays).
 //
+// phys.point(gx) comes before a point's call, for functors with terms that
+// depend on its place along x (PointFree: those without).
+//
 // The element outputs are accumulated through acc: acc.s(o, a, c1, v1, c2, v2)
 // adds c1 v1 + c2 v2 (two FMAs) to value-and-flux output o at corner a,
 // acc.p(o, a, c, v) adds c v to value-only output o (RegAcc: register arrays;
 // StridedAcc: a lane's slots in memory).
+struct PointFree {
+  __device__ __forceinline__ void point(int) {}
+};
+
 template <int NS, int NP>
 struct RegAcc {
   double (&os)[NS > 0 ? NS : 1][8];
@@ -248,6 +255,7 @@ __device__ __forceinline__ void quad3g(const Geo& G, Load& load, Acc& acc, Phys&
 #pragma unroll
         for (int f = 0; f < NV; ++f) vv[f] = fma(bx1, dqw[f], qw[f][0]);
         double s[NS > 0 ? NS : 1], fl[NS > 0 ? NS : 1][3], p[NP > 0 ? NP : 1];
+        phys.point(gx);
         phys(gv, gg, vv, s, fl, p);
         const double wq = Q1::w(gx), w0 = Q1::c0(gx), w1 = Q1::c1(gx);
         phys.weight(wq);
@@ -390,6 +398,7 @@ __device__ __forceinline__ void quad2(const Geo& G, const double (&ng)[NG][4],
 #pragma unroll
       for (int f = 0; f < NV; ++f) vv[f] = fma(bx1, dqw[f], qw[f][0]);
       double s[NS > 0 ? NS : 1], fl[NS > 0 ? NS : 1][3], p[NP > 0 ? NP : 1];
+      phys.point(gx);
       phys(gv, gg, vv, s, fl, p);
       const double wq = Q1::w(gx), w0 = Q1::c0(gx), w1 = Q1::c1(gx);
       phys.weight(wq);
@@ -439,6 +448,8 @@ struct Aniso {
   // J_k = g_k t_k, t_k = a^2 + aqc (g_k^2 - S/Q) formed as
   // (a^2 - aqc S/Q) + aqc g_k^2 (one FMA per component).
   double q, S, iQ, iQ2, a, a2, b, aqc, SQ, g2[3], J[3];
+  // kSteps: Newton steps of 1/Q (rcp_nr1, rcp_nr)
+  template <int kSteps = 1>
   __device__ __forceinline__ void flux(const double* g, const Geo& G) {
     q = 0.0;
     S = 0.0;
@@ -448,7 +459,7 @@ struct Aniso {
       q += g2[k];
       S = fma(g2[k], g2[k], S);
     }
-    iQ = rcp_nr1(q + G.delta2);
+    iQ = kSteps == 1 ? rcp_nr1(q + G.delta2) : rcp_nr(q + G.delta2);
     iQ2 = iQ * iQ;
     a = fma(G.e4x4 * S, iQ2, G.a0);
     SQ = S * iQ;
@@ -503,7 +514,7 @@ struct Aniso {
 // Residual F1 (Gauss part): gradient field {phi}; value fields {u, phi - phi^n};
 // output s = a^2 (phi - phi^n)/dt - (phi - phi^3 - lambda (1 - phi^2)^2 u), f = J.
 template <int DIM>
-struct PhysResidual {
+struct PhysResidual : PointFree {
   // all three points of a row unrolled, rows one at a time: more independent
   // work per row within the two-waves-per-SIMD register budget
   static constexpr int kGxUnroll = 3;
@@ -537,7 +548,7 @@ struct PhysResidual {
 // Tangent of F1 (Gauss part): gradient fields {phi, v_phi}; value fields
 // {u, phi - phi^n, v_u}.
 template <int DIM>
-struct PhysJvp {
+struct PhysJvp : PointFree {
   static constexpr int kGxUnroll = PF_TAN_GX_UNROLL;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
@@ -569,7 +580,7 @@ struct PhysJvp {
 // term) and gUprev_phi (time term); accumulates w1 . dF1/d eps4 and
 // w1 . dF1/d lambda (F2 does not depend on the parameters).
 template <int DIM>
-struct PhysVjp {
+struct PhysVjp : PointFree {
   static constexpr int kGxUnroll = PF_TAN_GX_UNROLL;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
@@ -621,7 +632,7 @@ struct PhysVjp {
 // Adjoint of F1 restricted to (dF1/dU)^T w1: gradient fields {phi, w1}; value
 // fields {u, phi - phi^n}; outputs gU_phi (value + flux) and value-only gU_u.
 template <int DIM>
-struct PhysVjpU {
+struct PhysVjpU : PointFree {
   static constexpr int kGxUnroll = PF_TAN_GX_UNROLL;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
@@ -653,7 +664,7 @@ struct PhysVjpU {
 // output, gUprev_phi (time term); the parameter sums as PhysVjp.  No
 // (dF1/dU)^T w1 part, so no Hessian-vector product.
 template <int DIM>
-struct PhysVjpPrev {
+struct PhysVjpPrev : PointFree {
   static constexpr int kGxUnroll = PF_TAN_GX_UNROLL;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;

@@ -8,9 +8,8 @@
 // are summed in LDS in a fixed order (pf_tile2.h; order 2 below).  3-D: two
 // passes, one thread per element evaluates the element vectors into the
 // element buffer, then the gather of pf_residual.hip forms the node sums.  The
-// analytic
-// tangent runs the pointwise template on dual numbers.
-#include "pf_dual.h"
+// analytic tangent differentiates the pointwise terms by hand, the anisotropic
+// flux through the Hessian-vector product of pf_element.h.
 #include "pf_tile2.h"
 
 namespace pf {
@@ -19,51 +18,58 @@ namespace {
 
 constexpr int kFgBlock = 128;
 
-// Pointwise terms: s1, f1 (phi rows), s3, f3 (T rows); a2 receives a^2.
-template <int DIM, class T>
-__device__ __forceinline__ void fg_point(const Geo& G, const FgConst& C, const T& phi,
-                                         const T (&g)[3], const T& tem, const T (&gT)[3],
-                                         const T& dphi, const T& dT, double hist, T& s1,
-                                         T (&f1)[3], T& s3, T (&f3)[3], double& a2) {
-  T g2[3], q = g[0] * g[0], S;
-  g2[0] = q;
-  S = g2[0] * g2[0];
-#pragma unroll
-  for (int k = 1; k < DIM; ++k) {
-    g2[k] = g[k] * g[k];
-    q = q + g2[k];
-    S = S + g2[k] * g2[k];
-  }
-  const T iQ = rcp_t(q + G.delta2);
-  const T iQ2 = iQ * iQ;
-  const T a = G.a0 + G.e4x4 * (S * iQ2);
-  const T SQ = S * iQ;
-  const T aa = a * a;
-  const T aqc = a * q * (G.e16 * iQ2);
-  const T om = 1.0 - phi;
-  const T pom = phi * om;
+// Pointwise terms of the residual: s[0], f[0] (phi rows), s[1], f[1] (T rows).
+// a2 receives a^2.
+template <int DIM>
+__device__ __forceinline__ void fg_residual_point(const Geo& G, const FgConst& C, double phi,
+                                                  const double* g, double tem, const double* gT,
+                                                  double dphi, double dT, double hist, double* s,
+                                                  double (*f)[3], double& a2) {
+  Aniso<DIM> A;
+  A.template flux<2>(g, G);
+  const double om = 1.0 - phi, pom = phi * om;
   // G2 = bg phi (1-phi)(1-2phi)/W^2 - 5 beta (Tm - T) phi^2 (1-phi)^2 / W
-  const T G2 = pom * (C.c_dw * (1.0 - 2.0 * phi) - C.c_drv * ((C.Tm - tem) * pom));
-  s1 = aa * dphi * G.idt + C.theta * G2;
-  const T ph = (C.theta * G.idt) * dphi + hist;
-  s3 = G.idt * dT - C.Lcp * ph;
-  const double tb = C.theta * C.bg, ta = C.theta * C.alpha;
+  const double G2 = pom * fma(C.c_dw, om - phi, -C.c_drv * ((C.Tm - tem) * pom));
+  s[0] = fma(A.a2 * dphi, G.idt, C.theta * G2);
+  const double ph = fma(C.theta * G.idt, dphi, hist);
+  s[1] = fma(G.idt, dT, -C.Lcp * ph);
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    if (k < DIM) {
-      f1[k] = tb * (g[k] * (aa + aqc * (g2[k] - SQ)));
-      f3[k] = ta * gT[k];
-    } else {
-      f1[k] = T{};
-      f3[k] = T{};
-    }
+    f[0][k] = k < DIM ? (C.theta * C.bg) * A.J[k] : 0.0;
+    f[1][k] = k < DIM ? (C.theta * C.alpha) * gT[k] : 0.0;
   }
-  a2 = val(aa);
+  a2 = A.a2;
+}
+
+// The same differentiated along (tp, tT): the T rows are linear, and with
+// pom = phi (1 - phi), dpom = (1 - 2 phi) tp,
+//   dG2 = dpom (c_dw (1 - 2 phi) - 2 c_drv (Tm - T) pom)
+//         + pom (c_drv pom tT - 2 c_dw tp).
+template <int DIM>
+__device__ __forceinline__ void fg_tangent_point(const Geo& G, const FgConst& C, double phi,
+                                                 const double* g, double tem, double dphi, double tp,
+                                                 const double* tg, double tT, const double* tgT,
+                                                 double* s, double (*f)[3]) {
+  Aniso<DIM> A;
+  A.template flux<2>(g, G);
+  double Hv[3] = {0.0, 0.0, 0.0}, da, gtv, gmv;
+  A.template hvp_c<false>(g, tg, 0.0, Hv, da, gtv, gmv);
+  const double om = 1.0 - phi, pom = phi * om, w = om - phi;
+  const double dr = C.c_drv * ((C.Tm - tem) * pom);
+  const double dG2 = fma(w * tp, fma(C.c_dw, w, -2.0 * dr),
+                         pom * fma(C.c_drv * pom, tT, (-2.0 * C.c_dw) * tp));
+  s[0] = fma(fma((A.a + A.a) * da, dphi, A.a2 * tp), G.idt, C.theta * dG2);
+  s[1] = G.idt * fma(-C.Lcp * C.theta, tp, tT);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    f[0][k] = k < DIM ? (C.theta * C.bg) * Hv[k] : 0.0;
+    f[1][k] = k < DIM ? (C.theta * C.alpha) * tgT[k] : 0.0;
+  }
 }
 
 // Order 1.  Residual: gradient fields {phi, T}; value fields {dphi, dT, hist}.
 template <int DIM>
-struct PhysFgRes {
+struct PhysFgRes : PointFree {
   static constexpr int kGxUnroll = 1;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
@@ -78,16 +84,13 @@ struct PhysFgRes {
   __device__ __forceinline__ void operator()(const double* gv, const double (*gg)[3],
                                              const double* vv, double* s, double (*f)[3],
                                              double*) {
-    const double g[3] = {gg[0][0], gg[0][1], gg[0][2]};
-    const double gT[3] = {gg[1][0], gg[1][1], gg[1][2]};
-    fg_point<DIM, double>(G, C, gv[0], g, gv[1], gT, vv[0], vv[1], vv[2], s[0], f[0], s[1], f[1],
-                          a2);
+    fg_residual_point<DIM>(G, C, gv[0], gg[0], gv[1], gg[1], vv[0], vv[1], vv[2], s, f, a2);
   }
 };
 
-// Order 1.  Tangent: gradient fields {phi, T, v_phi, v_T}; value fields as above.
+// Order 1.  Tangent: gradient fields {phi, tp, tT}; value fields {T, dphi}.
 template <int DIM>
-struct PhysFgJvp {
+struct PhysFgJvp : PointFree {
   static constexpr int kGxUnroll = 1;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
@@ -98,24 +101,7 @@ struct PhysFgJvp {
   __device__ __forceinline__ void operator()(const double* gv, const double (*gg)[3],
                                              const double* vv, double* s, double (*f)[3],
                                              double*) {
-    const Dual phi{gv[0], gv[2]}, tem{gv[1], gv[3]};
-    Dual g[3], gT[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      g[k] = Dual{gg[0][k], gg[2][k]};
-      gT[k] = Dual{gg[1][k], gg[3][k]};
-    }
-    const Dual dphi{vv[0], gv[2]}, dT{vv[1], gv[3]};
-    Dual s1, s3, f1[3], f3[3];
-    double a2;
-    fg_point<DIM, Dual>(G, C, phi, g, tem, gT, dphi, dT, vv[2], s1, f1, s3, f3, a2);
-    s[0] = s1.d;
-    s[1] = s3.d;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      f[0][k] = f1[k].d;
-      f[1][k] = f3[k].d;
-    }
+    fg_tangent_point<DIM>(G, C, gv[0], gg[0], vv[0], vv[1], gv[1], gg[1], gv[2], gg[2], s, f);
   }
 };
 
@@ -132,43 +118,44 @@ __device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long 
   constexpr int NA = 1 << DIM;
   const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
-  double ng[4][NA], nv[3][NA];
+  constexpr int NG = MODE == MODE_JVP ? 3 : 2, NV = MODE == MODE_JVP ? 2 : 3;
+  double ng[NG][NA], nv[NV][NA];
 #pragma unroll
   for (int a = 0; a < NA; ++a) {
     const long long node = base + (a & 1) + ((a >> 1) & 1) * s1 + (DIM == 3 ? ((a >> 2) & 1) * s2 : 0);
     double2 u = U[node];
     const double2 up = Up[node];
-    double2 v = make_double2(0.0, 0.0);
-    if (MODE != MODE_RES) v = V[node];
-    if (MODE == MODE_FD) {
-      u.x = fma(eps, v.x, u.x);
-      u.y = fma(eps, v.y, u.y);
+    if constexpr (MODE == MODE_JVP) {
+      const double2 v = V[node];
+      ng[0][a] = u.x;
+      ng[1][a] = v.x;
+      ng[2][a] = v.y;
+      nv[0][a] = u.y;
+      nv[1][a] = u.x - up.x;
+    } else {
+      if constexpr (MODE == MODE_FD) {
+        const double2 v = V[node];
+        u.x = fma(eps, v.x, u.x);
+        u.y = fma(eps, v.y, u.y);
+      }
+      ng[0][a] = u.x;
+      ng[1][a] = u.y;
+      nv[0][a] = u.x - up.x;
+      nv[1][a] = u.y - up.y;
+      nv[2][a] = C.use_hist ? H.at(node, up) : 0.0;
     }
-    ng[0][a] = u.x;
-    ng[1][a] = u.y;
-    ng[2][a] = v.x;
-    ng[3][a] = v.y;
-    nv[0][a] = u.x - up.x;
-    nv[1][a] = u.y - up.y;
-    nv[2][a] = C.use_hist ? H.at(node, up) : 0.0;
   }
   double dummy[1][NA];
 #pragma unroll
   for (int a = 0; a < NA; ++a) out[0][a] = out[1][a] = 0.0;
   if constexpr (MODE == MODE_JVP) {
     PhysFgJvp<DIM> ph(G, C);
-    if constexpr (DIM == 3) quad3<4, 3, 2, 0>(G, ng, nv, out, dummy, ph);
-    else quad2<4, 3, 2, 0>(G, ng, nv, out, dummy, ph);
+    if constexpr (DIM == 3) quad3<3, 2, 2, 0>(G, ng, nv, out, dummy, ph);
+    else quad2<3, 2, 2, 0>(G, ng, nv, out, dummy, ph);
   } else {
-    double ng2[2][NA];
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      ng2[0][a] = ng[0][a];
-      ng2[1][a] = ng[1][a];
-    }
     PhysFgRes<DIM> ph(G, C);
-    if constexpr (DIM == 3) quad3<2, 3, 2, 0>(G, ng2, nv, out, dummy, ph);
-    else quad2<2, 3, 2, 0>(G, ng2, nv, out, dummy, ph);
+    if constexpr (DIM == 3) quad3<2, 3, 2, 0>(G, ng, nv, out, dummy, ph);
+    else quad2<2, 3, 2, 0>(G, ng, nv, out, dummy, ph);
     ca = ph.ca;
   }
 }
@@ -271,9 +258,10 @@ __global__ void __launch_bounds__(kTile2Threads)
       for (int lx = 0; lx < 3; ++lx) out[o][ly][lx] = 0.0;
   if (elem) {
     const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
-    // gradient fields: 0 phi, 1 T, (2 v_phi, 3 v_T); value fields: 0 dphi, 1 dT, 2 hist
-    constexpr int NG = MODE == MODE_JVP ? 4 : 2;
-    double g[NG][3][3], w[3][3][3];
+    // gradient fields: residual {phi, T}, tangent {phi, tp, tT}; value fields:
+    // residual {dphi, dT, hist}, tangent {T, dphi}
+    constexpr int NG = MODE == MODE_JVP ? 3 : 2, NV = MODE == MODE_JVP ? 2 : 3;
+    double g[NG][3][3], w[NV][3][3];
 #pragma unroll
     for (int ly = 0; ly < 3; ++ly)
 #pragma unroll
@@ -281,28 +269,32 @@ __global__ void __launch_bounds__(kTile2Threads)
         const long long node = base + lx + nn0 * ly;
         double2 u = U[node];
         const double2 up = Up[node];
-        if constexpr (MODE != MODE_RES) {
+        if constexpr (MODE == MODE_JVP) {
           const double2 v = V[node];
+          g[0][ly][lx] = u.x;
+          g[1][ly][lx] = v.x;
+          g[2][ly][lx] = v.y;
+          w[0][ly][lx] = u.y;
+          w[1][ly][lx] = u.x - up.x;
+        } else {
           if constexpr (MODE == MODE_FD) {
+            const double2 v = V[node];
             u.x = fma(eps, v.x, u.x);
             u.y = fma(eps, v.y, u.y);
-          } else {
-            g[2][ly][lx] = v.x;
-            g[3][ly][lx] = v.y;
           }
+          g[0][ly][lx] = u.x;
+          g[1][ly][lx] = u.y;
+          w[0][ly][lx] = u.x - up.x;
+          w[1][ly][lx] = u.y - up.y;
+          w[2][ly][lx] = C.use_hist ? H.at(node, up) : 0.0;
         }
-        g[0][ly][lx] = u.x;
-        g[1][ly][lx] = u.y;
-        w[0][ly][lx] = u.x - up.x;
-        w[1][ly][lx] = u.y - up.y;
-        w[2][ly][lx] = C.use_hist ? H.at(node, up) : 0.0;
       }
     const double ih0 = G.ih[0], ih1 = G.ih[1], jac = G.h[0] * G.h[1];
     double ca = 0.0;
 #pragma unroll 1
     for (int qy = 0; qy < 3; ++qy) {
       // along y: values (and y derivatives of the gradient fields) on the row
-      double gy[NG][3], dy[NG][3], wy[3][3];
+      double gy[NG][3], dy[NG][3], wy[NV][3];
 #pragma unroll
       for (int lx = 0; lx < 3; ++lx) {
 #pragma unroll
@@ -312,7 +304,7 @@ __global__ void __launch_bounds__(kTile2Threads)
                        P2::d(2, qy) * g[f][2][lx]) * ih1;
         }
 #pragma unroll
-        for (int f = 0; f < 3; ++f)
+        for (int f = 0; f < NV; ++f)
           wy[f][lx] = P2::b(0, qy) * w[f][0][lx] + P2::b(1, qy) * w[f][1][lx] + P2::b(2, qy) * w[f][2][lx];
       }
       // the row's outputs along x: value and x-flux part, y-flux part
@@ -322,7 +314,7 @@ __global__ void __launch_bounds__(kTile2Threads)
       for (int qx = 0; qx < 3; ++qx) {
         const double b0 = P2::b(0, qx), b1 = P2::b(1, qx), b2 = P2::b(2, qx);
         const double d0 = P2::d(0, qx), d1 = P2::d(1, qx), d2 = P2::d(2, qx);
-        double val[NG], dx[NG], dv[NG], wv[3];
+        double val[NG], dx[NG], dv[NG], wv[NV];
 #pragma unroll
         for (int f = 0; f < NG; ++f) {
           val[f] = b0 * gy[f][0] + b1 * gy[f][1] + b2 * gy[f][2];
@@ -330,27 +322,14 @@ __global__ void __launch_bounds__(kTile2Threads)
           dv[f] = b0 * dy[f][0] + b1 * dy[f][1] + b2 * dy[f][2];
         }
 #pragma unroll
-        for (int f = 0; f < 3; ++f) wv[f] = b0 * wy[f][0] + b1 * wy[f][1] + b2 * wy[f][2];
+        for (int f = 0; f < NV; ++f) wv[f] = b0 * wy[f][0] + b1 * wy[f][1] + b2 * wy[f][2];
         double s[2], fl[2][3], a2 = 0.0;
+        const double gp[3] = {dx[0], dv[0], 0.0}, gq[3] = {dx[1], dv[1], 0.0};
         if constexpr (MODE == MODE_JVP) {
-          const Dual phi{val[0], val[2]}, tem{val[1], val[3]};
-          const Dual gp[3] = {Dual{dx[0], dx[2]}, Dual{dv[0], dv[2]}, Dual{0.0, 0.0}};
-          const Dual gT[3] = {Dual{dx[1], dx[3]}, Dual{dv[1], dv[3]}, Dual{0.0, 0.0}};
-          const Dual dphi{wv[0], val[2]}, dT{wv[1], val[3]};
-          Dual s1, s3, f1[3], f3[3];
-          fg_point<2, Dual>(G, C, phi, gp, tem, gT, dphi, dT, wv[2], s1, f1, s3, f3, a2);
-          s[0] = s1.d;
-          s[1] = s3.d;
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            fl[0][k] = f1[k].d;
-            fl[1][k] = f3[k].d;
-          }
+          const double gr[3] = {dx[2], dv[2], 0.0};
+          fg_tangent_point<2>(G, C, val[0], gp, wv[0], wv[1], val[1], gq, val[2], gr, s, fl);
         } else {
-          const double gp[3] = {dx[0], dv[0], 0.0};
-          const double gT[3] = {dx[1], dv[1], 0.0};
-          fg_point<2, double>(G, C, val[0], gp, val[1], gT, wv[0], wv[1], wv[2], s[0], fl[0], s[1],
-                              fl[1], a2);
+          fg_residual_point<2>(G, C, val[0], gp, val[1], gq, wv[0], wv[1], wv[2], s, fl, a2);
         }
         car = fma(Q1::w(qx), a2, car);
 #pragma unroll
