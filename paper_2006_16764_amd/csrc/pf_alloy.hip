@@ -41,9 +41,10 @@ struct Frozen {
 // factor of the time term (the preconditioner's phi-block coefficient).
 template <int DIM>
 struct PhysAlloyRes {
-  // unroll choices measured at 1024 x 256 x 256 (points and rows unrolled)
+  // 3-D: points unrolled, rows one at a time (with rows unrolled too, 18
+  // VGPRs spill at two wavefronts per SIMD)
   static constexpr int kGxUnroll = 3;
-  static constexpr int kGyUnroll = PF_GY_UNROLL;
+  static constexpr int kGyUnroll = 1;
   const Geo& G;
   const AlloyConst& C;
   Frozen T;
@@ -86,7 +87,7 @@ struct PhysAlloyRes {
 //   dph = theta tp/dt,  d(ph cu) = dph cu + ph omk tu,  drs = -rs gv/Q,
 //   d(mob grad u + at g) = mob grad tu - (theta D/2) tp grad u + at grad tp + dat g.
 // On dual numbers the same took about half as many operations again: 3-D
-// element pass on 512 x 128 x 128 DUALOLD -> DUALNEW us.
+// analytic Jv on 512 x 128 x 128 2190 -> 1990 us.
 template <int DIM>
 struct PhysAlloyJvp {
   // points unrolled, rows one at a time (measured at 1024 x 256 x 256)
@@ -237,8 +238,16 @@ __global__ void __launch_bounds__(kTile2Threads)
   tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
+// 3-D element vectors, one element per lane, into the element buffer.  The
+// residual (and the difference quotient's residual) reads its corners again at
+// every Gauss plane and keeps its element vector in its own LDS slots: 240
+// VGPRs, two wavefronts per SIMD, where the same with both in registers takes
+// 370 and one.  512 x 128 x 128: residual 1466 -> 1279 us, difference quotient
+// 1522 -> 1447 us.  The tangent carries two more gradient fields and spills at
+// two wavefronts (4226 us against 1990 at one), and at one the reloads only
+// cost time (2092 us): corners and element vector stay in registers.
 template <int MODE>
-__global__ void __launch_bounds__(kAlloyBlock)
+__global__ void __launch_bounds__(kAlloyBlock, MODE == MODE_JVP ? 1 : 2)
     k_alloy_elem3(Geo G, AlloyConst C, const double2* __restrict__ U,
                   const double2* __restrict__ Up, const double2* __restrict__ V,
                   const double* __restrict__ eps_dev, HistArg H, double* __restrict__ E,
@@ -252,14 +261,32 @@ __global__ void __launch_bounds__(kAlloyBlock)
   const int ez = (int)blockIdx.y;
   const long long e = (long long)ez * pe + q;
   const long long base = ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez);
-  double out[2][8];
-  double ge = 0.0;
-  alloy_element<3, MODE>(G, C, ex, base, U, Up, V, eps_dev, H, out, ge);
-  if (MODE == MODE_RES && coef) coef[e] = ge / (8.0 * G.jac);
+  if constexpr (MODE == MODE_JVP) {
+    double out[2][8];
+    double ge = 0.0;
+    alloy_element<3, MODE>(G, C, ex, base, U, Up, V, eps_dev, H, out, ge);
 #pragma unroll
-  for (int o = 0; o < 2; ++o)
+    for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = out[o][a];
+      for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = out[o][a];
+  } else {
+    __shared__ double sh[2][8][kAlloyBlock];
+    const int t = (int)threadIdx.x;
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int a = 0; a < 8; ++a) sh[o][a][t] = 0.0;
+    const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
+    const ReloadRes<MODE == MODE_FD> load{G, U, Up, V, C.use_hist ? H.rate : nullptr, base, eps};
+    StridedAcc acc{&sh[0][0][t], nullptr, kAlloyBlock};
+    PhysAlloyRes<3> ph(G, C, ex);
+    quad3g<2, 3, 2, 0>(G, load, acc, ph);
+    if (MODE == MODE_RES && coef) coef[e] = ph.ca / (8.0 * G.jac);
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = sh[o][a][t];
+  }
 }
 
 __global__ void k_history(long long n, const double2* __restrict__ Un,

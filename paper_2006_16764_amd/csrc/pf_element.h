@@ -344,6 +344,39 @@ __device__ __forceinline__ void quad3(const Geo& G, const double (&ng)[NG][8],
   quad3g<NG, NV, NS, NP>(G, load, acc, phys);
 }
 
+// Loader for the residuals of two gradient fields and three value fields
+// {U - U^n, history rate}: reads the corners of the element with first corner
+// base at every plane.  The barrier keeps the compiler from reading them once
+// and holding 40 doubles over all planes.
+template <bool kFd>
+struct ReloadRes {
+  const Geo& G;
+  const double2 *U, *Up, *V;
+  const double* rate;  // null: no history term
+  long long base;
+  double eps;
+  __device__ __forceinline__ void operator()(int, double (&ng)[2][8], double (&nv)[3][8]) const {
+    __asm__ volatile("" ::: "memory");
+    const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+      const long long node = base + (a & 1) + ((a >> 1) & 1) * s1 + (a >> 2) * s2;
+      double2 u = U[node];
+      const double2 up = Up[node];
+      if constexpr (kFd) {
+        const double2 v = V[node];
+        u.x = fma(eps, v.x, u.x);
+        u.y = fma(eps, v.y, u.y);
+      }
+      ng[0][a] = u.x;
+      ng[1][a] = u.y;
+      nv[0][a] = u.x - up.x;
+      nv[1][a] = u.y - up.y;
+      nv[2][a] = rate ? rate[node] : 0.0;
+    }
+  }
+};
+
 // ----------------------------------------------------------------- Gauss-rule part, 2-D
 template <int NG, int NV, int NS, int NP, class Phys>
 __device__ __forceinline__ void quad2(const Geo& G, const double (&ng)[NG][4],

@@ -70,7 +70,8 @@ __device__ __forceinline__ void fg_tangent_point(const Geo& G, const FgConst& C,
 // Order 1.  Residual: gradient fields {phi, T}; value fields {dphi, dT, hist}.
 template <int DIM>
 struct PhysFgRes : PointFree {
-  static constexpr int kGxUnroll = 1;
+  // 3-D: points and rows unrolled (rows one at a time: 575 us against 561)
+  static constexpr int kGxUnroll = 3;
   static constexpr int kGyUnroll = PF_GY_UNROLL;
   const Geo& G;
   const FgConst& C;
@@ -91,8 +92,10 @@ struct PhysFgRes : PointFree {
 // Order 1.  Tangent: gradient fields {phi, tp, tT}; value fields {T, dphi}.
 template <int DIM>
 struct PhysFgJvp : PointFree {
-  static constexpr int kGxUnroll = 1;
-  static constexpr int kGyUnroll = PF_GY_UNROLL;
+  // 3-D: points unrolled, rows one at a time (rows unrolled spill: 1018 us
+  // against 674 on 256 x 128 x 128)
+  static constexpr int kGxUnroll = 3;
+  static constexpr int kGyUnroll = 1;
   const Geo& G;
   const FgConst& C;
   __device__ PhysFgJvp(const Geo& g, const FgConst& c) : G(g), C(c) {}
@@ -105,24 +108,23 @@ struct PhysFgJvp : PointFree {
   }
 };
 
-// The element vector of the element whose first corner is node base.  ca: the
+// 2-D: the element vector of the element whose first corner is node base.  ca: the
 // cell integral of a^2.
-template <int DIM, int MODE>
+template <int MODE>
 __device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long long base,
                                            const double2* __restrict__ U,
                                            const double2* __restrict__ Up,
                                            const double2* __restrict__ V,
                                            const double* __restrict__ eps_dev,
-                                           const HistArg& H, double (&out)[2][1 << DIM],
+                                           const HistArg& H, double (&out)[2][4],
                                            double& ca) {
-  constexpr int NA = 1 << DIM;
-  const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
+  const long long s1 = G.nn[0];
   const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
   constexpr int NG = MODE == MODE_JVP ? 3 : 2, NV = MODE == MODE_JVP ? 2 : 3;
-  double ng[NG][NA], nv[NV][NA];
+  double ng[NG][4], nv[NV][4];
 #pragma unroll
-  for (int a = 0; a < NA; ++a) {
-    const long long node = base + (a & 1) + ((a >> 1) & 1) * s1 + (DIM == 3 ? ((a >> 2) & 1) * s2 : 0);
+  for (int a = 0; a < 4; ++a) {
+    const long long node = base + (a & 1) + (a >> 1) * s1;
     double2 u = U[node];
     const double2 up = Up[node];
     if constexpr (MODE == MODE_JVP) {
@@ -145,17 +147,15 @@ __device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long 
       nv[2][a] = C.use_hist ? H.at(node, up) : 0.0;
     }
   }
-  double dummy[1][NA];
+  double dummy[1][4];
 #pragma unroll
-  for (int a = 0; a < NA; ++a) out[0][a] = out[1][a] = 0.0;
+  for (int a = 0; a < 4; ++a) out[0][a] = out[1][a] = 0.0;
   if constexpr (MODE == MODE_JVP) {
-    PhysFgJvp<DIM> ph(G, C);
-    if constexpr (DIM == 3) quad3<3, 2, 2, 0>(G, ng, nv, out, dummy, ph);
-    else quad2<3, 2, 2, 0>(G, ng, nv, out, dummy, ph);
+    PhysFgJvp<2> ph(G, C);
+    quad2<3, 2, 2, 0>(G, ng, nv, out, dummy, ph);
   } else {
-    PhysFgRes<DIM> ph(G, C);
-    if constexpr (DIM == 3) quad3<2, 3, 2, 0>(G, ng, nv, out, dummy, ph);
-    else quad2<2, 3, 2, 0>(G, ng, nv, out, dummy, ph);
+    PhysFgRes<2> ph(G, C);
+    quad2<2, 3, 2, 0>(G, ng, nv, out, dummy, ph);
     ca = ph.ca;
   }
 }
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(kTile2Threads)
   double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
   double ca = 0.0;
   if (P.elem) {
-    fg_element<2, MODE>(G, C, P.base, U, Up, V, eps_dev, H, out, ca);
+    fg_element<MODE>(G, C, P.base, U, Up, V, eps_dev, H, out, ca);
     if (MODE == MODE_RES && coef && P.node)
       coef[P.ex + (long long)G.n[0] * P.ey] = ca / (4.0 * G.jac);
   }
@@ -180,8 +180,14 @@ __global__ void __launch_bounds__(kTile2Threads)
   tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
+// 3-D element vectors, one element per lane, into the element buffer.  The
+// corners are read again at every Gauss plane and the element vector lies in
+// the lane's own LDS slots: at most 246 VGPRs, two wavefronts per SIMD, where
+// the same with both in registers takes 310 to 350 and one.  256 x 128 x 128
+// elements: residual 751 -> 561 us, analytic Jv 899 -> 674 us, difference
+// quotient 807 -> 639 us.
 template <int MODE>
-__global__ void __launch_bounds__(kFgBlock)
+__global__ void __launch_bounds__(kFgBlock, 2)
     k_fg_elem3(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
                const double2* __restrict__ V, const double* __restrict__ eps_dev,
                HistArg H, double* __restrict__ E, double* __restrict__ coef) {
@@ -191,15 +197,42 @@ __global__ void __launch_bounds__(kFgBlock)
   const long long ex = e % n0;
   const long long rest = e / n0;
   const long long ey = rest % n1, ez = rest / n1;
-  double out[2][8];
-  double ca = 0.0;
-  fg_element<3, MODE>(G, C, ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez), U, Up, V,
-                      eps_dev, H, out, ca);
-  if (MODE == MODE_RES && coef) coef[e] = ca / (8.0 * G.jac);
+  const long long base = ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez);
+  __shared__ double sh[2][8][kFgBlock];
+  const int t = (int)threadIdx.x;
 #pragma unroll
   for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = out[o][a];
+    for (int a = 0; a < 8; ++a) sh[o][a][t] = 0.0;
+  StridedAcc acc{&sh[0][0][t], nullptr, kFgBlock};
+  if constexpr (MODE == MODE_JVP) {
+    auto load = [&](int, double (&ng)[3][8], double (&nv)[2][8]) {
+      __asm__ volatile("" ::: "memory");
+      const long long s1 = G.nn[0], s2 = (long long)G.nn[0] * G.nn[1];
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        const long long node = base + (a & 1) + ((a >> 1) & 1) * s1 + (a >> 2) * s2;
+        const double2 u = U[node], v = V[node];
+        ng[0][a] = u.x;
+        ng[1][a] = v.x;
+        ng[2][a] = v.y;
+        nv[0][a] = u.y;
+        nv[1][a] = u.x - Up[node].x;
+      }
+    };
+    PhysFgJvp<3> ph(G, C);
+    quad3g<3, 2, 2, 0>(G, load, acc, ph);
+  } else {
+    const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
+    const ReloadRes<MODE == MODE_FD> load{G, U, Up, V, C.use_hist ? H.rate : nullptr, base, eps};
+    PhysFgRes<3> ph(G, C);
+    quad3g<2, 3, 2, 0>(G, load, acc, ph);
+    if (MODE == MODE_RES && coef) coef[e] = ph.ca / (8.0 * G.jac);
+  }
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = sh[o][a][t];
 }
 
 // ----------------------------------------------------------------- order 2 (2-D)
