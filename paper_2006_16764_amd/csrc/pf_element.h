@@ -41,6 +41,21 @@
 
 namespace pf {
 
+// Workgroup barrier for LDS only: this wave's LDS operations have completed
+// and no memory access is moved across it by the compiler, but global loads
+// and stores issued before it may still be in flight.  __syncthreads() also
+// waits for those (a workgroup release fence), which exposes the latency of
+// every store a wave issued just before it.  Used where the threads of a
+// workgroup exchange data through LDS only (no thread reads another's global
+// writes within a launch).
+#ifndef PF_LDS_BARRIER
+#define PF_LDS_BARRIER 1
+#endif
+__device__ __forceinline__ void lds_barrier() {
+  if (PF_LDS_BARRIER) __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else __syncthreads();
+}
+
 struct Q1 {
   static constexpr double s = 0.77459666924148337704;  // sqrt(3/5)
   __host__ __device__ static constexpr double b0(int g) {
@@ -544,7 +559,7 @@ struct Aniso {
   }
 };
 
-// Residual F1 (Gauss part): gradient field {phi}; value fields {u, phi - phi^n};
+// Residual F1 (Gauss part): gradient field {phi}; value fields {lambda u, (phi - phi^n)/dt};
 // output s = a^2 (phi - phi^n)/dt - (phi - phi^3 - lambda (1 - phi^2)^2 u), f = J.
 template <int DIM>
 struct PhysResidual : PointFree {
@@ -562,16 +577,15 @@ struct PhysResidual : PointFree {
     ca = fma(wrow, car, ca);
     car = 0.0;
   }
-  // vv[1] holds (phi - phi^n)/dt
   __device__ __forceinline__ void operator()(const double* gv, const double (*gg)[3],
                                              const double* vv, double* s, double (*f)[3],
                                              double*) {
-    const double phi = gv[0], u = vv[0], dphi_dt = vv[1];
+    const double phi = gv[0], lu = vv[0], dphi_dt = vv[1];
     Aniso<DIM> A;
     A.flux(gg[0], G);
     a2 = A.a * A.a;
     const double om = fma(-phi, phi, 1.0);
-    const double R = om * fma(-G.lam * om, u, phi);  // phi - phi^3 - lambda (1-phi^2)^2 u
+    const double R = om * fma(-om, lu, phi);  // phi - phi^3 - lambda (1-phi^2)^2 u
     s[0] = fma(a2, dphi_dt, -R);
 #pragma unroll
     for (int k = 0; k < 3; ++k) f[0][k] = (k < DIM) ? A.J[k] : 0.0;
@@ -750,6 +764,10 @@ template <int DIM, int MODE>
 struct Element {
   static constexpr int NA = 1 << DIM;
   static constexpr int NO = MODE == MODE_VJP ? 4 : 2;
+  // 3-D residual, FD and analytic products: the element vector is the Gauss
+  // part of F1 over theta; the caller scales it and forms the linear part (all
+  // of output 1) at the nodes
+  static constexpr bool kF1Only = DIM == 3 && (MODE == MODE_RES || MODE == MODE_FD || MODE == MODE_JVP);
 
   template <int NG, int NV, int NS, int NP, class Phys>
   __device__ __forceinline__ static void quad(const Geo& G, const double (&ng)[NG][NA],
@@ -795,26 +813,11 @@ struct Element {
         src.loaded(gz);
       };
       double* o0 = src.out(0);
-      double* o1 = src.out(1);
 #pragma unroll
       for (int a = 0; a < NA; ++a) o0[a * T] = 0.0;
       StridedAcc acc{o0, nullptr, T};
       PhysJvp<DIM> ph(G);
       quad3g<2, 3, 1, 0>(G, load, acc, ph);
-      // d F2 = M (v_u - theta v_phi/2)/dt + theta D K v_u
-      double y[NA], v1[NA], f2[NA];
-#pragma unroll
-      for (int a = 0; a < NA; ++a) {
-        double2 u, p, v;
-        src.corner(a, u, p, v);
-        v1[a] = v.y;
-        y[a] = v.y - G.hth * v.x;
-        f2[a] = 0.0;
-        o0[a * T] = G.theta * o0[a * T];
-      }
-      lin(G, y, G.idt, v1, G.Dth, f2);
-#pragma unroll
-      for (int a = 0; a < NA; ++a) o1[a * T] = f2[a];
     } else {
       // adjoint modes: gradient fields {phi, w1}, value fields {u, phi - phi^n}
       auto load = [&](int gz, double (&ng)[2][NA], double (&nv)[2][NA]) {
@@ -928,24 +931,26 @@ struct Element {
     double dummy[1][NA];
     if constexpr (MODE == MODE_RES || MODE == MODE_FD) {
       // F2 = M (du - theta dphi/2)/dt + theta D K u
-      double y[NA];
+      if constexpr (!kF1Only) {
+        double y[NA];
 #pragma unroll
-      for (int a = 0; a < NA; ++a) y[a] = (u1[a] - p1[a]) - G.hth * dphi[a];
-      lin(G, y, G.idt, u1, G.Dth, out[1]);
+        for (int a = 0; a < NA; ++a) y[a] = (u1[a] - p1[a]) - G.hth * dphi[a];
+        lin(G, y, G.idt, u1, G.Dth, out[1]);
+      }
       // F1 = theta [a^2 dphi/(theta dt) - R + J]: the Gauss rule sees the time
       // term over theta and the element vector is scaled once
       double ngv[1][NA], nvv[2][NA], os[1][NA];
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
         ngv[0][a] = u0[a];
-        nvv[0][a] = u1[a];
+        nvv[0][a] = G.lam * u1[a];
         nvv[1][a] = dphi[a] * G.idtm;
         os[0][a] = 0.0;
       }
       PhysResidual<DIM> ph(G);
       quad<1, 2, 1, 0>(G, ngv, nvv, os, dummy, ph);
 #pragma unroll
-      for (int a = 0; a < NA; ++a) out[0][a] = G.theta * os[0][a];
+      for (int a = 0; a < NA; ++a) out[0][a] = kF1Only ? os[0][a] : G.theta * os[0][a];
       ge = ph.ca;  // cell integral of a^2 (the cell mean times the cell volume)
     } else if constexpr (MODE == MODE_JVP) {
       // d F2 = M (v_u - theta v_phi/2)/dt + theta D K v_u

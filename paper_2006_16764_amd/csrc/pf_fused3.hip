@@ -1,20 +1,22 @@
 // Single-pass 3-D residual family (F, fused FD Jv, analytic Jv, VJP).
 //
 // A workgroup of 256 lanes owns a tile of 16 x 16 element columns and marches
-// through KZ element layers in z.  Per layer it stages the next node plane
-// (17 x 17 nodes of U, U^n and the direction/cotangent V; for the FD product
-// the perturbed state U + eps V) in LDS, every lane evaluates one element
-// (pf_element.h) and the node sums are formed in LDS in a fixed order:
-//   plane k = (top contributions of layer k-1, carried in registers)
+// through KZ element layers in z.  Per layer the next-but-one node plane (17 x
+// 17 nodes of U, U^n and the direction/cotangent V) is copied into LDS, every
+// lane evaluates one element (pf_element.h) and the node sums are formed from
+// the element vectors in LDS in a fixed order:
+//   plane k = (top contributions of layer k-1, carried in LDS)
 //           + (bottom contributions of layer k).
 // Nodes strictly inside the tile box are complete and written once.  Nodes on
 // the tile's side faces or on its first/last plane also receive contributions
 // from neighbouring tiles; their partial sums go to a side buffer that holds,
 // per tile and densely, only those ring nodes (the first and last planes
 // whole, the perimeter of every plane between them), and k_fixup3 -- one
-// workgroup per tile, over the ring nodes that tile owns -- adds the partials
+// slot of the tile per lane, for the ring nodes that tile owns -- adds the partials
 // of the <= 8 tiles that share such a node, in a fixed tile order.  No atomics:
 // results are bitwise reproducible.
+#include <type_traits>
+
 #include "pf_element.h"
 
 namespace pf {
@@ -39,10 +41,10 @@ constexpr int SN = 2 * PN + (KZ - 1) * RING;
 // a tile plane: bottom edge left to right, right edge upwards, top edge right
 // to left, left edge downwards (2 (lxmax + lymax) positions).
 __device__ __forceinline__ int ring_pos(int lx, int ly, int lxmax, int lymax) {
-  if (ly == 0 && lx < lxmax) return lx;
-  if (lx == lxmax && ly < lymax) return lxmax + ly;
-  if (ly == lymax && lx > 0) return lxmax + lymax + (lxmax - lx);
-  return 2 * lxmax + lymax + (lymax - ly);
+  int p = 2 * (lxmax + lymax) - ly;
+  p = ly == lymax && lx > 0 ? 2 * lxmax + lymax - lx : p;
+  p = lx == lxmax && ly < lymax ? lxmax + ly : p;
+  return ly == 0 && lx < lxmax ? lx : p;
 }
 
 // Inverse of ring_pos; false for positions beyond the perimeter.
@@ -85,17 +87,9 @@ struct Tiles {
   int ntx, nty, ntz;
 };
 
-// Residual and FD product: node planes go from HBM straight into LDS
-// (global_load_lds_dwordx4, one double2 per lane, no registers) two planes
-// ahead through a ring of three plane slots.  PF_FUSED_DMA=0 at build time
-// keeps the register-staged loads instead.
-#ifndef PF_FUSED_DMA
-#define PF_FUSED_DMA 1
-#endif
-// the same copies for the tangent and adjoint kernels (else register prefetch)
-#ifndef PF_FUSED_DMA_ALL
-#define PF_FUSED_DMA_ALL 1
-#endif
+// Node planes go from HBM straight into LDS (global_load_lds_dwordx4, one
+// double2 per lane, no registers) two planes ahead through a ring of three
+// plane slots.
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
 
@@ -110,22 +104,13 @@ __device__ __forceinline__ void dma16(const double2* src, double2* lds_row, int 
 // copies into LDS included, have completed.
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-#ifndef PF_TAN_SRC
-#define PF_TAN_SRC 1
-#endif
-// the residual stages all 8 corners of its element vectors at once (0: halves)
-#ifndef PF_RES_CB8
-#define PF_RES_CB8 1
-#endif
-// waves per SIMD of the analytic product and the lean adjoint products when
-// they read corners from the staged planes (a build-time knob: 1 or 2)
+// waves per SIMD of the analytic product and the lean adjoint products (a
+// build-time knob: 1 or 2)
 #ifndef PF_TAN_WAVES
 #define PF_TAN_WAVES 2
 #endif
 template <int MODE>
-constexpr int kWavesPerSimd = (MODE == MODE_RES || MODE == MODE_FD) ? 2
-                              : (MODE == MODE_VJP || !PF_TAN_SRC || !PF_FUSED_DMA || !PF_FUSED_DMA_ALL) ? 1
-                                                                                      : PF_TAN_WAVES;
+constexpr int kWavesPerSimd = (MODE == MODE_RES || MODE == MODE_FD) ? 2 : MODE == MODE_VJP ? 1 : PF_TAN_WAVES;
 
 // Corner source of Element::run_src built from three callables.
 template <class C, class P, class L>
@@ -145,9 +130,25 @@ struct LdsCorners {
 
 template <int MODE>
 struct ModeInfo {
-  static constexpr bool kHasV = MODE != MODE_RES;
   static constexpr int NO = MODE == MODE_VJP ? 4 : 2;  // doubles per node output
+  static constexpr bool kHasV = MODE != MODE_RES;
+  // Residual, FD and analytic products: output 1 is the exact linear part
+  // alone, M y + theta D K x of two nodal fields, which is formed at the nodes
+  // (NodalLin) instead of per element.
+  static constexpr bool kNodal = MODE == MODE_RES || MODE == MODE_FD || MODE == MODE_JVP;
+  static constexpr int NE = kNodal ? 1 : NO;  // fields of the element vectors
 };
+
+// Coefficients of the nodal linear part, see k_fused3.
+struct NodalLin {
+  double m, kx, ky, q;
+};
+
+NodalLin nodal_lin(const Geo& G) {
+  const double hx6 = G.h[0] / 6.0, hy6 = G.h[1] / 6.0, hz6 = G.h[2] / 6.0;
+  return NodalLin{G.idt * hx6 * hy6 * hz6, G.Dth * G.ih[0] * hy6 * hz6, G.Dth * hx6 * G.ih[1] * hz6,
+                  G.Dth * hx6 * hy6 * G.ih[2]};
+}
 
 __device__ __forceinline__ long long gnode(const Geo& G, int x, int y, int z) {
   return x + (long long)G.nn[0] * (y + (long long)G.nn[1] * z);
@@ -160,37 +161,53 @@ __device__ __forceinline__ long long gnode(const Geo& G, int x, int y, int z) {
 // only): also write the cell means of a^2 for the preconditioner -- a
 // separate instantiation, so that the plain residual carries no branch or
 // store for it and profiles name the two kernels apart.
+//
+// Nodal linear part (ModeInfo::kNodal).  The tile's elements contribute to
+// M y + theta D K x the tensor products of their 1-D matrices, and over the
+// tile those assemble to products of 1-D three-point rows, the mass rows
+// (h/6)(f_l + 2 a f + f_r) and the stiffness rows (1/h)((f - f_l) + (f - f_r)),
+// with a the number of the tile's elements beside the node along that axis and
+// absent neighbours left out.  Every difference is taken on the field itself
+// and the mass rows act on the differences: differences of mass sums would lose
+// two digits where x is smooth.  With P_k the share of plane k,
+// m (Mx My y) + kx (My Kx x) + ky (Mx Ky x), and Q_k = q Mx My (x_k - x_(k+1)),
+// an element layer between planes k and k + 1 adds 2 P_k + P_(k+1) + Q_k to
+// plane k and P_k + 2 P_(k+1) - Q_k to plane k + 1.
+// y, x and x_k - x_(k+1) of a plane are formed once per node, in LDS with a
+// border of zeros, where the sums read 9 neighbours at fixed offsets.
+// The residual's kernels are bound by FP64 issue (86 % of the cycles in which
+// waves are resident): about 55 operations per node instead of 210 per element
+// and a second field in the element vectors' LDS exchange.
+//
+// The node phase between a layer's two barriers is a third of a layer's time
+// when its LDS reads wait for each other and one wave takes the 33 nodes beyond
+// the 256 lanes after its own (6200 of 19000 clocks); with the reads of all
+// slots issued together, both parts in one stream of instructions and one store
+// per node it is 4300 of 17000, which the other workgroup of the compute unit
+// fills with element work.  Measured (with k_fixup3): residual 257^3 nodes 1160
+// -> 1040 us, FD product 1385 -> 1262 and on 129^3 201 -> 174, analytic product
+// 1850 -> 1760, adjoint on 130 x 98 x 114 367 -> 326.
 template <int MODE, bool kCoef = false>
 __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
-    k_fused3(Geo G, Tiles T, const double2* __restrict__ U, const double2* __restrict__ Up,
+    k_fused3(Geo G, Tiles T, NodalLin L, const double2* __restrict__ U, const double2* __restrict__ Up,
              const double2* __restrict__ V, const double* __restrict__ eps_dev,
              const double2* __restrict__ F0, double2* __restrict__ out0, double2* __restrict__ out1,
              double* __restrict__ side, double* __restrict__ vjp_part, double* __restrict__ coef) {
   using MI = ModeInfo<MODE>;
-  constexpr int NO = MI::NO;
-  // plane copies straight into LDS (residual, FD product): three slots
-  constexpr bool kDma = PF_FUSED_DMA && (PF_FUSED_DMA_ALL || MODE == MODE_RES || MODE == MODE_FD);
-  constexpr int NS = kDma ? 3 : 2;
-  // FD through the copies: raw U and V staged, U + eps V formed at the corner reads
-  constexpr bool kRawV = kDma && MODE == MODE_FD;
-  // tangent and adjoint modes with copies: corner values read from the staged
-  // planes at every Gauss plane instead of held in registers (PF_TAN_SRC=0 at
-  // build time keeps them in registers)
-  constexpr bool kSrc = PF_TAN_SRC && kDma && !(MODE == MODE_RES || MODE == MODE_FD);
-  __shared__ double2 su[NS][PN];
-  __shared__ double2 sp[NS][PN];
-  __shared__ double2 sv[(MI::kHasV && MODE != MODE_FD) || kRawV ? NS : 1]
-                       [(MI::kHasV && MODE != MODE_FD) || kRawV ? PN : 1];
-  // FD product: F0 of the staged planes, so that the node writes need no load
-  __shared__ double2 sf[MODE == MODE_FD ? NS : 1][MODE == MODE_FD ? PN : 1];
-  // element vectors for the node sums: corner halves staged one at a time
-  // (4 corners), or -- the modes that read corners from the planes -- all 8
-  // corners, accumulated there by the element routine itself
-  // (the residual stages all 8 too: two barriers per layer fewer; the FD
-  // product keeps the halves, its staged F0 planes leave no LDS for them)
-  constexpr bool kCb8 = kSrc || (MODE == MODE_RES && PF_RES_CB8);
-  constexpr int kCbA = kCb8 ? 8 : 4;
-  __shared__ double cb[NO][kCbA][kThreads];
+  constexpr int NO = MI::NO, NE = MI::NE;
+  constexpr bool kNodal = MI::kNodal;
+  // residual and FD product hold their corner values in registers over the
+  // Gauss planes; the others read them from the staged planes at every one
+  constexpr bool kSrc = !(MODE == MODE_RES || MODE == MODE_FD);
+  __shared__ double2 su[3][PN];
+  __shared__ double2 sp[3][PN];
+  __shared__ double2 sv[MI::kHasV ? 3 : 1][MI::kHasV ? PN : 1];
+  // FD product: F0 of planes kz and kz + 1, so that the node writes need no load
+  __shared__ double2 sf[MODE == MODE_FD ? 2 : 1][MODE == MODE_FD ? PN : 1];
+  // element vectors for the node sums, all 8 corners; zeros for lanes without
+  // an element and in the slot kThreads
+  constexpr int kCb = kThreads + 1;
+  __shared__ double cb[NE][8][kCb];
 
   const int tid = threadIdx.x;
   const int tile = (int)xcd_tile(blockIdx.x, gridDim.x);
@@ -207,221 +224,248 @@ __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
   const double eps = (MODE == MODE_FD) ? eps_dev[0] : 0.0;
   const double ieps = (MODE == MODE_FD) ? eps_dev[1] : 0.0;
 
-  // node ownership for the gathers: lane owns node tid and, for tid < PN - 256, node 256 + tid
-  constexpr int kSecond = PN - kThreads;  // 33
-  const int nA = tid, nB = tid + kThreads;
-  const bool ownB = tid < kSecond;
-  // top-corner sums carried to the next plane, per owned node, in LDS (only
-  // the owning lane reads and writes its entries): no registers held across
+  // A plane has more nodes than lanes.  Node sums: lane t takes node (t % 16,
+  // t / 16), and one wave the 33 nodes of the last column and row, another
+  // wave every layer, so that the four SIMDs share that work.  Copies (nodes
+  // in storage order): likewise for the nodes beyond the first kThreads.
+  constexpr int kSecond = PX + TY;
+  static_assert(kSecond <= 64 && PN - kThreads <= 64 && TX == 16, "one wave takes the second part");
+  // the lane's index, formed anew where it is used: what follows from it (node
+  // coordinates, neighbours' offsets, flags) is then not kept in registers over
   // the element evaluation
+  auto lane = [&]() {
+    int t = tid;
+    __asm__ volatile("" : "+v"(t));
+    return t;
+  };
+  auto turn = [&](int t, int kz) { return __builtin_amdgcn_readfirstlane(t >> 6) == (kz & 3); };
+  struct Node {
+    int lx, ly, n;
+    bool ok;  // in the tile's box
+  };
+  auto node1 = [&](int t) {
+    const int lx = t % TX, ly = t / TX;
+    return Node{lx, ly, lx + PX * ly, lx <= lxmax && ly <= lymax};
+  };
+  // lanes past the last of the 33 repeat it, so that the sums need no branch
+  auto node2 = [&](int t) {
+    const int k = min(t & 63, kSecond - 1);
+    const int lx = k < PY ? TX : k - PY, ly = k < PY ? k : TY;
+    return Node{lx, ly, lx + PX * ly, (t & 63) < kSecond && lx <= lxmax && ly <= lymax};
+  };
+  // per node of the plane: the contributions of the layer below, carried in
+  // LDS (no registers held across the element evaluation).  Nodal linear part:
+  // carry[1] also holds 2 P of the layer above.
   __shared__ double carry[NO][PN];
+  for (int n = tid; n < PN; n += kThreads)
 #pragma unroll
-  for (int o = 0; o < NO; ++o) {
-    carry[o][nA] = 0.0;
-    if (ownB) carry[o][nB] = 0.0;
-  }
+    for (int o = 0; o < NO; ++o) carry[o][n] = 0.0;
+  // Nodal linear part: (y, x) and x_k - x_(k+1) of the plane kz + 1 and its
+  // nodes' P (the lane's first node in a register)
+  constexpr int kRow = PX + 1, kFields = kNodal ? kRow * (PY + 2) + 1 : 1;
+  __shared__ double2 yx[kFields];
+  __shared__ double xd[kFields];
+  __shared__ double pn2[kNodal ? kSecond : 1];
+  double pn1 = 0.0;
 
-  auto load_plane = [&](int slot, int z) {
-    for (int n = tid; n < PN; n += kThreads) {
-      const int lx = n % PX, ly = n / PX;
-      if (lx <= lxmax && ly <= lymax) {
-        const long long g = gnode(G, x0 + lx, y0 + ly, z);
-        double2 u = U[g];
-        if (MODE == MODE_FD) {
-          const double2 v = V[g];
-          u.x = fma(eps, v.x, u.x);
-          u.y = fma(eps, v.y, u.y);
-          sf[slot][n] = F0[g];
-        } else if (MI::kHasV) {
-          sv[slot][n] = V[g];
-        }
-        su[slot][n] = u;
-        sp[slot][n] = Up[g];
-      }
-    }
-  };
-
-  // Plane z into ring slot `slot` by direct copies into LDS (kDma modes); the
-  // copies complete by the wave's next wait_vm().
-  auto dma_plane = [&](int slot, int z) {
-    for (int n = tid; n < PN; n += kThreads) {
-      const int lx = n % PX, ly = n / PX;
-      if (lx <= lxmax && ly <= lymax) {
-        const long long g = gnode(G, x0 + lx, y0 + ly, z);
-        dma16(U + g, &su[slot][0], n);
-        dma16(Up + g, &sp[slot][0], n);
-        if (kRawV) {
-          dma16(V + g, &sv[slot][0], n);
-          dma16(F0 + g, &sf[slot][0], n);
-        } else if (MI::kHasV && MODE != MODE_FD) {
-          dma16(V + g, &sv[slot][0], n);
-        }
-      }
-    }
-  };
-
-  // Plane prefetch (modes at one wave per SIMD, whose single workgroup per
-  // compute unit would otherwise wait out every plane load): the next-but-one
-  // node plane is read right after the element evaluation and stored to its
-  // LDS slot after the next barrier, so its memory latency is spent in the
-  // node-sum phase.  The residual and FD product run two workgroups per
-  // compute unit, which cover each other's loads, and have no registers to
-  // spare for it.
-  constexpr bool kPrefetch = !kDma && !(MODE == MODE_RES || MODE == MODE_FD);
-  static_assert(!(kPrefetch && MODE == MODE_FD), "the prefetch path does not stage F0");
-  // Node tid of the plane goes through registers; the few nodes beyond the
-  // first kThreads are read when stored.
-  double2 fu, fp, fv;
-  bool fok;
-  auto fetch_plane = [&](int z) {
-    const int lx = tid % PX, ly = tid / PX;
-    fok = lx <= lxmax && ly <= lymax;
-    if (fok) {
+  // Plane z into ring slot `slot` by direct copies into LDS; the copies
+  // complete by the wave's next wait_vm().
+  auto dma_part = [&](int n, int slot, int z) {
+    const int lx = n % PX, ly = n / PX;
+    if (lx <= lxmax && ly <= lymax) {
       const long long g = gnode(G, x0 + lx, y0 + ly, z);
-      fu = U[g];
-      fp = Up[g];
-      if (MI::kHasV) fv = V[g];
+      dma16(U + g, su[slot], n);
+      dma16(Up + g, sp[slot], n);
+      if (MI::kHasV) dma16(V + g, sv[slot], n);
     }
   };
-  auto store_plane = [&](int slot, int z) {
-    if (fok) {
-      double2 u = fu;
-      if (MODE == MODE_FD) {
-        u.x = fma(eps, fv.x, u.x);
-        u.y = fma(eps, fv.y, u.y);
-      } else if (MI::kHasV) {
-        sv[slot][tid] = fv;
-      }
-      su[slot][tid] = u;
-      sp[slot][tid] = fp;
+  auto dma_plane = [&](int slot, int z) {
+    const int t = lane();
+    dma_part(t, slot, z);
+    if (turn(t, z) && (t & 63) < PN - kThreads) dma_part(kThreads + (t & 63), slot, z);
+  };
+  auto dma_f0 = [&](int lz) {
+    if constexpr (MODE == MODE_FD) {
+      auto part = [&](int n) {
+        const int lx = n % PX, ly = n / PX;
+        if (lx <= lxmax && ly <= lymax) dma16(F0 + gnode(G, x0 + lx, y0 + ly, z0 + lz), sf[lz & 1], n);
+      };
+      const int t = lane();
+      part(t);
+      if (turn(t, lz) && (t & 63) < PN - kThreads) part(kThreads + (t & 63));
     }
-    for (int n = tid + kThreads; n < PN; n += kThreads) {
-      const int lx = n % PX, ly = n / PX;
-      if (lx <= lxmax && ly <= lymax) {
-        const long long g = gnode(G, x0 + lx, y0 + ly, z);
-        double2 u = U[g];
-        if (MODE == MODE_FD) {
-          const double2 v = V[g];
-          u.x = fma(eps, v.x, u.x);
-          u.y = fma(eps, v.y, u.y);
-        } else if (MI::kHasV) {
-          sv[slot][n] = V[g];
-        }
-        su[slot][n] = u;
-        sp[slot][n] = Up[g];
+  };
+
+  // The fields of the nodal linear part at node N of the staged plane in `slot`.
+  auto fields = [&](const Node& N, int slot) {
+    if (!N.ok) return;
+    const int q = kRow + 1 + N.lx + kRow * N.ly;
+    double y, x;
+    if constexpr (MODE == MODE_JVP) {
+      const double2 v = sv[slot][N.n];
+      y = fma(-G.hth, v.x, v.y);
+      x = v.y;
+    } else {
+      double2 u = su[slot][N.n];
+      const double2 p = sp[slot][N.n];
+      if constexpr (MODE == MODE_FD) {
+        const double2 v = sv[slot][N.n];
+        u.x = fma(eps, v.x, u.x);
+        u.y = fma(eps, v.y, u.y);
       }
+      y = fma(-G.hth, u.x - p.x, u.y - p.y);
+      x = u.y;
     }
+    xd[q] = yx[q].y - x;
+    yx[q] = make_double2(y, x);
+  };
+  // P of node (lx, ly) of the plane whose fields are formed, and Q of the plane
+  // below it.
+  auto nodal = [&](int lx, int ly, double& P, double& Q) {
+    const double l = lx > 0 ? 1.0 : 0.0, r = lx < lxmax ? 1.0 : 0.0;
+    const double d = ly > 0 ? 1.0 : 0.0, t = ly < lymax ? 1.0 : 0.0;
+    const double ax = l + r, ay = d + t;
+    const double ax2 = ax + ax, ay2 = ay + ay;
+    double m[3][3], x[3][3], z[3][3];
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        const int q = lx + dx + kRow * (ly + dy);
+        const double2 v = yx[q];
+        m[dy][dx] = v.x;
+        x[dy][dx] = v.y;
+        z[dy][dx] = xd[q];
+      }
+    // mass rows along x and y, and the stiffness rows
+    auto mass = [](double a2, const double (&f)[3]) { return fma(a2, f[1], f[0] + f[2]); };
+    double Mm[3], Mz[3], Kx[3], Ky[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      Mm[k] = mass(ax2, m[k]);
+      Mz[k] = mass(ax2, z[k]);
+      Kx[k] = fma(l, x[k][1], -x[k][0]) + fma(r, x[k][1], -x[k][2]);
+      Ky[k] = fma(d, x[1][k], -x[0][k]) + fma(t, x[1][k], -x[2][k]);
+    }
+    P = fma(L.m, mass(ay2, Mm), fma(L.kx, mass(ay2, Kx), L.ky * mass(ax2, Ky)));
+    Q = L.q * mass(ay2, Mz);
   };
 
   const long long tile_base = (long long)tile * SN;
-  // Write the sum of node n (local) of plane lz: final value or side-buffer
-  // partial.  Plane lz is staged in slot lz % 3 (plane copies) or lz & 1.
-  auto emit = [&](int n, int lz, const double* acc) {
-    const int lx = n % PX, ly = n / PX;
-    if (lx > lxmax || ly > lymax) return;
-    const bool ring = lx == 0 || lx == lxmax || ly == 0 || ly == lymax || lz == 0 || lz == kzmax;
-    if (ring) {
-      double* s = side + (tile_base + side_slot(lx, ly, lz, lxmax, lymax, kzmax)) * NO;
-      if (MODE == MODE_FD) {
-        // the tile that owns the node in the fixup (below its upper extent
-        // along every axis, or on the mesh's upper face) subtracts F0 from its
-        // partial, so that the fixup needs no F0: Jv = (sum of partials)/eps
-        const bool owned = (lx < lxmax || tx == T.ntx - 1) && (ly < lymax || ty == T.nty - 1) &&
-                           (lz < kzmax || tz == T.ntz - 1);
-        const double2 f0 = owned ? sf[kDma ? lz % 3 : lz & 1][n] : make_double2(0.0, 0.0);
-        s[0] = acc[0] - f0.x;
-        s[1] = acc[1] - f0.y;
-        return;
-      }
-#pragma unroll
-      for (int o = 0; o < NO; ++o) s[o] = acc[o];
-      return;
-    }
+  // Write the sum of a node of plane lz: final value or side-buffer partial
+  // (always the latter on the tile's last column and row: kSide).  One store
+  // per output whichever it is: every wave has nodes of both kinds.
+  double2* const side_base = reinterpret_cast<double2*>(side) + tile_base * (NO / 2);
+  auto emit = [&](auto kSide, const Node& N, int lz, const double* acc) {
+    const int lx = N.lx, ly = N.ly;
+    const bool ring = kSide() || lx == 0 || lx == lxmax || ly == 0 || ly == lymax || lz == 0 || lz == kzmax;
+    double2* const ps = side_base + side_slot(lx, ly, lz, lxmax, lymax, kzmax) * (NO / 2);
     const long long g = gnode(G, x0 + lx, y0 + ly, z0 + lz);
-    if (MODE == MODE_FD) {
-      const double2 f0 = sf[kDma ? lz % 3 : lz & 1][n];
-      out0[g] = make_double2((acc[0] - f0.x) * ieps, (acc[1] - f0.y) * ieps);
+    if constexpr (MODE == MODE_FD) {
+      // the tile that owns the node in the fixup (below its upper extent
+      // along every axis, or on the mesh's upper face) subtracts F0 from its
+      // partial, so that the fixup needs no F0: Jv = (sum of partials)/eps
+      const bool owned = (lx < lxmax || tx == T.ntx - 1) && (ly < lymax || ty == T.nty - 1) &&
+                         (lz < kzmax || tz == T.ntz - 1);
+      double2 f0 = sf[lz & 1][N.n];
+      if (ring && !owned) f0 = make_double2(0.0, 0.0);
+      const double sc = ring ? 1.0 : ieps;
+      *(ring ? ps : out0 + g) = make_double2((acc[0] - f0.x) * sc, (acc[1] - f0.y) * sc);
     } else {
-      if (out0) out0[g] = make_double2(acc[0], acc[1]);
-      if (NO == 4 && out1) out1[g] = make_double2(acc[2 % NO], acc[3 % NO]);
+      if (ring || out0) *(ring ? ps : out0 + g) = make_double2(acc[0], acc[1]);
+      if (NO == 4 && (ring || out1)) *(ring ? ps + 1 : out1 + g) = make_double2(acc[2 % NO], acc[3 % NO]);
     }
   };
 
-  // Sum of corner half h (0 = bottom corners a = 0..3, 1 = top a = 4..7) of the
-  // <= 4 in-plane elements around local node n.
-  auto gather = [&](int n, double* acc, int half) {
-    const int lx = n % PX, ly = n / PX;
+  // Node n of plane kz: its sum is complete (bottom corners of layer kz and
+  // the carried part) and written; the top corners are carried to plane kz + 1.
+  // Every element's slot is read without a branch (the zero slot for absent
+  // ones), so that all LDS reads of a node are in flight together: with one
+  // branch per element the reads of a layer's two sums cost 8 LDS latencies.
+  auto finish = [&](const Node& N, int kz, double& pn, double (&acc)[NO]) {
+    const int lx = N.lx, ly = N.ly, n = N.n;
+    double P = 0.0, Q = 0.0;
+    if constexpr (kNodal) nodal(lx, ly, P, Q);
+    const bool le = lx > 0, re = lx < TX, de = ly > 0, te = ly < TY;
+    const int e = lx + TX * ly;
+    const int slot[4] = {le && de ? e - TX - 1 : kThreads, re && de ? e - TX : kThreads,
+                         le && te ? e - 1 : kThreads, re && te ? e : kThreads};
+    double up[NE];
 #pragma unroll
-    for (int o = 0; o < NO; ++o) acc[o] = 0.0;
-#pragma unroll
-    for (int by = 0; by < 2; ++by) {
-      const int e_j = ly - 1 + by;
-      if (e_j < 0 || e_j >= lymax) continue;
-#pragma unroll
-      for (int bx = 0; bx < 2; ++bx) {
-        const int e_i = lx - 1 + bx;
-        if (e_i < 0 || e_i >= lxmax) continue;
-        const int lane = e_i + TX * e_j;
-        const int a = (1 - bx) + 2 * (1 - by);
-#pragma unroll
-        for (int o = 0; o < NO; ++o) acc[o] += cb[o][(kCb8 ? 4 * half : 0) + a][lane];
-      }
+    for (int o = 0; o < NE; ++o) {
+      // corner 3 - k of the k-th element around the node
+      acc[o] = cb[o][3][slot[0]] + cb[o][2][slot[1]] + cb[o][1][slot[2]] + cb[o][0][slot[3]];
+      up[o] = cb[o][7][slot[0]] + cb[o][6][slot[1]] + cb[o][5][slot[2]] + cb[o][4][slot[3]];
+      acc[o] += carry[o][n];
     }
+    if constexpr (kNodal) {
+      acc[0] *= G.theta;
+      acc[1] = carry[1][n] + (P + Q);
+      carry[1][n] = (pn - Q) + (kz + 1 < kzmax ? 4.0 : 2.0) * P;
+      pn = P;
+    }
+#pragma unroll
+    for (int o = 0; o < NE; ++o) carry[o][n] = up[o];
   };
+  const auto first_part = std::integral_constant<bool, false>{};
+  const auto second_part = std::integral_constant<bool, true>{};
 
   double ge = 0.0, gl = 0.0;
-  if (kDma) {
-    dma_plane(0, z0);
-    dma_plane(1, z0 + 1);
-    wait_vm();
+  for (int n = tid; n < NE * 8 * kCb; n += kThreads) (&cb[0][0][0])[n] = 0.0;
+  for (int n = tid; kNodal && n < kFields; n += kThreads) {
+    yx[n] = make_double2(0.0, 0.0);
+    xd[n] = 0.0;
+  }
+  dma_plane(0, z0);
+  dma_plane(1, z0 + 1);
+  dma_f0(0);
+  wait_vm();
+  __syncthreads();
+  if constexpr (kNodal) {
+    fields(node1(tid), 0);
+    if (turn(tid, 0)) fields(node2(tid), 0);
     __syncthreads();
-  } else {
-    load_plane(0, z0);
-    if (kPrefetch) {
-      load_plane(1, z0 + 1);
-      __syncthreads();
-    }
+    auto start = [&](const Node& N, double& pn) {
+      double Q;
+      nodal(N.lx, N.ly, pn, Q);
+      carry[1][N.n] = pn + pn;
+    };
+    start(node1(tid), pn1);
+    if (turn(tid, 0)) start(node2(tid), pn2[min(tid & 63, kSecond - 1)]);
+    __syncthreads();
   }
   for (int kz = 0; kz < kzmax; ++kz) {
-    // ring slots: plane kz in kz % 3 (copies) or kz & 1
-    const int bot = kDma ? kz % 3 : kz & 1;
-    const int top = kDma ? (kz + 1) % 3 : bot ^ 1;
-    const bool more = kPrefetch && kz + 2 <= kzmax;  // plane z0 + kz + 2 exists in this chunk
-    if (!kDma && !kPrefetch) {
-      load_plane(top, z0 + kz + 1);
-      __syncthreads();
-    }
-    double out[NO][8];
+    // ring slots: plane kz in kz % 3
+    const int bot = kz % 3, top = (kz + 1) % 3;
+    auto at = [&](int a) {
+      return ((a & 4) ? top : bot) * PN + (ei + (a & 1)) + PX * (ej + ((a >> 1) & 1));
+    };
+    // the next-but-one plane: slot (kz + 2) % 3 last held plane kz - 1, which
+    // no lane reads any more
+    auto ahead = [&]() {
+      if (kz + 2 <= kzmax) dma_plane((kz + 2) % 3, z0 + kz + 2);
+      dma_f0(kz + 1);
+    };
     double u0[8], u1[8], p0[8], p1[8], v0[8], v1[8];
     if (!kSrc && has_elem) {
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
-        const int slot = (a & 4) ? top : bot;
-        const int n = (ei + (a & 1)) + PX * (ej + ((a >> 1) & 1));
-        double2 u = su[slot][n];
-        if (kRawV) {
-          const double2 v = sv[slot][n];
+        const int n = at(a);
+        double2 u = su[0][n];
+        if (MODE == MODE_FD) {
+          const double2 v = sv[0][n];
           u.x = fma(eps, v.x, u.x);
           u.y = fma(eps, v.y, u.y);
         }
-        const double2 up = sp[slot][n];
         u0[a] = u.x;
         u1[a] = u.y;
-        p0[a] = up.x;
-        p1[a] = up.y;
-        if (MODE == MODE_JVP || MODE == MODE_VJP || MODE == MODE_VJPU || MODE == MODE_VJPP) {
-          const double2 v = sv[slot][n];
-          v0[a] = v.x;
-          v1[a] = v.y;
-        } else {
-          v0[a] = v1[a] = 0.0;
-        }
+        p0[a] = sp[0][n].x;
+        p1[a] = v0[a] = v1[a] = 0.0;
       }
     }
-    // the next-but-one plane is copied once the corner values are in registers
-    // (the compiler orders LDS reads of the ring after copies into it): slot
-    // (kz + 2) % 3 last held plane kz - 1, which no lane reads any more
-    if (kDma && kz + 2 <= kzmax && !(kSrc && has_elem)) dma_plane((kz + 2) % 3, z0 + kz + 2);
+    // copied once the corner values are in registers (the compiler orders LDS
+    // reads of the ring after copies into it)
+    if (!(kSrc && has_elem)) ahead();
     if (has_elem) {
       double eg = 0.0, lg = 0.0;
       if constexpr (kSrc) {
@@ -430,22 +474,23 @@ __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
         // copy then overlaps the first plane's work: the reads of the next
         // planes wait for it)
         auto corner = [&](int a, double2& u, double2& p, double2& v) {
-          const int slot = (a & 4) ? top : bot;
-          const int n = (ei + (a & 1)) + PX * (ej + ((a >> 1) & 1));
-          u = su[slot][n];
-          p = sp[slot][n];
-          v = sv[slot][n];
+          const int n = at(a);
+          u = su[0][n];
+          p = sp[0][n];
+          v = sv[0][n];
         };
         auto plane = [&](int) { __asm__ volatile("" ::: "memory"); };
         auto loaded = [&](int gz) {
-          if (gz == 0 && kz + 2 <= kzmax) dma_plane((kz + 2) % 3, z0 + kz + 2);
+          if (gz == 0) ahead();
         };
         LdsCorners<decltype(corner), decltype(plane), decltype(loaded)> src{corner, plane, loaded,
-                                                                            &cb[0][0][tid], kCbA * kThreads,
-                                                                            kThreads};
+                                                                            &cb[0][0][tid], 8 * kCb, kCb};
         Element<3, MODE>::run_src(G, src, eg, lg);
       } else {
+        double out[2][8];
         Element<3, MODE>::run(G, u0, u1, p0, p1, v0, v1, out, eg, lg);
+#pragma unroll
+        for (int a = 0; a < 8; ++a) cb[0][a][tid] = out[0][a];
       }
       if (MODE == MODE_RES) {
         // cell mean of a^2 for the preconditioner (weights sum to 8 jac)
@@ -455,72 +500,52 @@ __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
         ge += eg;
         gl += lg;
       }
-    } else {
-#pragma unroll
-      for (int o = 0; o < NO; ++o)
-#pragma unroll
-        for (int a = 0; a < 8; ++a) out[o][a] = 0.0;
     }
-    // bottom corners -> plane kz (kSrc: all corners are in cb already;
-    // kCb8: all corners staged at once)
-    if constexpr (!kSrc) {
-#pragma unroll
-      for (int o = 0; o < NO; ++o)
-#pragma unroll
-        for (int a = 0; a < kCbA; ++a) cb[o][a][tid] = out[o][a];
+    if constexpr (kNodal) {
+      const int t = lane();
+      fields(node1(t), top);
+      if (turn(t, kz)) fields(node2(t), top);
     }
-    if (more) fetch_plane(z0 + kz + 2);
-    __syncthreads();
+    // the copies of this layer are complete here, before the node writes go
+    // out: waiting for them at the end of the layer would wait for the writes
+    // as well
+    wait_vm();
+    lds_barrier();
+    // the wave of the other workgroup on this SIMD is in its element
+    // evaluation most of the time and fills what this phase leaves idle
+    // (residual 1094 -> 1079 us at 256^3; the tangent and adjoint kernels gain
+    // nothing)
+    if (!kSrc) __builtin_amdgcn_s_setprio(2);
     {
+      const int t = lane();
+      const Node N = node1(t);
       double acc[NO];
-      gather(nA, acc, 0);
-#pragma unroll
-      for (int o = 0; o < NO; ++o) acc[o] += carry[o][nA];
-      emit(nA, kz, acc);
-      if (ownB) {
-        gather(nB, acc, 0);
-#pragma unroll
-        for (int o = 0; o < NO; ++o) acc[o] += carry[o][nB];
-        emit(nB, kz, acc);
+      if (turn(t, kz)) {
+        const Node N2 = node2(t);
+        double acc2[NO];
+        finish(N, kz, pn1, acc);
+        finish(N2, kz, pn2[min(t & 63, kSecond - 1)], acc2);
+        if (N.ok) emit(first_part, N, kz, acc);
+        if (N2.ok) emit(second_part, N2, kz, acc2);
+      } else {
+        finish(N, kz, pn1, acc);
+        if (N.ok) emit(first_part, N, kz, acc);
       }
     }
-    // slot bot (plane kz) is no longer read: every lane has passed the
-    // element evaluation; it takes plane kz + 2
-    if (more) store_plane(bot, z0 + kz + 2);
-    // top corners -> carried to plane kz + 1
-    if constexpr (!kCb8) {
-      __syncthreads();
-#pragma unroll
-      for (int o = 0; o < NO; ++o)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) cb[o][a][tid] = out[o][a + 4];
-      __syncthreads();
-    }
-    {
-      double acc[NO];
-      gather(nA, acc, 1);
-#pragma unroll
-      for (int o = 0; o < NO; ++o) carry[o][nA] = acc[o];
-      if (ownB) {
-        gather(nB, acc, 1);
-#pragma unroll
-        for (int o = 0; o < NO; ++o) carry[o][nB] = acc[o];
-      }
-    }
-    // the plane copied at the top of this iteration is read in the next one
-    if (kDma) wait_vm();
-    __syncthreads();
+    if (!kSrc) __builtin_amdgcn_s_setprio(0);
+    lds_barrier();
   }
   {
-    double acc[NO];
+    auto last = [&](const Node& N) {
+      if (!N.ok) return;
+      double acc[NO];
 #pragma unroll
-    for (int o = 0; o < NO; ++o) acc[o] = carry[o][nA];
-    emit(nA, kzmax, acc);
-    if (ownB) {
-#pragma unroll
-      for (int o = 0; o < NO; ++o) acc[o] = carry[o][nB];
-      emit(nB, kzmax, acc);
-    }
+      for (int o = 0; o < NO; ++o) acc[o] = carry[o][N.n];
+      if constexpr (kNodal) acc[0] *= G.theta;
+      emit(second_part, N, kzmax, acc);
+    };
+    last(node1(tid));
+    if (turn(tid, kzmax)) last(node2(tid));
   }
 
   if (MODE == MODE_VJP || MODE == MODE_VJPP) {
@@ -543,37 +568,39 @@ __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
   }
 }
 
-// Tiles containing coordinate c along an axis with tile width w, tile count nt
-// and last node index nmax; returns the count and fills t[0..1], l[0..1].
-__device__ __forceinline__ int axis_tiles(int c, int w, int nt, int nmax, int* t, int* l) {
-  int k = 0;
+// Tiles containing coordinate c along an axis with tile width w and tile count
+// nt: t[0] (node l[0] of it) and, for two, t[1] (l[1]); returns whether there
+// are two, else t[1], l[1] repeat the first.
+__device__ __forceinline__ bool axis_tiles(int c, int w, int nt, int (&t)[2], int (&l)[2]) {
   const int hi = c / w;
-  if (c % w == 0 && hi - 1 >= 0) {
-    t[k] = hi - 1;
-    l[k] = w;
-    ++k;
-  }
-  if (hi < nt) {
-    t[k] = hi;
-    l[k] = c - hi * w;
-    ++k;
-  }
-  (void)nmax;
-  return k;
+  const bool face = c % w == 0;
+  const bool below = face && hi > 0, above = hi < nt;
+  t[0] = below ? hi - 1 : hi;
+  l[0] = below ? w : c - hi * w;
+  t[1] = above ? hi : t[0];
+  l[1] = above ? c - hi * w : l[0];
+  return below && above;
 }
 
-// One workgroup per tile: the ring nodes the tile owns -- those whose local
-// coordinates are below the tile's upper extent along every axis, or on the
-// mesh's upper face along that axis -- each receive the sum of the partials of
-// all tiles sharing the node, taken in increasing tile order.  The tile's own
-// side-buffer slots enumerate its ring nodes (a superset of the owned ones).
+// kFixParts workgroups per tile, one slot per lane: the ring nodes the tile
+// owns -- those whose local coordinates are below the tile's upper extent along
+// every axis, or on the mesh's upper face along that axis -- each receive the
+// sum of the partials of all tiles sharing the node, taken in increasing tile
+// order.  The tile's own side-buffer slots enumerate its ring nodes (a superset
+// of the owned ones).  Bound by the latency of the partials' loads, which are
+// issued together (at most 8, only those that exist): 257^3 nodes, 79 us with one
+// workgroup per tile and the loads one after the other, 62 us now; 129^3 nodes,
+// 18 -> 9.
+constexpr int kFixParts = (SN + 255) / 256;
+
 template <int MODE>
 __global__ void __launch_bounds__(256)
     k_fixup3(Geo G, Tiles T, const double* __restrict__ side,
              const double* __restrict__ eps_dev, double2* __restrict__ out0,
              double2* __restrict__ out1) {
   constexpr int NO = ModeInfo<MODE>::NO;
-  const int tile = (int)xcd_tile(blockIdx.x, gridDim.x);
+  const int block = (int)xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = block / kFixParts;
   const int tx = tile % T.ntx;
   const int ty = (tile / T.ntx) % T.nty;
   const int tz = tile / (T.ntx * T.nty);
@@ -583,50 +610,59 @@ __global__ void __launch_bounds__(256)
   const int kzmax = min(KZ, G.n[2] - z0);
   const bool lastx = tx == T.ntx - 1, lasty = ty == T.nty - 1, lastz = tz == T.ntz - 1;
   const double ie = MODE == MODE_FD ? eps_dev[1] : 0.0;  // 1/eps
-  for (int i = (int)threadIdx.x; i < SN; i += 256) {
-    int lx, ly, lz;
-    if (i < PN) {
-      lz = 0;
-      lx = i % PX;
-      ly = i / PX;
-    } else if (i < 2 * PN) {
-      if (!lastz) continue;  // the next tile's first plane
-      lz = kzmax;
-      lx = (i - PN) % PX;
-      ly = (i - PN) / PX;
-    } else {
-      const int j = i - 2 * PN;
-      lz = 1 + j / RING;
-      if (lz >= kzmax || !ring_node(j % RING, lxmax, lymax, lx, ly)) continue;
-    }
-    if (lx > lxmax || ly > lymax) continue;
-    if ((lx == lxmax && !lastx) || (ly == lymax && !lasty)) continue;  // a neighbour's node
-    const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-    int txs[2], lxs[2], tys[2], lys[2], tzs[2], lzs[2];
-    const int nx = axis_tiles(x, TX, T.ntx, G.n[0], txs, lxs);
-    const int ny = axis_tiles(y, TY, T.nty, G.n[1], tys, lys);
-    const int nz = axis_tiles(z, KZ, T.ntz, G.n[2], tzs, lzs);
-    double acc[NO];
+  const int i = (block % kFixParts) * 256 + (int)threadIdx.x;
+  if (i >= SN) return;
+  int lx, ly, lz;
+  if (i < PN) {
+    lz = 0;
+    lx = i % PX;
+    ly = i / PX;
+  } else if (i < 2 * PN) {
+    if (!lastz) return;  // the next tile's first plane
+    lz = kzmax;
+    lx = (i - PN) % PX;
+    ly = (i - PN) / PX;
+  } else {
+    const int j = i - 2 * PN;
+    lz = 1 + j / RING;
+    if (lz >= kzmax || !ring_node(j % RING, lxmax, lymax, lx, ly)) return;
+  }
+  if (lx > lxmax || ly > lymax) return;
+  if ((lx == lxmax && !lastx) || (ly == lymax && !lasty)) return;  // a neighbour's node
+  const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+  int txs[2], lxs[2], tys[2], lys[2], tzs[2], lzs[2];
+  const bool nx = axis_tiles(x, TX, T.ntx, txs, lxs);
+  const bool ny = axis_tiles(y, TY, T.nty, tys, lys);
+  const bool nz = axis_tiles(z, KZ, T.ntz, tzs, lzs);
+  const double2* const side2 = reinterpret_cast<const double2*>(side);
+  double2 v[8][NO / 2];
 #pragma unroll
-    for (int o = 0; o < NO; ++o) acc[o] = 0.0;
-    for (int c = 0; c < nz; ++c)
-      for (int b = 0; b < ny; ++b)
-        for (int a = 0; a < nx; ++a) {
-          const long long t = txs[a] + (long long)T.ntx * (tys[b] + (long long)T.nty * tzs[c]);
-          const int slot = side_slot(lxs[a], lys[b], lzs[c], min(TX, G.n[0] - TX * txs[a]),
-                                     min(TY, G.n[1] - TY * tys[b]), min(KZ, G.n[2] - KZ * tzs[c]));
-          const double* sp = side + (t * SN + slot) * NO;
+  for (int k = 0; k < 8; ++k) {
+    const int a = k & 1, b = (k >> 1) & 1, c = k >> 2;
 #pragma unroll
-          for (int o = 0; o < NO; ++o) acc[o] += sp[o];
-        }
-    const long long g = gnode(G, x, y, z);
-    if (MODE == MODE_FD) {
-      // the owning tile's partial already holds -F0 (k_fused3)
-      out0[g] = make_double2(acc[0] * ie, acc[1] * ie);
-    } else {
-      if (out0) out0[g] = make_double2(acc[0], acc[1]);
-      if (NO == 4 && out1) out1[g] = make_double2(acc[2 % NO], acc[3 % NO]);
+    for (int o = 0; o < NO / 2; ++o) v[k][o] = make_double2(0.0, 0.0);
+    if ((a == 0 || nx) && (b == 0 || ny) && (c == 0 || nz)) {
+      const long long t = txs[a] + (long long)T.ntx * (tys[b] + (long long)T.nty * tzs[c]);
+      const int slot = side_slot(lxs[a], lys[b], lzs[c], min(TX, G.n[0] - TX * txs[a]),
+                                 min(TY, G.n[1] - TY * tys[b]), min(KZ, G.n[2] - KZ * tzs[c]));
+#pragma unroll
+      for (int o = 0; o < NO / 2; ++o) v[k][o] = side2[(t * SN + slot) * (NO / 2) + o];
     }
+  }
+#pragma unroll
+  for (int k = 1; k < 8; ++k)
+#pragma unroll
+    for (int o = 0; o < NO / 2; ++o) {
+      v[0][o].x += v[k][o].x;
+      v[0][o].y += v[k][o].y;
+    }
+  const long long g = gnode(G, x, y, z);
+  if (MODE == MODE_FD) {
+    // the owning tile's partial already holds -F0 (k_fused3)
+    out0[g] = make_double2(v[0][0].x * ie, v[0][0].y * ie);
+  } else {
+    if (out0) out0[g] = v[0][0];
+    if (NO == 4 && out1) out1[g] = v[0][NO / 2 - 1];
   }
 }
 
@@ -646,21 +682,22 @@ int launch_mode(const Geo& G, double* side, const double* U, const double* Uprev
                 double* vjp_part, double* coef, hipStream_t s) {
   const Tiles T = tiles_for(G);
   const unsigned nt = (unsigned)(T.ntx * T.nty * T.ntz);
+  const NodalLin L = nodal_lin(G);
   auto d2 = [](const double* p) { return reinterpret_cast<const double2*>(p); };
   bool with_coef = false;
   if constexpr (MODE == MODE_RES) with_coef = coef != nullptr;
   if constexpr (MODE == MODE_RES) {
     if (with_coef)
-      hipLaunchKernelGGL((k_fused3<MODE_RES, true>), dim3(nt), dim3(kThreads), 0, s, G, T, d2(U),
+      hipLaunchKernelGGL((k_fused3<MODE_RES, true>), dim3(nt), dim3(kThreads), 0, s, G, T, L, d2(U),
                          d2(Uprev), d2(v), eps_dev, d2(F0), reinterpret_cast<double2*>(out0),
                          reinterpret_cast<double2*>(out1), side, vjp_part, coef);
   }
   if (!with_coef)
-    hipLaunchKernelGGL((k_fused3<MODE, false>), dim3(nt), dim3(kThreads), 0, s, G, T, d2(U),
+    hipLaunchKernelGGL((k_fused3<MODE, false>), dim3(nt), dim3(kThreads), 0, s, G, T, L, d2(U),
                        d2(Uprev), d2(v), eps_dev, d2(F0), reinterpret_cast<double2*>(out0),
                        reinterpret_cast<double2*>(out1), side, vjp_part, nullptr);
   PF_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL((k_fixup3<MODE>), dim3(nt), dim3(256), 0, s, G, T, side,
+  hipLaunchKernelGGL((k_fixup3<MODE>), dim3(nt * kFixParts), dim3(256), 0, s, G, T, side,
                      eps_dev, reinterpret_cast<double2*>(out0), reinterpret_cast<double2*>(out1));
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;

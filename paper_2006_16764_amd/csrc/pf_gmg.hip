@@ -37,20 +37,6 @@ namespace {
 
 constexpr int kT = 256;
 
-// Workgroup barrier for LDS only: this wave's LDS operations have completed
-// and no memory access is moved across it by the compiler, but global loads
-// and stores issued before it may still be in flight.  __syncthreads() also
-// waits for those (a workgroup release fence), which exposes the latency of
-// every store a wave issued just before it.  Used where the threads of a
-// workgroup exchange data through LDS only (the tiled sweeps and the tiled
-// restriction: no thread reads another's global writes within a launch).
-#ifndef PF_LDS_BARRIER
-#define PF_LDS_BARRIER 1
-#endif
-__device__ __forceinline__ void lds_barrier() {
-  if (PF_LDS_BARRIER) __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else __syncthreads();
-}
 constexpr int kCoarseMin = 4;
 // 3-D restriction through LDS-staged fine planes (0: one thread per coarse
 // node gathering its 27 fine neighbours)
