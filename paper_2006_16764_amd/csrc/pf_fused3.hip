@@ -1,7 +1,7 @@
 // Single-pass 3-D residual family (F, fused FD Jv, analytic Jv, VJP).
 //
 // A workgroup of 256 lanes owns a tile of 16 x 16 element columns and marches
-// through KZ element layers in z.  Per layer the next-but-one node plane (17 x
+// through a chunk of element layers in z.  Per layer the next-but-one node plane (17 x
 // 17 nodes of U, U^n and the direction/cotangent V) is copied into LDS, every
 // lane evaluates one element (pf_element.h) and the node sums are formed from
 // the element vectors in LDS in a fixed order:
@@ -15,6 +15,7 @@
 // slot of the tile per lane, for the ring nodes that tile owns -- adds the partials
 // of the <= 8 tiles that share such a node, in a fixed tile order.  No atomics:
 // results are bitwise reproducible.
+#include <algorithm>
 #include <type_traits>
 
 #include "pf_element.h"
@@ -23,19 +24,14 @@ namespace pf {
 
 namespace {
 
-// element layers per z-chunk (a build-time tuning knob: 8 and 32 measured
-// 1-2 % slower for the residual and FD product at 256^3)
-#ifndef PF_FUSED_KZ
-#define PF_FUSED_KZ 16
-#endif
-constexpr int TX = 16, TY = 16, KZ = PF_FUSED_KZ;
+constexpr int TX = 16, TY = 16;
 constexpr int PX = TX + 1, PY = TY + 1;
 constexpr int PN = PX * PY;  // nodes per staged plane
 constexpr int kThreads = TX * TY;
 // side buffer: per tile the first plane (PN nodes), the last plane (PN) and
-// the perimeter ring of each of the KZ - 1 planes between them (RING nodes)
+// the perimeter ring of each of the kz - 1 planes between them (RING nodes)
 constexpr int RING = 2 * (TX + TY);
-constexpr int SN = 2 * PN + (KZ - 1) * RING;
+__host__ __device__ constexpr int side_nodes(int kz) { return 2 * PN + (kz - 1) * RING; }
 
 // Position of node (lx, ly) on the perimeter of the lxmax x lymax node box of
 // a tile plane: bottom edge left to right, right edge upwards, top edge right
@@ -75,7 +71,7 @@ __device__ __forceinline__ bool ring_node(int r, int lxmax, int lymax, int& lx, 
   return false;
 }
 
-// Side-buffer node slot (0 .. SN - 1) of ring node (lx, ly, lz) of a tile with
+// Side-buffer node slot (0 .. side_nodes - 1) of ring node (lx, ly, lz) of a tile with
 // node extents lxmax, lymax, kzmax.
 __device__ __forceinline__ int side_slot(int lx, int ly, int lz, int lxmax, int lymax, int kzmax) {
   if (lz == 0) return lx + PX * ly;
@@ -83,8 +79,9 @@ __device__ __forceinline__ int side_slot(int lx, int ly, int lz, int lxmax, int 
   return 2 * PN + (lz - 1) * RING + ring_pos(lx, ly, lxmax, lymax);
 }
 
+// Tile counts, and the element layers of a z-chunk.
 struct Tiles {
-  int ntx, nty, ntz;
+  int ntx, nty, ntz, kz;
 };
 
 // Node planes go from HBM straight into LDS (global_load_lds_dwordx4, one
@@ -214,10 +211,10 @@ __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
   const int tx = tile % T.ntx;
   const int ty = (tile / T.ntx) % T.nty;
   const int tz = tile / (T.ntx * T.nty);
-  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * KZ;
+  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * T.kz;
   const int lxmax = min(TX, G.n[0] - x0);  // last local node index in x
   const int lymax = min(TY, G.n[1] - y0);
-  const int kzmax = min(KZ, G.n[2] - z0);  // element layers in this chunk
+  const int kzmax = min(T.kz, G.n[2] - z0);  // element layers in this chunk
   const int ei = tid % TX, ej = tid / TX;  // this lane's element column
   const bool has_elem = ei < lxmax && ej < lymax;
   // FD product: eps_dev holds eps and 1/eps (0 when eps is 0)
@@ -351,7 +348,7 @@ __global__ void __launch_bounds__(kThreads, kWavesPerSimd<MODE>)
     Q = L.q * mass(ay2, Mz);
   };
 
-  const long long tile_base = (long long)tile * SN;
+  const long long tile_base = (long long)tile * side_nodes(T.kz);
   // Write the sum of a node of plane lz: final value or side-buffer partial
   // (always the latter on the tile's last column and row: kSide).  One store
   // per output whichever it is: every wave has nodes of both kinds.
@@ -582,7 +579,7 @@ __device__ __forceinline__ bool axis_tiles(int c, int w, int nt, int (&t)[2], in
   return below && above;
 }
 
-// kFixParts workgroups per tile, one slot per lane: the ring nodes the tile
+// fix_parts workgroups per tile, one slot per lane: the ring nodes the tile
 // owns -- those whose local coordinates are below the tile's upper extent along
 // every axis, or on the mesh's upper face along that axis -- each receive the
 // sum of the partials of all tiles sharing the node, taken in increasing tile
@@ -591,7 +588,7 @@ __device__ __forceinline__ bool axis_tiles(int c, int w, int nt, int (&t)[2], in
 // issued together (at most 8, only those that exist): 257^3 nodes, 79 us with one
 // workgroup per tile and the loads one after the other, 62 us now; 129^3 nodes,
 // 18 -> 9.
-constexpr int kFixParts = (SN + 255) / 256;
+__host__ __device__ constexpr int fix_parts(int kz) { return (side_nodes(kz) + 255) / 256; }
 
 template <int MODE>
 __global__ void __launch_bounds__(256)
@@ -600,18 +597,19 @@ __global__ void __launch_bounds__(256)
              double2* __restrict__ out1) {
   constexpr int NO = ModeInfo<MODE>::NO;
   const int block = (int)xcd_tile(blockIdx.x, gridDim.x);
-  const int tile = block / kFixParts;
+  const int parts = fix_parts(T.kz), nside = side_nodes(T.kz);
+  const int tile = block / parts;
   const int tx = tile % T.ntx;
   const int ty = (tile / T.ntx) % T.nty;
   const int tz = tile / (T.ntx * T.nty);
-  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * KZ;
+  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * T.kz;
   const int lxmax = min(TX, G.n[0] - x0);
   const int lymax = min(TY, G.n[1] - y0);
-  const int kzmax = min(KZ, G.n[2] - z0);
+  const int kzmax = min(T.kz, G.n[2] - z0);
   const bool lastx = tx == T.ntx - 1, lasty = ty == T.nty - 1, lastz = tz == T.ntz - 1;
   const double ie = MODE == MODE_FD ? eps_dev[1] : 0.0;  // 1/eps
-  const int i = (block % kFixParts) * 256 + (int)threadIdx.x;
-  if (i >= SN) return;
+  const int i = (block % parts) * 256 + (int)threadIdx.x;
+  if (i >= nside) return;
   int lx, ly, lz;
   if (i < PN) {
     lz = 0;
@@ -633,7 +631,7 @@ __global__ void __launch_bounds__(256)
   int txs[2], lxs[2], tys[2], lys[2], tzs[2], lzs[2];
   const bool nx = axis_tiles(x, TX, T.ntx, txs, lxs);
   const bool ny = axis_tiles(y, TY, T.nty, tys, lys);
-  const bool nz = axis_tiles(z, KZ, T.ntz, tzs, lzs);
+  const bool nz = axis_tiles(z, T.kz, T.ntz, tzs, lzs);
   const double2* const side2 = reinterpret_cast<const double2*>(side);
   double2 v[8][NO / 2];
 #pragma unroll
@@ -644,9 +642,9 @@ __global__ void __launch_bounds__(256)
     if ((a == 0 || nx) && (b == 0 || ny) && (c == 0 || nz)) {
       const long long t = txs[a] + (long long)T.ntx * (tys[b] + (long long)T.nty * tzs[c]);
       const int slot = side_slot(lxs[a], lys[b], lzs[c], min(TX, G.n[0] - TX * txs[a]),
-                                 min(TY, G.n[1] - TY * tys[b]), min(KZ, G.n[2] - KZ * tzs[c]));
+                                 min(TY, G.n[1] - TY * tys[b]), min(T.kz, G.n[2] - T.kz * tzs[c]));
 #pragma unroll
-      for (int o = 0; o < NO / 2; ++o) v[k][o] = side2[(t * SN + slot) * (NO / 2) + o];
+      for (int o = 0; o < NO / 2; ++o) v[k][o] = side2[(t * nside + slot) * (NO / 2) + o];
     }
   }
 #pragma unroll
@@ -666,22 +664,60 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-Tiles tiles_for(const Geo& G) {
+// The z-chunks of a mode: the division of the mesh into tiles whose estimated
+// time is least.  `resident` workgroups run at a time, one or two per compute
+// unit; two on a compute unit take 1.67 times as long per layer as one (residual:
+// 8.0 and 4.8 us), and a chunk costs one layer besides its own.  Short chunks
+// where the mesh has few tiles, and equal ones: 16 layers each, the rest in the
+// last chunk, were before.  Residual 64^3 89 -> 31 us, 20^3 92 -> 14, 100 x 150 x
+// 60 155 -> 90; adjoint 129 x 97 x 113 326 -> 287; 256^3 1054 with 16 layers, 1048
+// with 32.
+//
+// The division depends on the mesh and the mode alone (results are reproducible
+// and alike for all callers).  Its side buffer takes at most what 16 layers
+// each would take, or kSideMost doubles per output.
+constexpr int kCus = 256, kMostLayers = 32, kMostShort = 8 * kCus;
+constexpr long long kSideMost = (long long)kMostShort * side_nodes(15);
+static_assert(kSideMost * 2 * sizeof(double) <= 64LL << 20, "fits the fixed array of the call without allocation");
+
+Tiles tiles_for(const Geo& G, int resident) {
   Tiles T;
   T.ntx = (G.n[0] + TX - 1) / TX;
   T.nty = (G.n[1] + TY - 1) / TY;
-  T.ntz = (G.n[2] + KZ - 1) / KZ;
+  const long long columns = (long long)T.ntx * T.nty;
+  double best = 0.0;
+  T.kz = 0;
+  for (int c = 1; c <= kMostLayers; ++c) {
+    const int nz = (G.n[2] + c - 1) / c;
+    const int kz = (G.n[2] + nz - 1) / nz;  // nz equal chunks
+    const long long tiles = columns * nz, rounds = tiles / resident, rest = tiles % resident;
+    if (nz > (G.n[2] + 15) / 16 && tiles > kMostShort) continue;
+    const double full = resident > kCus ? 1.67 : 1.0;
+    const double cost = (kz + 1) * (rounds * full + (rest == 0 ? 0.0 : rest <= kCus ? 1.0 : full));
+    if (T.kz == 0 || cost <= best) {
+      best = cost;
+      T.kz = kz;
+    }
+  }
+  T.ntz = (G.n[2] + T.kz - 1) / T.kz;
   return T;
 }
 
+// Workgroups of a mode that run at a time.  The two adjoint products with
+// parameter sums share one division, that of the partial sums' buffer.
+template <int MODE>
+constexpr int kResident = kCus * (MODE == MODE_VJPP ? 1 : kWavesPerSimd<MODE>);
+
+int tile_count(const Tiles& T) { return T.ntx * T.nty * T.ntz; }
+
 // side: the tile-face partial sums, fused3_side_len(G) doubles (the first
-// tiles x SN x NO of them are used).
+// tiles x side_nodes x NO of them are used).
 template <int MODE>
 int launch_mode(const Geo& G, double* side, const double* U, const double* Uprev, const double* v,
                 const double* F0, const double* eps_dev, double* out0, double* out1,
                 double* vjp_part, double* coef, hipStream_t s) {
-  const Tiles T = tiles_for(G);
-  const unsigned nt = (unsigned)(T.ntx * T.nty * T.ntz);
+  const Tiles T = tiles_for(G, kResident<MODE>);
+  const unsigned nt = (unsigned)tile_count(T);
   const NodalLin L = nodal_lin(G);
   auto d2 = [](const double* p) { return reinterpret_cast<const double2*>(p); };
   bool with_coef = false;
@@ -697,7 +733,7 @@ int launch_mode(const Geo& G, double* side, const double* U, const double* Uprev
                        d2(Uprev), d2(v), eps_dev, d2(F0), reinterpret_cast<double2*>(out0),
                        reinterpret_cast<double2*>(out1), side, vjp_part, nullptr);
   PF_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL((k_fixup3<MODE>), dim3(nt * kFixParts), dim3(256), 0, s, G, T, side,
+  hipLaunchKernelGGL((k_fixup3<MODE>), dim3(nt * fix_parts(T.kz)), dim3(256), 0, s, G, T, side,
                      eps_dev, reinterpret_cast<double2*>(out0), reinterpret_cast<double2*>(out1));
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
@@ -706,18 +742,27 @@ int launch_mode(const Geo& G, double* side, const double* U, const double* Uprev
 }  // namespace
 
 long long fused3_side_len(const Geo& G) {
-  const Tiles T = tiles_for(G);
-  return (long long)T.ntx * T.nty * T.ntz * SN * 4;
+  long long most = 0;
+  auto mode = [&](int resident, int NO) {
+    const Tiles T = tiles_for(G, resident);
+    most = std::max(most, (long long)tile_count(T) * side_nodes(T.kz) * NO);
+  };
+  mode(kResident<MODE_RES>, 2);
+  mode(kResident<MODE_JVP>, 2);
+  mode(kResident<MODE_VJPU>, 2);
+  mode(kResident<MODE_VJP>, 4);
+  return most;
 }
 
-int fused3_tiles(const Geo& G) {
-  const Tiles T = tiles_for(G);
-  return T.ntx * T.nty * T.ntz;
-}
+int fused3_tiles(const Geo& G) { return tile_count(tiles_for(G, kResident<MODE_VJP>)); }
 
+// At least what chunks of 16 layers would take, the size that callers with a
+// fixed buffer document (the division in use exceeds it only below kSideMost
+// doubles per output).
 long long fused3_residual_side_len(const Geo& G) {
-  const Tiles T = tiles_for(G);
-  return (long long)T.ntx * T.nty * T.ntz * SN * ModeInfo<MODE_RES>::NO;
+  const Tiles T = tiles_for(G, kResident<MODE_RES>);
+  const long long by16 = (long long)T.ntx * T.nty * ((G.n[2] + 15) / 16) * side_nodes(16);
+  return std::max(by16, (long long)tile_count(T) * side_nodes(T.kz)) * ModeInfo<MODE_RES>::NO;
 }
 
 int launch_fused3_residual(const Geo& G, double* side, const double* U, const double* Uprev,

@@ -63,3 +63,36 @@ def test_thermal_tiles(n):
     pb.pf_vjp(dev(U), dev(Up), dev(v), gUprev=c, gparams=gp)
     check(host(c), gP, 1e-12, f"vjp gUprev alone {n}")
     assert pb.close() == 0
+
+
+def test_long_chunks():
+    """Small meshes are cut into short z-chunks; this one has enough tiles for
+    chunks of 19 layers.  The operators are local: on a box of 18 x 18 columns
+    the values at nodes off the box's cut faces are those of the box alone."""
+    from paper_2006_16764_amd import binding
+    n = (250, 250, 37)
+    print(f"[case] long chunks {n}", flush=True)
+    h = (0.4, 0.5, 0.3)
+    p = Params(dt=0.3, eps4=0.05, lam=1.6, D=2.0)
+    U, Up = inputs.random_state(3, n, 1), inputs.random_state(3, n, 2)
+    v = inputs.random_vector(U.shape[0], 3)
+    pb = binding.Problem(binding.make_params(3, n, [h[k] * n[k] for k in range(3)], p.dt, p.eps4, p.lam, p.D))
+    F, Jv, gU, gP = (pb.new_vector().fill_(float("nan")) for _ in range(4))
+    gp = torch.zeros(2, dtype=torch.float64, device="cuda")
+    pb.pf_residual(dev(U), dev(Up), F)
+    pb.pf_jvp(dev(U), dev(Up), dev(v), Jv)
+    pb.pf_vjp(dev(U), dev(Up), dev(v), gU, gP, gp)
+    shape = (n[2] + 1, n[1] + 1, n[0] + 1, 2)
+    for x0, y0 in ((0, 0), (5, 102), (232, 232)):
+        m = (18, 18, n[2])
+        box = np.s_[:, y0:y0 + 19, x0:x0 + 19]
+        # off the cut faces: those inside the mesh
+        inner = np.s_[:, (y0 > 0):19 - (y0 + 18 < n[1]), (x0 > 0):19 - (x0 + 18 < n[0])]
+        mesh = Mesh(3, m, [h[k] * m[k] for k in range(3)])
+        Ub, Upb, vb = (a.reshape(shape)[box].reshape(-1, 2) for a in (U, Up, v))
+        gUb, gPb, _, _ = deriv.vjp(mesh, Ub, Upb, vb, p)
+        for what, got, ref in (("residual", F, fem.residual(mesh, Ub, Upb, p)),
+                               ("jvp", Jv, deriv.jvp(mesh, Ub, Upb, vb, p)), ("gU", gU, gUb), ("gUprev", gP, gPb)):
+            check(host(got).reshape(shape)[box][inner].reshape(-1, 2),
+                  np.asarray(ref).reshape(38, 19, 19, 2)[inner].reshape(-1, 2), 1e-12, f"{what} at {x0}, {y0}")
+    assert pb.close() == 0
