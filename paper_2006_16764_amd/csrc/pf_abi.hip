@@ -222,9 +222,11 @@ struct Op {
     unorm2 = d;
     return PF_OK;
   }
-  int apply(const double* z, double* w, hipStream_t s) const {
+  // zparts: partials of |z|^2 in red_partials (0: none), see pc_apply
+  int apply(const double* z, double* w, hipStream_t s, int zparts = 0) const {
     if (kind == 0) {
-      PF_TRY(blas_fd_eps_cached(pb, unorm2, z, pb->n_dof, pb->eps_dev, s));
+      if (zparts > 0) PF_TRY(blas_fd_eps_parts(pb, unorm2, zparts, pb->eps_dev, s));
+      else PF_TRY(blas_fd_eps_cached(pb, unorm2, z, pb->n_dof, pb->eps_dev, s));
       return launch_residual_family(pb, MODE_FD, U, Uprev, z, F0, pb->eps_dev, w, nullptr, nullptr, s);
     }
     if (kind == 1)
@@ -325,8 +327,9 @@ int fgmres_cycles(pf_problem* pb, const Op& op, const double* b, double bsign, d
       double* vj = V + (long long)j * n;
       double* zj = Z + (long long)j * n;
       double* w = V + (long long)(j + 1) * n;
-      PF_TRY(pc_apply(pb, vj, zj, s));
-      PF_TRY(op.apply(zj, w, s));
+      int zparts = 0;
+      PF_TRY(pc_apply(pb, vj, zj, s, op.kind == 0 ? &zparts : nullptr));
+      PF_TRY(op.apply(zj, w, s, zparts));
       // products and update are queued together; the host reads both results
       // while the update runs.  When the column of V_{j-1} turns out to end the
       // cycle the update was for nothing (x = Z y needs no V).

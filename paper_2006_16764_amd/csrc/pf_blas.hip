@@ -471,9 +471,8 @@ int reduce_rows(pf_problem* pb, int rows, double* out_dev, double* out_host, hip
   return PF_OK;
 }
 
-int reduce_norm(pf_problem* pb, const NormOut& O, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_norm, dim3(1), dim3(kRedThreads), 0, s, pb->red_partials,
-                     pb->n_red_blocks, O);
+int reduce_norm(pf_problem* pb, const NormOut& O, int nparts, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_norm, dim3(1), dim3(kRedThreads), 0, s, pb->red_partials, nparts, O);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }
@@ -486,7 +485,7 @@ int norm_sq(pf_problem* pb, const double* x, long long n, const NormOut& O, hipS
   }
   hipLaunchKernelGGL(k_norm, dim3(pb->n_red_blocks), dim3(kRedThreads), 0, s, x, n, pb->red_partials);
   PF_HIP_CHECK(hipGetLastError());
-  return reduce_norm(pb, O, s);
+  return reduce_norm(pb, O, pb->n_red_blocks, s);
 }
 
 }  // namespace
@@ -524,7 +523,7 @@ int blas_axpby_norm(pf_problem* pb, double a, const double* x, double b, const d
   hipLaunchKernelGGL(k_axpby_norm, dim3(pb->n_red_blocks), dim3(kRedThreads), 0, s, a, x, b, y, z, n,
                      pb->red_partials);
   PF_HIP_CHECK(hipGetLastError());
-  return reduce_norm(pb, O, s);
+  return reduce_norm(pb, O, pb->n_red_blocks, s);
 }
 
 int blas_dot(pf_problem* pb, const double* x, const double* y, long long n, double* out_dev,
@@ -634,6 +633,10 @@ int blas_fd_eps(pf_problem* pb, const double* U, const double* v, long long n, d
 int blas_fd_eps_cached(pf_problem* pb, const double* unorm2_dev, const double* v, long long n,
                        double* eps_dev, hipStream_t s) {
   return norm_sq(pb, v, n, NormOut{pb->red_out + kSlotFdV, nullptr, unorm2_dev, eps_dev}, s);
+}
+
+int blas_fd_eps_parts(pf_problem* pb, const double* unorm2_dev, int nparts, double* eps_dev, hipStream_t s) {
+  return reduce_norm(pb, NormOut{pb->red_out + kSlotFdV, nullptr, unorm2_dev, eps_dev}, nparts, s);
 }
 
 int blas_reduce_partials(const double* partials, int nparts, int k, double* out_dev, hipStream_t s) {

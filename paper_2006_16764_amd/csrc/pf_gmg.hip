@@ -299,6 +299,25 @@ __device__ __forceinline__ void diag_only(const LvK& g, const T* __restrict__ c,
   d1 = (T)g.Ae[1][0] * n;
 }
 
+// The workgroup's sum of acc as its entry of part, one partial of |z|^2: the
+// difference quotient's step needs the norm of what the preconditioner just
+// wrote, and a sweep of its own took 51 us on 257^3 nodes, 7 on 129^3 and a launch
+// on small meshes.
+template <int THREADS>
+__device__ __forceinline__ void put_partial(double acc, double* part) {
+  __shared__ double sh[THREADS / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o);
+  if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) t += sh[w];
+    part[blockIdx.x] = t;
+  }
+}
+
 // ----------------------------------------------------------------- kernels
 // c_e = sum_q w_q a(grad phi_q)^2 / sum_q w_q on every fine cell (FP64)
 template <int DIM>
@@ -734,6 +753,7 @@ struct StArgs {
   const double2* r64;
   T2* bout;
   const T* dg;
+  double* part;  // OP 2: partials of |z64|^2 per workgroup (NULL: not wanted)
 };
 
 // OP 0: r = b - A x.  OP 1: Chebyshev step (x_out, d).  OP 2: Chebyshev step
@@ -903,6 +923,7 @@ __global__ void __launch_bounds__(SBX * SBY) k_stencil3(LvK g, StArgs<T> A) {
     }
   };
   fetch_b(z0);
+  double zz = 0.0;
   for (int z = z0; z < zend; ++z) {
     const int k = z - z0;
     const int sm = k % 3, s0 = (k + 1) % 3, sp = (k + 2) % 3;
@@ -1049,7 +1070,9 @@ __global__ void __launch_bounds__(SBX * SBY) k_stencil3(LvK g, StArgs<T> A) {
         const T dn0 = (al0 == (T)0 ? (T)0 : al0 * dv.x) + div_diag(be0 * r0, dg0);
         const T dn1 = (al1 == (T)0 ? (T)0 : al1 * dv.y) + div_diag(be1 * r1, dg1);
         if (OP == 2) {
-          z64[i] = make_double2((double)(xi.x + dn0), (double)(xi.y + dn1));
+          const double2 zv = make_double2((double)(xi.x + dn0), (double)(xi.y + dn1));
+          z64[i] = zv;
+          zz = fma(zv.y, zv.y, fma(zv.x, zv.x, zz));
         } else {
           T2 dn, xo;
           dn.x = dn0;
@@ -1065,6 +1088,7 @@ __global__ void __launch_bounds__(SBX * SBY) k_stencil3(LvK g, StArgs<T> A) {
     // stores are left in flight (no thread reads another's outputs here)
     lds_barrier();
   }
+  if (OP == 2 && A.part) put_partial<SBX * SBY>(zz, A.part);
 }
 
 // Coarsest level: COARSE_DEGREE Chebyshev steps for both blocks by one
@@ -1217,28 +1241,33 @@ __global__ void __launch_bounds__(kCoarseSmall)
   if (own) x_res[i] = xv;
 }
 
-__global__ void k_jacobi(Geo G, const double* __restrict__ c, const double2* __restrict__ r,
-                         double2* __restrict__ z, double ae0, double ae1) {
+__global__ void __launch_bounds__(kT)
+    k_jacobi(Geo G, const double* __restrict__ c, const double2* __restrict__ r,
+             double2* __restrict__ z, double ae0, double ae1, double* __restrict__ part) {
   const long long i = (long long)blockIdx.x * kT + threadIdx.x;
-  if (i >= G.n_nodes) return;
-  LvK g{};
-  for (int k = 0; k < 3; ++k) {
-    g.n[k] = G.n[k];
-    g.nn[k] = G.nn[k];
+  double2 v = make_double2(0.0, 0.0);
+  if (i < G.n_nodes) {
+    LvK g{};
+    for (int k = 0; k < 3; ++k) {
+      g.n[k] = G.n[k];
+      g.nn[k] = G.nn[k];
+    }
+    g.Ae[0][0] = ae0;
+    g.Ae[1][0] = ae1;
+    int ix, iy, iz;
+    double d0, d1;
+    if (G.dim == 3) {
+      node_ijk<3>(g, i, ix, iy, iz);
+      diag_only<3, double>(g, c, ix, iy, iz, d0, d1);
+    } else {
+      node_ijk<2>(g, i, ix, iy, iz);
+      diag_only<2, double>(g, c, ix, iy, iz, d0, d1);
+    }
+    const double2 a = r[i];
+    v = make_double2(a.x / d0, a.y / d1);
+    z[i] = v;
   }
-  g.Ae[0][0] = ae0;
-  g.Ae[1][0] = ae1;
-  int ix, iy, iz;
-  double d0, d1;
-  if (G.dim == 3) {
-    node_ijk<3>(g, i, ix, iy, iz);
-    diag_only<3, double>(g, c, ix, iy, iz, d0, d1);
-  } else {
-    node_ijk<2>(g, i, ix, iy, iz);
-    diag_only<2, double>(g, c, ix, iy, iz, d0, d1);
-  }
-  const double2 a = r[i];
-  z[i] = make_double2(a.x / d0, a.y / d1);
+  if (part) put_partial<kT>(fma(v.x, v.x, v.y * v.y), part);
 }
 
 template <class T>
@@ -1265,6 +1294,15 @@ __global__ void k_merge(const typename V2<T>::type* __restrict__ x, double2* __r
 __global__ void k_copy2(const double2* __restrict__ x, double2* __restrict__ y, long long n) {
   const long long i = (long long)blockIdx.x * kT + threadIdx.x;
   if (i < n) y[i] = x[i];
+}
+
+__global__ void __launch_bounds__(kT)
+    k_copy_norm(const double2* __restrict__ x, double2* __restrict__ y, long long n,
+                double* __restrict__ part) {
+  const long long i = (long long)blockIdx.x * kT + threadIdx.x;
+  double2 v = make_double2(0.0, 0.0);
+  if (i < n) y[i] = v = x[i];
+  put_partial<kT>(fma(v.x, v.x, v.y * v.y), part);
 }
 
 inline unsigned blocks(long long n) { return (unsigned)((n + kT - 1) / kT); }
@@ -1547,6 +1585,19 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
   return PF_OK;
 }
 
+// Partials of |z|^2 asked of the kernel that writes z: room for `room` of them at
+// part; the kernel's launch sets count (0: not formed).
+struct NormParts {
+  double* part;
+  long long room;
+  int count;
+};
+inline double* claim(NormParts* np, unsigned groups) {
+  if (!np || groups > np->room) return nullptr;
+  np->count = (int)groups;
+  return np->part;
+}
+
 // Levels whose x rows span at least one tile use the 2.5-D kernels.
 template <class T>
 inline dim3 tiled_grid(const Level<T>& L) {
@@ -1558,7 +1609,7 @@ inline dim3 tiled_grid(const Level<T>& L) {
 template <int DIM, class T, int IN, int OUT, int FL>
 int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::type* x_out,
                 const double* al, const double* be, int k, const double* r64, double* z64,
-                hipStream_t s) {
+                hipStream_t s, NormParts* np = nullptr) {
   if (IN == 2 && L.kz > 0) {
     constexpr int OP = OUT == 1 ? 2 : 1;
     StArgs<T> A{};
@@ -1573,7 +1624,9 @@ int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::t
     A.be1 = (T)be[2 * k + 1];
     A.z64 = reinterpret_cast<double2*>(z64);
     A.kz = L.kz;
-    hipLaunchKernelGGL((k_stencil3<T, OP, FL>), tiled_grid(L), dim3(SBX * SBY), 0, s, L.k, A);
+    const dim3 grid = tiled_grid(L);
+    if (OP == 2) A.part = claim(np, grid.x);
+    hipLaunchKernelGGL((k_stencil3<T, OP, FL>), grid, dim3(SBX * SBY), 0, s, L.k, A);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }
@@ -1588,7 +1641,8 @@ int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::t
 // V-cycle from level l on the right-hand side in lv[l].b (or r64 at level 0);
 // the result is left in lv[l].xb (or written to z64 at level 0).
 template <int DIM, class T>
-int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64, hipStream_t s) {
+int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64, hipStream_t s,
+           NormParts* np = nullptr) {
   Level<T>& L = H.lv[l];
   const bool top = l == 0;
   if (l + 1 == H.lv.size()) {
@@ -1701,7 +1755,7 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
   // post-smoothing from the corrected iterate: xb -> xa -> xb (or z64); only
   // the first step's direction is read again
   PF_TRY((smooth_step<DIM, T, 2, 0, kWriteD>(L, L.xb, L.xa, al, be, 0, nullptr, nullptr, s)));
-  if (top) PF_TRY((smooth_step<DIM, T, 2, 1, kReadD>(L, L.xa, nullptr, al, be, 1, nullptr, z64, s)));
+  if (top) PF_TRY((smooth_step<DIM, T, 2, 1, kReadD>(L, L.xa, nullptr, al, be, 1, nullptr, z64, s, np)));
   else PF_TRY((smooth_step<DIM, T, 2, 0, kReadD>(L, L.xa, L.xb, al, be, 1, nullptr, nullptr, s)));
   return PF_OK;
 }
@@ -1727,16 +1781,16 @@ int down2(Level<T>& L, Level<T>& C, const double2* r64, hipStream_t s) {
 
 template <class T>
 int up2(Level<T>& L, Level<T>& C, const typename V2<T>::type* e, const double2* r64, double2* z64,
-        hipStream_t s) {
+        hipStream_t s, NormParts* np) {
   using T2 = typename V2<T>::type;
   const Cheb2<T> K = cheb2(L);
   const dim3 grid = tiles2(L.k, kUp2), lanes(kReg2 * kReg2);
   if (r64)
     hipLaunchKernelGGL((k_up2<T, true>), grid, lanes, 0, s, L.k, C.k, (const T*)L.c,
-                       (const T2*)nullptr, r64, K, (const T2*)L.xb, e, (T2*)nullptr, z64);
+                       (const T2*)nullptr, r64, K, (const T2*)L.xb, e, (T2*)nullptr, z64, claim(np, grid.x));
   else
     hipLaunchKernelGGL((k_up2<T, false>), grid, lanes, 0, s, L.k, C.k, (const T*)L.c,
-                       (const T2*)L.b, r64, K, (const T2*)L.xb, e, L.xa, z64);
+                       (const T2*)L.b, r64, K, (const T2*)L.xb, e, L.xa, z64, (double*)nullptr);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }
@@ -1745,7 +1799,8 @@ int up2(Level<T>& L, Level<T>& C, const typename V2<T>::type* e, const double2* 
 // iterate and direction alternating between (xa, d) and (xb, r); result in xb,
 // or z64 when the hierarchy has this one level.
 template <class T, int S, bool TOP>
-int coarsest2(const Hier<T>& H, const Level<T>& B, const double2* r64, double2* z64, hipStream_t s) {
+int coarsest2(const Hier<T>& H, const Level<T>& B, const double2* r64, double2* z64, hipStream_t s,
+              NormParts* np) {
   using T2 = typename V2<T>::type;
   static_assert(kCoarseDegree % (2 * S) == 0, "the last of an even number of launches writes xb");
   const dim3 grid = tiles2(B.k, cheb2_own(S)), lanes(kRegC2 * kRegC2);
@@ -1756,13 +1811,13 @@ int coarsest2(const Hier<T>& H, const Level<T>& B, const double2* r64, double2* 
     T2 *xo = odd ? B.xb : B.xa, *dd = odd ? B.r : B.d;
     if (k == 0)
       hipLaunchKernelGGL((k_cheb2<T, S, true, false, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
-                         (const T2*)B.b, r64, K, (const T2*)nullptr, (const T2*)nullptr, xo, dd, z64);
+                         (const T2*)B.b, r64, K, (const T2*)nullptr, (const T2*)nullptr, xo, dd, z64, (double*)nullptr);
     else if (k + S < kCoarseDegree)
       hipLaunchKernelGGL((k_cheb2<T, S, false, false, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
-                         (const T2*)B.b, r64, K, x, d, xo, dd, z64);
+                         (const T2*)B.b, r64, K, x, d, xo, dd, z64, (double*)nullptr);
     else
       hipLaunchKernelGGL((k_cheb2<T, S, false, true, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
-                         (const T2*)B.b, r64, K, x, d, xo, (T2*)nullptr, z64);
+                         (const T2*)B.b, r64, K, x, d, xo, (T2*)nullptr, z64, TOP ? claim(np, grid.x) : nullptr);
     PF_HIP_CHECK(hipGetLastError());
   }
   return PF_OK;
@@ -1777,7 +1832,7 @@ constexpr long long kCheb2Large = 100000;
 // One 2-D V-cycle from r to z (see pf_gmg2.h): down to the tail or the coarsest
 // level, there, and back up.
 template <class T>
-int vcycle2(Hier<T>& H, const double* r, double* z, hipStream_t s) {
+int vcycle2(Hier<T>& H, const double* r, double* z, hipStream_t s, NormParts* np) {
   using T2 = typename V2<T>::type;
   auto r64 = reinterpret_cast<const double2*>(r);
   auto z64 = reinterpret_cast<double2*>(z);
@@ -1795,15 +1850,15 @@ int vcycle2(Hier<T>& H, const double* r, double* z, hipStream_t s) {
                          z64);
     PF_HIP_CHECK(hipGetLastError());
   } else if (B.k.nnodes >= kCheb2Large) {
-    if (bottom == 0) PF_TRY((coarsest2<T, 4, true>(H, B, r64, z64, s)));
-    else PF_TRY((coarsest2<T, 4, false>(H, B, r64, z64, s)));
+    if (bottom == 0) PF_TRY((coarsest2<T, 4, true>(H, B, r64, z64, s, np)));
+    else PF_TRY((coarsest2<T, 4, false>(H, B, r64, z64, s, np)));
   } else {
-    if (bottom == 0) PF_TRY((coarsest2<T, 8, true>(H, B, r64, z64, s)));
-    else PF_TRY((coarsest2<T, 8, false>(H, B, r64, z64, s)));
+    if (bottom == 0) PF_TRY((coarsest2<T, 8, true>(H, B, r64, z64, s, np)));
+    else PF_TRY((coarsest2<T, 8, false>(H, B, r64, z64, s, np)));
   }
   for (size_t l = bottom; l-- > 0;) {
     const T2* e = l + 1 == bottom ? H.lv[l + 1].xb : H.lv[l + 1].xa;
-    PF_TRY((up2<T>(H.lv[l], H.lv[l + 1], e, l == 0 ? r64 : nullptr, z64, s)));
+    PF_TRY((up2<T>(H.lv[l], H.lv[l + 1], e, l == 0 ? r64 : nullptr, z64, s, np)));
   }
   return PF_OK;
 }
@@ -1816,9 +1871,9 @@ int setup_gmg(pf_problem* pb, PcState* st, Hier<T>& H, hipStream_t s) {
 }
 
 template <class T>
-int apply_gmg(pf_problem* pb, Hier<T>& H, const double* r, double* z, hipStream_t s) {
-  if (pb->geo.dim == 3) return vcycle<3, T>(pb, H, 0, r, z, s);
-  return vcycle2<T>(H, r, z, s);
+int apply_gmg(pf_problem* pb, Hier<T>& H, const double* r, double* z, hipStream_t s, NormParts* np) {
+  if (pb->geo.dim == 3) return vcycle<3, T>(pb, H, 0, r, z, s, np);
+  return vcycle2<T>(H, r, z, s, np);
 }
 
 // The V-cycle on small meshes: r is copied into the fixed input vector, the
@@ -1830,7 +1885,7 @@ int apply_gmg(pf_problem* pb, Hier<T>& H, const double* r, double* z, hipStream_
 // bit.
 template <class T>
 int apply_gmg_graph(pf_problem* pb, PcState* st, Hier<T>& H, GraphCache& gc, const double* r,
-                    double* z, hipStream_t s) {
+                    double* z, hipStream_t s, NormParts* np) {
   const long long n = pb->geo.n_nodes;
   if (!st->gin) {
     if (hipMalloc(&st->gin, (size_t)2 * n * sizeof(double)) != hipSuccess ||
@@ -1853,7 +1908,7 @@ int apply_gmg_graph(pf_problem* pb, PcState* st, Hier<T>& H, GraphCache& gc, con
       gc.exec = nullptr;
     }
     PF_HIP_CHECK(hipStreamBeginCapture(st->cap, hipStreamCaptureModeThreadLocal));
-    const int rc = apply_gmg<T>(pb, H, st->gin, st->gout, st->cap);
+    const int rc = apply_gmg<T>(pb, H, st->gin, st->gout, st->cap, nullptr);
     hipGraph_t graph = nullptr;
     const hipError_t ec = hipStreamEndCapture(st->cap, &graph);
     if (rc != PF_OK) {
@@ -1872,8 +1927,12 @@ int apply_gmg_graph(pf_problem* pb, PcState* st, Hier<T>& H, GraphCache& gc, con
                      reinterpret_cast<double2*>(st->gin), n);
   PF_HIP_CHECK(hipGetLastError());
   PF_HIP_CHECK(hipGraphLaunch(gc.exec, s));
-  hipLaunchKernelGGL(k_copy2, dim3(blocks(n)), dim3(kT), 0, s,
-                     reinterpret_cast<const double2*>(st->gout), reinterpret_cast<double2*>(z), n);
+  if (double* part = claim(np, blocks(n)))
+    hipLaunchKernelGGL(k_copy_norm, dim3(blocks(n)), dim3(kT), 0, s,
+                       reinterpret_cast<const double2*>(st->gout), reinterpret_cast<double2*>(z), n, part);
+  else
+    hipLaunchKernelGGL(k_copy2, dim3(blocks(n)), dim3(kT), 0, s,
+                       reinterpret_cast<const double2*>(st->gout), reinterpret_cast<double2*>(z), n);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }
@@ -1939,8 +1998,9 @@ int pc_setup(pf_problem* pb, const double* U, int kind, int precision, hipStream
   return setup_gmg<double>(pb, st, st->h64, s);
 }
 
-int pc_apply(pf_problem* pb, const double* r, double* z, hipStream_t s) {
-  PcState* st = static_cast<PcState*>(pb->pc);
+namespace {
+
+int apply_pc(pf_problem* pb, PcState* st, const double* r, double* z, hipStream_t s, NormParts* np) {
   const Geo& G = pb->geo;
   const long long n = G.n_nodes;
   switch (pb->pc_kind) {
@@ -1957,19 +2017,30 @@ int pc_apply(pf_problem* pb, const double* r, double* z, hipStream_t s) {
       element_table(G.dim, G.h, sm[1], sk[1], Ae1);
       hipLaunchKernelGGL(k_jacobi, dim3(blocks(n)), dim3(kT), 0, s, G, (const double*)st->coef0,
                          reinterpret_cast<const double2*>(r), reinterpret_cast<double2*>(z),
-                         Ae0[0], Ae1[0]);
+                         Ae0[0], Ae1[0], claim(np, blocks(n)));
       PF_HIP_CHECK(hipGetLastError());
       return PF_OK;
     }
     default:
       if (st->graph_enabled && G.dim == 3 && pb->n_dof <= kGraphMaxDof) {
         if (pb->pc_precision == PF_FP32)
-          return apply_gmg_graph<float>(pb, st, st->h32, st->g32, r, z, s);
-        return apply_gmg_graph<double>(pb, st, st->h64, st->g64, r, z, s);
+          return apply_gmg_graph<float>(pb, st, st->h32, st->g32, r, z, s, np);
+        return apply_gmg_graph<double>(pb, st, st->h64, st->g64, r, z, s, np);
       }
-      if (pb->pc_precision == PF_FP32) return apply_gmg<float>(pb, st->h32, r, z, s);
-      return apply_gmg<double>(pb, st->h64, r, z, s);
+      if (pb->pc_precision == PF_FP32) return apply_gmg<float>(pb, st->h32, r, z, s, np);
+      return apply_gmg<double>(pb, st->h64, r, z, s, np);
   }
+}
+
+}  // namespace
+
+// norm_parts (may be NULL): the number of partials of |z|^2 left in
+// red_partials, 0 if the kernel that wrote z forms none.
+int pc_apply(pf_problem* pb, const double* r, double* z, hipStream_t s, int* norm_parts) {
+  NormParts parts{pb->red_partials, (long long)kRedRows * pb->n_red_blocks, 0};
+  const int rc = apply_pc(pb, static_cast<PcState*>(pb->pc), r, z, s, norm_parts ? &parts : nullptr);
+  if (norm_parts) *norm_parts = parts.count;
+  return rc;
 }
 
 }  // namespace pf

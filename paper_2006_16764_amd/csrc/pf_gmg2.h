@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(kReg2 * kReg2)
     k_up2(LvK g, LvK cg, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
           const double2* __restrict__ r64, Cheb2<T> K, const typename V2<T>::type* __restrict__ x,
           const typename V2<T>::type* __restrict__ e, typename V2<T>::type* __restrict__ out,
-          double2* __restrict__ z64) {
+          double2* __restrict__ z64, double* __restrict__ part) {
   using T2 = typename V2<T>::type;
   __shared__ T2 xs[2][kReg2 * kReg2];
   constexpr int O = kUp2;
@@ -259,9 +259,13 @@ __global__ void __launch_bounds__(kReg2 * kReg2)
   apply2<T>(N, xs[1], t, kReg2, L.xlo, L.xhi, L.ylo, L.yhi, y0, y1);
   v.x += K.al1[0] * d0 + (K.be1[0] * (bb.x - y0)) * N.rd0;
   v.y += K.al1[1] * d1 + (K.be1[1] * (bb.y - y1)) * N.rd1;
-  if (L.in && L.tx >= 2 && L.tx < 2 + O && L.ty >= 2 && L.ty < 2 + O) {
-    if constexpr (TOP) z64[L.i] = make_double2((double)v.x, (double)v.y);
-    else out[L.i] = v;
+  const bool own = L.in && L.tx >= 2 && L.tx < 2 + O && L.ty >= 2 && L.ty < 2 + O;
+  if constexpr (TOP) {
+    const double2 z = own ? make_double2((double)v.x, (double)v.y) : make_double2(0.0, 0.0);
+    if (own) z64[L.i] = z;
+    if (part) put_partial<kReg2 * kReg2>(fma(z.x, z.x, z.y * z.y), part);
+  } else if (own) {
+    out[L.i] = v;
   }
 }
 
@@ -280,7 +284,7 @@ __global__ void __launch_bounds__(kRegC2 * kRegC2)
             const double2* __restrict__ r64, ChebSteps<T, S> K,
             const typename V2<T>::type* __restrict__ x, const typename V2<T>::type* __restrict__ d,
             typename V2<T>::type* __restrict__ xout, typename V2<T>::type* __restrict__ dout,
-            double2* __restrict__ z64) {
+            double2* __restrict__ z64, double* __restrict__ part) {
   using T2 = typename V2<T>::type;
   __shared__ T2 xs[2][kRegC2 * kRegC2];
   constexpr int O = cheb2_own(S);
@@ -317,10 +321,12 @@ __global__ void __launch_bounds__(kRegC2 * kRegC2)
     v.x += dv.x;
     v.y += dv.y;
   }
-  if (!L.in || L.tx < S || L.tx >= S + O || L.ty < S || L.ty >= S + O) return;
-  if (TOP && LAST) {
-    z64[L.i] = make_double2((double)v.x, (double)v.y);
-  } else {
+  const bool own = L.in && L.tx >= S && L.tx < S + O && L.ty >= S && L.ty < S + O;
+  if constexpr (TOP && LAST) {
+    const double2 z = own ? make_double2((double)v.x, (double)v.y) : make_double2(0.0, 0.0);
+    if (own) z64[L.i] = z;
+    if (part) put_partial<kRegC2 * kRegC2>(fma(z.x, z.x, z.y * z.y), part);
+  } else if (own) {
     xout[L.i] = v;
     if (!LAST) dout[L.i] = dv;
   }

@@ -214,6 +214,8 @@ int blas_fd_eps(pf_problem* pb, const double* U, const double* v, long long n, d
 // eps from a precomputed |U|^2 (device scalar) and |v|^2 computed here
 int blas_fd_eps_cached(pf_problem* pb, const double* unorm2_dev, const double* v, long long n,
                        double* eps_dev, hipStream_t s);
+// the same from the nparts partials of |v|^2 in red_partials
+int blas_fd_eps_parts(pf_problem* pb, const double* unorm2_dev, int nparts, double* eps_dev, hipStream_t s);
 int blas_reduce_partials(const double* partials, int nparts, int k, double* out_dev, hipStream_t s);
 int blas_sub_scalars(double* acc_dev, const double* x_dev, int k, hipStream_t s);
 
@@ -226,7 +228,7 @@ int pc_setup(pf_problem* pb, const double* U, int kind, int precision, hipStream
 // same state) into pc_coef_buffer(pb).
 int pc_setup_prepared(pf_problem* pb, int kind, int precision, hipStream_t s);
 double* pc_coef_buffer(pf_problem* pb);
-int pc_apply(pf_problem* pb, const double* r, double* z, hipStream_t s);
+int pc_apply(pf_problem* pb, const double* r, double* z, hipStream_t s, int* norm_parts = nullptr);
 
 // ----------------------------------------------------------------- misc kernels
 int misfit_launch(pf_problem* pb, const double* U, const double* target, double* L_dev,

@@ -89,3 +89,33 @@ def test_krylov_space_exhausted(n):
     assert st["gmres_its_total"] <= pb.n_dof + 1
     assert err <= 1e-12
     assert pb.close() == 0
+
+
+STEPS = [((40, 40, 40), "gmg", 0), ((40, 40, 40), "gmg", 1), ((33, 35, 17), "gmg", 0), ((64, 64, 72), "gmg", 0),
+         ((64, 64), "jacobi", 0), ((20, 18, 16), "jacobi", 0), ((72, 104), "gmg", 1), ((75, 101), "gmg", 0),
+         ((16, 16), "gmg", 0)]
+
+
+@pytest.mark.parametrize("n,pc,prec", STEPS, ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_step_with_the_norm_formed_by_the_preconditioner(n, pc, prec):
+    """FD steps take |z| from the kernel that writes z (finest sweep, replayed
+    cycle's copy, one-level solve, Jacobi) or from a sweep of its own.  Both
+    Jacobian products lead to the root of F: Newton steps to 1e-10 |F0| agree to
+    1e-8 of the increment, as those of the other step tests with the oracle's."""
+    from paper_2006_16764_amd import binding
+    print(f"[case] step {n} {pc} {prec}", flush=True)
+    dim = len(n)
+    pb = binding.Problem(binding.make_params(dim, n, [0.4 * k for k in n], 0.1, 0.05, 1.6, 2.0), 40)
+    U0 = dev(inputs.random_state(dim, n, 1))
+    got = []
+    for mode in (binding.PF_JV_FD, binding.PF_JV_ANALYTIC):
+        opts = binding.default_opts(tau_r=1e-10, jv_mode=mode, pc_precision=prec,
+                                    pc=binding.PF_PC_GMG if pc == "gmg" else binding.PF_PC_JACOBI)
+        U = U0.clone()
+        st = pb.pf_newton_step(U0, U, opts)
+        assert st["f_final"] <= 1e-10 * st["f0"], st
+        got.append(U - U0)
+    r = float((got[0] - got[1]).norm() / got[1].norm())
+    print(f"[parity] FD and analytic step {n} {pc}: {r:.3e}", flush=True)
+    assert r < 1e-8, r
+    assert pb.close() == 0
