@@ -13,8 +13,19 @@ namespace pf {
 
 namespace {
 
+// Wavefronts per SIMD asked of the compiler, where that spills nothing: left to
+// itself it takes 204 VGPRs for the analytic product (two wavefronts) and 142 for
+// the residual (three).  1024^2, 20 calls back to back: analytic product 45.4 ->
+// 39.6 us, residual 27.5 -> 26.4 us; with one more the product spills 51 registers and takes
+// 101 us.
 template <int MODE>
-__global__ void __launch_bounds__(kTile2Threads)
+constexpr int kTile2Waves = MODE == MODE_RES || MODE == MODE_FD    ? 4
+                            : MODE == MODE_JVP || MODE == MODE_VJPU ? 3
+                            : MODE == MODE_VJPP                     ? 2
+                                                                    : 1;
+
+template <int MODE>
+__global__ void __launch_bounds__(kTile2Threads, kTile2Waves<MODE>)
     k_tile2(Geo G, const double2* __restrict__ U, const double2* __restrict__ Up,
             const double2* __restrict__ V, const double* __restrict__ eps_dev,
             const double2* __restrict__ F0, double2* __restrict__ out0,
