@@ -711,7 +711,18 @@ constexpr int SBX = PF_SBX, SBY = PF_SBY, SKZ = 32;
 #endif
 constexpr long long kTiledMinGroups = PF_TILED_MIN_GROUPS;
 
-inline bool use_tiled(const LvK& k, int dim) { return dim == 3 && k.nn[0] >= SBX && k.nn[1] >= SBY; }
+// Levels taken by the tiled kernels: those that fill a tile's rows, and small
+// ones, where idle lanes cost nothing and the tiled kernels save two launches
+// per level (both pre-smoothing steps in one sweep, the prolongation in
+// another).  Cycle with the small levels untiled and tiled, FP64/FP32: 16^3 77/64
+// and 60/58 us, 64^3 159/135 and 139/127, 96 x 160 x 48 222/182 and 196/173, 128^3
+// 308/248 and 288/239.  Large levels of few columns stay untiled: most of a
+// tile's lanes would idle.
+constexpr long long kTiledSmall = 16384;
+
+inline bool use_tiled(const LvK& k, int dim) {
+  return dim == 3 && ((k.nn[0] >= SBX && k.nn[1] >= SBY) || k.nnodes <= kTiledSmall);
+}
 
 // z-march length: the longest power of two up to SKZ that still gives at
 // least min_groups workgroups
@@ -1671,7 +1682,7 @@ inline double* claim(NormParts* np, unsigned groups) {
   return np->part;
 }
 
-// Levels whose x rows span at least one tile use the 2.5-D kernels.
+// Levels with kz > 0 use the 2.5-D kernels.
 template <class T>
 inline dim3 tiled_grid(const Level<T>& L) {
   const LvK& k = L.k;
