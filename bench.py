@@ -110,19 +110,19 @@ def flops_per_element(dim):
     return 24 + 88 + 3 * (20 + 5 + 4 + 22) + 9 * (8 + 36 + 10)
 
 
-# FP64 flops per element counted for the roofline.  3-D: the counter value
-# (rocprofv3 SQ_INSTS_VALU_FLOPS_FP64 of k_fused3<0, false>, x 64 lanes / 256^3
-# elements), 2913 -- 63 below the source-level count of flops_per_element(3)
-# (the compiler folds constant point weights of the unrolled rows and shares
-# some products between the three points of a row); the executed count is the
-# one reported.  2-D: the source-level count.
+# FP64 flops per element of the operations taken element by element (the linear
+# part as element matrices).  3-D: counter value of that form, 63 below the
+# source-level count of flops_per_element(3) (the compiler folds constant point
+# weights of the unrolled rows and shares some products between the three points
+# of a row).  2-D: the source-level count.
 FLOPS_PER_ELEM = {3: 2913, 2: flops_per_element(2)}
-# The same counter for every 3-D element kernel of the residual family
-# (k_fused3<0..5>: residual, FD Jv, analytic Jv, VJP with all outputs, the
-# transposed-operator product alone, the previous-state and parameter product),
-# for the per-kernel FP64 rates reported beside the roofline.
 KERNEL_FLOPS_PER_ELEM_3D = {"residual": 2913, "fd_jv": 2952, "analytic_jv": 4795, "vjp": 5862,
                             "vjp_gU_only": 4927, "vjp_prev_and_params": 3067}
+# What the 3-D kernels execute (rocprofv3 SQ_INSTS_VALU_FLOPS_FP64 of k_fused3<0..5>,
+# x 64 lanes / 256^3 elements): the residual and the two Jacobian products form
+# the linear part at the nodes.  The rates reported are of these.
+EXECUTED_FLOPS_PER_ELEM_3D = {"residual": 2619, "fd_jv": 2660, "analytic_jv": 4581, "vjp": 5849,
+                              "vjp_gU_only": 4920, "vjp_prev_and_params": 3060}
 BYTES_PER_NODE_RES = 48  # U, U^n read, F written (16 B each)
 
 # HBM bytes moved by one pf_residual call (k_fused3<0, false> + k_fixup3<0>) on
@@ -134,8 +134,8 @@ BYTES_PER_NODE_RES = 48  # U, U^n read, F written (16 B each)
 # carried over to new sources).
 RESIDUAL_TRAFFIC = {
     "workload": "seeds3d_256",
-    "bytes": 1097776352,
-    "sources_sha256": "3e5bea3ed740c915c011467c5a98a91f3c3cf2e9f721f81426302cb58ebeafc0",
+    "bytes": 1046012240,
+    "sources_sha256": "1420ed3807b530b2b097bc98c0c59be4d09194d5b80a2031a820f3bddff09fc8",
 }
 TRAFFIC_SOURCES = ("paper_2006_16764_amd/csrc/pf_fused3.hip", "paper_2006_16764_amd/csrc/pf_element.h",
                    "paper_2006_16764_amd/csrc/pf_internal.h")
@@ -158,10 +158,26 @@ def residual_traffic(workload_name):
     return t["bytes"]
 
 
+def vcycle_moved(dim, n, s):
+    """vcycle_bytes less what the 3-D cycle no longer moves: the first
+    post-smoothing step adds the coarse correction itself (no sweep that reads
+    and writes the iterate, 4s per node above the coarsest grid), and in FP64 the
+    finest level keeps no copy of the right-hand side (2s per node)."""
+    total, sizes = vcycle_bytes(dim, n, s), [n]
+    while n % 2 == 0 and n > 4:
+        n //= 2
+        sizes.append(n)
+    if dim == 3 and len(sizes) > 1:
+        nodes = [(m + 1) ** 3 for m in sizes]
+        total -= 4 * s * sum(nodes[:-1]) + (2 * s * nodes[0] if s == 8 else 0)
+    return total
+
+
 def vcycle_bytes(dim, n, s):
     """Algorithmic HBM bytes of one V-cycle (both blocks, element size s = 4
-    for FP32, 8 for FP64) on a cubic mesh of n elements per side: every array a
-    kernel touches is counted once per node (cell arrays as one entry per node).
+    for FP32, 8 for FP64) on a cubic mesh of n elements per side, a launch per
+    operation: every array a kernel touches is counted once per node (cell arrays
+    as one entry per node).
 
     Finest level, per node: the fused zero-start two steps read the FP64
     right-hand side (16 B), the stored phi-block diagonal and the cell
@@ -278,7 +294,7 @@ def main():
     t_pc64 = time_call(lambda: pb.pf_precond_apply(vdir, Jv), reps)
     log("kernel timings done")
     n_elem = w.n_elems
-    flops = FLOPS_PER_ELEM[w.dim] * n_elem
+    flops = (EXECUTED_FLOPS_PER_ELEM_3D["residual"] if w.dim == 3 else FLOPS_PER_ELEM[w.dim]) * n_elem
     achieved = flops / (t_res * 1e-3) / 1e12
     peak = 78.6
     hbm_gbs = BYTES_PER_NODE_RES * w.n_nodes / (t_res * 1e-3) / 1e9
@@ -409,17 +425,17 @@ def main():
         "kernels_mdofs": {k: round(n / (v * 1e-3) / 1e6, 1) for k, v in
                           (("residual", t_res), ("fd_jv", t_fd), ("analytic_jv", t_jv), ("vjp", t_vjp),
                            ("vjp_gU_only", t_vjp_u), ("vjp_prev_and_params", t_vjp_prev))},
-        "kernels_fp64": ({k: {"tflops": round(KERNEL_FLOPS_PER_ELEM_3D[k] * n_elem / (v * 1e-3) / 1e12, 2),
-                              "frac": round(KERNEL_FLOPS_PER_ELEM_3D[k] * n_elem / (v * 1e-3) / 1e12 / peak, 3)}
+        "kernels_fp64": ({k: {"tflops": round(EXECUTED_FLOPS_PER_ELEM_3D[k] * n_elem / (v * 1e-3) / 1e12, 2),
+                              "frac": round(EXECUTED_FLOPS_PER_ELEM_3D[k] * n_elem / (v * 1e-3) / 1e12 / peak, 3)}
                           for k, v in (("residual", t_res), ("fd_jv", t_fd), ("analytic_jv", t_jv),
                                        ("vjp", t_vjp), ("vjp_gU_only", t_vjp_u),
                                        ("vjp_prev_and_params", t_vjp_prev))
-                          if k in KERNEL_FLOPS_PER_ELEM_3D}
+                          if k in EXECUTED_FLOPS_PER_ELEM_3D}
                          if w.dim == 3 else None),
         "vcycle_hbm": {name: {"bytes": int(vb), "gbs": round(vb / (t * 1e-3) / 1e9, 1),
                               "frac": round(vb / (t * 1e-3) / 8e12, 3)}
-                       for name, vb, t in (("fp32", vcycle_bytes(w.dim, w.n, 4), t_pc32),
-                                           ("fp64", vcycle_bytes(w.dim, w.n, 8), t_pc64))},
+                       for name, vb, t in (("fp32", vcycle_moved(w.dim, w.n, 4), t_pc32),
+                                           ("fp64", vcycle_moved(w.dim, w.n, 8), t_pc64))},
         "newton": [{"its": s["newton_its"], "gmres": s["gmres_its_total"], "ms": round(s["t_total_ms"], 1)}
                    for s in newton],
         "adjoint": [{"gmres": s["gmres_its_total"], "ms": round(s["t_total_ms"], 1)} for s in adj],

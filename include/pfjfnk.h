@@ -415,7 +415,7 @@ int pf_fg_residual(pf_problem* pb, const double* U, const double* Uprev, const d
 int pf_fg_explicit(pf_problem* pb, const double* Uprev, double* E, void* stream);
 
 /* [async] Jv of the implicit part (modes as pf_jvp; the analytic product is
- * forward-mode differentiation of the pointwise terms on dual numbers). */
+ * the derivative of the pointwise terms along v, written out). */
 int pf_fg_jvp(pf_problem* pb, const double* U, const double* Uprev, const double* Uprev2,
               const double* v, const double* F0, int mode, double* Jv, void* stream);
 
