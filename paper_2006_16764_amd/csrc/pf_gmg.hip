@@ -26,7 +26,6 @@
 // processed by the same thread and stored as interleaved (phi, u) pairs.
 #include <cmath>
 #include <cstdlib>
-#include <cstring>
 #include <vector>
 
 #include "pf_element.h"
@@ -91,9 +90,7 @@ struct Hier {
   bool allocated = false;
   size_t tail_at = 0;       // 2-D: first level of the one-workgroup tail (lv.size(): none)
   std::vector<Tail2<T>> tail;  // its kernel argument (0 or 1)
-  bool coarse_sent = false;
-  double coarse_host[4 * kCoarseDegree] = {};  // per-step (alpha, beta) of the coarsest solve
-  double* coarse_dev = nullptr;
+  double coarse[4 * kCoarseDegree] = {};  // per-step (alpha, beta) of the coarsest solve
 };
 
 // A V-cycle captured as one HIP graph: its launches (a few microseconds each on
@@ -1172,11 +1169,11 @@ __global__ void __launch_bounds__(SBX * SBY) k_stencil3(LvK g, StArgs<T> A) {
 }
 
 // Coarsest level: COARSE_DEGREE Chebyshev steps for both blocks by one
-// workgroup, iterates in LDS.  al/be: per-step coefficients, [step][block].
+// workgroup, iterates in LDS.
 template <int DIM, class T>
 __global__ void __launch_bounds__(1024)
     k_coarse(LvK g, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
-             typename V2<T>::type* __restrict__ x_res, const double* __restrict__ coef) {
+             typename V2<T>::type* __restrict__ x_res, ChebSteps<T, kCoarseDegree> K) {
   using T2 = typename V2<T>::type;
   __shared__ T2 xs[2][kCoarseLdsNodes];
   __shared__ T2 ds[kCoarseLdsNodes];
@@ -1192,8 +1189,7 @@ __global__ void __launch_bounds__(1024)
   __syncthreads();
   for (int k = 0; k < kCoarseDegree; ++k) {
     const int src = k & 1, dst = src ^ 1;
-    const T al0 = (T)coef[4 * k + 0], al1 = (T)coef[4 * k + 1];
-    const T be0 = (T)coef[4 * k + 2], be1 = (T)coef[4 * k + 3];
+    const T al0 = K.al[k][0], al1 = K.al[k][1], be0 = K.be[k][0], be1 = K.be[k][1];
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
       int ix, iy, iz;
       node_ijk<DIM>(g, i, ix, iy, iz);
@@ -1256,7 +1252,7 @@ constexpr int kCoarseSmall = 256;
 template <int DIM, class T>
 __global__ void __launch_bounds__(kCoarseSmall)
     k_coarse_small(LvK g, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
-                   typename V2<T>::type* __restrict__ x_res, const double* __restrict__ coef) {
+                   typename V2<T>::type* __restrict__ x_res, ChebSteps<T, kCoarseDegree> K) {
   using T2 = typename V2<T>::type;
   constexpr int NW = DIM == 3 ? 27 : 9, NC = NW / 9;
   __shared__ T2 xs[2][kCoarseSmall];
@@ -1266,7 +1262,13 @@ __global__ void __launch_bounds__(kCoarseSmall)
   const int i = threadIdx.x;
   const bool own = i < n;
   if (i < g.ncells) cs[i] = c[i];
-  if (i < 4 * kCoarseDegree) co[i] = (T)coef[i];
+  if (i < kCoarseDegree) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      co[4 * i + f] = K.al[i][f];
+      co[4 * i + 2 + f] = K.be[i][f];
+    }
+  }
   __syncthreads();
   T2 bb{};
   T w0[NW], w1[NW], rd0 = 0, rd1 = 0;
@@ -1509,7 +1511,6 @@ int hier_alloc(pf_problem* pb, Hier<T>& H) {
       h[k] *= 2.0;
     }
   }
-  if (hipMalloc(&H.coarse_dev, sizeof(H.coarse_host)) != hipSuccess) return PF_ERR_OOM;
   H.allocated = true;
   return PF_OK;
 }
@@ -1524,11 +1525,6 @@ hipError_t hier_free(Hier<T>& H) {
       const hipError_t e = hipFree(p);
       if (first == hipSuccess) first = e;
     }
-  }
-  if (H.coarse_dev) {
-    const hipError_t e = hipFree(H.coarse_dev);
-    if (first == hipSuccess) first = e;
-    H.coarse_dev = nullptr;
   }
   H.lv.clear();
   H.allocated = false;
@@ -1586,8 +1582,8 @@ ChebSteps<T, S> cheb_steps(const Hier<T>& H, int first) {
   ChebSteps<T, S> K;
   for (int k = 0; k < S; ++k)
     for (int f = 0; f < 2; ++f) {
-      K.al[k][f] = (T)H.coarse_host[4 * (first + k) + f];
-      K.be[k][f] = (T)H.coarse_host[4 * (first + k) + 2 + f];
+      K.al[k][f] = (T)H.coarse[4 * (first + k) + f];
+      K.be[k][f] = (T)H.coarse[4 * (first + k) + 2 + f];
     }
   return K;
 }
@@ -1645,27 +1641,18 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
     PF_HIP_CHECK(hipGetLastError());
   }
   // per-step coefficients of the coarsest solve, [step][alpha0, alpha1, beta0, beta1];
-  // copied to the device when they differ from the last set-up's (the copy
-  // waits for the stream)
+  // its kernels take them by value: a copy on the device could be overwritten
+  // while an earlier apply reads it, and kept stale by a copy that failed
   const Level<T>& C = H.lv.back();
-  double before[4 * kCoarseDegree];
-  std::memcpy(before, H.coarse_host, sizeof(before));
   for (int f = 0; f < 2; ++f) {
     double a[kCoarseDegree], b[kCoarseDegree];
     cheb_coefs(C.lmin[f], kChebSafety * C.lmax[f], kCoarseDegree, a, b);
     for (int k = 0; k < kCoarseDegree; ++k) {
-      H.coarse_host[4 * k + f] = a[k];
-      H.coarse_host[4 * k + 2 + f] = b[k];
+      H.coarse[4 * k + f] = a[k];
+      H.coarse[4 * k + 2 + f] = b[k];
     }
   }
-  if (DIM == 2) {
-    tail2_setup(H);
-    return PF_OK;
-  }
-  if (!H.coarse_sent || std::memcmp(before, H.coarse_host, sizeof(before)) != 0) {
-    PF_HIP_CHECK(hipMemcpy(H.coarse_dev, H.coarse_host, sizeof(H.coarse_host), hipMemcpyHostToDevice));
-    H.coarse_sent = true;
-  }
+  if (DIM == 2) tail2_setup(H);
   return PF_OK;
 }
 
@@ -1755,14 +1742,14 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
     if (L.k.nnodes <= kCoarseSmall) {
       hipLaunchKernelGGL((k_coarse_small<DIM, T>), dim3(1), dim3(kCoarseSmall), 0, s, L.k,
                          (const T*)L.c, (const typename V2<T>::type*)L.b, L.xb,
-                         (const double*)H.coarse_dev);
+                         cheb_steps<T, kCoarseDegree>(H, 0));
       PF_HIP_CHECK(hipGetLastError());
     } else if (L.k.nnodes <= kCoarseLdsNodes) {
       hipLaunchKernelGGL((k_coarse<DIM, T>), dim3(1), dim3(1024), 0, s, L.k, (const T*)L.c,
-                         (const typename V2<T>::type*)L.b, L.xb, (const double*)H.coarse_dev);
+                         (const typename V2<T>::type*)L.b, L.xb, cheb_steps<T, kCoarseDegree>(H, 0));
       PF_HIP_CHECK(hipGetLastError());
     } else {
-      const double* co = H.coarse_host;
+      const double* co = H.coarse;
       double al[2 * kCoarseDegree], be[2 * kCoarseDegree];
       for (int k = 0; k < kCoarseDegree; ++k) {
         al[2 * k] = co[4 * k];

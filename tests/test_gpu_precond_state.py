@@ -1,0 +1,80 @@
+"""What a preconditioner handle keeps between calls: an apply uses the operator
+of the last set-up that succeeded, whatever was called before it.
+
+A handle with a history of calls is compared with a fresh handle of the same
+parameters: bit for bit, since both run the same kernels on the same values.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2006_16764_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# coarsest grids solved by one workgroup of 256 (5^3 nodes) and of 1024 (7 x 8 x 7) lanes, and in 2-D
+SIZES = [(16, 16, 16), (12, 14, 12), (48, 40)]
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(np.asarray(a, dtype=np.float64).reshape(-1))).cuda()
+
+
+def params(n, dt):
+    from paper_2006_16764_amd import binding
+    return binding.make_params(len(n), n, [0.4 * k for k in n], dt, 0.05, 1.6, 2.0)
+
+
+def cycle(pb, r):
+    return pb.pf_precond_apply(r, pb.new_vector()).clone()
+
+
+def fresh(n, dt, U, r, prec):
+    from paper_2006_16764_amd import binding
+    pb = binding.Problem(params(n, dt), 1)
+    pb.pf_precond_setup(U, binding.PF_PC_GMG, prec)
+    z = cycle(pb, r)
+    assert pb.close() == 0
+    return z
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("n", SIZES, ids=lambda n: "x".join(map(str, n)))
+def test_set_up_after_one_under_capture(n, prec):
+    """A set-up while a graph is captured, with another time step: it either is
+    captured as a whole or fails, and the next set-up outside is complete."""
+    from paper_2006_16764_amd import binding
+    print(f"[case] set-up under capture {n} precision {prec}", flush=True)
+    U = dev(inputs.random_state(len(n), n, 1))
+    r = dev(inputs.random_vector(U.numel() // 2, 2))
+    want = fresh(n, 0.02, U, r, prec)
+    pb = binding.Problem(params(n, 0.5), 1)
+    pb.pf_precond_setup(U, binding.PF_PC_GMG, prec)
+    assert not torch.equal(cycle(pb, r), want)
+    pb.set_params(params(n, 0.02))
+    torch.cuda.synchronize()
+    graph, stream, captured = torch.cuda.CUDAGraph(), torch.cuda.Stream(), True
+    with torch.cuda.stream(stream):
+        graph.capture_begin(capture_error_mode="global")
+        try:
+            pb.pf_precond_setup(U, binding.PF_PC_GMG, prec)
+        except binding.PFError as e:
+            print(f"[case] {e}", flush=True)
+            captured = False
+        finally:
+            try:
+                graph.capture_end()
+            except RuntimeError as e:
+                print(f"[case] {e}", flush=True)
+                captured = False
+    torch.cuda.synchronize()
+    pb.pf_precond_setup(U, binding.PF_PC_GMG, prec)
+    assert torch.equal(cycle(pb, r), want)
+    assert captured
+    U2 = dev(inputs.random_state(len(n), n, 3))
+    want2 = fresh(n, 0.02, U2, r, prec)
+    U.copy_(U2)
+    for _ in range(3):
+        graph.replay()
+        assert torch.equal(cycle(pb, r), want2)
+    assert pb.close() == 0
