@@ -84,22 +84,32 @@ struct Level {
 template <class T>
 struct Tail2;
 
+// The blocks' scales: block f is sum_e c_e (sm[f] M_e + sk[f] K_e).
+struct Scales {
+  double sm[2] = {0.0, 0.0}, sk[2] = {0.0, 0.0};
+  bool operator==(const Scales& o) const {
+    return sm[0] == o.sm[0] && sm[1] == o.sm[1] && sk[0] == o.sk[0] && sk[1] == o.sk[1];
+  }
+};
+
 template <class T>
 struct Hier {
   std::vector<Level<T>> lv;
   bool allocated = false;
+  Scales scales;            // of the last set-up
   size_t tail_at = 0;       // 2-D: first level of the one-workgroup tail (lv.size(): none)
   std::vector<Tail2<T>> tail;  // its kernel argument (0 or 1)
   double coarse[4 * kCoarseDegree] = {};  // per-step (alpha, beta) of the coarsest solve
 };
 
 // A V-cycle captured as one HIP graph: its launches (a few microseconds each on
-// small grids) replay as one submission.  sig holds the block scales the
-// captured kernel arguments were derived from and level0 the hierarchy they
-// point into; either changing forces a new capture.
+// small grids) replay as one submission.  scales are those the captured kernel
+// arguments were derived from (the hierarchy's, not the handle's present ones:
+// its parameters may have been set since the last set-up) and level0 the
+// hierarchy they point into; either changing forces a new capture.
 struct GraphCache {
   hipGraphExec_t exec = nullptr;
-  double sig[4] = {0.0, 0.0, 0.0, 0.0};
+  Scales scales;
   const void* level0 = nullptr;
 };
 
@@ -1535,16 +1545,18 @@ hipError_t hier_free(Hier<T>& H) {
 // theta K_c; u block (1/dt) M + theta D K (thermal) or (1+k)/(2 dt) M +
 // theta D K (alloy, the one-sided mobility at its liquid value).  Free
 // growth: (1/dt) M_c + theta beta Gamma K_c and (1/dt) M + theta alpha K.
-void block_scales(const pf_problem* pb, double* sm, double* sk) {
+Scales block_scales(const pf_problem* pb) {
   const double idt = 1.0 / pb->params.dt, th = pb->params.theta;
-  sm[0] = idt;
-  sk[0] = th;
-  sm[1] = pb->model == 1 ? 0.5 * (1.0 + pb->alloy.k) * idt : idt;
-  sk[1] = th * pb->params.D;
+  Scales c;
+  c.sm[0] = idt;
+  c.sk[0] = th;
+  c.sm[1] = pb->model == 1 ? 0.5 * (1.0 + pb->alloy.k) * idt : idt;
+  c.sk[1] = th * pb->params.D;
   if (pb->model == 2) {
-    sk[0] = th * pb->fg.beta * pb->fg.Gamma;
-    sk[1] = th * pb->fg.alpha;
+    c.sk[0] = th * pb->fg.beta * pb->fg.Gamma;
+    c.sk[1] = th * pb->fg.alpha;
   }
+  return c;
 }
 
 // coefficients of the level's degree-2 smoother, [k][block]
@@ -1620,8 +1632,8 @@ void tail2_setup(Hier<T>& H) {
 
 template <int DIM, class T>
 int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) {
-  double sm[2], sk[2];
-  block_scales(pb, sm, sk);
+  H.scales = block_scales(pb);
+  const double *sm = H.scales.sm, *sk = H.scales.sk;
   for (size_t l = 0; l < H.lv.size(); ++l) {
     Level<T>& L = H.lv[l];
     for (int f = 0; f < 2; ++f) {
@@ -1990,13 +2002,8 @@ int apply_gmg_graph(pf_problem* pb, PcState* st, Hier<T>& H, GraphCache& gc, con
     }
   }
   if (!st->cap) PF_HIP_CHECK(hipStreamCreateWithFlags(&st->cap, hipStreamNonBlocking));
-  double sm[2], sk[2];
-  block_scales(pb, sm, sk);
-  const double sig[4] = {sm[0], sm[1], sk[0], sk[1]};
   const void* level0 = H.lv.empty() ? nullptr : (const void*)H.lv[0].c;
-  bool same = gc.exec != nullptr && gc.level0 == level0;
-  for (int i = 0; i < 4 && same; ++i) same = gc.sig[i] == sig[i];
-  if (!same) {
+  if (gc.exec == nullptr || gc.level0 != level0 || !(gc.scales == H.scales)) {
     if (gc.exec) {
       PF_HIP_CHECK(hipGraphExecDestroy(gc.exec));
       gc.exec = nullptr;
@@ -2014,7 +2021,7 @@ int apply_gmg_graph(pf_problem* pb, PcState* st, Hier<T>& H, GraphCache& gc, con
     (void)hipGraphDestroy(graph);
     if (ei != hipSuccess) gc.exec = nullptr;
     PF_HIP_CHECK(ei);
-    for (int i = 0; i < 4; ++i) gc.sig[i] = sig[i];
+    gc.scales = H.scales;
     gc.level0 = level0;
   }
   hipLaunchKernelGGL(k_copy2, dim3(blocks(n)), dim3(kT), 0, s, reinterpret_cast<const double2*>(r),
@@ -2105,10 +2112,9 @@ int apply_pc(pf_problem* pb, PcState* st, const double* r, double* z, hipStream_
       return PF_OK;
     case PF_PC_JACOBI: {
       double Ae0[8], Ae1[8];
-      double sm[2], sk[2];
-      block_scales(pb, sm, sk);
-      element_table(G.dim, G.h, sm[0], sk[0], Ae0);
-      element_table(G.dim, G.h, sm[1], sk[1], Ae1);
+      const Scales c = block_scales(pb);
+      element_table(G.dim, G.h, c.sm[0], c.sk[0], Ae0);
+      element_table(G.dim, G.h, c.sm[1], c.sk[1], Ae1);
       hipLaunchKernelGGL(k_jacobi, dim3(blocks(n)), dim3(kT), 0, s, G, (const double*)st->coef0,
                          reinterpret_cast<const double2*>(r), reinterpret_cast<double2*>(z),
                          Ae0[0], Ae1[0], claim(np, blocks(n)));

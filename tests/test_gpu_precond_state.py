@@ -78,3 +78,26 @@ def test_set_up_after_one_under_capture(n, prec):
         graph.replay()
         assert torch.equal(cycle(pb, r), want2)
     assert pb.close() == 0
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("n", SIZES, ids=lambda n: "x".join(map(str, n)))
+def test_parameters_set_between_applies(n, prec):
+    """New parameters reach the cycle with the next set-up: an apply before it
+    still is the old operator, and leaves nothing that an apply after it uses."""
+    from paper_2006_16764_amd import binding
+    print(f"[case] parameters between applies {n} precision {prec}", flush=True)
+    U = dev(inputs.random_state(len(n), n, 1))
+    r = dev(inputs.random_vector(U.numel() // 2, 2))
+    old, new = fresh(n, 0.5, U, r, prec), fresh(n, 0.02, U, r, prec)
+    assert not torch.equal(old, new)
+    pb = binding.Problem(params(n, 0.5), 1)
+    for _ in range(2):
+        pb.set_params(params(n, 0.5))
+        pb.pf_precond_setup(U, binding.PF_PC_GMG, prec)
+        assert torch.equal(cycle(pb, r), old)
+        pb.set_params(params(n, 0.02))
+        assert torch.equal(cycle(pb, r), old)
+        pb.pf_precond_setup(U, binding.PF_PC_GMG, prec)
+        assert torch.equal(cycle(pb, r), new)
+    assert pb.close() == 0
