@@ -218,14 +218,14 @@ __device__ __forceinline__ void alloy_element(const Geo& G, const AlloyConst& C,
                                                             out, ge);
 }
 
-template <int MODE>
+template <int MODE, bool kSquare>
 __global__ void __launch_bounds__(kTile2Threads)
-    k_alloy_tile2(Geo G, AlloyConst C, const double2* __restrict__ U,
+    k_alloy_tile2(Geo G, Tiles2 T, AlloyConst C, const double2* __restrict__ U,
                   const double2* __restrict__ Up, const double2* __restrict__ V,
                   const double* __restrict__ eps_dev, HistArg H, const double2* __restrict__ F0,
                   double2* __restrict__ F, double* __restrict__ coef) {
-  __shared__ double sh[2 * 3 * kTile2Threads];
-  const Tile2 P = tile2_pos(G);
+  __shared__ double sh[2 * 3 * kTile2Slots<kSquare>];
+  const Tile2 P = tile2_pos<kSquare>(T, G);
   double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
   double ge = 0.0;
   if (P.elem) {
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(kTile2Threads)
       coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
   }
   double acc[2];
-  tile2_sum<2>(P, out, sh, acc);
+  tile2_sum<2, kSquare>(T, P, out, sh, acc);
   tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
@@ -305,9 +305,15 @@ int launch_mode(pf_problem* pb, const AlloyConst& C, const double* U, const doub
   auto P2 = reinterpret_cast<const double2*>(Uprev);
   auto V2 = reinterpret_cast<const double2*>(v);
   if (G.dim == 2) {
-    hipLaunchKernelGGL((k_alloy_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G, C,
-                       U2, P2, V2, eps_dev, H, reinterpret_cast<const double2*>(F0),
-                       reinterpret_cast<double2*>(out0), coef);
+    const Tiles2 T = tiles2(G);
+    auto F02 = reinterpret_cast<const double2*>(F0);
+    auto F2 = reinterpret_cast<double2*>(out0);
+    if (T.square())
+      hipLaunchKernelGGL((k_alloy_tile2<MODE, true>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2,
+                         V2, eps_dev, H, F02, F2, coef);
+    else
+      hipLaunchKernelGGL((k_alloy_tile2<MODE, false>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2,
+                         V2, eps_dev, H, F02, F2, coef);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }

@@ -162,14 +162,14 @@ __device__ __forceinline__ void fg_element(const Geo& G, const FgConst& C, long 
 
 // (three wavefronts per SIMD: the analytic product would take 210 VGPRs and two;
 // 1024^2 48.4 -> 45.7 us)
-template <int MODE>
+template <int MODE, bool kSquare>
 __global__ void __launch_bounds__(kTile2Threads, 3)
-    k_fg_tile2(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
+    k_fg_tile2(Geo G, Tiles2 T, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
                const double2* __restrict__ V, const double* __restrict__ eps_dev,
                HistArg H, const double2* __restrict__ F0, double2* __restrict__ F,
                double* __restrict__ coef) {
-  __shared__ double sh[2 * 3 * kTile2Threads];
-  const Tile2 P = tile2_pos(G);
+  __shared__ double sh[2 * 3 * kTile2Slots<kSquare>];
+  const Tile2 P = tile2_pos<kSquare>(T, G);
   double out[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
   double ca = 0.0;
   if (P.elem) {
@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(kTile2Threads, 3)
       coef[P.ex + (long long)G.n[0] * P.ey] = ca / (4.0 * G.jac);
   }
   double acc[2];
-  tile2_sum<2>(P, out, sh, acc);
+  tile2_sum<2, kSquare>(T, P, out, sh, acc);
   tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
@@ -270,20 +270,13 @@ struct P2 {
 // 349 us now.
 constexpr int kQ2Pass = 5;  // local nodes passed on: (2,2), (0,2), (1,2), (2,0), (2,1)
 
-template <int MODE>
-__global__ void __launch_bounds__(kTile2Threads)
-    k_fg_q2(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
+template <int MODE, bool kSquare>
+__global__ void __launch_bounds__(kTile2Threads, 2)
+    k_fg_q2(Geo G, Tiles2 T, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
             const double2* __restrict__ V, const double* __restrict__ eps_dev, HistArg H,
             const double2* __restrict__ F0, double2* __restrict__ F, double* __restrict__ coef) {
-  __shared__ double sh[2][kQ2Pass][kTile2Threads];
-  const unsigned ntx = (unsigned)(C.n_macro[0] / kTile2Own + 1);
-  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int t = (int)threadIdx.x, tx = t % kTile2, ty = t / kTile2;
-  const int ex = (int)(tile % ntx) * kTile2Own - 1 + tx, ey = (int)(tile / ntx) * kTile2Own - 1 + ty;
-  const bool elem = ex >= 0 && ex < C.n_macro[0] && ey >= 0 && ey < C.n_macro[1];
-  const bool own = tx > 0 && ty > 0 && ex <= C.n_macro[0] && ey <= C.n_macro[1];
+  __shared__ double sh[2][kQ2Pass][kTile2Slots<kSquare>];
   const long long nn0 = G.nn[0];
-  const long long base = 2LL * ex + nn0 * (2LL * ey);
   double out[2][3][3];
 #pragma unroll
   for (int o = 0; o < 2; ++o)
@@ -291,7 +284,10 @@ __global__ void __launch_bounds__(kTile2Threads)
     for (int ly = 0; ly < 3; ++ly)
 #pragma unroll
       for (int lx = 0; lx < 3; ++lx) out[o][ly][lx] = 0.0;
-  if (elem) {
+  const int t = (int)threadIdx.x;
+  Tile2 P = tile2_pos<kSquare>(T, C.n_macro[0], C.n_macro[1], 0);
+  P.base = 2LL * P.ex + nn0 * (2LL * P.ey);
+  if (P.elem) {
     const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
     // gradient fields: residual {phi, T}, tangent {phi, tp, tT}; value fields:
     // residual {dphi, dT, hist}, tangent {T, dphi}
@@ -301,7 +297,7 @@ __global__ void __launch_bounds__(kTile2Threads)
     for (int ly = 0; ly < 3; ++ly)
 #pragma unroll
       for (int lx = 0; lx < 3; ++lx) {
-        const long long node = base + lx + nn0 * ly;
+        const long long node = P.base + lx + nn0 * ly;
         double2 u = U[node];
         const double2 up = Up[node];
         if constexpr (MODE == MODE_JVP) {
@@ -389,14 +385,14 @@ __global__ void __launch_bounds__(kTile2Threads)
             out[o][ly][lx] = fma(cb, rs[o][lx], fma(cd, ry[o][lx], out[o][ly][lx]));
       }
     }
-    if (MODE == MODE_RES && coef && own) {
+    if (MODE == MODE_RES && coef && P.node) {
       // element mean of a^2 on its four grid cells (the preconditioner's grid)
       const double c = ca / (4.0 * jac);
 #pragma unroll
       for (int sy = 0; sy < 2; ++sy)
 #pragma unroll
         for (int sx = 0; sx < 2; ++sx)
-          coef[(2 * ex + sx) + (long long)G.n[0] * (2 * ey + sy)] = c;
+          coef[(2 * P.ex + sx) + (long long)G.n[0] * (2 * P.ey + sy)] = c;
     }
   }
 #pragma unroll
@@ -407,23 +403,24 @@ __global__ void __launch_bounds__(kTile2Threads)
     sh[o][3][t] = out[o][0][2];
     sh[o][4][t] = out[o][1][2];
   }
+  if (!kSquare && t < 2 * kQ2Pass) (&sh[0][0][0])[t * kTile2Slots<kSquare> + kTile2Threads] = 0.0;
   __syncthreads();
-  if (!own) return;
-  const int l = t - 1, b = t - kTile2, lb = t - kTile2 - 1;
+  if (!P.node) return;
+  const Around2 A = around2<kSquare>(T, P);
   double a[2][2][2];  // [j][i][output]
 #pragma unroll
   for (int o = 0; o < 2; ++o) {
-    a[0][0][o] = ((sh[o][0][lb] + sh[o][1][b]) + sh[o][3][l]) + out[o][0][0];
-    a[0][1][o] = sh[o][2][b] + out[o][0][1];
-    a[1][0][o] = sh[o][4][l] + out[o][1][0];
+    a[0][0][o] = ((sh[o][0][A.lb] + sh[o][1][A.b]) + sh[o][3][A.l]) + out[o][0][0];
+    a[0][1][o] = sh[o][2][A.b] + out[o][0][1];
+    a[1][0][o] = sh[o][4][A.l] + out[o][1][0];
     a[1][1][o] = out[o][1][1];
   }
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      if ((i == 1 && ex == C.n_macro[0]) || (j == 1 && ey == C.n_macro[1])) continue;
-      const long long node = base + i + nn0 * j;
+      if ((i == 1 && P.ex == C.n_macro[0]) || (j == 1 && P.ey == C.n_macro[1])) continue;
+      const long long node = P.base + i + nn0 * j;
       double a0 = a[j][i][0], a1 = a[j][i][1];
       if constexpr (MODE == MODE_FD) {
         const double e = eps_dev[0];
@@ -462,16 +459,24 @@ int launch_mode(pf_problem* pb, const FgConst& C, const double* U, const double*
   auto F02 = reinterpret_cast<const double2*>(F0);
   auto out2 = reinterpret_cast<double2*>(out0);
   if (pb->params.order == 2) {
-    const long long tiles =
-        (long long)(C.n_macro[0] / kTile2Own + 1) * (C.n_macro[1] / kTile2Own + 1);
-    hipLaunchKernelGGL((k_fg_q2<MODE>), dim3((unsigned)tiles), dim3(kTile2Threads), 0, s, G, C, U2, P2p,
-                       V2, eps_dev, H, F02, out2, coef);
+    const Tiles2 T = tiles2(C.n_macro[0] + 1, C.n_macro[1] + 1);
+    if (T.square())
+      hipLaunchKernelGGL((k_fg_q2<MODE, true>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2p, V2,
+                         eps_dev, H, F02, out2, coef);
+    else
+      hipLaunchKernelGGL((k_fg_q2<MODE, false>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2p, V2,
+                         eps_dev, H, F02, out2, coef);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }
   if (G.dim == 2) {
-    hipLaunchKernelGGL((k_fg_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G, C, U2,
-                       P2p, V2, eps_dev, H, F02, out2, coef);
+    const Tiles2 T = tiles2(G);
+    if (T.square())
+      hipLaunchKernelGGL((k_fg_tile2<MODE, true>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2p, V2,
+                         eps_dev, H, F02, out2, coef);
+    else
+      hipLaunchKernelGGL((k_fg_tile2<MODE, false>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2p, V2,
+                         eps_dev, H, F02, out2, coef);
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }

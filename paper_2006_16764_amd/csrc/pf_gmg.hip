@@ -1909,20 +1909,21 @@ int coarsest2(const Hier<T>& H, const Level<T>& B, const double2* r64, double2* 
               NormParts* np) {
   using T2 = typename V2<T>::type;
   static_assert(kCoarseDegree % (2 * S) == 0, "the last of an even number of launches writes xb");
-  const dim3 grid = tiles2(B.k, cheb2_own(S)), lanes(kRegC2 * kRegC2);
+  const Regions2 R = regions2(B.k, S);
+  const dim3 grid(R.nt), lanes(kCheb2Lanes);
   for (int k = 0; k < kCoarseDegree; k += S) {
     const bool odd = (k / S) % 2 == 1;
     const auto K = cheb_steps<T, S>(H, k);
     const T2 *x = odd ? B.xa : B.xb, *d = odd ? B.d : B.r;
     T2 *xo = odd ? B.xb : B.xa, *dd = odd ? B.r : B.d;
     if (k == 0)
-      hipLaunchKernelGGL((k_cheb2<T, S, true, false, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
+      hipLaunchKernelGGL((k_cheb2<T, S, true, false, TOP>), grid, lanes, 0, s, B.k, R, (const T*)B.c,
                          (const T2*)B.b, r64, K, (const T2*)nullptr, (const T2*)nullptr, xo, dd, z64, (double*)nullptr);
     else if (k + S < kCoarseDegree)
-      hipLaunchKernelGGL((k_cheb2<T, S, false, false, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
+      hipLaunchKernelGGL((k_cheb2<T, S, false, false, TOP>), grid, lanes, 0, s, B.k, R, (const T*)B.c,
                          (const T2*)B.b, r64, K, x, d, xo, dd, z64, (double*)nullptr);
     else
-      hipLaunchKernelGGL((k_cheb2<T, S, false, true, TOP>), grid, lanes, 0, s, B.k, (const T*)B.c,
+      hipLaunchKernelGGL((k_cheb2<T, S, false, true, TOP>), grid, lanes, 0, s, B.k, R, (const T*)B.c,
                          (const T2*)B.b, r64, K, x, d, xo, (T2*)nullptr, z64, TOP ? claim(np, grid.x) : nullptr);
     PF_HIP_CHECK(hipGetLastError());
   }

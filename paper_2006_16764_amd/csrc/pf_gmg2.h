@@ -17,7 +17,8 @@
 // Each step's result is wrong in the region's outermost ring of still valid
 // nodes, so the valid part shrinks by one node per step: with 16 x 16 lanes
 // k_down2 owns 10 x 10 fine nodes (5 x 5 coarse ones) and k_up2 12 x 12; with
-// 32 x 32 lanes k_cheb2 owns 16 x 16 nodes (8 steps) or 24 x 24 (4 steps).  The
+// 32 x 32 lanes k_cheb2 owns 16 x 16 nodes (8 steps) or 24 x 24 (4 steps);
+// regions2 gives narrow grids others.  The
 // nodes evaluated more than once cost less than the launches.  One V-cycle, FP64,
 // by launch per step and now: 64^2 77 -> 30 us, 150^2 67 -> 22, 512^2 172 -> 61,
 // 1024^2 252 -> 99, 1023 x 1001 (one level) 292 -> 128.
@@ -28,8 +29,8 @@
 constexpr int kReg2 = 16;                  // region side of k_down2 and k_up2
 constexpr int kDown2 = (kReg2 - 6) / 2;    // coarse nodes per side owned by k_down2
 constexpr int kUp2 = kReg2 - 4;            // fine nodes per side owned by k_up2
-constexpr int kRegC2 = 32;                 // region side of k_cheb2
-constexpr int cheb2_own(int steps) { return kRegC2 - 2 * steps; }  // nodes per side it owns
+constexpr int kRegC2 = 32;                 // side of k_cheb2's square region
+constexpr int kCheb2Lanes = kRegC2 * kRegC2;
 constexpr int kTail2Lanes = 1024;          // most nodes of k_tail2's first level
 constexpr int kTail2Levels = 6;            // most levels k_tail2 takes
 
@@ -162,20 +163,51 @@ struct Lane2 {
   bool xlo, xhi, ylo, yhi;  // neighbours inside the region
   long long i;           // node index (0 outside the mesh)
 };
-template <int R>
-__device__ __forceinline__ Lane2 lane2(const LvK& g, int x0, int y0) {
+__device__ __forceinline__ Lane2 lane2(const LvK& g, int x0, int y0, int tx, int ty, int w, int h) {
   Lane2 L;
-  L.tx = (int)threadIdx.x % R;
-  L.ty = (int)threadIdx.x / R;
-  L.ix = x0 + L.tx;
-  L.iy = y0 + L.ty;
-  L.in = L.ix >= 0 && L.ix < g.nn[0] && L.iy >= 0 && L.iy < g.nn[1];
-  L.xlo = L.tx > 0;
-  L.xhi = L.tx < R - 1;
-  L.ylo = L.ty > 0;
-  L.yhi = L.ty < R - 1;
+  L.tx = tx;
+  L.ty = ty;
+  L.ix = x0 + tx;
+  L.iy = y0 + ty;
+  const bool held = ty < h;  // lanes beyond the region hold nothing and read themselves
+  L.in = held && L.ix >= 0 && L.ix < g.nn[0] && L.iy >= 0 && L.iy < g.nn[1];
+  L.xlo = held && tx > 0;
+  L.xhi = held && tx < w - 1;
+  L.ylo = held && ty > 0;
+  L.yhi = held && ty < h - 1;
   L.i = L.in ? L.ix + (long long)g.nn[0] * L.iy : 0;
   return L;
+}
+template <int R>
+__device__ __forceinline__ Lane2 lane2(const LvK& g, int x0, int y0) {
+  return lane2(g, x0, y0, (int)threadIdx.x % R, (int)threadIdx.x / R, R, R);
+}
+
+// The regions of a k_cheb2 launch of S steps: w x h lanes, of which the S
+// outermost columns (hx = S) and rows (hy = S) overlap the neighbouring regions;
+// ntx regions along x, nt in all.  mul: lane / w = lane * mul >> 20.
+struct Regions2 {
+  int w, h, hx, hy;
+  unsigned ntx, nt, mul;
+};
+inline Regions2 regions2(const LvK& g, int S) {
+  auto make = [&](int w, int h, int hx, int hy) {
+    const unsigned ox = (unsigned)(w - 2 * hx), oy = (unsigned)(h - 2 * hy);
+    Regions2 R{w, h, hx, hy, ((unsigned)g.nn[0] + ox - 1) / ox, 0, ((1u << 20) + (unsigned)w - 1) / (unsigned)w};
+    R.nt = R.ntx * (((unsigned)g.nn[1] + oy - 1) / oy);
+    return R;
+  };
+  // narrow grids: regions as wide (high) as the grid, which overlap along one
+  // axis only, where that gives fewer (FP64 cycle
+  // of 1 x 10^6 elements 2162 -> 145 us, of 4 x 250000 551 -> 99 us)
+  Regions2 best = make(kRegC2, kRegC2, S, S);
+  const int most = kCheb2Lanes / (2 * S + 1);
+  auto take = [&](const Regions2& R) {
+    if (R.nt < best.nt) best = R;
+  };
+  if (g.nn[0] <= most) take(make(g.nn[0], kCheb2Lanes / g.nn[0], 0, S));
+  if (g.nn[1] <= most) take(make(kCheb2Lanes / g.nn[1], g.nn[1], S, 0));
+  return best;
 }
 
 // Pre-smoothing from zero, residual and restriction: x (fine nodes) and bc
@@ -279,19 +311,18 @@ struct ChebSteps {
 // (x, d); results to (xout, dout), the last ones (LAST) to xout alone, or to z64
 // in a hierarchy of one level (TOP).  The outputs must not be the inputs.
 template <class T, int S, bool FIRST, bool LAST, bool TOP>
-__global__ void __launch_bounds__(kRegC2 * kRegC2)
-    k_cheb2(LvK g, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
+__global__ void __launch_bounds__(kCheb2Lanes)
+    k_cheb2(LvK g, Regions2 R, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
             const double2* __restrict__ r64, ChebSteps<T, S> K,
             const typename V2<T>::type* __restrict__ x, const typename V2<T>::type* __restrict__ d,
             typename V2<T>::type* __restrict__ xout, typename V2<T>::type* __restrict__ dout,
             double2* __restrict__ z64, double* __restrict__ part) {
   using T2 = typename V2<T>::type;
-  __shared__ T2 xs[2][kRegC2 * kRegC2];
-  constexpr int O = cheb2_own(S);
-  const int ntx = (g.nn[0] + O - 1) / O;
-  const int tile = (int)xcd_tile(blockIdx.x, gridDim.x);
-  const Lane2 L = lane2<kRegC2>(g, (tile % ntx) * O - S, (tile / ntx) * O - S);
-  const int t = (int)threadIdx.x;
+  __shared__ T2 xs[2][kCheb2Lanes];
+  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int t = (int)threadIdx.x, ty = (int)(((unsigned)t * R.mul) >> 20), tx = t - ty * R.w;
+  const Lane2 L = lane2(g, (int)(tile % R.ntx) * (R.w - 2 * R.hx) - R.hx,
+                        (int)(tile / R.ntx) * (R.h - 2 * R.hy) - R.hy, tx, ty, R.w, R.h);
   T2 bb{}, v{}, dv{};
   if (L.in) {
     bb = rhs2<T, TOP>(b, r64, L.i);
@@ -315,17 +346,17 @@ __global__ void __launch_bounds__(kRegC2 * kRegC2)
     xs[k & 1][t] = v;
     __syncthreads();
     T y0, y1;
-    apply2<T>(N, xs[k & 1], t, kRegC2, L.xlo, L.xhi, L.ylo, L.yhi, y0, y1);
+    apply2<T>(N, xs[k & 1], t, R.w, L.xlo, L.xhi, L.ylo, L.yhi, y0, y1);
     dv.x = K.al[k][0] * dv.x + (K.be[k][0] * (bb.x - y0)) * N.rd0;
     dv.y = K.al[k][1] * dv.y + (K.be[k][1] * (bb.y - y1)) * N.rd1;
     v.x += dv.x;
     v.y += dv.y;
   }
-  const bool own = L.in && L.tx >= S && L.tx < S + O && L.ty >= S && L.ty < S + O;
+  const bool own = L.in && L.tx >= R.hx && L.tx < R.w - R.hx && L.ty >= R.hy && L.ty < R.h - R.hy;
   if constexpr (TOP && LAST) {
     const double2 z = own ? make_double2((double)v.x, (double)v.y) : make_double2(0.0, 0.0);
     if (own) z64[L.i] = z;
-    if (part) put_partial<kRegC2 * kRegC2>(fma(z.x, z.x, z.y * z.y), part);
+    if (part) put_partial<kCheb2Lanes>(fma(z.x, z.x, z.y * z.y), part);
   } else if (own) {
     xout[L.i] = v;
     if (!LAST) dout[L.i] = dv;

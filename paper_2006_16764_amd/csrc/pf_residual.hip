@@ -24,15 +24,15 @@ constexpr int kTile2Waves = MODE == MODE_RES || MODE == MODE_FD    ? 4
                             : MODE == MODE_VJPP                     ? 2
                                                                     : 1;
 
-template <int MODE>
+template <int MODE, bool kSquare>
 __global__ void __launch_bounds__(kTile2Threads, kTile2Waves<MODE>)
-    k_tile2(Geo G, const double2* __restrict__ U, const double2* __restrict__ Up,
+    k_tile2(Geo G, Tiles2 T, const double2* __restrict__ U, const double2* __restrict__ Up,
             const double2* __restrict__ V, const double* __restrict__ eps_dev,
             const double2* __restrict__ F0, double2* __restrict__ out0,
             double2* __restrict__ out1, double* __restrict__ vjp_part, double* __restrict__ coef) {
   constexpr int NO = (MODE == MODE_VJP) ? 4 : 2;
-  __shared__ double sh[NO * 3 * kTile2Threads];
-  const Tile2 P = tile2_pos(G);
+  __shared__ double sh[NO * 3 * kTile2Slots<kSquare>];
+  const Tile2 P = tile2_pos<kSquare>(T, G);
   double out[NO][4];
 #pragma unroll
   for (int o = 0; o < NO; ++o)
@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(kTile2Threads, kTile2Waves<MODE>)
       coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
   }
   double acc[NO];
-  tile2_sum<NO>(P, out, sh, acc);
+  tile2_sum<NO, kSquare>(T, P, out, sh, acc);
   if (out0) tile2_write(P, acc[0], acc[1], out0, MODE == MODE_FD, F0, eps_dev);
   if (MODE == MODE_VJP && out1) tile2_write(P, acc[2 % NO], acc[3 % NO], out1, false, nullptr, nullptr);
   if (MODE == MODE_VJP || MODE == MODE_VJPP) {
@@ -146,11 +146,15 @@ template <int MODE>
 int launch_tile2(const Geo& G, const double* U, const double* Uprev, const double* v,
                  const double* F0, const double* eps_dev, double* out0, double* out1,
                  double* vjp_part, double* coef, hipStream_t s) {
-  hipLaunchKernelGGL((k_tile2<MODE>), dim3(tile2_blocks(G)), dim3(kTile2Threads), 0, s, G,
-                     reinterpret_cast<const double2*>(U), reinterpret_cast<const double2*>(Uprev),
-                     reinterpret_cast<const double2*>(v), eps_dev,
-                     reinterpret_cast<const double2*>(F0), reinterpret_cast<double2*>(out0),
-                     reinterpret_cast<double2*>(out1), vjp_part, coef);
+  const Tiles2 T = tiles2(G);
+  auto d2 = [](const double* p) { return reinterpret_cast<const double2*>(p); };
+  auto o2 = [](double* p) { return reinterpret_cast<double2*>(p); };
+  if (T.square())
+    hipLaunchKernelGGL((k_tile2<MODE, true>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, d2(U), d2(Uprev),
+                       d2(v), eps_dev, d2(F0), o2(out0), o2(out1), vjp_part, coef);
+  else
+    hipLaunchKernelGGL((k_tile2<MODE, false>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, d2(U), d2(Uprev),
+                       d2(v), eps_dev, d2(F0), o2(out0), o2(out1), vjp_part, coef);
   PF_HIP_CHECK(hipGetLastError());
   return PF_OK;
 }
@@ -213,7 +217,7 @@ int launch_residual_family(pf_problem* pb, int mode, const double* U, const doub
 // Number of per-block partial sums the VJP writes (one per workgroup).
 int elem_blocks(const pf_problem* pb) {
   if (pb->geo.dim == 3) return fused3_tiles(pb->geo);
-  return (int)tile2_blocks(pb->geo);
+  return (int)tiles2(pb->geo).nt;
 }
 
 }  // namespace pf

@@ -1,12 +1,19 @@
-// Single-pass node sums of the 2-D order-1 element kernels.
+// Single-pass node sums of the 2-D element kernels.
 //
-// A workgroup of 256 lanes evaluates a 16 x 16 tile of elements, one per lane,
-// and owns the 15 x 15 nodes whose four elements all lie in the tile: the
-// tile's first element row and column are evaluated by the neighbouring tile
-// too (256/225 = 1.14 evaluations per element).  Lane (tx, ty) holds element
-// (ex, ey) and owns node (ex, ey), the element's first corner, when tx, ty >= 1;
-// the contributions of the three other corners go through LDS.  The sum over
-// the node's elements runs in the fixed order (left, below), below, left, own.
+// A workgroup of 256 lanes evaluates a tile of elements, one per lane, and owns
+// the nodes whose four elements all lie in the tile.  Tiles are 16 x 16 elements
+// and own 15 x 15 nodes: the first element row and column are evaluated by the
+// neighbouring tile too (256/225 = 1.14 evaluations per element).  Lane (tx, ty)
+// holds element (ex, ey) and owns node (ex, ey), the element's first corner,
+// when tx, ty >= 1; the contributions of the three other corners go through LDS.
+// The sum over the node's elements runs in the fixed order (left, below), below,
+// left, own.
+//
+// Narrow meshes take tiles as wide (high) as the mesh: no column (row) is
+// evaluated twice, and lanes that a 16 x 16 tile would leave without an element
+// hold further rows (columns).  Where that gives fewer tiles it is taken
+// (1 x 10^6 elements, residual 250 -> 36 us, all-outputs VJP 1419 -> 140; 4 x 250000
+// residual 65 -> 25 us; 16 x 62500 analytic Jv 57 -> 33 us).
 //
 // Why: the former pair of kernels (element vectors to memory, then a gather)
 // moved 128 B of element vectors per element against 64-80 B of input and
@@ -21,14 +28,39 @@
 
 namespace pf {
 
-constexpr int kTile2 = 16;               // elements per tile side
-constexpr int kTile2Own = kTile2 - 1;    // owned nodes per tile side
+constexpr int kTile2 = 16;  // elements per side of the square tile
 constexpr int kTile2Threads = kTile2 * kTile2;
+// LDS slots per value: one per lane, and a zero for missing neighbours.  Lanes of
+// a square tile's first row and column own no node: their sums are not used.
+template <bool kSquare>
+constexpr int kTile2Slots = kTile2Threads + (kSquare ? 0 : 1);
 
-inline unsigned tile2_blocks(const Geo& G) {
-  return (unsigned)(((G.nn[0] + kTile2Own - 1) / kTile2Own) *
-                    (long long)((G.nn[1] + kTile2Own - 1) / kTile2Own));
+// The tiles of a mesh: tx x ty lanes, hx (hy) = 1 where the first column (row) of
+// lanes belongs to the neighbouring tile; ntx tiles along x, nt in all.
+// mul: lane / tx = lane * mul >> 20 for lanes below 1024.
+struct Tiles2 {
+  int tx, ty, hx, hy;
+  unsigned ntx, nt, mul;
+  bool square() const { return hx && hy; }
+};
+
+// For nn0 x nn1 nodes (order 2: first nodes of elements, and one more per axis).
+inline Tiles2 tiles2(int nn0, int nn1) {
+  auto make = [&](int tx, int ty, int hx, int hy) {
+    const unsigned ox = (unsigned)(tx - hx), oy = (unsigned)(ty - hy);
+    Tiles2 T{tx, ty, hx, hy, ((unsigned)nn0 + ox - 1) / ox, 0, ((1u << 20) + (unsigned)tx - 1) / (unsigned)tx};
+    T.nt = T.ntx * (((unsigned)nn1 + oy - 1) / oy);
+    return T;
+  };
+  Tiles2 best = make(kTile2, kTile2, 1, 1);
+  auto take = [&](const Tiles2& T) {
+    if (T.nt < best.nt) best = T;
+  };
+  if (nn0 <= kTile2Threads / 2) take(make(nn0, kTile2Threads / nn0, 0, 1));
+  if (nn1 <= kTile2Threads / 2) take(make(kTile2Threads / nn1, nn1, 1, 0));
+  return best;
 }
+inline Tiles2 tiles2(const Geo& G) { return tiles2(G.nn[0], G.nn[1]); }
 
 struct Tile2 {
   int tx, ty;
@@ -38,39 +70,65 @@ struct Tile2 {
   long long base;  // index of node (ex, ey); only meaningful when elem or node
 };
 
-// Tiles are dealt to the XCDs in contiguous runs (neighbours share halo rows).
-__device__ __forceinline__ Tile2 tile2_pos(const Geo& G) {
-  const unsigned ntx = (unsigned)((G.nn[0] + kTile2Own - 1) / kTile2Own);
+// Of n0 x n1 elements with rows of nn0 nodes.  Tiles are dealt to the XCDs in
+// contiguous runs (neighbours share halo rows).
+//
+// kSquare: T is of square tiles, whose sides are constants then (T is set to
+// them).  The kernels are compiled for these and for any shape: with the shape an
+// argument alone, the order-2 tangent spills (2048^2 elements 331 us against 327)
+// and the free-growth residual on 1024^2 takes 38.4 us against 37.7.
+template <bool kSquare>
+__device__ __forceinline__ Tile2 tile2_pos(Tiles2& T, int n0, int n1, int nn0) {
+  if constexpr (kSquare) {
+    T.tx = T.ty = kTile2;
+    T.hx = T.hy = 1;
+  }
   const unsigned t = xcd_tile(blockIdx.x, gridDim.x);
   Tile2 P;
-  P.tx = (int)threadIdx.x % kTile2;
-  P.ty = (int)threadIdx.x / kTile2;
-  P.ex = (int)(t % ntx) * kTile2Own - 1 + P.tx;
-  P.ey = (int)(t / ntx) * kTile2Own - 1 + P.ty;
-  P.elem = P.ex >= 0 && P.ex < G.n[0] && P.ey >= 0 && P.ey < G.n[1];
-  P.node = P.tx > 0 && P.ty > 0 && P.ex < G.nn[0] && P.ey < G.nn[1];
-  P.base = P.ex + (long long)G.nn[0] * P.ey;
+  P.ty = kSquare ? (int)threadIdx.x / kTile2 : (int)((threadIdx.x * T.mul) >> 20);
+  P.tx = kSquare ? (int)threadIdx.x % kTile2 : (int)threadIdx.x - P.ty * T.tx;
+  P.ex = (int)(t % T.ntx) * (T.tx - T.hx) - T.hx + P.tx;
+  P.ey = (int)(t / T.ntx) * (T.ty - T.hy) - T.hy + P.ty;
+  const bool in = kSquare || P.ty < T.ty;  // lanes beyond the tile hold nothing
+  P.elem = in && P.ex >= 0 && P.ex < n0 && P.ey >= 0 && P.ey < n1;
+  P.node = in && P.tx >= T.hx && P.ty >= T.hy && P.ex <= n0 && P.ey <= n1;
+  P.base = P.ex + (long long)nn0 * P.ey;
   return P;
+}
+template <bool kSquare>
+__device__ __forceinline__ Tile2 tile2_pos(Tiles2& T, const Geo& G) {
+  return tile2_pos<kSquare>(T, G.n[0], G.n[1], G.nn[0]);
+}
+
+// LDS slots of the elements to the left, below, and left below of a lane's node.
+struct Around2 {
+  int l, b, lb;
+};
+template <bool kSquare>
+__device__ __forceinline__ Around2 around2(const Tiles2& T, const Tile2& P) {
+  const int t = (int)threadIdx.x, zero = kSquare ? t : kTile2Threads;
+  return Around2{P.tx > 0 ? t - 1 : zero, P.ty > 0 ? t - T.tx : zero,
+                 P.tx > 0 && P.ty > 0 ? t - T.tx - 1 : zero};
 }
 
 // acc[o] = node sum of output o at the lane's node; out must be zero where the
-// element does not exist.  sh: NO * 3 * kTile2Threads doubles of LDS.
-template <int NO>
-__device__ __forceinline__ void tile2_sum(const Tile2& P, const double (&out)[NO][4],
+// element does not exist.  sh: NO * 3 * kTile2Slots<kSquare> doubles of LDS.
+template <int NO, bool kSquare>
+__device__ __forceinline__ void tile2_sum(const Tiles2& T, const Tile2& P, const double (&out)[NO][4],
                                           double* __restrict__ sh, double (&acc)[NO]) {
+  constexpr int kSlots = kTile2Slots<kSquare>;
   const int t = (int)threadIdx.x;
 #pragma unroll
   for (int o = 0; o < NO; ++o)
 #pragma unroll
-    for (int a = 1; a < 4; ++a) sh[(o * 3 + a - 1) * kTile2Threads + t] = out[o][a];
+    for (int a = 1; a < 4; ++a) sh[(o * 3 + a - 1) * kSlots + t] = out[o][a];
+  if (!kSquare && t < NO * 3) sh[t * kSlots + kTile2Threads] = 0.0;
   __syncthreads();
-  // lanes of the first row or column own no node: any address in range will do
-  const int l = P.tx > 0 ? t - 1 : t, b = P.ty > 0 ? t - kTile2 : t;
-  const int lb = P.tx > 0 && P.ty > 0 ? t - kTile2 - 1 : t;
+  const Around2 A = around2<kSquare>(T, P);
 #pragma unroll
   for (int o = 0; o < NO; ++o) {
-    const double* s = sh + o * 3 * kTile2Threads;
-    acc[o] = ((s[2 * kTile2Threads + lb] + s[kTile2Threads + b]) + s[l]) + out[o][0];
+    const double* s = sh + o * 3 * kSlots;
+    acc[o] = ((s[2 * kSlots + A.lb] + s[kSlots + A.b]) + s[A.l]) + out[o][0];
   }
 }
 
