@@ -1,11 +1,11 @@
 """The single-pass 3-D element kernels at the edges of their tiles.
 
-A workgroup evaluates 16 x 16 element columns over chunks of 16 layers, forms
-the linear part of the residual and the tangent at the tile's nodes from
+A workgroup evaluates 16 x 16 element columns over a chunk of layers, forms the
+linear part of the residual and the tangent at the tile's nodes from
 one-dimensional rows, and a second kernel adds the partial sums of up to 8
 tiles.  Meshes of one element, one layer, and one less, as many and one more
-than a multiple of 16 per axis, with a different spacing on every axis, take
-every kind of tile side.  Tolerances as in the 2-D test of the same name: 1e-12
+than a multiple of 16 columns per axis, with a different spacing on every axis,
+take every kind of tile side.  They are small and cut into chunks of one layer.  Tolerances as in the 2-D test of the same name: 1e-12
 against the oracle, 1e-6 norm-wise for an FD product against the quotient of two
 residual calls.
 """
