@@ -158,18 +158,27 @@ def residual_traffic(workload_name):
     return t["bytes"]
 
 
+# Levels of the 3-D V-cycle that its tiled sweeps take: at least a tile's side of
+# nodes along x and y, or few nodes.
+TILED_SIDES = (32, 8)
+TILED_SMALL = 16384
+
+
 def vcycle_moved(dim, n, s):
-    """vcycle_bytes less what the 3-D cycle no longer moves: the first
-    post-smoothing step adds the coarse correction itself (no sweep that reads
-    and writes the iterate, 4s per node above the coarsest grid), and in FP64 the
-    finest level keeps no copy of the right-hand side (2s per node)."""
+    """vcycle_bytes less what tiled levels do not move: the first post-smoothing
+    step adds the coarse correction itself (no sweep that reads and writes the
+    iterate, 4s per node above the coarsest grid), and in FP64 a tiled finest level
+    keeps no copy of the right-hand side (2s per node).  None in 2-D, where a launch
+    takes several operations on values it holds in LDS and registers."""
+    if dim == 2:
+        return None
     total, sizes = vcycle_bytes(dim, n, s), [n]
     while n % 2 == 0 and n > 4:
         n //= 2
         sizes.append(n)
-    if dim == 3 and len(sizes) > 1:
-        nodes = [(m + 1) ** 3 for m in sizes]
-        total -= 4 * s * sum(nodes[:-1]) + (2 * s * nodes[0] if s == 8 else 0)
+    for level, m in enumerate(sizes[:-1]):
+        if m + 1 >= max(TILED_SIDES) or (m + 1) ** 3 <= TILED_SMALL:
+            total -= (4 + (2 if level == 0 and s == 8 else 0)) * s * (m + 1) ** 3
     return total
 
 
@@ -435,7 +444,8 @@ def main():
         "vcycle_hbm": {name: {"bytes": int(vb), "gbs": round(vb / (t * 1e-3) / 1e9, 1),
                               "frac": round(vb / (t * 1e-3) / 8e12, 3)}
                        for name, vb, t in (("fp32", vcycle_moved(w.dim, w.n, 4), t_pc32),
-                                           ("fp64", vcycle_moved(w.dim, w.n, 8), t_pc64))},
+                                           ("fp64", vcycle_moved(w.dim, w.n, 8), t_pc64))
+                       if vb is not None} or None,
         "newton": [{"its": s["newton_its"], "gmres": s["gmres_its_total"], "ms": round(s["t_total_ms"], 1)}
                    for s in newton],
         "adjoint": [{"gmres": s["gmres_its_total"], "ms": round(s["t_total_ms"], 1)} for s in adj],
