@@ -176,12 +176,13 @@ int pf_residual(pf_problem* pb, const double* U, const double* Uprev, const doub
  * kernels' scratch (3-D: tile-face partial sums; 2-D: none) is a fixed
  * array of 64 MiB inside the library, one copy per device, held from the
  * first call on that device until the process ends; its device address is
- * looked up on that first call.  Meshes whose scratch exceeds it -- beyond
- * 2727 tiles of 16^3 elements in 3-D (128^3 and 192^3 fit, 256^3 does not),
- * or 2^20 elements in 2-D (1024^2 fits) -- are rejected with
- * PF_ERR_INVALID_ARG before anything is launched.  All calls on one device share that array: calls that overlap in
- * time on one device (other streams or threads) race and must not be issued.
- * The array holds the last call's partial sums; nothing in it needs clearing.
+ * looked up on that first call.  3-D meshes whose scratch exceeds it -- beyond
+ * 2727 tiles of 16^3 elements (128^3 and 192^3 fit, 256^3 does not) -- and 2-D
+ * meshes of more than 2^20 elements (1024^2 fits) are rejected with
+ * PF_ERR_INVALID_ARG before anything is launched.  All 3-D calls on one device
+ * share that array: calls that overlap in time on one device (other streams or
+ * threads) race and must not be issued.  The array holds the last call's partial
+ * sums; nothing in it needs clearing.
  * U, Uprev, F: device, 2*n_nodes doubles; F must not alias U or Uprev. */
 int pf_residual_noalloc(const pf_params* params, const double* U, const double* Uprev, double* F,
                         void* stream);

@@ -17,10 +17,9 @@ namespace pf {
 namespace {
 
 // 64 MiB: 2727 tiles of 16^3 elements (192^3 fits).  2-D meshes are accepted up
-// to the documented 2^20 elements, the former size of their element vectors (8
-// doubles each) in the array.
+// to the documented 2^20 elements; their kernel needs no scratch.
 constexpr long long kScratchBytes = 64LL << 20;
-constexpr long long kElemDoubles2 = 8;
+constexpr long long kMostElems2 = 1LL << 20;
 constexpr long long kScratchDoubles = kScratchBytes / (long long)sizeof(double);
 
 static __device__ __align__(256) double scratch[kScratchDoubles];
@@ -71,11 +70,16 @@ extern "C" int pf_residual_noalloc(const pf_params* params, const double* U, con
   pf_params p = *params;
   p.order = 1;
   const Geo G = make_geo(p);
-  const long long need = G.dim == 3 ? fused3_residual_side_len(G) : kElemDoubles2 * G.n_elems;
+  if (G.dim == 2 && G.n_elems > kMostElems2) {
+    set_error("pf_residual_noalloc: " + std::to_string(G.n_elems) +
+              " elements, more than the 2^20 that 2-D calls take (they use no scratch)");
+    return PF_ERR_INVALID_ARG;
+  }
+  const long long need = G.dim == 3 ? fused3_residual_side_len(G) : 0;
   if (need > kScratchDoubles) {
     set_error("pf_residual_noalloc: mesh needs " + std::to_string(need * 8) +
               " bytes of scratch, more than the fixed " + std::to_string(kScratchBytes) +
-              " (3-D: at most 2727 tiles of 16^3 elements; 2-D: at most 2^20 elements)");
+              " (at most 2727 tiles of 16^3 elements)");
     return PF_ERR_INVALID_ARG;
   }
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
