@@ -144,8 +144,8 @@ __device__ __forceinline__ void node_ijk(const LvK& g, long long i, int& ix, int
   iz = DIM == 2 ? 0 : (int)(r / g.nn[1]);
 }
 
-// Node-wise kernels run on a 2-D grid: blockIdx.y is the node plane (z; 0 in
-// 2-D) and blockIdx.x * kT + threadIdx.x the node within the plane, so that the
+// Node-wise kernels run on a 2-D grid: blockIdx.y is the node plane and
+// blockIdx.x * kT + threadIdx.x the node within the plane, so that the
 // coordinates come from 32-bit arithmetic.  Returns false past the plane's end.
 __device__ __forceinline__ bool plane_node(const LvK& g, int& ix, int& iy, int& iz, long long& i) {
   const int pn = g.nn[0] * g.nn[1];
@@ -225,46 +225,46 @@ __device__ __forceinline__ void stencil_weights(const LvK& g, const T (&cc)[DIM 
 }
 
 
-template <int DIM, class T>
+template <class T>
 __device__ __forceinline__ void stencil(const LvK& g, const T* __restrict__ c, int ix, int iy,
-                                        int iz, T (&w0)[DIM == 3 ? 27 : 9],
-                                        T (&w1)[DIM == 3 ? 27 : 9]) {
-  constexpr int NZ = DIM == 3 ? 2 : 1;
+                                        int iz, T (&w0)[27],
+                                        T (&w1)[27]) {
+  constexpr int NZ = 2;
   T cc[NZ][2][2];  // [bz][by][bx]
   bool ex[2], ey[2], ez[2];
   ex[0] = ix - 1 >= 0;
   ex[1] = ix < g.n[0];
   ey[0] = iy - 1 >= 0;
   ey[1] = iy < g.n[1];
-  ez[0] = DIM == 2 ? true : iz - 1 >= 0;
-  ez[1] = DIM == 2 ? true : iz < g.n[2];
+  ez[0] = iz - 1 >= 0;
+  ez[1] = iz < g.n[2];
 #pragma unroll
   for (int bz = 0; bz < NZ; ++bz)
 #pragma unroll
     for (int by = 0; by < 2; ++by)
 #pragma unroll
       for (int bx = 0; bx < 2; ++bx) {
-        const bool e = ex[bx] && ey[by] && (DIM == 2 || ez[bz]);
-        const int cx = ix - 1 + bx, cy = iy - 1 + by, cz = DIM == 3 ? iz - 1 + bz : 0;
+        const bool e = ex[bx] && ey[by] && ez[bz];
+        const int cx = ix - 1 + bx, cy = iy - 1 + by, cz = iz - 1 + bz;
         T v = 0;
         if (e) v = c ? c[cx + (long long)g.n[0] * (cy + (long long)g.n[1] * cz)] : (T)1;
         cc[bz][by][bx] = v;
       }
-  stencil_weights<DIM, T>(g, cc, ex, ey, ez, w0, w1);
+  stencil_weights<3, T>(g, cc, ex, ey, ez, w0, w1);
 }
 
 // (A x)_i for both blocks and the two diagonals.
-template <int DIM, class T>
+template <class T>
 __device__ __forceinline__ void apply_A(const LvK& g, const T* __restrict__ c,
                                         const typename V2<T>::type* __restrict__ x, int ix, int iy,
                                         int iz, T& y0, T& y1, T& d0, T& d1) {
-  T w0[DIM == 3 ? 27 : 9], w1[DIM == 3 ? 27 : 9];
-  stencil<DIM, T>(g, c, ix, iy, iz, w0, w1);
+  T w0[27], w1[27];
+  stencil<T>(g, c, ix, iy, iz, w0, w1);
   y0 = 0;
   y1 = 0;
 #pragma unroll
-  for (int tz = 0; tz < (DIM == 3 ? 3 : 1); ++tz) {
-    const int jz = DIM == 3 ? min(max(iz + tz - 1, 0), g.nn[2] - 1) : 0;
+  for (int tz = 0; tz < 3; ++tz) {
+    const int jz = min(max(iz + tz - 1, 0), g.nn[2] - 1);
 #pragma unroll
     for (int ty = 0; ty < 3; ++ty) {
       const int jy = min(max(iy + ty - 1, 0), g.nn[1] - 1);
@@ -278,9 +278,8 @@ __device__ __forceinline__ void apply_A(const LvK& g, const T* __restrict__ c,
       }
     }
   }
-  const int tc = DIM == 3 ? 13 : 4;
-  d0 = w0[tc];
-  d1 = w1[tc];
+  d0 = w0[13];
+  d1 = w1[13];
 }
 
 template <int DIM, class T>
@@ -401,13 +400,13 @@ __global__ void k_coarsen(LvK fg, LvK cg, const T* __restrict__ cf, T* __restric
 
 // dg[i] = phi-block diagonal of node i (the sum of the coefficients of its
 // cells times the element-matrix diagonal entry)
-template <int DIM, class T>
+template <class T>
 __global__ void __launch_bounds__(kT) k_diag(LvK g, const T* __restrict__ c, T* __restrict__ dg) {
   int ix, iy, iz;
   long long i;
   if (!plane_node(g, ix, iy, iz, i)) return;
   T d0, d1;
-  diag_only<DIM, T>(g, c, ix, iy, iz, d0, d1);
+  diag_only<3, T>(g, c, ix, iy, iz, d0, d1);
   dg[i] = d0;
 }
 
@@ -428,7 +427,7 @@ constexpr int kWriteD = 1, kReadD = 2, kDIsX = 4, kProlong = 8;
 // IN: 0 zero start (x_in = 0, b from the level array); 1 zero start with b
 // read from the FP64 interleaved r64 and stored into b; 2 general step.
 // OUT: 0 writes x_out; 1 writes the FP64 interleaved z64 (last step).
-template <int DIM, class T, int IN, int OUT, int FL>
+template <class T, int IN, int OUT, int FL>
 __global__ void __launch_bounds__(kT)
     k_smooth(LvK g, const T* __restrict__ c, typename V2<T>::type* __restrict__ b,
              const typename V2<T>::type* __restrict__ x_in, typename V2<T>::type* __restrict__ x_out,
@@ -450,7 +449,7 @@ __global__ void __launch_bounds__(kT)
   T r0, r1, dg0, dg1, xi0 = 0, xi1 = 0, dn0, dn1;
   if (IN == 2) {
     T y0, y1;
-    apply_A<DIM, T>(g, c, x_in, ix, iy, iz, y0, y1, dg0, dg1);
+    apply_A<T>(g, c, x_in, ix, iy, iz, y0, y1, dg0, dg1);
     r0 = bb.x - y0;
     r1 = bb.y - y1;
     const auto xv = x_in[i];
@@ -466,7 +465,7 @@ __global__ void __launch_bounds__(kT)
     dg0 = dgp[i];
     T n = (T)((ix - 1 >= 0 ? 1 : 0) + (ix < g.n[0] ? 1 : 0)) *
           (T)((iy - 1 >= 0 ? 1 : 0) + (iy < g.n[1] ? 1 : 0));
-    if (DIM == 3) n *= (T)((iz - 1 >= 0 ? 1 : 0) + (iz < g.n[2] ? 1 : 0));
+    n *= (T)((iz - 1 >= 0 ? 1 : 0) + (iz < g.n[2] ? 1 : 0));
     dg1 = (T)g.Ae[1][0] * n;
     dn0 = div_diag(be0 * bb.x, dg0);
     dn1 = div_diag(be1 * bb.y, dg1);
@@ -485,7 +484,7 @@ __global__ void __launch_bounds__(kT)
   }
 }
 
-template <int DIM, class T>
+template <class T>
 __global__ void __launch_bounds__(kT)
     k_resid(LvK g, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
             const typename V2<T>::type* __restrict__ x, typename V2<T>::type* __restrict__ r) {
@@ -493,7 +492,7 @@ __global__ void __launch_bounds__(kT)
   long long i;
   if (!plane_node(g, ix, iy, iz, i)) return;
   T y0, y1, d0, d1;
-  apply_A<DIM, T>(g, c, x, ix, iy, iz, y0, y1, d0, d1);
+  apply_A<T>(g, c, x, ix, iy, iz, y0, y1, d0, d1);
   const auto bv = b[i];
   typename V2<T>::type o;
   o.x = bv.x - y0;
@@ -503,7 +502,7 @@ __global__ void __launch_bounds__(kT)
 
 // b_c[I] = sum_i P[i, I] r_f[i]: fine neighbours 2I-1, 2I, 2I+1 per axis with
 // weights 1/2, 1, 1/2.
-template <int DIM, class T>
+template <class T>
 __global__ void __launch_bounds__(kT)
     k_restrict(LvK fg, LvK cg, const typename V2<T>::type* __restrict__ rf,
                typename V2<T>::type* __restrict__ bc) {
@@ -512,10 +511,10 @@ __global__ void __launch_bounds__(kT)
   if (!plane_node(cg, cx, cy, cz, I)) return;
   T a0 = 0, a1 = 0;
 #pragma unroll
-  for (int dz = -1; dz <= (DIM == 3 ? 1 : -1); ++dz) {
-    const int fz = DIM == 3 ? 2 * cz + dz : 0;
-    if (DIM == 3 && (fz < 0 || fz >= fg.nn[2])) continue;
-    const T wz = DIM == 3 ? (dz == 0 ? (T)1 : (T)0.5) : (T)1;
+  for (int dz = -1; dz <= 1; ++dz) {
+    const int fz = 2 * cz + dz;
+    if (fz < 0 || fz >= fg.nn[2]) continue;
+    const T wz = dz == 0 ? (T)1 : (T)0.5;
 #pragma unroll
     for (int dy = -1; dy <= 1; ++dy) {
       const int fy = 2 * cy + dy;
@@ -636,11 +635,11 @@ __global__ void __launch_bounds__(RCX * RCY)
 }
 
 // x_f[i] += sum_I P[i, I] e_c[I], by coarse node: the thread of coarse node
-// (cx, cy, cz) updates the fine nodes 2c + o, o in {0, 1}^DIM, that exist.  A
+// (cx, cy, cz) updates the fine nodes 2c + o, o in {0, 1}^3, that exist.  A
 // fine node with odd coordinates along m axes takes the sum of its 2^m coarse
 // neighbours times 2^-m.  Neighbouring threads touch neighbouring fine pairs,
 // so the fine rows are read and written once, coalesced.
-template <int DIM, class T>
+template <class T>
 __global__ void __launch_bounds__(kT)
     k_prolong_add(LvK fg, LvK cg, const typename V2<T>::type* __restrict__ ec,
                   typename V2<T>::type* __restrict__ xf) {
@@ -649,7 +648,7 @@ __global__ void __launch_bounds__(kT)
   long long I;
   if (!plane_node(cg, cx, cy, cz, I)) return;
   const bool hx = cx + 1 < cg.nn[0], hy = cy + 1 < cg.nn[1];
-  const bool hz = DIM == 3 && cz + 1 < cg.nn[2];
+  const bool hz = cz + 1 < cg.nn[2];
   const long long sy = cg.nn[0], sz = (long long)cg.nn[0] * cg.nn[1];
   // coarse corner values e[dz][dy][dx]; absent corners are never used
   T2 e[2][2][2];
@@ -663,9 +662,9 @@ __global__ void __launch_bounds__(kT)
         e[dz][dy][dx] = ok ? ec[I + dx + dy * sy + dz * sz] : ec[I];
       }
   const long long fsy = fg.nn[0], fsz = (long long)fg.nn[0] * fg.nn[1];
-  const long long f0 = 2LL * cx + fsy * (2LL * cy) + (DIM == 3 ? fsz * (2LL * cz) : 0LL);
+  const long long f0 = 2LL * cx + fsy * (2LL * cy) + fsz * (2LL * cz);
 #pragma unroll
-  for (int oz = 0; oz < (DIM == 3 ? 2 : 1); ++oz) {
+  for (int oz = 0; oz < 2; ++oz) {
     if (oz == 1 && !hz) continue;
 #pragma unroll
     for (int oy = 0; oy < 2; ++oy) {
@@ -1180,7 +1179,7 @@ __global__ void __launch_bounds__(SBX * SBY) k_stencil3(LvK g, StArgs<T> A) {
 
 // Coarsest level: COARSE_DEGREE Chebyshev steps for both blocks by one
 // workgroup, iterates in LDS.
-template <int DIM, class T>
+template <class T>
 __global__ void __launch_bounds__(1024)
     k_coarse(LvK g, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
              typename V2<T>::type* __restrict__ x_res, ChebSteps<T, kCoarseDegree> K) {
@@ -1202,21 +1201,21 @@ __global__ void __launch_bounds__(1024)
     const T al0 = K.al[k][0], al1 = K.al[k][1], be0 = K.be[k][0], be1 = K.be[k][1];
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
       int ix, iy, iz;
-      node_ijk<DIM>(g, i, ix, iy, iz);
+      node_ijk<3>(g, i, ix, iy, iz);
       const T2 bb = bs[i];
       T dn0, dn1, x0 = 0, x1 = 0;
       if (k == 0) {
         T dg0, dg1;
-        diag_only<DIM, T>(g, cs, ix, iy, iz, dg0, dg1);
+        diag_only<3, T>(g, cs, ix, iy, iz, dg0, dg1);
         dn0 = div_diag(be0 * bb.x, dg0);
         dn1 = div_diag(be1 * bb.y, dg1);
       } else {
-        T w0[DIM == 3 ? 27 : 9], w1[DIM == 3 ? 27 : 9];
-        stencil<DIM, T>(g, cs, ix, iy, iz, w0, w1);
+        T w0[27], w1[27];
+        stencil<T>(g, cs, ix, iy, iz, w0, w1);
         T y0 = 0, y1 = 0;
 #pragma unroll
-        for (int tz = 0; tz < (DIM == 3 ? 3 : 1); ++tz) {
-          const int jz = DIM == 3 ? min(max(iz + tz - 1, 0), g.nn[2] - 1) : 0;
+        for (int tz = 0; tz < 3; ++tz) {
+          const int jz = min(max(iz + tz - 1, 0), g.nn[2] - 1);
 #pragma unroll
           for (int ty = 0; ty < 3; ++ty) {
             const int jy = min(max(iy + ty - 1, 0), g.nn[1] - 1);
@@ -1230,13 +1229,12 @@ __global__ void __launch_bounds__(1024)
             }
           }
         }
-        const int tc = DIM == 3 ? 13 : 4;
         const T2 xv = xs[src][i];
         x0 = xv.x;
         x1 = xv.y;
         const T2 dv = ds[i];
-        dn0 = al0 * dv.x + be0 * (bb.x - y0) / w0[tc];
-        dn1 = al1 * dv.y + be1 * (bb.y - y1) / w1[tc];
+        dn0 = al0 * dv.x + be0 * (bb.x - y0) / w0[13];
+        dn1 = al1 * dv.y + be1 * (bb.y - y1) / w1[13];
       }
       T2 dn, xo;
       dn.x = dn0;
@@ -1259,12 +1257,12 @@ __global__ void __launch_bounds__(1024)
 // lie in LDS (read from memory in the loop, every other step waited for a
 // cache line).  125 nodes, FP64: 15 -> 11 us.
 constexpr int kCoarseSmall = 256;
-template <int DIM, class T>
+template <class T>
 __global__ void __launch_bounds__(kCoarseSmall)
     k_coarse_small(LvK g, const T* __restrict__ c, const typename V2<T>::type* __restrict__ b,
                    typename V2<T>::type* __restrict__ x_res, ChebSteps<T, kCoarseDegree> K) {
   using T2 = typename V2<T>::type;
-  constexpr int NW = DIM == 3 ? 27 : 9, NC = NW / 9;
+  constexpr int NW = 27, NC = NW / 9;
   __shared__ T2 xs[2][kCoarseSmall];
   __shared__ T cs[kCoarseSmall];
   __shared__ T co[4 * kCoarseDegree];
@@ -1286,13 +1284,13 @@ __global__ void __launch_bounds__(kCoarseSmall)
   if (own) {
     bb = b[i];
     int ix, iy, iz;
-    node_ijk<DIM>(g, i, ix, iy, iz);
-    stencil<DIM, T>(g, cs, ix, iy, iz, w0, w1);
+    node_ijk<3>(g, i, ix, iy, iz);
+    stencil<T>(g, cs, ix, iy, iz, w0, w1);
     rd0 = (T)1 / w0[NW / 2];
     rd1 = (T)1 / w1[NW / 2];
 #pragma unroll
     for (int tz = 0; tz < NC; ++tz) {
-      const int jz = DIM == 3 ? min(max(iz + tz - 1, 0), g.nn[2] - 1) : 0;
+      const int jz = min(max(iz + tz - 1, 0), g.nn[2] - 1);
 #pragma unroll
       for (int ty = 0; ty < 3; ++ty) {
         const int jy = min(max(iy + ty - 1, 0), g.nn[1] - 1);
@@ -1649,7 +1647,7 @@ int hier_setup(pf_problem* pb, Hier<T>& H, const double* c0_dev, hipStream_t s) 
     }
     PF_HIP_CHECK(hipGetLastError());
     if (DIM == 2) continue;
-    hipLaunchKernelGGL((k_diag<DIM, T>), plane_grid(L.k), dim3(kT), 0, s, L.k, (const T*)L.c, L.dg);
+    hipLaunchKernelGGL((k_diag<T>), plane_grid(L.k), dim3(kT), 0, s, L.k, (const T*)L.c, L.dg);
     PF_HIP_CHECK(hipGetLastError());
   }
   // per-step coefficients of the coarsest solve, [step][alpha0, alpha1, beta0, beta1];
@@ -1700,7 +1698,7 @@ const typename V2<T>::type* level_rhs(const Level<T>& L, const double* r64) {
   return L.b;
 }
 
-template <int DIM, class T, int IN, int OUT, int FL>
+template <class T, int IN, int OUT, int FL>
 int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::type* x_out,
                 const double* al, const double* be, int k, const double* r64, double* z64,
                 hipStream_t s, NormParts* np = nullptr, const Level<T>* C = nullptr) {
@@ -1729,7 +1727,7 @@ int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::t
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }
-  hipLaunchKernelGGL((k_smooth<DIM, T, IN, OUT, FL>), plane_grid(L.k), dim3(kT), 0, s, L.k,
+  hipLaunchKernelGGL((k_smooth<T, IN, OUT, FL>), plane_grid(L.k), dim3(kT), 0, s, L.k,
                      (const T*)L.c, L.b, x_in, x_out, L.d, (T)al[2 * k], (T)al[2 * k + 1],
                      (T)be[2 * k], (T)be[2 * k + 1], reinterpret_cast<const double2*>(r64),
                      reinterpret_cast<double2*>(z64), (const T*)L.dg);
@@ -1739,7 +1737,7 @@ int smooth_step(Level<T>& L, const typename V2<T>::type* x_in, typename V2<T>::t
 
 // V-cycle from level l on the right-hand side in lv[l].b (or r64 at level 0);
 // the result is left in lv[l].xb (or written to z64 at level 0).
-template <int DIM, class T>
+template <class T>
 int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64, hipStream_t s,
            NormParts* np = nullptr) {
   Level<T>& L = H.lv[l];
@@ -1752,12 +1750,12 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
       PF_HIP_CHECK(hipGetLastError());
     }
     if (L.k.nnodes <= kCoarseSmall) {
-      hipLaunchKernelGGL((k_coarse_small<DIM, T>), dim3(1), dim3(kCoarseSmall), 0, s, L.k,
+      hipLaunchKernelGGL((k_coarse_small<T>), dim3(1), dim3(kCoarseSmall), 0, s, L.k,
                          (const T*)L.c, (const typename V2<T>::type*)L.b, L.xb,
                          cheb_steps<T, kCoarseDegree>(H, 0));
       PF_HIP_CHECK(hipGetLastError());
     } else if (L.k.nnodes <= kCoarseLdsNodes) {
-      hipLaunchKernelGGL((k_coarse<DIM, T>), dim3(1), dim3(1024), 0, s, L.k, (const T*)L.c,
+      hipLaunchKernelGGL((k_coarse<T>), dim3(1), dim3(1024), 0, s, L.k, (const T*)L.c,
                          (const typename V2<T>::type*)L.b, L.xb, cheb_steps<T, kCoarseDegree>(H, 0));
       PF_HIP_CHECK(hipGetLastError());
     } else {
@@ -1770,11 +1768,11 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
         be[2 * k + 1] = co[4 * k + 3];
       }
       // ping-pong ending in xb (kCoarseDegree is even)
-      PF_TRY((smooth_step<DIM, T, 0, 0, kWriteD>(L, nullptr, L.xa, al, be, 0, nullptr, nullptr, s)));
+      PF_TRY((smooth_step<T, 0, 0, kWriteD>(L, nullptr, L.xa, al, be, 0, nullptr, nullptr, s)));
       for (int k = 1; k < kCoarseDegree; ++k) {
         auto* in = (k & 1) ? L.xa : L.xb;
         auto* out = (k & 1) ? L.xb : L.xa;
-        PF_TRY((smooth_step<DIM, T, 2, 0, kReadD | kWriteD>(L, in, out, al, be, k, nullptr, nullptr,
+        PF_TRY((smooth_step<T, 2, 0, kReadD | kWriteD>(L, in, out, al, be, k, nullptr, nullptr,
                                                             s)));
       }
     }
@@ -1812,9 +1810,9 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
       hipLaunchKernelGGL((k_stencil3<T, 4, 0>), tiled_grid(L), dim3(SBX * SBY), 0, s, L.k, A);
     PF_HIP_CHECK(hipGetLastError());
   } else {
-    if (top) PF_TRY((smooth_step<DIM, T, 1, 0, 0>(L, nullptr, L.xa, al, be, 0, r64, nullptr, s)));
-    else PF_TRY((smooth_step<DIM, T, 0, 0, 0>(L, nullptr, L.xa, al, be, 0, nullptr, nullptr, s)));
-    PF_TRY((smooth_step<DIM, T, 2, 0, kDIsX>(L, L.xa, L.xb, al, be, 1, nullptr, nullptr, s)));
+    if (top) PF_TRY((smooth_step<T, 1, 0, 0>(L, nullptr, L.xa, al, be, 0, r64, nullptr, s)));
+    else PF_TRY((smooth_step<T, 0, 0, 0>(L, nullptr, L.xa, al, be, 0, nullptr, nullptr, s)));
+    PF_TRY((smooth_step<T, 2, 0, kDIsX>(L, L.xa, L.xb, al, be, 1, nullptr, nullptr, s)));
   }
   if (L.kz > 0) {
     StArgs<T> A{};
@@ -1825,13 +1823,13 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
     A.kz = L.kz;
     hipLaunchKernelGGL((k_stencil3<T, 0, 0>), tiled_grid(L), dim3(SBX * SBY), 0, s, L.k, A);
   } else {
-    hipLaunchKernelGGL((k_resid<DIM, T>), plane_grid(L.k), dim3(kT), 0, s, L.k,
+    hipLaunchKernelGGL((k_resid<T>), plane_grid(L.k), dim3(kT), 0, s, L.k,
                        (const T*)L.c, (const typename V2<T>::type*)L.b,
                        (const typename V2<T>::type*)L.xb, L.r);
   }
   PF_HIP_CHECK(hipGetLastError());
   Level<T>& C = H.lv[l + 1];
-  if (DIM == 3 && PF_RESTRICT_TILED) {
+  if (PF_RESTRICT_TILED) {
     // coarse z-chunks: the longest power of two up to 16 planes that still
     // gives half the stencils' workgroup target (PF_GMG_TILE_GROUPS overrides
     // it as for the stencils)
@@ -1843,26 +1841,26 @@ int vcycle(pf_problem* pb, Hier<T>& H, size_t l, const double* r64, double* z64,
     hipLaunchKernelGGL((k_restrict3t<T>), dim3(nb), dim3(RCX * RCY), 0, s, L.k, C.k,
                        (const typename V2<T>::type*)L.r, C.b, kz);
   } else {
-    hipLaunchKernelGGL((k_restrict<DIM, T>), plane_grid(C.k), dim3(kT), 0, s, L.k, C.k,
+    hipLaunchKernelGGL((k_restrict<T>), plane_grid(C.k), dim3(kT), 0, s, L.k, C.k,
                        (const typename V2<T>::type*)L.r, C.b);
   }
   PF_HIP_CHECK(hipGetLastError());
-  PF_TRY((vcycle<DIM, T>(pb, H, l + 1, nullptr, nullptr, s)));
+  PF_TRY((vcycle<T>(pb, H, l + 1, nullptr, nullptr, s)));
   // post-smoothing from the corrected iterate: xb -> xa -> xb (or z64); only
   // the first step's direction is read again.  Tiled levels add the prolonged
   // correction while the first step stages its input, which saves a sweep over x
   // (cycle 256^3 FP32 977 -> 921 us, FP64 1549 -> 1426; 64^3 FP64 163 -> 159).
   if (L.kz > 0) {
-    PF_TRY((smooth_step<DIM, T, 2, 0, kWriteD | kProlong>(L, L.xb, L.xa, al, be, 0, r64, nullptr, s,
+    PF_TRY((smooth_step<T, 2, 0, kWriteD | kProlong>(L, L.xb, L.xa, al, be, 0, r64, nullptr, s,
                                                           nullptr, &C)));
   } else {
-    hipLaunchKernelGGL((k_prolong_add<DIM, T>), plane_grid(C.k), dim3(kT), 0, s, L.k, C.k,
+    hipLaunchKernelGGL((k_prolong_add<T>), plane_grid(C.k), dim3(kT), 0, s, L.k, C.k,
                        (const typename V2<T>::type*)C.xb, L.xb);
     PF_HIP_CHECK(hipGetLastError());
-    PF_TRY((smooth_step<DIM, T, 2, 0, kWriteD>(L, L.xb, L.xa, al, be, 0, nullptr, nullptr, s)));
+    PF_TRY((smooth_step<T, 2, 0, kWriteD>(L, L.xb, L.xa, al, be, 0, nullptr, nullptr, s)));
   }
-  if (top) PF_TRY((smooth_step<DIM, T, 2, 1, kReadD>(L, L.xa, nullptr, al, be, 1, r64, z64, s, np)));
-  else PF_TRY((smooth_step<DIM, T, 2, 0, kReadD>(L, L.xa, L.xb, al, be, 1, nullptr, nullptr, s)));
+  if (top) PF_TRY((smooth_step<T, 2, 1, kReadD>(L, L.xa, nullptr, al, be, 1, r64, z64, s, np)));
+  else PF_TRY((smooth_step<T, 2, 0, kReadD>(L, L.xa, L.xb, al, be, 1, nullptr, nullptr, s)));
   return PF_OK;
 }
 
@@ -1979,7 +1977,7 @@ int setup_gmg(pf_problem* pb, PcState* st, Hier<T>& H, hipStream_t s) {
 
 template <class T>
 int apply_gmg(pf_problem* pb, Hier<T>& H, const double* r, double* z, hipStream_t s, NormParts* np) {
-  if (pb->geo.dim == 3) return vcycle<3, T>(pb, H, 0, r, z, s, np);
+  if (pb->geo.dim == 3) return vcycle<T>(pb, H, 0, r, z, s, np);
   return vcycle2<T>(H, r, z, s, np);
 }
 
