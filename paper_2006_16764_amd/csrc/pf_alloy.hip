@@ -238,16 +238,23 @@ __global__ void __launch_bounds__(kTile2Threads)
   tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
-// 3-D element vectors, one element per lane, into the element buffer.  The
-// residual (and the difference quotient's residual) reads its corners again at
-// every Gauss plane and keeps its element vector in its own LDS slots: 240
+// 3-D element vectors, one element per lane, into the element buffer.  kReload:
+// the residual (and the difference quotient's residual) reads its corners again
+// at every Gauss plane and keeps its element vector in its own LDS slots: 240
 // VGPRs, two wavefronts per SIMD, where the same with both in registers takes
-// 370 and one.  512 x 128 x 128: residual 1466 -> 1279 us, difference quotient
+// 332 and one.  512 x 128 x 128: residual 1466 -> 1279 us, difference quotient
 // 1522 -> 1447 us.  The tangent carries two more gradient fields and spills at
 // two wavefronts (4226 us against 1990 at one), and at one the reloads only
 // cost time (2092 us): corners and element vector stay in registers.
-template <int MODE>
-__global__ void __launch_bounds__(kAlloyBlock, MODE == MODE_JVP ? 1 : 2)
+//
+// So they do for meshes whose wavefronts all run at once at one per SIMD: there
+// no second wavefront hides the reloads' latency.  Residual with corners in
+// registers and reloaded: 33^3 18.7 and 24.5 us, 36^3 (396 workgroups) 19.4 and
+// 25.2, 40^3 (520) 28.4 and 26.7, 48^3 30.0 and 28.7.
+constexpr unsigned kOneWaveBlocks = 1024 * 64 / kAlloyBlock;  // 1024 SIMDs
+
+template <int MODE, bool kReload>
+__global__ void __launch_bounds__(kAlloyBlock, kReload ? 2 : 1)
     k_alloy_elem3(Geo G, AlloyConst C, const double2* __restrict__ U,
                   const double2* __restrict__ Up, const double2* __restrict__ V,
                   const double* __restrict__ eps_dev, HistArg H, double* __restrict__ E,
@@ -261,10 +268,11 @@ __global__ void __launch_bounds__(kAlloyBlock, MODE == MODE_JVP ? 1 : 2)
   const int ez = (int)blockIdx.y;
   const long long e = (long long)ez * pe + q;
   const long long base = ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez);
-  if constexpr (MODE == MODE_JVP) {
+  if constexpr (!kReload) {
     double out[2][8];
     double ge = 0.0;
     alloy_element<3, MODE>(G, C, ex, base, U, Up, V, eps_dev, H, out, ge);
+    if (MODE == MODE_RES && coef) coef[e] = ge / (8.0 * G.jac);
 #pragma unroll
     for (int o = 0; o < 2; ++o)
 #pragma unroll
@@ -319,8 +327,13 @@ int launch_mode(pf_problem* pb, const AlloyConst& C, const double* U, const doub
   }
   const dim3 eb((unsigned)(((long long)G.n[0] * G.n[1] + kAlloyBlock - 1) / kAlloyBlock),
                 (unsigned)G.n[2]);
-  hipLaunchKernelGGL((k_alloy_elem3<MODE>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2, P2, V2,
-                     eps_dev, H, pb->elem_buf, coef);
+  constexpr bool kForms = MODE != MODE_JVP;
+  if (kForms && eb.x * eb.y > kOneWaveBlocks)
+    hipLaunchKernelGGL((k_alloy_elem3<MODE, kForms>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2, P2, V2,
+                       eps_dev, H, pb->elem_buf, coef);
+  else
+    hipLaunchKernelGGL((k_alloy_elem3<MODE, false>), dim3(eb), dim3(kAlloyBlock), 0, s, G, C, U2, P2, V2,
+                       eps_dev, H, pb->elem_buf, coef);
   PF_HIP_CHECK(hipGetLastError());
   return launch_gather3(pb, out0, F0, eps_dev, MODE == MODE_FD ? 1 : 0, s);
 }

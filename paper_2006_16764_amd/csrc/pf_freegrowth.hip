@@ -10,6 +10,8 @@
 // element buffer, then the gather of pf_residual.hip forms the node sums.  The
 // analytic tangent differentiates the pointwise terms by hand, the anisotropic
 // flux through the Hessian-vector product of pf_element.h.
+#include <type_traits>
+
 #include "pf_tile2.h"
 
 namespace pf {
@@ -182,14 +184,22 @@ __global__ void __launch_bounds__(kTile2Threads, 3)
   tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
-// 3-D element vectors, one element per lane, into the element buffer.  The
-// corners are read again at every Gauss plane and the element vector lies in
+// 3-D element vectors, one element per lane, into the element buffer.  kReload:
+// the corners are read again at every Gauss plane and the element vector lies in
 // the lane's own LDS slots: at most 246 VGPRs, two wavefronts per SIMD, where
-// the same with both in registers takes 310 to 350 and one.  256 x 128 x 128
+// the same with both in registers takes 304 to 360 and one.  256 x 128 x 128
 // elements: residual 751 -> 561 us, analytic Jv 899 -> 674 us, difference
 // quotient 807 -> 639 us.
-template <int MODE>
-__global__ void __launch_bounds__(kFgBlock, 2)
+//
+// Corners and element vector in registers for meshes whose wavefronts all run at
+// once at one per SIMD: there no second wavefront hides the reloads' latency.
+// Residual and analytic Jv with corners in registers, then reloaded: 33^3 17.1,
+// 17.5 and 21.9, 23.6 us; 40^3 (500 workgroups) 19.0, 19.5 and 23.8, 25.2; 44^3
+// (666) 27.1, 29.9 and 25.6, 26.6.
+constexpr unsigned kOneWaveBlocks = 1024 * 64 / kFgBlock;  // 1024 SIMDs
+
+template <int MODE, bool kReload>
+__global__ void __launch_bounds__(kFgBlock, kReload ? 2 : 1)
     k_fg_elem3(Geo G, FgConst C, const double2* __restrict__ U, const double2* __restrict__ Up,
                const double2* __restrict__ V, const double* __restrict__ eps_dev,
                HistArg H, double* __restrict__ E, double* __restrict__ coef) {
@@ -200,13 +210,35 @@ __global__ void __launch_bounds__(kFgBlock, 2)
   const long long rest = e / n0;
   const long long ey = rest % n1, ez = rest / n1;
   const long long base = ex + (long long)G.nn[0] * (ey + (long long)G.nn[1] * ez);
-  __shared__ double sh[2][8][kFgBlock];
-  const int t = (int)threadIdx.x;
+  // the element vector from the corners that load(gz, ng, nv) reads
+  auto element = [&](auto& load, auto& ph, auto NG, auto NV) {
+    if constexpr (kReload) {
+      __shared__ double sh[2][8][kFgBlock];
+      const int t = (int)threadIdx.x;
 #pragma unroll
-  for (int o = 0; o < 2; ++o)
+      for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int a = 0; a < 8; ++a) sh[o][a][t] = 0.0;
-  StridedAcc acc{&sh[0][0][t], nullptr, kFgBlock};
+        for (int a = 0; a < 8; ++a) sh[o][a][t] = 0.0;
+      StridedAcc acc{&sh[0][0][t], nullptr, kFgBlock};
+      quad3g<NG(), NV(), 2, 0>(G, load, acc, ph);
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = sh[o][a][t];
+    } else {
+      double ng[NG()][8], nv[NV()][8], out[2][8], none[1][8];
+      load(0, ng, nv);
+#pragma unroll
+      for (int a = 0; a < 8; ++a) out[0][a] = out[1][a] = 0.0;
+      quad3<NG(), NV(), 2, 0>(G, ng, nv, out, none, ph);
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = out[o][a];
+    }
+  };
+  constexpr std::integral_constant<int, 2> two;
+  constexpr std::integral_constant<int, 3> three;
   if constexpr (MODE == MODE_JVP) {
     auto load = [&](int, double (&ng)[3][8], double (&nv)[2][8]) {
       __asm__ volatile("" ::: "memory");
@@ -223,18 +255,14 @@ __global__ void __launch_bounds__(kFgBlock, 2)
       }
     };
     PhysFgJvp<3> ph(G, C);
-    quad3g<3, 2, 2, 0>(G, load, acc, ph);
+    element(load, ph, three, two);
   } else {
     const double eps = (MODE == MODE_FD) ? *eps_dev : 0.0;
     const ReloadRes<MODE == MODE_FD> load{G, U, Up, V, C.use_hist ? H.rate : nullptr, base, eps};
     PhysFgRes<3> ph(G, C);
-    quad3g<2, 3, 2, 0>(G, load, acc, ph);
+    element(load, ph, two, three);
     if (MODE == MODE_RES && coef) coef[e] = ph.ca / (8.0 * G.jac);
   }
-#pragma unroll
-  for (int o = 0; o < 2; ++o)
-#pragma unroll
-    for (int a = 0; a < 8; ++a) E[(long long)(o * 8 + a) * G.n_elems + e] = sh[o][a][t];
 }
 
 // ----------------------------------------------------------------- order 2 (2-D)
@@ -480,8 +508,13 @@ int launch_mode(pf_problem* pb, const FgConst& C, const double* U, const double*
     PF_HIP_CHECK(hipGetLastError());
     return PF_OK;
   }
-  hipLaunchKernelGGL((k_fg_elem3<MODE>), dim3((unsigned)((G.n_elems + kFgBlock - 1) / kFgBlock)),
-                     dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, H, pb->elem_buf, coef);
+  const dim3 eb((unsigned)((G.n_elems + kFgBlock - 1) / kFgBlock));
+  if (eb.x > kOneWaveBlocks)
+    hipLaunchKernelGGL((k_fg_elem3<MODE, true>), eb, dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, H,
+                       pb->elem_buf, coef);
+  else
+    hipLaunchKernelGGL((k_fg_elem3<MODE, false>), eb, dim3(kFgBlock), 0, s, G, C, U2, P2p, V2, eps_dev, H,
+                       pb->elem_buf, coef);
   PF_HIP_CHECK(hipGetLastError());
   return launch_gather3(pb, out0, F0, eps_dev, MODE == MODE_FD ? 1 : 0, s);
 }
