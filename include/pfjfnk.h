@@ -208,7 +208,7 @@ int pf_jvp(pf_problem* pb, const double* U, const double* Uprev, const double* v
  *   gU     = (dF/dU)^T w         (may be NULL)
  *   gUprev = (dF/dUprev)^T w     (may be NULL)
  *   gparams[0] = w . dF/d eps4, gparams[1] = w . dF/d lambda  (device, 2
- *   doubles; may be NULL).  Reductions are deterministic.  With gU NULL a 3-D
+ *   doubles; may be NULL).  Reductions are deterministic.  With gU NULL the
  *   call runs a lighter kernel that forms gUprev and gparams only (no
  *   Hessian-vector product of the anisotropic flux); its results equal those
  *   of a call with gU to rounding.  With gU alone (gUprev and gparams NULL)
@@ -358,8 +358,8 @@ int pf_alloy_residual(pf_problem* pb, const double* U, const double* Uprev, cons
 int pf_alloy_explicit(pf_problem* pb, const double* Uprev, double t_prev, double* E, void* stream);
 
 /* [async] Jv of the implicit part (modes as pf_jvp: PF_JV_FD with F0 the
- * implicit part at U, or NULL; PF_JV_ANALYTIC exact, by forward-mode
- * differentiation of the pointwise terms). */
+ * implicit part at U, or NULL; PF_JV_ANALYTIC exact: the derivative of the
+ * pointwise terms along v, written out). */
 int pf_alloy_jvp(pf_problem* pb, const double* U, const double* Uprev, const double* Uprev2,
                  double t, const double* v, const double* F0, int mode, double* Jv, void* stream);
 

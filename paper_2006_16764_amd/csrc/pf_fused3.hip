@@ -172,8 +172,8 @@ __device__ __forceinline__ long long gnode(const Geo& G, int x, int y, int z) {
 // plane k and P_k + 2 P_(k+1) - Q_k to plane k + 1.
 // y, x and x_k - x_(k+1) of a plane are formed once per node, in LDS with a
 // border of zeros, where the sums read 9 neighbours at fixed offsets.
-// The residual's kernels are bound by FP64 issue (86 % of the cycles in which
-// waves are resident): about 55 operations per node instead of 210 per element
+// The residual's kernels are bound by FP64 issue (the vector ALUs issue in 81 %
+// of its cycles): about 55 operations per node instead of 210 per element
 // and a second field in the element vectors' LDS exchange.
 //
 // The node phase between a layer's two barriers is a third of a layer's time

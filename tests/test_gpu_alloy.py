@@ -1,7 +1,7 @@
 """GPU parity of the alloy (directional solidification) model against the oracle.
 
 The implicit part of the theta step, its explicit part, the analytic tangent
-(dual-number forward mode on the GPU, complex step in the oracle) and the FD
+(derivatives written out on the GPU, complex step in the oracle) and the FD
 product are compared on seeded random states (2-D and 3-D, ragged sizes); a
 Newton step and a short run on the seeded directional-growth state are
 compared with the oracle's exact-Jacobian Newton and certified by the oracle's

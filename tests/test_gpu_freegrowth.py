@@ -1,7 +1,7 @@
 """GPU parity of the free-growth model (Sec. 4.1) on Q1 and Q2 elements.
 
 The implicit part of the theta step, its explicit part, the analytic tangent
-(dual numbers on the GPU, complex step in the oracle) and the FD product are
+(derivatives written out on the GPU, complex step in the oracle) and the FD product are
 compared with the FP64 oracle on seeded random states (Q1 in 2-D and 3-D, Q2 in
 2-D, ragged sizes); Newton steps (with a real history rate) and a short run on
 the seeded quarter-seed state are compared with the oracle's exact-Jacobian
