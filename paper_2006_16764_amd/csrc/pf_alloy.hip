@@ -233,9 +233,9 @@ __global__ void __launch_bounds__(kTile2Threads)
     if (MODE == MODE_RES && coef && P.node)
       coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
   }
-  double acc[2];
-  tile2_sum<2, kSquare>(T, P, out, sh, acc);
-  tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
+  double acc[2], more[2];
+  tile2_sum<2, kSquare>(T, P, out, sh, acc, more);
+  tile2_write<kSquare>(T, P, G.nn[0], acc[0], acc[1], more[0], more[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
 // 3-D element vectors, one element per lane, into the element buffer.  kReload:

@@ -179,9 +179,9 @@ __global__ void __launch_bounds__(kTile2Threads, 3)
     if (MODE == MODE_RES && coef && P.node)
       coef[P.ex + (long long)G.n[0] * P.ey] = ca / (4.0 * G.jac);
   }
-  double acc[2];
-  tile2_sum<2, kSquare>(T, P, out, sh, acc);
-  tile2_write(P, acc[0], acc[1], F, MODE == MODE_FD, F0, eps_dev);
+  double acc[2], more[2];
+  tile2_sum<2, kSquare>(T, P, out, sh, acc, more);
+  tile2_write<kSquare>(T, P, G.nn[0], acc[0], acc[1], more[0], more[1], F, MODE == MODE_FD, F0, eps_dev);
 }
 
 // 3-D element vectors, one element per lane, into the element buffer.  kReload:
@@ -443,21 +443,31 @@ __global__ void __launch_bounds__(kTile2Threads, 2)
     a[1][0][o] = sh[o][4][A.l] + out[o][1][0];
     a[1][1][o] = out[o][1][1];
   }
+  auto put = [&](long long node, double a0, double a1) {
+    if constexpr (MODE == MODE_FD) {
+      const double e = eps_dev[0];
+      const double2 f0 = F0[node];
+      a0 = e == 0.0 ? 0.0 : (a0 - f0.x) / e;
+      a1 = e == 0.0 ? 0.0 : (a1 - f0.y) / e;
+    }
+    F[node] = make_double2(a0, a1);
+  };
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       if ((i == 1 && P.ex == C.n_macro[0]) || (j == 1 && P.ey == C.n_macro[1])) continue;
-      const long long node = P.base + i + nn0 * j;
-      double a0 = a[j][i][0], a1 = a[j][i][1];
-      if constexpr (MODE == MODE_FD) {
-        const double e = eps_dev[0];
-        const double2 f0 = F0[node];
-        a0 = e == 0.0 ? 0.0 : (a0 - f0.x) / e;
-        a1 = e == 0.0 ? 0.0 : (a1 - f0.y) / e;
-      }
-      F[node] = make_double2(a0, a1);
+      put(P.base + i + nn0 * j, a[j][i][0], a[j][i][1]);
     }
+  if (!kSquare && P.more) {
+    // the nodes beyond the element along x (hx = 0) or y
+    const bool x = T.hx == 0;
+    const long long node = P.base + (x ? 2 : 2 * nn0);
+    put(node, sh[0][0][A.more] + (x ? out[0][0][2] : out[0][2][0]),
+        sh[1][0][A.more] + (x ? out[1][0][2] : out[1][2][0]));
+    if (x ? P.ey < C.n_macro[1] : P.ex < C.n_macro[0])
+      put(node + (x ? nn0 : 1), x ? out[0][1][2] : out[0][2][1], x ? out[1][1][2] : out[1][2][1]);
+  }
 }
 
 FgConst fg_const(const pf_problem* pb, double theta, int use_hist) {
@@ -487,7 +497,7 @@ int launch_mode(pf_problem* pb, const FgConst& C, const double* U, const double*
   auto F02 = reinterpret_cast<const double2*>(F0);
   auto out2 = reinterpret_cast<double2*>(out0);
   if (pb->params.order == 2) {
-    const Tiles2 T = tiles2(C.n_macro[0] + 1, C.n_macro[1] + 1);
+    const Tiles2 T = tiles2(C.n_macro[0], C.n_macro[1]);
     if (T.square())
       hipLaunchKernelGGL((k_fg_q2<MODE, true>), dim3(T.nt), dim3(kTile2Threads), 0, s, G, T, C, U2, P2p, V2,
                          eps_dev, H, F02, out2, coef);

@@ -65,10 +65,13 @@ __global__ void __launch_bounds__(kTile2Threads, kTile2Waves<MODE>)
     if (MODE == MODE_RES && coef && P.node)
       coef[P.ex + (long long)G.n[0] * P.ey] = ge / (4.0 * G.jac);
   }
-  double acc[NO];
-  tile2_sum<NO, kSquare>(T, P, out, sh, acc);
-  if (out0) tile2_write(P, acc[0], acc[1], out0, MODE == MODE_FD, F0, eps_dev);
-  if (MODE == MODE_VJP && out1) tile2_write(P, acc[2 % NO], acc[3 % NO], out1, false, nullptr, nullptr);
+  double acc[NO], more[NO];
+  tile2_sum<NO, kSquare>(T, P, out, sh, acc, more);
+  if (out0)
+    tile2_write<kSquare>(T, P, G.nn[0], acc[0], acc[1], more[0], more[1], out0, MODE == MODE_FD, F0, eps_dev);
+  if (MODE == MODE_VJP && out1)
+    tile2_write<kSquare>(T, P, G.nn[0], acc[2 % NO], acc[3 % NO], more[2 % NO], more[3 % NO], out1, false,
+                         nullptr, nullptr);
   if (MODE == MODE_VJP || MODE == MODE_VJPP) {
     // fixed-order workgroup reduction of the two parameter sums
     __syncthreads();

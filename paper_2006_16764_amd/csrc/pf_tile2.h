@@ -10,10 +10,12 @@
 // left, own.
 //
 // Narrow meshes take tiles as wide (high) as the mesh: no column (row) is
-// evaluated twice, and lanes that a 16 x 16 tile would leave without an element
-// hold further rows (columns).  Where that gives fewer tiles it is taken
-// (1 x 10^6 elements, residual 250 -> 36 us, all-outputs VJP 1419 -> 140; 4 x 250000
-// residual 65 -> 25 us; 16 x 62500 analytic Jv 57 -> 33 us).
+// evaluated twice, lanes that a 16 x 16 tile would leave without an element hold
+// further rows (columns), and the last lane of a row (column) also owns the node
+// beyond its element.  Taken where it leaves at most 7/8 of the tiles.  Square
+// tiles and these, per 10^6 elements: one across, residual 250 and 25 us, analytic
+// Jv 398 and 37, all-outputs VJP 1419 and 80; four across, residual 65 and 24; 16
+// across, analytic Jv 57 and 33 us.
 //
 // Why: the former pair of kernels (element vectors to memory, then a gather)
 // moved 128 B of element vectors per element against 64-80 B of input and
@@ -35,8 +37,9 @@ constexpr int kTile2Threads = kTile2 * kTile2;
 template <bool kSquare>
 constexpr int kTile2Slots = kTile2Threads + (kSquare ? 0 : 1);
 
-// The tiles of a mesh: tx x ty lanes, hx (hy) = 1 where the first column (row) of
-// lanes belongs to the neighbouring tile; ntx tiles along x, nt in all.
+// The tiles of a mesh: tx x ty lanes.  hx = 1 where the first column of lanes
+// belongs to the neighbouring tile, 0 where the tile is as wide as the mesh (tx
+// elements; the last lanes own two nodes); hy alike.  ntx tiles along x, nt in all.
 // mul: lane / tx = lane * mul >> 20 for lanes below 1024.
 struct Tiles2 {
   int tx, ty, hx, hy;
@@ -44,29 +47,32 @@ struct Tiles2 {
   bool square() const { return hx && hy; }
 };
 
-// For nn0 x nn1 nodes (order 2: first nodes of elements, and one more per axis).
-inline Tiles2 tiles2(int nn0, int nn1) {
+inline Tiles2 tiles2(int n0, int n1) {
+  auto count = [](int n, int lanes, int halo) {
+    return halo ? ((unsigned)n + 1 + (unsigned)lanes - 2) / ((unsigned)lanes - 1) : 1u;
+  };
   auto make = [&](int tx, int ty, int hx, int hy) {
-    const unsigned ox = (unsigned)(tx - hx), oy = (unsigned)(ty - hy);
-    Tiles2 T{tx, ty, hx, hy, ((unsigned)nn0 + ox - 1) / ox, 0, ((1u << 20) + (unsigned)tx - 1) / (unsigned)tx};
-    T.nt = T.ntx * (((unsigned)nn1 + oy - 1) / oy);
-    return T;
+    const unsigned ntx = count(n0, tx, hx);
+    return Tiles2{tx, ty, hx, hy, ntx, ntx * count(n1, ty, hy),
+                  ((1u << 20) + (unsigned)tx - 1) / (unsigned)tx};
   };
-  Tiles2 best = make(kTile2, kTile2, 1, 1);
+  const Tiles2 square = make(kTile2, kTile2, 1, 1);
+  Tiles2 best = square;
   auto take = [&](const Tiles2& T) {
-    if (T.nt < best.nt) best = T;
+    if (8 * T.nt <= 7 * square.nt && T.nt < best.nt) best = T;
   };
-  if (nn0 <= kTile2Threads / 2) take(make(nn0, kTile2Threads / nn0, 0, 1));
-  if (nn1 <= kTile2Threads / 2) take(make(kTile2Threads / nn1, nn1, 1, 0));
+  if (n0 <= kTile2Threads / 2) take(make(n0, kTile2Threads / n0, 0, 1));
+  if (n1 <= kTile2Threads / 2) take(make(kTile2Threads / n1, n1, 1, 0));
   return best;
 }
-inline Tiles2 tiles2(const Geo& G) { return tiles2(G.nn[0], G.nn[1]); }
+inline Tiles2 tiles2(const Geo& G) { return tiles2(G.n[0], G.n[1]); }
 
 struct Tile2 {
   int tx, ty;
   int ex, ey;      // this lane's element, and the node it owns
   bool elem;       // the element exists
   bool node;       // the lane owns node (ex, ey)
+  bool more;       // and (ex + 1, ey) (hx = 0) or (ex, ey + 1) (hy = 0)
   long long base;  // index of node (ex, ey); only meaningful when elem or node
 };
 
@@ -92,6 +98,7 @@ __device__ __forceinline__ Tile2 tile2_pos(Tiles2& T, int n0, int n1, int nn0) {
   const bool in = kSquare || P.ty < T.ty;  // lanes beyond the tile hold nothing
   P.elem = in && P.ex >= 0 && P.ex < n0 && P.ey >= 0 && P.ey < n1;
   P.node = in && P.tx >= T.hx && P.ty >= T.hy && P.ex <= n0 && P.ey <= n1;
+  P.more = !kSquare && P.node && (T.hx == 0 ? P.tx == T.tx - 1 : T.hy == 0 && P.ty == T.ty - 1);
   P.base = P.ex + (long long)nn0 * P.ey;
   return P;
 }
@@ -100,22 +107,24 @@ __device__ __forceinline__ Tile2 tile2_pos(Tiles2& T, const Geo& G) {
   return tile2_pos<kSquare>(T, G.n[0], G.n[1], G.nn[0]);
 }
 
-// LDS slots of the elements to the left, below, and left below of a lane's node.
+// LDS slots of the elements to the left, below, and left below of a lane's node,
+// and of the element left below of its second one.
 struct Around2 {
-  int l, b, lb;
+  int l, b, lb, more;
 };
 template <bool kSquare>
 __device__ __forceinline__ Around2 around2(const Tiles2& T, const Tile2& P) {
   const int t = (int)threadIdx.x, zero = kSquare ? t : kTile2Threads;
   return Around2{P.tx > 0 ? t - 1 : zero, P.ty > 0 ? t - T.tx : zero,
-                 P.tx > 0 && P.ty > 0 ? t - T.tx - 1 : zero};
+                 P.tx > 0 && P.ty > 0 ? t - T.tx - 1 : zero,
+                 P.more ? (T.hx == 0 ? t - T.tx : t - 1) : zero};
 }
 
-// acc[o] = node sum of output o at the lane's node; out must be zero where the
-// element does not exist.  sh: NO * 3 * kTile2Slots<kSquare> doubles of LDS.
+// acc[o] = node sum of output o at the lane's node, more[o] at its second one; out
+// must be zero where the element does not exist.  sh: NO * 3 * kTile2Slots<kSquare> doubles of LDS.
 template <int NO, bool kSquare>
 __device__ __forceinline__ void tile2_sum(const Tiles2& T, const Tile2& P, const double (&out)[NO][4],
-                                          double* __restrict__ sh, double (&acc)[NO]) {
+                                          double* __restrict__ sh, double (&acc)[NO], double (&more)[NO]) {
   constexpr int kSlots = kTile2Slots<kSquare>;
   const int t = (int)threadIdx.x;
 #pragma unroll
@@ -129,23 +138,29 @@ __device__ __forceinline__ void tile2_sum(const Tiles2& T, const Tile2& P, const
   for (int o = 0; o < NO; ++o) {
     const double* s = sh + o * 3 * kSlots;
     acc[o] = ((s[2 * kSlots + A.lb] + s[kSlots + A.b]) + s[A.l]) + out[o][0];
+    // the lane's element is the one to the left (below) of the second node
+    more[o] = kSquare ? 0.0 : s[2 * kSlots + A.more] + (T.hx == 0 ? out[o][1] : out[o][2]);
   }
 }
 
-// The node's result: the sums, or (sums - F0)/eps for the FD product
+// The results at the lane's nodes: the sums, or (sums - F0)/eps for the FD product
 // (eps_dev[1] = 1/eps, 0 when eps is 0: the product is 0 then).
-__device__ __forceinline__ void tile2_write(const Tile2& P, double a0, double a1,
-                                            double2* __restrict__ out, bool fd,
+template <bool kSquare>
+__device__ __forceinline__ void tile2_write(const Tiles2& T, const Tile2& P, int nn0, double a0, double a1,
+                                            double m0, double m1, double2* __restrict__ out, bool fd,
                                             const double2* __restrict__ F0,
                                             const double* __restrict__ eps_dev) {
-  if (!P.node) return;
-  if (fd) {
-    const double ie = eps_dev[1];
-    const double2 f0 = F0[P.base];
-    a0 = ie == 0.0 ? 0.0 : (a0 - f0.x) * ie;
-    a1 = ie == 0.0 ? 0.0 : (a1 - f0.y) * ie;
-  }
-  out[P.base] = make_double2(a0, a1);
+  auto put = [&](long long node, double a0, double a1) {
+    if (fd) {
+      const double ie = eps_dev[1];
+      const double2 f0 = F0[node];
+      a0 = ie == 0.0 ? 0.0 : (a0 - f0.x) * ie;
+      a1 = ie == 0.0 ? 0.0 : (a1 - f0.y) * ie;
+    }
+    out[node] = make_double2(a0, a1);
+  };
+  if (P.node) put(P.base, a0, a1);
+  if (!kSquare && P.more) put(P.base + (T.hx == 0 ? 1 : nn0), m0, m1);
 }
 
 }  // namespace pf

@@ -2,9 +2,8 @@
 
 Element tiles and the regions of the coarsest Chebyshev solve are 16 x 16 and
 32 x 32 lanes; where a mesh is narrower than they are, they are as wide (high) as
-the mesh instead.  Widths on either side of each lane count that divides a tile,
-lengths of one tile and of several with a remainder, both orientations, against
-the oracle with the tolerances of the tests of the square tiles; and the time of
+the mesh instead.  Lengths that end with a tile, begin another one, and leave a
+remainder, both orientations, against the oracle with the tolerances of the tests of the square tiles; and the time of
 a strip against that of a square of as many elements.
 """
 import numpy as np
@@ -17,7 +16,7 @@ import test_gpu_vcycle2d as vcycle
 pytestmark = pytest.mark.gpu
 
 # (elements across, elements along)
-STRIPS = [(1, 127), (1, 300), (2, 85), (3, 200), (7, 64), (16, 61), (24, 90)]
+STRIPS = [(1, 254), (1, 255), (2, 126), (2, 300), (3, 200), (7, 64), (16, 61), (24, 90)]
 BOTH = [n for s in STRIPS for n in (s, s[::-1])]
 ident = lambda n: f"{n[0]}x{n[1]}"  # noqa: E731
 
@@ -62,9 +61,8 @@ def fastest(f):
 
 
 def test_time_of_a_strip():
-    """One element across: twice the nodes of a square and half the lanes of a
-    tile hold an element, so up to twice the square's time plus what the wider
-    reads cost; a tile row per 15 nodes takes 6 to 12 times as long.  Line: 4."""
+    """One element across: twice the nodes of a square, no element evaluated twice;
+    a square tile per 15 rows takes 6 to 12 times as long.  Line: 4."""
     from paper_2006_16764_amd import binding
     times = {}
     for n in ((1000, 1000), (1, 1000000), (1000000, 1)):
