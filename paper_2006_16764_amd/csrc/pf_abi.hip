@@ -16,7 +16,7 @@
 
 namespace pf {
 
-int elem_blocks(const pf_problem* pb);
+int vjp_blocks(const pf_problem* pb, int mode);
 constexpr int kNumTmp = 6;
 static_assert(sizeof(((pf_problem*)nullptr)->tmp_vec) == kNumTmp * sizeof(double*), "tmp_vec size");
 
@@ -804,7 +804,6 @@ int pf_create(const pf_params* params, int gmres_m_max, pf_problem** out) {
   const long long n = pb->n_dof;
   long long rb = (n / 2 + 255) / 256;
   pb->n_red_blocks = (int)std::min<long long>(std::max<long long>(rb, 1), 1024);
-  pb->n_elem_blocks = elem_blocks(pb);
   pb->elem_buf_len = 1;  // grown by the models whose kernels take two passes
   pb->side_len = pb->geo.dim == 3 ? fused3_side_len(pb->geo) : 1;
   if (hipMalloc(&pb->red_partials, (size_t)kRedRows * pb->n_red_blocks * sizeof(double)) !=
@@ -816,7 +815,8 @@ int pf_create(const pf_params* params, int gmres_m_max, pf_problem** out) {
           hipSuccess ||
       hipMalloc(&pb->elem_buf, (size_t)pb->elem_buf_len * sizeof(double)) != hipSuccess ||
       hipMalloc(&pb->side_buf, (size_t)pb->side_len * sizeof(double)) != hipSuccess ||
-      hipMalloc(&pb->vjp_partials, (size_t)2 * pb->n_elem_blocks * sizeof(double)) != hipSuccess ||
+      hipMalloc(&pb->vjp_partials, (size_t)2 * std::max(vjp_blocks(pb, MODE_VJP), vjp_blocks(pb, MODE_VJPP)) * sizeof(double)) !=
+          hipSuccess ||
       hipMalloc(&pb->eps_dev, 8 * sizeof(double)) != hipSuccess) {
     set_error("device allocation failed (workspace)");
     return fail(PF_ERR_OOM);
@@ -963,9 +963,10 @@ int pf_vjp(pf_problem* pb, const double* U, const double* Uprev, const double* w
   if (gU && !gUprev && !gparams)
     return launch_residual_family(pb, MODE_VJPU, U, Uprev, w, nullptr, nullptr, gU, nullptr,
                                   nullptr, s);
-  PF_TRY(launch_residual_family(pb, gU ? MODE_VJP : MODE_VJPP, U, Uprev, w, nullptr, nullptr, gU,
-                                gUprev, pb->vjp_partials, s));
-  if (gparams) PF_TRY(blas_reduce_partials(pb->vjp_partials, pb->n_elem_blocks, 2, gparams, s));
+  const int mode = gU ? MODE_VJP : MODE_VJPP;
+  PF_TRY(launch_residual_family(pb, mode, U, Uprev, w, nullptr, nullptr, gU, gUprev, pb->vjp_partials, s));
+  if (gparams)
+    PF_TRY(blas_reduce_partials(pb->vjp_partials, vjp_blocks(pb, mode), 2, gparams, s));
   return PF_OK;
 }
 
@@ -1160,7 +1161,7 @@ int pf_adjoint_step(pf_problem* pb, const double* U, const double* Uprev, const 
   double* gp_local = pb->red_out + kSlotParams;
   PF_TRY(launch_residual_family(pb, MODE_VJPP, U, Uprev, lam, nullptr, nullptr, nullptr, gP,
                                 pb->vjp_partials, s));
-  PF_TRY(blas_reduce_partials(pb->vjp_partials, pb->n_elem_blocks, 2, gp_local, s));
+  PF_TRY(blas_reduce_partials(pb->vjp_partials, vjp_blocks(pb, MODE_VJPP), 2, gp_local, s));
   PF_TRY(blas_sub_scalars(gparams, gp_local, 2, s));
   if (mu_prev) PF_TRY(blas_axpby(-1.0, gP, 0.0, gP, mu_prev, pb->n_dof, s));
   PF_HIP_CHECK(hipStreamSynchronize(s));

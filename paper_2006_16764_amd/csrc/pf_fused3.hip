@@ -712,10 +712,11 @@ Tiles tiles_for(const Geo& G, int resident) {
   return T;
 }
 
-// Workgroups of a mode that run at a time.  The two adjoint products with
-// parameter sums share one division, that of the partial sums' buffer.
+// Workgroups of a mode that run at a time.  (With the all-outputs product's
+// division the previous-state product, at two waves per SIMD, took 178 us on 129 x
+// 97 x 113 and 361 on 4 x 4 x 20000; with its own 159 and 283.)
 template <int MODE>
-constexpr int kResident = kCus * (MODE == MODE_VJPP ? 1 : kWavesPerSimd<MODE>);
+constexpr int kResident = kCus * kWavesPerSimd<MODE>;
 
 int tile_count(const Tiles& T) { return T.ntx * T.nty * T.ntz; }
 
@@ -759,11 +760,14 @@ long long fused3_side_len(const Geo& G) {
   mode(kResident<MODE_RES>, 2);
   mode(kResident<MODE_JVP>, 2);
   mode(kResident<MODE_VJPU>, 2);
+  mode(kResident<MODE_VJPP>, 2);
   mode(kResident<MODE_VJP>, 4);
   return most;
 }
 
-int fused3_tiles(const Geo& G) { return tile_count(tiles_for(G, kResident<MODE_VJP>)); }
+int fused3_tiles(const Geo& G, int mode) {
+  return tile_count(tiles_for(G, mode == MODE_VJPP ? kResident<MODE_VJPP> : kResident<MODE_VJP>));
+}
 
 // At least what chunks of 16 layers would take, the size that callers with a
 // fixed buffer document (the division in use exceeds it only below kSideMost

@@ -113,7 +113,7 @@ enum Mode { MODE_RES = 0, MODE_FD = 1, MODE_JVP = 2, MODE_VJP = 3, MODE_VJPU = 4
 // is the step eps and eps_dev[1] its reciprocal (0 when eps is 0), both
 // written by blas_fd_eps / blas_fd_eps_cached.
 long long fused3_side_len(const Geo& G);
-int fused3_tiles(const Geo& G);
+int fused3_tiles(const Geo& G, int mode);  // MODE_VJP or MODE_VJPP
 int launch_fused3(pf_problem* pb, int mode, const double* U, const double* Uprev, const double* v,
                   const double* F0, const double* eps_dev, double* out0, double* out1,
                   double* vjp_part, double* coef, hipStream_t s);
@@ -254,10 +254,9 @@ struct pf_problem {
   // residual-family scratch
   double* elem_buf;      // element contributions (two-pass alloy and free-growth kernels)
   long long elem_buf_len;
-  double* vjp_partials;  // 2 * n_elem_blocks
+  double* vjp_partials;  // two parameter sums per workgroup of a VJP
   double* side_buf;      // 3-D: partial node sums on tile boundaries
   long long side_len;
-  int n_elem_blocks;
   double* eps_dev;       // FD epsilon (device scalar)
   double* tmp_vec[6];    // work vectors of n_dof doubles (kNumTmp)
   double* load_vec;      // theta < 1: the explicit part E of the step (lazy)

@@ -218,8 +218,8 @@ int launch_residual_family(pf_problem* pb, int mode, const double* U, const doub
 }
 
 // Number of per-block partial sums the VJP writes (one per workgroup).
-int elem_blocks(const pf_problem* pb) {
-  if (pb->geo.dim == 3) return fused3_tiles(pb->geo);
+int vjp_blocks(const pf_problem* pb, int mode) {
+  if (pb->geo.dim == 3) return fused3_tiles(pb->geo, mode);
   return (int)tiles2(pb->geo).nt;
 }
 

@@ -93,3 +93,22 @@ def test_outputs(n, theta):
             check(host(got).reshape(shape)[box][inner].reshape(-1, 2),
                   np.asarray(ref).reshape(bshape)[inner].reshape(-1, 2), 1e-12, f"{what} at {at0}")
     assert pb.close() == 0
+
+
+def test_time_of_the_previous_state_product():
+    """It forms less than the transposed product at as many wavefronts (0.65 to
+    0.75 of its time on other meshes): its z-chunks have to be those of two
+    workgroups per compute unit too.  Line: 0.8."""
+    from paper_2006_16764_amd import binding
+    from test_gpu_strips2d import fastest
+    n = (4, 4, 20000)
+    print(f"[case] time {n}", flush=True)
+    pb = binding.Problem(binding.make_params(3, n, [0.4 * k for k in n], 0.3, 0.05, 1.6, 2.0), 1)
+    rng = torch.Generator(device="cuda").manual_seed(1)
+    U, Up, v = (torch.randn(pb.n_dof, dtype=torch.float64, device="cuda", generator=rng) for _ in range(3))
+    G, gp = pb.new_vector(), torch.zeros(2, dtype=torch.float64, device="cuda")
+    full = fastest(lambda: pb.pf_vjp(U, Up, v, gU=G))
+    prev = fastest(lambda: pb.pf_vjp(U, Up, v, gUprev=G, gparams=gp))
+    print(f"[time] transposed {1e3 * full:.1f} us, previous state {1e3 * prev:.1f} us", flush=True)
+    assert prev < 0.8 * full
+    assert pb.close() == 0
